@@ -103,6 +103,9 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     hbp_params_t p;
     hbp_default_params(&p);
     if (params) p = *params;
+    const bool scheduled = p.num_workers != 0 || p.fixed_fraction_q8 >= 0 || p.claim_chunk != 0 || p.threads_per_worker != 0 ||
+                           p.rounds_per_batch != 0 || p.slot_weight >= 0 || p.group_weight >= 0 || p.round_weight >= 0 ||
+                           p.column_weight >= 0 || p.heavy_group_rounds != 0 || (p.flags & HBP_FLAG_PAPER_SCHEDULE);
     if (p.group_width == 0) p.group_width = 64;
     if (p.fixed_fraction_q8 < 0) p.fixed_fraction_q8 = 240;
     if (p.heavy_group_rounds == 0) p.heavy_group_rounds = 2048;
@@ -131,6 +134,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     h->n_rows = n_rows; h->n_cols = n_cols;
     h->value_bytes = value_bytes;
     h->flags = p.flags;
+    h->scheduled = scheduled;
     h->first_ticket_block = -1;
     h->R = p.rows_per_block; h->C = p.cols_per_block; h->W = p.group_width;
     h->NBR = (n_rows + h->R - 1) / h->R;
@@ -383,8 +387,10 @@ int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stre
     const hbp::SpmvScratch fixed{static_cast<unsigned char *>(base) + kStaticTicketBytes, static_cast<uint32_t *>(base)};
     // whatever the last call on this device left in the counters goes (a fill kernel, not a memset
     // node: the call may be recorded into a HIP graph)
-    k_clear_u32<<<dim3((unsigned)((h->P + 255) / 256)), 256, 0, (hipStream_t)stream>>>(fixed.ticket, h->P);
-    HBP_HIP(hipGetLastError());
+    if (h->flat_wpg == 0) {
+        k_clear_u32<<<dim3((unsigned)((h->P + 255) / 256)), 256, 0, (hipStream_t)stream>>>(fixed.ticket, h->P);
+        HBP_HIP(hipGetLastError());
+    }
     rc = hbp::launch_spmv_part(h, x, y, (hipStream_t)stream, fixed);
     if (rc != HBP_OK) return rc;
     return hbp::launch_combine(h, y, (hipStream_t)stream, fixed);

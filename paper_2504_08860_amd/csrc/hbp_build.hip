@@ -678,14 +678,15 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,
                                                      int32_t *__restrict__ slot_j, uint32_t *__restrict__ group_nnz, uint32_t *__restrict__ group_longest,
                                                      int32_t *__restrict__ group_slot, int32_t *__restrict__ group_blk, uint32_t heavy_rounds,
-                                                     uint32_t *__restrict__ longest_all, int32_t reorder, uint32_t R,
+                                                     uint32_t *__restrict__ longest_all, uint32_t *__restrict__ n_long,
+                                                     int32_t *__restrict__ long_groups, int32_t flat_wpg, int32_t reorder, uint32_t R,
                                                      const int32_t *__restrict__ a_ptr, int32_t *__restrict__ blk_shift,
                                                      uint32_t *__restrict__ slot_key)
 {
     extern __shared__ __align__(8) uint32_t order_lds[];  // two arrays of cap entries, then 16 counters per tile of 64
     __shared__ uint32_t sh_hist[14];
     __shared__ int32_t sh_shift;
-    __shared__ uint32_t sh_max_key, sh_wave[4];
+    __shared__ uint32_t sh_max_key, sh_wave[4], sh_long_n, sh_long_at;
     constexpr uint32_t kHole = 0xffffffffu;
     constexpr int kSmallBlock = 256;  // slots: one entry per thread
     const int cap = (int)((R + 63u) & ~63u);
@@ -699,6 +700,7 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
     if (threadIdx.x < 14) sh_hist[threadIdx.x] = 0u;
     if (threadIdx.x == 0) {
         sh_max_key = 0u;
+        sh_long_n = 0u;
         sh_shift = *a_ptr;
     }
     __syncthreads();
@@ -846,6 +848,7 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
     __syncthreads();
     // a wavefront per group (W <= 64 slots): nonzeros and longest row by a reduction over the lanes
     const int g0 = blk_group_ptr[b], ng = (m + W - 1) / W;
+    int32_t *listed = reinterpret_cast<int32_t *>(from);  // the block's long groups (as many as groups at most)
     for (int gi = wave; gi < ng; gi += 4) {
         const int i = gi * W + lane;
         uint32_t sum = lane < W && i < m ? to[i] : 0u, longest = sum;
@@ -860,8 +863,16 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
             if (longest > heavy_rounds) atomicMax(longest_all, longest);  // only that long rows matter to the caller
             group_slot[g0 + gi] = s0 + gi * W;
             group_blk[g0 + gi] = b;
+            if (long_groups && is_long_group((int32_t)sum, (int32_t)longest, flat_wpg)) listed[atomicAdd(&sh_long_n, 1u)] = g0 + gi;
         }
     }
+    if (!long_groups) return;
+    __syncthreads();
+    const uint32_t found = sh_long_n;
+    if (found == 0) return;
+    if (threadIdx.x == 0) sh_long_at = atomicAdd(n_long, found);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < found; i += 256) long_groups[sh_long_at + i] = listed[i];
 }
 
 // ------------------------------------------------------------------ step 7: fill
@@ -1407,7 +1418,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         Arena own1(true);
         own1.reserve(&h->blk_bm, 1); own1.reserve(&h->blk_bn, 1); own1.reserve(&h->slot_ptr, 1);
         own1.reserve(&h->blk_group_ptr, 1); own1.reserve(&h->stripe_blk, 1); own1.reserve(&h->group_ptr, 1);
-        own1.reserve(&h->group_slot, 1); own1.reserve(&h->group_rounds, 1); own1.reserve(&h->row_local, 1); own1.reserve(&h->seg_len, 1); own1.reserve(&h->blk_shift, 1);
+        own1.reserve(&h->group_slot, 1); own1.reserve(&h->group_rounds, 1); own1.reserve(&h->group_blk, 1);
+        own1.reserve(&h->row_local, 1); own1.reserve(&h->seg_len, 1); own1.reserve(&h->blk_shift, 1);
         own1.reserve(&h->col_local, 1); own1.reserve_bytes(&h->data, 8); own1.reserve_bytes(&h->partial, 8);
         own1.reserve(&h->unit_stripe, NBR + 1); own1.reserve(&h->unit_k, NBR + 2); own1.reserve(&h->multi_stripes, 1);
         HBP_TRY(own1.commit());
@@ -1500,6 +1512,9 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own1.reserve(&h->slot_ptr, B + 1); own1.reserve(&h->blk_group_ptr, B + 1);
     own1.reserve(&h->stripe_blk, B + 1);
     own1.reserve(&h->group_ptr, G + 1); own1.reserve(&h->group_slot, G + 1); own1.reserve(&h->group_rounds, G + 1);
+    own1.reserve(&h->group_blk, G + 1);
+    h->flat_wpg = h->scheduled ? 0 : flat_wavefronts(nnz, S, n_rows, NBC);
+    if (h->flat_wpg) own1.reserve(&h->long_groups, G + 1);
     own1.reserve(&h->row_local, S + 1); own1.reserve(&h->seg_len, S + 1);
     own1.reserve(&h->blk_shift, B + 1);
     if (p.flags & HBP_FLAG_KEEP_KEYS) own1.reserve(&h->slot_key, S + 1);
@@ -1519,13 +1534,14 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     Arena tmp2(false, h->device, 1);
     uint32_t *stripe_cum, *unit_cnt, *multi_idx;
     tmp2.reserve(&stripe_cum, B + 1); tmp2.reserve(&unit_cnt, NBR + 1); tmp2.reserve(&multi_idx, NBR + 1);
-    uint32_t *bucket_len_row, *group_nnz, *group_longest, *longest_all;
+    uint32_t *bucket_len_row, *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *bucket_j;
-    int32_t *slot_j, *group_blk;
+    int32_t *slot_j;
     tmp2.reserve(&bucket_len_row, S); tmp2.reserve(&bucket_j, S);
-    tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 1); tmp2.reserve(&group_blk, G + 1);
+    tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 1); tmp2.reserve(&d_n_long, 1);
     HBP_TRY(tmp2.commit());
     HBP_HIP(hipMemsetAsync(longest_all, 0, sizeof(uint32_t), st));
+    HBP_HIP(hipMemsetAsync(d_n_long, 0, sizeof(uint32_t), st));
 
     k_compact_blocks<<<blocks_for(std::max<int64_t>(D, NBC) + 1, 256), 256, 0, st>>>(
         dense_cnt, slot_off, group_off, blk_id, D, (int32_t)NBR, (int32_t)NBC, h->blk_bm, h->blk_bn, h->slot_ptr,
@@ -1563,8 +1579,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_HIP(hipFuncSetAttribute((const void *)k_order_block, hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds));
     k_order_block<<<dim3((unsigned)B), 256, order_lds, st>>>(bucket_len_row, bucket_j, h->slot_ptr, h->blk_group_ptr, W,
                                                             h->row_local, h->seg_len, slot_j, group_nnz, group_longest, h->group_slot,
-                                                            group_blk, (uint32_t)long_rounds_of(h->heavy_rounds), longest_all,
-                                                            reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);
+                                                            h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds), longest_all,
+                                                            d_n_long, h->long_groups, h->flat_wpg, reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);
     HBP_TRY(exclusive_scan<kOpIdentity>(group_nnz, (uint32_t *)h->group_ptr, G, 1, scan_tmp, st));
     HBP_TRY(exclusive_scan<kOpIdentity>(group_longest, (uint32_t *)h->group_rounds, G, 1, scan_tmp, st));
     k_set_i32<<<1, 64, 0, st>>>(h->group_slot + G, (int32_t)S);
@@ -1575,11 +1591,11 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     if (parts == 0) {
         if (h->value_bytes == 8)
             k_fill_flat<double><<<blocks_for(G, 4), 256, 0, st>>>(csr_col, static_cast<const double *>(csr_val), h->group_ptr, h->group_slot,
-                                                                  group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C, nnz, h->col_local,
+                                                                  h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C, nnz, h->col_local,
                                                                   static_cast<double *>(h->data));
         else
             k_fill_flat<float><<<blocks_for(G, 4), 256, 0, st>>>(csr_col, static_cast<const float *>(csr_val), h->group_ptr, h->group_slot,
-                                                                 group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C, nnz, h->col_local,
+                                                                 h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C, nnz, h->col_local,
                                                                  static_cast<float *>(h->data));
     } else if (h->value_bytes == 8) {
         k_fill<double><<<stripe_grid, 256, 0, st>>>(h->stripe_ptr, h->stripe_blk, (int32_t)NBR, (int32_t)B, parts, csr_col,
@@ -1591,12 +1607,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                    h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, static_cast<float *>(h->data));
     }
     HBP_HIP(hipGetLastError());
-    uint32_t n_units = 0, n_multi = 0, longest = 0;
+    uint32_t n_units = 0, n_multi = 0, longest = 0, n_long = 0;
+    HBP_HIP(hipMemcpyAsync(&n_long, d_n_long, 4, hipMemcpyDeviceToHost, st));
     HBP_HIP(hipMemcpyAsync(&longest, longest_all, 4, hipMemcpyDeviceToHost, st));
     HBP_HIP(hipMemcpyAsync(&n_units, h->unit_ptr + NBR, 4, hipMemcpyDeviceToHost, st));
     HBP_HIP(hipMemcpyAsync(&n_multi, multi_idx + NBR, 4, hipMemcpyDeviceToHost, st));
     HBP_HIP(hipStreamSynchronize(st));
-    h->U = n_units; h->NM = n_multi;
+    h->U = n_units; h->NM = n_multi; h->n_long = (int32_t)n_long;
     h->longest_segment = (int32_t)longest;  // 0 unless it makes a group long
     return HBP_OK;
 }

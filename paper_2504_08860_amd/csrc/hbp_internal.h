@@ -17,6 +17,27 @@ constexpr int64_t kMaxDense = int64_t(1) << 27;  // NBR * NBC table entries
 // rows longer than this (and up to heavy_group_rounds) make their group a "long" one
 inline int32_t long_rounds_of(int32_t heavy_rounds) { return heavy_rounds / 8 > 0 ? heavy_rounds / 8 : 1; }
 
+// Matrices small enough for k_spmv_flat (one group after the other across the grid, x read from L2) in
+// place of k_spmv_part (persistent workers with x staged in LDS): the wavefronts it gives a group, or 0.
+// The workers spend 5-7 us before the first product and have at most a pack or two per wavefront here;
+// against that x comes out of L2 at some 100 G random elements/s for the whole chip (rows that each stay in a block
+// column or two of several, as a grid operator's, read neighbouring elements and are not held up by that).
+// Measured, us per product, workers / flat: 20K nonzeros in one block column 20.5 / 3.8; random columns 1.2M
+// 43 / 19, 2.4M (fp64) 45 / 47, 4.2M 26.6 / 32, 9.7M 70 / 91; R-MAT 3.9M 89 / 59; 5-point grid 5M 37 / 25, 11M
+// 56 / 46; 27-point grid 2.4M 22 / 13.6, 7.9M 27.8 / 30.
+// Segments of 8 nonzeros and more on average get four wavefronts per group, shorter ones would leave three idle:
+// 27-point grid 0.75M 17.9 (one) / 7.3 (four); 5-point grid 5M 25 / 51.
+inline int flat_wavefronts(int64_t nnz, int64_t S, int64_t n_rows, int64_t NBC)
+{
+    const bool short_segments = nnz < 8 * S;
+    const bool local = NBC >= 4 && S <= 2 * n_rows && nnz >= 2 * S;
+    const int64_t most = !local ? 3000000 : short_segments ? 12000000 : 4000000;
+    return nnz > most ? 0 : short_segments ? 1 : 4;
+}
+// whether k_spmv_flat with `wpg` wavefronts per group gives a group a workgroup of its own: one wavefront
+// takes 8 rounds, up to 512 nonzeros, per memory round trip
+__host__ __device__ inline bool is_long_group(int32_t nnz, int32_t longest, int wpg) { return nnz > 2048 || (wpg > 1 && longest > 64); }
+
 // Device-side view of the layout, passed by value to kernels.
 struct Layout {
     int32_t R, C, W;
@@ -26,7 +47,7 @@ struct Layout {
     int32_t ticket_b0;    // the paper's schedule: first block behind the single ticket counter; -1: not in use
     int64_t n_rows, n_cols;
     const int32_t *blk_bm, *blk_bn, *slot_ptr, *blk_group_ptr, *col_blk_ptr, *stripe_ptr, *stripe_blk;
-    const int32_t *group_ptr, *group_slot, *group_rounds;
+    const int32_t *group_ptr, *group_slot, *group_rounds, *group_blk, *long_groups;
     const int32_t *col_group_ptr, *comp_lo, *comp_col, *fixed_start, *fixed_col;  // schedule (Section 3.3)
     const int32_t *unit_ptr, *unit_stripe, *unit_k, *multi_stripes;               // combine work units
     int32_t NM;                                                        // row blocks with several units
@@ -56,6 +77,11 @@ struct hbp_handle_s {
     int32_t *group_ptr, *group_slot;
     int32_t *col_group_ptr, *comp_lo, *comp_col, *fixed_start, *fixed_col;
     int32_t *group_rounds;               // [G+1] prefix sums of the groups' longest rows
+    int32_t *group_blk;                  // [G] block of each group
+    int32_t *long_groups;                // [n_long] groups that k_spmv_flat gives a workgroup of their own
+    int32_t n_long;
+    int32_t flat_wpg;                    // wavefronts per group of k_spmv_flat; 0: k_spmv_part runs
+    bool scheduled;                      // the caller chose something about the workers or their schedule
     int32_t *unit_ptr, *unit_stripe, *unit_k, *multi_stripes;
     int64_t U, NM;       // combine work units, row blocks cut into several units
     int32_t unit_slots;  // target slots per combine unit
@@ -109,7 +135,7 @@ struct SpmvScratch {
     uint32_t *ticket;
 };
 int launch_spmv_part(const hbp_handle_s *h, const void *x, void *y, hipStream_t stream, SpmvScratch scratch);
-int launch_combine(const hbp_handle_s *h, void *y, hipStream_t stream, SpmvScratch scratch);
+int launch_combine(const hbp_handle_s *h, void *y, hipStream_t stream, SpmvScratch scratch);  // nothing where k_spmv_flat has written y
 int launch_csr(int kind, int value_bytes, const int32_t *ptr, const int32_t *col, const void *val, const void *x, void *y,
                int64_t n_rows, hipStream_t stream);
 

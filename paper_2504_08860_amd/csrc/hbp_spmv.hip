@@ -30,6 +30,7 @@ Layout hbp_view(const hbp_handle_s *h)
     L.blk_bm = h->blk_bm; L.blk_bn = h->blk_bn; L.slot_ptr = h->slot_ptr; L.blk_group_ptr = h->blk_group_ptr;
     L.col_blk_ptr = h->col_blk_ptr; L.stripe_ptr = h->stripe_ptr; L.stripe_blk = h->stripe_blk;
     L.group_ptr = h->group_ptr; L.group_slot = h->group_slot; L.group_rounds = h->group_rounds;
+    L.group_blk = h->group_blk; L.long_groups = h->long_groups;
     L.row_local = h->row_local; L.seg_len = h->seg_len; L.col_local = h->col_local; L.data = h->data;
     L.col_group_ptr = h->col_group_ptr; L.comp_lo = h->comp_lo; L.comp_col = h->comp_col;
     L.fixed_start = h->fixed_start; L.fixed_col = h->fixed_col;

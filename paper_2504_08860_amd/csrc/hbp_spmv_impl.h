@@ -174,6 +174,36 @@ __device__ __forceinline__ void consume_wide(const WideBatch<CH, T> &b, const T 
     }
 }
 
+// Where to cut a group so that `target` of its nonzeros lie in front: the smallest round k with at
+// least that many nonzeros in the rounds 0 .. k-1, and their number.  lens: the 64 rows' lengths, in LDS.
+__device__ __forceinline__ void cut_rounds(const int32_t *lens, uint32_t target, int lane, int32_t &cut_k, uint32_t &cut_pos)
+{
+    // nonzeros of the group in rounds 0 .. k-1; every lane may ask for another k
+    auto before = [&](int32_t k) __attribute__((always_inline)) {
+        uint32_t sum = 0;
+#pragma unroll 16
+        for (int t = 0; t < 64; t++) sum += (uint32_t)min(lens[t], k);
+        return sum;
+    };
+    cut_k = 0;
+    cut_pos = 0;
+    if (target == 0) return;  // wave-uniform
+    // three 64-way splits of (0, 65536]: a segment has fewer than 65536 nonzeros, so all of the
+    // group's lie in front of round 65536
+    int32_t lo = 0;
+    auto split = [&](int32_t step) __attribute__((always_inline)) {
+        // candidates lo + step, lo + 2 step, ...: the last one is known to reach the target
+        const uint32_t got = before(lo + (lane + 1) * step);
+        const int first = __builtin_ctzll(__ballot(got >= target));
+        lo += first * step;
+        return (uint32_t)__shfl(got, first);
+    };
+    split(1024);
+    split(16);
+    cut_pos = split(1);
+    cut_k = lo + 1;
+}
+
 template <int THREADS, int U, int GP, bool HEAVY, typename T>
 // (second launch bound: four wavefronts per SIMD, i.e. at most 128 vector registers per lane
 // whatever the workgroup size; with more, two 512-thread workers no longer fit a CU together)
@@ -677,32 +707,9 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             lens[lane] = len;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            // nonzeros of the group in rounds 0 .. k-1; every lane may ask for another k
-            auto before = [&](int32_t k) __attribute__((always_inline)) {
-                uint32_t sum = 0;
-#pragma unroll 16
-                for (int t = 0; t < 64; t++) sum += (uint32_t)min(lens[t], k);
-                return sum;
-            };
-            // smallest k with before(k) >= target, by three 64-way splits of (0, 65536]: a segment
-            // has fewer than 65536 nonzeros, so before(65536) = total >= target
-            const uint32_t target = (uint32_t)(((uint64_t)total * (uint32_t)wave) / (uint32_t)kWaves);
-            int32_t cut_k = 0;
-            uint32_t cut_pos = 0;
-            if (target > 0) {
-                int32_t lo = 0;
-                auto split = [&](int32_t step) __attribute__((always_inline)) {
-                    // candidates lo + step, lo + 2 step, ...: the last one is known to reach the target
-                    const uint32_t got = before(lo + (lane + 1) * step);
-                    const int first = __builtin_ctzll(__ballot(got >= target));
-                    lo += first * step;
-                    return (uint32_t)__shfl(got, first);
-                };
-                split(1024);
-                split(16);
-                cut_pos = split(1);
-                cut_k = lo + 1;
-            }
+            int32_t cut_k;
+            uint32_t cut_pos;
+            cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)wave) / (uint32_t)kWaves), lane, cut_k, cut_pos);
             if (lane == 0) { sh_cut_k[wave] = cut_k; sh_cut_pos[wave] = cut_pos; }
             if (threadIdx.x == 0) sh_cut_k[kWaves] = 0x10000;
             __syncthreads();
@@ -829,6 +836,170 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         const int64_t r0 = (int64_t)L.multi_stripes[ms] * L.R;
         const int32_t rows = (int32_t)min((int64_t)L.R, L.n_rows - r0);
         for (int32_t r = threadIdx.x; r < rows; r += THREADS) y[r0 + r] = T(0);
+    }
+}
+
+// SpMV part of a small matrix (flat_wavefronts says which): one group after the other across the grid, no
+// workers, no schedule, x read straight from L2.  Bound by latency: a group's chain is metadata -> lane
+// lengths -> columns and values -> x, four dependent loads, and every group of the matrix is in flight at
+// once.  (5-point grid of 64 x 64: 16 us for k_spmv_part and 6.6 us for the combine part -> 3.8 us for this
+// kernel, which then writes y itself.)
+// Workgroups of 16 wavefronts.  The first n_long take one of the matrix's long groups (is_long_group) each,
+// cut at rounds into 16 pieces of equal nonzeros: one wavefront walks such a group at U rounds per memory
+// round trip (R-MAT of 2^16 rows: 722 us without, 40 us with them).  The others take 16 / WPG groups, WPG
+// wavefronts per group, wavefront w of them the rounds U w .. U w + U - 1, then those U WPG further on, ...;
+// round k starts at the group's first position plus the sum over its rows of min(length, k).  The sums of a
+// group's wavefronts meet in LDS, in wavefront order.
+// DIRECT: the matrix has one block column, so a row has one slot at most and the slot's sum is y's
+// value: it is stored there too and no combine part follows.  The last NBR workgroups of the grid
+// (only launched where rows are empty) then write the zeros of the rows without a slot.
+template <int WPG, int U, bool DIRECT, typename T>
+__global__ __launch_bounds__(1024) void k_spmv_flat(Layout L, const T *__restrict__ x, T *__restrict__ partial, T *__restrict__ y,
+                                                    int32_t n_long, int32_t group_wgs)
+{
+    constexpr int kThreads = 1024, kWaves = 16, kGroups = kWaves / WPG;
+    __shared__ T sh_sum[kThreads];
+    __shared__ int32_t sh_left[kThreads];  // per wavefront: rounds left in the rows it is folded onto
+    __shared__ int32_t sh_len[64];
+    __shared__ int32_t sh_cut_k[kWaves + 1];
+    const T *__restrict__ const data = static_cast<const T *>(L.data);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t wg = (int32_t)blockIdx.x - n_long;
+    if (DIRECT && wg >= group_wgs) {
+        uint32_t *present = reinterpret_cast<uint32_t *>(sh_left);  // a bit per row of the row block
+        const int32_t bm = wg - group_wgs;
+        const int64_t r0 = (int64_t)bm * L.R;
+        const int32_t rows = (int32_t)min((int64_t)L.R, L.n_rows - r0);
+        for (int32_t i = threadIdx.x; i < kMaxR / 32; i += kThreads) present[i] = 0u;
+        __syncthreads();
+        for (int32_t k = L.stripe_ptr[bm]; k < L.stripe_ptr[bm + 1]; k++) {
+            const int32_t b = L.stripe_blk[k];
+            for (int32_t s = L.slot_ptr[b] + (int32_t)threadIdx.x; s < L.slot_ptr[b + 1]; s += kThreads) {
+                const uint32_t r = L.row_local[s];
+                atomicOr(&present[r >> 5], 1u << (r & 31u));
+            }
+        }
+        __syncthreads();
+        for (int32_t i = threadIdx.x; i < rows; i += kThreads)
+            if (!((present[i >> 5] >> (i & 31)) & 1u)) y[r0 + i] = T(0);
+        return;
+    }
+    // rows of y that the combine part adds into with atomics start at zero (see k_spmv_part)
+    if constexpr (!DIRECT)
+        for (int32_t ms = (int32_t)blockIdx.x; ms < L.NM; ms += (int32_t)gridDim.x) {
+            const int64_t r0 = (int64_t)L.multi_stripes[ms] * L.R;
+            const int32_t rows = (int32_t)min((int64_t)L.R, L.n_rows - r0);
+            for (int32_t r = threadIdx.x; r < rows; r += kThreads) y[r0 + r] = T(0);
+        }
+    const bool is_long = wg < 0;
+    const int part = is_long ? wave : wave % WPG;
+    int32_t g = is_long ? uniform_load(L.long_groups, (int32_t)blockIdx.x) : wg * kGroups + wave / WPG;
+    int32_t s0 = 0, s1 = 0, bn = 0, bm = 0;
+    uint32_t first = 0;
+    if (!is_long && (g >= L.G || is_long_group(uniform_load(L.group_ptr, g + 1) - uniform_load(L.group_ptr, g),
+                                              uniform_load(L.group_rounds, g + 1) - uniform_load(L.group_rounds, g), WPG))) {
+        if (WPG == 1) return;  // no barrier below
+    } else {
+        s0 = uniform_load(L.group_slot, g);
+        s1 = uniform_load(L.group_slot, g + 1);
+        first = (uint32_t)uniform_load(L.group_ptr, g);
+        const int32_t b = uniform_load(L.group_blk, g);
+        bn = uniform_load(L.blk_bn, b);
+        if (DIRECT) bm = uniform_load(L.blk_bm, b);
+    }
+    const bool mine = s0 + lane < s1;
+    const int32_t n = mine ? (int32_t)L.seg_len[s0 + lane] : 0;
+    uint32_t row = 0;
+    if (DIRECT && part == 0 && mine) row = L.row_local[s0 + lane];
+    const T *const xs = x + (int64_t)bn * L.C;
+    // U steps of the lanes' rows from step k on; `base` is the position of step k and advances past them
+    auto add_steps = [&](uint32_t &base, int32_t steps, int32_t k) __attribute__((always_inline)) {
+        Batch<U, T> bt;
+        issue_batch<U>(bt, L.col_local, data, base, steps, k);
+        T xv[U], sum = T(0);
+#pragma unroll
+        for (int u = 0; u < U; u++) xv[u] = xs[k + u < steps ? bt.c[u] : 0u];  // never index x with a foreign column
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const T more = fma_of(bt.v[u], xv[u], sum);
+            sum = k + u < steps ? more : sum;
+        }
+        return sum;
+    };
+    T acc = T(0);
+    // rounds k, k + 1, ... of the group until no lane has any left (up to end); `base` is the position of round k
+    auto walk = [&](uint32_t base, int32_t end, int32_t k) __attribute__((always_inline)) {
+        int32_t *left = sh_left + wave * 64;
+        T *hand = sh_sum + wave * 64;
+        for (;;) {
+            const uint64_t live = __ballot(k < end);
+            if (!live) break;
+            const int32_t m = __popcll(live);
+            if (m > 32 || !__ballot(k + U < end)) {
+                acc += add_steps(base, end, k);
+                k += U;
+                continue;
+            }
+            // few rows left, one of them for a while: the wavefront is folded, lane j * mm + c serving the c-th live row in the
+            // rounds k + j, k + j + 64 / mm, ... (see walk_rounds in k_spmv_part)
+            const int sh = m > 16 ? 5 : m > 8 ? 4 : m > 4 ? 3 : m > 2 ? 2 : m > 1 ? 1 : 0;  // mm = 2^sh
+            left[lane] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (k < end) left[lanes_below(live)] = end - k;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int32_t rest = left[lane & ((1 << sh) - 1)], j = lane >> sh;
+            const int32_t steps = rest > j ? (rest - j + (64 >> sh) - 1) >> (6 - sh) : 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            hand[lane] = add_steps(base, steps, 0);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (k < end)
+                for (int32_t t = lanes_below(live); t < 64; t += 1 << sh) acc += hand[t];
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            k += U << (6 - sh);
+        }
+    };
+    if (is_long) {
+        const uint32_t total = (uint32_t)uniform_load(L.group_ptr, g + 1) - first;
+        if (wave == 0) sh_len[lane] = n;
+        __syncthreads();
+        int32_t k;
+        uint32_t base;
+        cut_rounds(sh_len, (uint32_t)(((uint64_t)total * (uint32_t)wave) / kWaves), lane, k, base);
+        base += first;
+        if (lane == 0) sh_cut_k[wave] = k;
+        if (threadIdx.x == 0) sh_cut_k[kWaves] = 0x10000;
+        __syncthreads();
+        walk(base, min(n, sh_cut_k[wave + 1]), k);
+    } else if constexpr (WPG == 1) {
+        walk(first, n, 0);
+    } else {
+        uint32_t base = first;
+        for (int32_t k = U * part; __ballot(k < n); k += U * WPG) {
+            if (WPG > 1 && k > 0) {  // position of round k
+                uint32_t before = (uint32_t)min(n, k);
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1) before += __shfl_xor(before, d);
+                base = first + before;
+            }
+            acc += add_steps(base, n, k);
+        }
+    }
+    if (WPG > 1 || is_long) {
+        const int count = is_long ? kWaves : WPG;
+        sh_sum[threadIdx.x] = acc;
+        __syncthreads();
+        if (part != 0) return;
+        for (int w = 1; w < count; w++) acc += sh_sum[(wave + w) * 64 + lane];
+    }
+    if (mine) {
+        partial[s0 + lane] = acc;
+        if constexpr (DIRECT) y[(int64_t)bm * L.R + row] = acc;
     }
 }
 
@@ -1118,9 +1289,30 @@ static int launch_part_u(const hbp_handle_s *h, const Layout &L, const T *x, T *
 }
 
 template <typename T>
+static int launch_flat(const hbp_handle_s *h, const Layout &L, const T *x, T *y, hipStream_t st, SpmvScratch sc)
+{
+    const bool direct = h->NBC == 1;
+    auto go = [&](auto wpg) {
+        constexpr int WPG = decltype(wpg)::value, U = 8, kGroups = 16 / WPG;
+        const int32_t group_wgs = (int32_t)((h->G + kGroups - 1) / kGroups), n_long = h->n_long;
+        if (direct) {
+            const int64_t wgs = (int64_t)n_long + group_wgs + (h->S < h->n_rows ? h->NBR : 0);
+            k_spmv_flat<WPG, U, true, T><<<dim3((unsigned)wgs), 1024, 0, st>>>(L, x, static_cast<T *>(sc.partial), y, n_long, group_wgs);
+        } else {
+            k_spmv_flat<WPG, U, false, T><<<dim3((unsigned)(n_long + group_wgs)), 1024, 0, st>>>(L, x, static_cast<T *>(sc.partial), y, n_long, group_wgs);
+        }
+    };
+    if (h->flat_wpg == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 4>{});
+    HBP_HIP(hipGetLastError());
+    return HBP_OK;
+}
+
+template <typename T>
 static int launch_part_t(const hbp_handle_s *h, const T *x, T *y, hipStream_t st, SpmvScratch sc)
 {
     const Layout L = hbp_view(h);
+    if (h->flat_wpg) return launch_flat<T>(h, L, x, y, st, sc);
     // the kernel that can share heavy groups among a worker's wavefronts only where the matrix has one
     if (h->longest_segment > long_rounds_of(h->heavy_rounds)) {
         if (h->threads == 1024) return launch_part_u<1024, true, T>(h, L, x, y, st, sc);
@@ -1137,6 +1329,7 @@ static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScr
 {
     const Layout L = hbp_view(h);
     const T *partial = static_cast<const T *>(sc.partial);
+    if (h->flat_wpg && h->NBC == 1) return HBP_OK;  // k_spmv_flat has written y
     if (h->R <= 1024) {
         // two copies of a short slice: enough workgroups per CU for the plain block-by-block walk
         k_combine<128, T, 0, 0><<<dim3((unsigned)h->U), 128, 2 * (size_t)h->R * sizeof(T), st>>>(L, partial, y, sc.ticket);

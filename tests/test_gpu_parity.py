@@ -546,3 +546,43 @@ def test_maximum_workers(H, oracle):
     with pytest.raises(H.HbpError) as e:
         H.hbp_build(ptr, col, val, m.n_rows, m.n_cols, num_workers=65537)
     assert e.value.status == -1
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("lens,n_cols,R,C,W", [
+    ([1], 1, 512, 512, 64),                                          # a single nonzero
+    ([0, 0, 3, 0], 5, 2, 8, 64),                                     # empty row blocks, empty first and last rows
+    ([5] * 1000 + [0] * 40 + [4] * 30, 600, 512, 1024, 64),          # one wavefront per group, rows without a slot
+    ([5] * 1000 + [0] * 40 + [4] * 30, 600, 512, 100, 64),           # the same over several block columns
+    ([32] * 64 + [33] * 64 + [31] * 7, 4096, 512, 4096, 64),         # 2048 nonzeros a group, and 64 more
+    ([64] * 20 + [65] * 20 + [9] * 100, 3000, 64, 3000, 20),         # rows around 64 nonzeros, narrow groups
+    ([1] * 300 + [3000, 2500, 17] + [2] * 300, 4000, 512, 4000, 64), # a long group that is nearly all one row
+    ([1] * 300 + [3000, 2500, 17] + [2] * 300, 4000, 200, 1500, 64),
+    ([700] * 130, 1400, 8, 1400, 3),                                 # more long groups than others
+])
+def test_small_matrices_without_workers(H, oracle, lens, n_cols, R, C, W, f64):
+    """Small matrices run without the workers' schedule: one wavefront or four per group, a workgroup
+    for a long group, y written directly where there is one block column."""
+    from workloads import CsrMatrix, widen_to_f64
+    rng = np.random.default_rng(len(lens) + n_cols)
+    lens = np.asarray(lens)
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    m = CsrMatrix("small", len(lens), n_cols, np.r_[0, np.cumsum(lens)].astype(np.int32), col,
+                  rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    if f64:
+        m = widen_to_f64(m)
+    check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C, group_width=W)
+    # an infinity in x reaches the rows that hold its column and no other
+    import torch
+    ptr, cols, val, x = to_dev(m)
+    c = int(m.col[len(m.col) // 2])
+    x[c] = float("inf")
+    build, spmv = (H.hbp_build_f64, H.hbp_spmv_f64) if f64 else (H.hbp_build, H.hbp_spmv)
+    h = build(ptr, cols, val, m.n_rows, m.n_cols, rows_per_block=R, cols_per_block=C, group_width=W)
+    try:
+        y = torch.zeros(m.n_rows, device="cuda", dtype=x.dtype)
+        spmv(h, x, y)
+        rows = np.repeat(np.arange(m.n_rows), lens)
+        assert np.array_equal(np.flatnonzero(~np.isfinite(y.cpu().numpy())), rows[m.col == c])
+    finally:
+        H.hbp_free(h)
