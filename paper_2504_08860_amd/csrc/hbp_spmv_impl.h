@@ -1324,6 +1324,8 @@ static int launch_part_t(const hbp_handle_s *h, const T *x, T *y, hipStream_t st
     return launch_part_u<256, false, T>(h, L, x, y, st, sc);
 }
 
+constexpr int kCombineLds = 4 * kMaxR * (int)sizeof(float);
+
 template <typename T>
 static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScratch sc)
 {
@@ -1334,18 +1336,28 @@ static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScr
         // two copies of a short slice: enough workgroups per CU for the plain block-by-block walk
         k_combine<128, T, 0, 0><<<dim3((unsigned)h->U), 128, 2 * (size_t)h->R * sizeof(T), st>>>(L, partial, y, sc.ticket);
     } else {
-        // four copies (up to 128 KB: kMaxR floats or kMaxR64 doubles); a ring of chunks in flight,
-        // shorter chunks and more of them where the blocks hold few slots on average
-        auto go = [&](auto kr, auto kc, std::atomic<uint64_t> &configured) {
-            constexpr int KR = decltype(kr)::value, KC = decltype(kc)::value;
-            const int rc = raise_lds_cap(configured, h->device, k_combine<256, T, KR, KC>, 4 * kMaxR * (int)sizeof(float));
+        // a copy per wavefront (up to 128 KB in all: kMaxR floats or kMaxR64 doubles for four of them); a ring
+        // of chunks in flight, shorter chunks and more of them where the blocks hold few slots on average
+        auto go = [&](auto kt, auto kr, auto kc) {
+            constexpr int KT = decltype(kt)::value, KR = decltype(kr)::value, KC = decltype(kc)::value;
+            static std::atomic<uint64_t> configured{0};  // per instantiation
+            const int rc = raise_lds_cap(configured, h->device, k_combine<KT, T, KR, KC>, kCombineLds);
             if (rc != HBP_OK) return rc;
-            k_combine<256, T, KR, KC><<<dim3((unsigned)h->U), 256, 4 * (size_t)h->R * sizeof(T), st>>>(L, partial, y, sc.ticket);
+            k_combine<KT, T, KR, KC><<<dim3((unsigned)h->U), KT, KT / 64 * (size_t)h->R * sizeof(T), st>>>(L, partial, y, sc.ticket);
             return (int)HBP_OK;
         };
-        static std::atomic<uint64_t> configured_long{0}, configured_short{0};
-        const int rc = h->S < 128 * h->B ? go(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{}, configured_short)
-                                         : go(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{}, configured_long);
+        auto pick = [&](auto kt) {
+            return h->S < 128 * h->B ? go(kt, std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{})
+                                     : go(kt, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+        };
+        // Few units: more wavefronts for each, as many as the copies' LDS lets one workgroup (up to 256 units, one
+        // per CU) or two of them (up to 512) have on a CU.  Whole products, us, four wavefronts per unit / now: 3.6M nonzeros
+        // in 74 units 51.6 / 47.0, 12.8M in 196 units 56.3 / 50.2; fp64 3.7M in 74 units 50.8 / 47.3.  (One workgroup
+        // of eight per CU for 489 fp64 units: combine part 12.1 / 17.7, hence the second bound.)
+        const int64_t copy = (int64_t)h->R * (int64_t)sizeof(T);
+        const int rc = h->U <= 256 && 16 * copy <= kCombineLds  ? pick(std::integral_constant<int, 1024>{})
+                       : (h->U <= 256 && 8 * copy <= kCombineLds) || (h->U <= 512 && 16 * copy <= kCombineLds) ? pick(std::integral_constant<int, 512>{})
+                                                                : pick(std::integral_constant<int, 256>{});
         if (rc != HBP_OK) return rc;
     }
     HBP_HIP(hipGetLastError());
