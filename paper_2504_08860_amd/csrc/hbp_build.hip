@@ -860,7 +860,8 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
         if (lane == 0) {
             group_nnz[g0 + gi] = sum;
             group_longest[g0 + gi] = longest;
-            if (longest > heavy_rounds) atomicMax(longest_all, longest);  // only that long rows matter to the caller
+            // only that long rows matter to the caller; most of them are not the longest so far
+            if (longest > heavy_rounds && longest > *(volatile uint32_t *)longest_all) atomicMax(longest_all, longest);
             group_slot[g0 + gi] = s0 + gi * W;
             group_blk[g0 + gi] = b;
             if (long_groups && is_long_group((int32_t)sum, (int32_t)longest, flat_wpg)) listed[atomicAdd(&sh_long_n, 1u)] = g0 + gi;
@@ -1579,7 +1580,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_HIP(hipFuncSetAttribute((const void *)k_order_block, hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds));
     k_order_block<<<dim3((unsigned)B), 256, order_lds, st>>>(bucket_len_row, bucket_j, h->slot_ptr, h->blk_group_ptr, W,
                                                             h->row_local, h->seg_len, slot_j, group_nnz, group_longest, h->group_slot,
-                                                            h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds), longest_all,
+                                                            h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all,
                                                             d_n_long, h->long_groups, h->flat_wpg, reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);
     HBP_TRY(exclusive_scan<kOpIdentity>(group_nnz, (uint32_t *)h->group_ptr, G, 1, scan_tmp, st));
     HBP_TRY(exclusive_scan<kOpIdentity>(group_longest, (uint32_t *)h->group_rounds, G, 1, scan_tmp, st));

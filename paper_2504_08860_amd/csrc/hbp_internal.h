@@ -14,8 +14,18 @@ constexpr int kMaxC = 32768;         // columns per block: fp32 vector segment o
 constexpr int kMaxC64 = 16384;       // the same 128 KB with fp64 values
 constexpr int kMaxR64 = 4096;        // fp64: the combine part keeps four copies of a y slice in LDS
 constexpr int64_t kMaxDense = int64_t(1) << 27;  // NBR * NBC table entries
-// rows longer than this (and up to heavy_group_rounds) make their group a "long" one
-inline int32_t long_rounds_of(int32_t heavy_rounds) { return heavy_rounds / 8 > 0 ? heavy_rounds / 8 : 1; }
+// Rows longer than long_rounds_of (and up to heavy_group_rounds) make their group a "long" one.  Where a worker has
+// few groups they are walked first, so that the others fill up the wavefronts that are done with theirs; the worker's
+// start then waits for its slice of x (2 us), and where it has many groups the long ones are lost among them.
+// Measured, us per product, after the others from 256 rounds on / first from 32 rounds on (groups per worker): lognormal rows
+// 400K x 100K (72) 70 / 46, fp64 (120) 66 / 57, 1.2M x 300K (473) 103 / 92, 4M x 1M (3037) 285 / 297; R-MAT 2^20 (241)
+// 120 / 114, fp64 (340) 119.6 / 121.5, 2^22 (1785) 299 / 309.
+inline bool walk_long_first(int64_t G, int64_t P) { return G < 1024 * P; }
+inline int32_t long_rounds_of(int32_t heavy_rounds, bool long_first)
+{
+    const int32_t rounds = heavy_rounds / (long_first ? 64 : 8);
+    return rounds > 0 ? rounds : 1;
+}
 
 // Matrices small enough for k_spmv_flat (one group after the other across the grid, x read from L2) in
 // place of k_spmv_part (persistent workers with x staged in LDS): the wavefronts it gives a group, or 0.
@@ -55,7 +65,8 @@ struct Layout {
     int32_t SW, RW, GW;  // schedule weights of a slot, a round, a group (a nonzero weighs 1)
     int32_t steal_min;   // weight a range's competitive part must have left for another worker to enter it
     int32_t heavy_rounds;  // a group with a longer row is walked by all wavefronts of a worker together
-    int32_t long_rounds;   // a group with a longer row (up to heavy_rounds) waits for a wavefront of its own
+    int32_t long_rounds;   // a group with a longer row (up to heavy_rounds) gets a wavefront of its own
+    int32_t lists_first;   // and is walked, like the heavy ones, before the other groups of its range
     const uint16_t *row_local, *seg_len, *col_local;
     const void *data;  // float or double, by the handle's value type
 };

@@ -40,7 +40,8 @@ Layout hbp_view(const hbp_handle_s *h)
     L.SW = h->slot_weight; L.RW = h->round_weight; L.GW = h->group_weight;
     L.steal_min = 2 * h->column_weight;
     L.heavy_rounds = h->heavy_rounds;
-    L.long_rounds = long_rounds_of(h->heavy_rounds);
+    L.lists_first = walk_long_first(h->G, h->P) ? 1 : 0;
+    L.long_rounds = long_rounds_of(h->heavy_rounds, L.lists_first);
     return L;
 }
 

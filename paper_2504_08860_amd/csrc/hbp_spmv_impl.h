@@ -174,6 +174,12 @@ __device__ __forceinline__ void consume_wide(const WideBatch<CH, T> &b, const T 
     }
 }
 
+// An element on its way to the lane of its row.
+template <typename T>
+struct alignas(2 * sizeof(T)) Routed {
+    T v, x;
+};
+
 // Where to cut a group so that `target` of its nonzeros lie in front: the smallest round k with at
 // least that many nonzeros in the rounds 0 .. k-1, and their number.  lens: the 64 rows' lengths, in LDS.
 __device__ __forceinline__ void cut_rounds(const int32_t *lens, uint32_t target, int lane, int32_t &cut_k, uint32_t &cut_pos)
@@ -219,13 +225,17 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_dry;   // nothing more to claim from the current competitive part
     __shared__ int32_t sh_lock;  // end of the last range reported as used up
     __shared__ int32_t sh_col[3];  // whose competitive part is being claimed, its first group, its end
-    __shared__ T sh_hand[THREADS];  // per wavefront: hand-over of span sums to the owning lanes
+    // per wavefront: elements (value, x) on their way to the lanes of their rows, or 64 sums
+    constexpr int kRoute = sizeof(T) == 4 ? 192 : 96;
+    __shared__ Routed<T> sh_route[THREADS / 64 * kRoute + 1];
     constexpr int kHeavyCap = 64;
     __shared__ int32_t sh_heavy[kHeavyCap];  // heavy groups of the current range, left to the whole worker
-    __shared__ int32_t sh_heavy_n;
     constexpr int kLongCap = 256;
     __shared__ int32_t sh_long[kLongCap];  // long groups of the current range, each left to the next free wavefront
-    __shared__ int32_t sh_long_n, sh_long_next;
+    // the same for the groups the range begins with, as offsets from its first group: known before it is walked
+    constexpr int kFirstHeavyCap = 64, kFirstLongCap = 1024;
+    __shared__ uint16_t sh_first_heavy[kFirstHeavyCap], sh_first_long[kFirstLongCap];
+    __shared__ int32_t sh_heavy_n[2], sh_long_n[2], sh_long_next[2];  // 0: known before, 1: found among the claimed groups
     __shared__ int32_t sh_lens[THREADS];  // per wavefront: segment lengths of the heavy group being cut
     __shared__ int32_t sh_cut_k[THREADS / 64 + 1];   // heavy group: first round of every wavefront's share
     __shared__ uint32_t sh_cut_pos[THREADS / 64 + 1];  // and the nonzeros before that round
@@ -245,30 +255,26 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         worker = (((i >> 2) << 3) + xcd) * 4 + (i & 3);
     }
 
-    // Copies the vector segment of block column bn into LDS (no barriers: the caller orders it).
+    // Starts the copy of the vector segment of block column bn into LDS: 16-byte loads that write LDS
+    // themselves (no registers, nothing to wait for here) when the slice is 16-byte aligned.
+    // The caller waits (wait_slice) and orders it with barriers.  (R-MAT 2^22 309 -> 300 us against loads
+    // into registers and stores to LDS.)
     auto copy_slice = [&](int32_t bn) __attribute__((always_inline)) {
         const int64_t c0 = (int64_t)bn * L.C;
         const int32_t width = (int32_t)min((int64_t)L.C, L.n_cols - c0);
-        // 16-byte loads, eight in flight per thread, when the slice is 16-byte aligned
-        typedef T vec16 __attribute__((ext_vector_type(16 / sizeof(T))));
         constexpr int32_t kPer = 16 / (int32_t)sizeof(T);
         const T *src = x + c0;
         const int32_t n4 = (reinterpret_cast<uintptr_t>(src) & 15u) == 0 ? width / kPer : 0;
-        for (int32_t i0 = 0; i0 < n4; i0 += THREADS * 8) {
-            vec16 t[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int32_t i = min(i0 + u * THREADS + (int32_t)threadIdx.x, n4 - 1);
-                t[u] = reinterpret_cast<const vec16 *>(src)[i];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int32_t i = i0 + u * THREADS + (int32_t)threadIdx.x;
-                if (i < n4) reinterpret_cast<vec16 *>(xs)[i] = t[u];
-            }
+        typedef __attribute__((address_space(1))) const uint32_t *global_ptr;
+        typedef __attribute__((address_space(3))) uint32_t *lds_ptr;
+        for (int32_t i0 = wave * 64; i0 < n4; i0 += THREADS) {  // a wavefront's 64 quads land side by side
+            const int32_t i = i0 + lane;
+            if (i < n4)
+                __builtin_amdgcn_global_load_lds((global_ptr)(uintptr_t)(src + kPer * i), (lds_ptr)(uint32_t)(uintptr_t)(xs + kPer * i0), 16, 0, 0);
         }
         for (int32_t i = kPer * n4 + threadIdx.x; i < width; i += THREADS) xs[i] = src[i];
     };
+    auto wait_slice = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };  // vmcnt(0)
 
     // The wavefronts of the worker share out the groups [*, g_end) of the current range by
     // drawing packs of GP consecutive groups from an LDS counter (wavefronts do not progress at
@@ -353,10 +359,57 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         pack_end = GP == 1 ? v + 1 : min(v + GP, end);
         return v;
     };
+    // The rest of a group, rounds from k on, `count` <= kRoute elements from `base` on: the wavefront reads them
+    // side by side and every lane picks the elements of its row out of LDS, round by round.  (A group of short rows
+    // with one or a few longer ones has most of its lanes idle after a few rounds: of the 8 % of the groups of the 4M x 1M
+    // lognormal matrix with more than 16 rounds 18 % of the lanes are alive.  Round by round they waited for memory
+    // every 16 rounds, two loads a round; product 295 -> 285 us.)
+    auto route = [&](uint32_t base, uint32_t count, int32_t n, int32_t k, T &acc) __attribute__((always_inline)) {
+        constexpr int E = (kRoute + 63) / 64;
+        Routed<T> *const way = sh_route + wave * kRoute;
+        uint32_t c[E];
+        T v[E];
+#pragma unroll
+        for (int u = 0; u < E; u++) {
+            c[u] = 0;
+            v[u] = T(0);
+            if (64u * u < count) {  // wave-uniform
+                const uint32_t o = base + min(64u * u + (uint32_t)lane, count - 1u);
+                c[u] = __builtin_nontemporal_load(L.col_local + o);
+                v[u] = __builtin_nontemporal_load(data + o);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < E; u++)
+            if (64u * u + (uint32_t)lane < count) way[64 * u + lane] = {v[u], xs[c[u]]};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        uint32_t off = 0;
+        for (; __ballot(k < n); k += 4) {
+            Routed<T> e[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const uint64_t live = __ballot(k + t < n);
+                e[t] = way[off + (uint32_t)lanes_below(live)];  // (a lane without one: some entry, or the one behind the last)
+                off += (uint32_t)__popcll(live);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const T more = fma_of(e[t].v, e[t].x, acc);
+                acc = k + t < n ? more : acc;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     // Rounds k, k+1, ... of one group until no lane has a nonzero left (lane q has n; `base` is
-    // the position of round k), added into acc.
-    auto walk_rounds = [&](uint32_t &base, int32_t n, int32_t k, T &acc) __attribute__((always_inline)) {
+    // the position of round k, `end` the one behind the last element), added into acc.
+    auto walk_rounds = [&](uint32_t &base, uint32_t end, int32_t n, int32_t k, T &acc) __attribute__((always_inline)) {
         for (;;) {
+            if (end - base <= (uint32_t)kRoute) {
+                if (end != base) route(base, end - base, n, k, acc);
+                break;
+            }
             const uint64_t live = __ballot(k < n);
             if (!live) break;
             const int32_t m = __popcll(live);
@@ -381,7 +434,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 // rounds are exactly what one step of a batch reads, so the batch code runs
                 // unchanged on the folded lanes' own counts and covers UL * f rounds.
                 const int sh = m > 16 ? 5 : m > 8 ? 4 : m > 4 ? 3 : m > 2 ? 2 : m > 1 ? 1 : 0;  // mm = 2^sh
-                int32_t *left = reinterpret_cast<int32_t *>(sh_hand + wave * 64);
+                int32_t *left = reinterpret_cast<int32_t *>(sh_route + wave * kRoute);
                 left[lane] = 0;
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
@@ -394,7 +447,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 __builtin_amdgcn_wave_barrier();
                 Batch<UL, T> deep;
                 issue_batch<UL>(deep, L.col_local, data, base, steps, 0);
-                T *hand = sh_hand + wave * 64;
+                T *hand = reinterpret_cast<T *>(sh_route + wave * kRoute);
                 hand[lane] = consume_batch<UL, true>(deep, xs, steps, 0);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
@@ -432,7 +485,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 }
                 for (; o < span; o += S) sum += data[base + o] * xs[L.col_local[base + o]];
             }
-            T *hand = sh_hand + wave * 64;
+            T *hand = reinterpret_cast<T *>(sh_route + wave * kRoute);
             hand[lane] = sum;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -444,28 +497,102 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             k = k_end;
         }
     };
-    // Runs the groups [g_begin, g_end) of block column bn with all wavefronts of the worker.
-    auto run_range = [&](int32_t bn, int32_t g_begin, int32_t g_end, bool compete, int32_t owner) __attribute__((always_inline)) {
+    // Runs the groups [g_begin, g_end) of block column bn with all wavefronts of the worker; where it
+    // competes, the groups claimed afterwards come from worker `owner`'s [c_lo, c_end).
+    auto run_range = [&](int32_t bn, int32_t g_begin, int32_t g_end, bool compete, int32_t owner, int32_t c_lo, int32_t c_end) __attribute__((always_inline)) {
         __syncthreads();  // every wavefront has left the previous range (and its slice of x)
         if (threadIdx.x == 0) {
             sh_rng = ((unsigned long long)(uint32_t)g_end << 32) | (uint32_t)g_begin;
             sh_dry = compete ? 0 : 1;
             sh_lock = -1;
-            sh_heavy_n = 0;
-            sh_long_n = 0;
-            sh_long_next = 0;
+            sh_heavy_n[0] = sh_heavy_n[1] = 0;
+            sh_long_n[0] = sh_long_n[1] = 0;
+            sh_long_next[0] = sh_long_next[1] = 0;
             sh_col[0] = owner;  // whose competitive groups are claimed from here on
-            sh_col[1] = L.comp_lo[owner];
-            sh_col[2] = L.fixed_start[owner + 1];
+            sh_col[1] = c_lo;
+            sh_col[2] = c_end;
         }
         stop = false;
         __syncthreads();
+        bool first_heavy = false, first_long = false;  // are the range's own heavy and long groups on the lists?
+        if (HEAVY && bn != staged_bn) copy_slice(bn);
+        if (HEAVY && L.lists_first) {
+            for (int32_t i = g_begin + (int32_t)threadIdx.x; i < g_end; i += THREADS) {
+                const int32_t longest = L.group_rounds[i + 1] - L.group_rounds[i];
+                if (longest > L.long_rounds) {
+                    const bool heavy = longest > L.heavy_rounds;
+                    const int32_t idx = atomicAdd(heavy ? &sh_heavy_n[0] : &sh_long_n[0], 1);
+                    if (idx < (heavy ? kFirstHeavyCap : kFirstLongCap)) (heavy ? sh_first_heavy : sh_first_long)[idx] = (uint16_t)(i - g_begin);
+                }
+            }
+            wait_slice();
+            __syncthreads();
+            staged_bn = bn;
+            first_heavy = sh_heavy_n[0] <= kFirstHeavyCap && g_end - g_begin <= 65536;
+            first_long = sh_long_n[0] <= kFirstLongCap && g_end - g_begin <= 65536;
+        }
+        // (HEAVY: the listed groups, the others, what the claims brought)
+        for (int pass = 0;; pass++) {
+        if constexpr (HEAVY) {
+            // Heavy groups: all wavefronts of the worker walk each of them together.  Wavefront w takes
+            // the rounds [k_w, k_{w+1}), where k_w is the first round that has w / kWaves of the group's
+            // nonzeros before it, and the per-lane sums of the wavefronts are added in LDS in wavefront order.
+            const int32_t n_heavy = pass ? min(sh_heavy_n[1], kHeavyCap) : first_heavy ? sh_heavy_n[0] : 0;
+            for (int32_t i = 0; i < n_heavy; i++) {
+                const int32_t gh = __builtin_amdgcn_readfirstlane(pass ? sh_heavy[i] : g_begin + (int32_t)sh_first_heavy[i]);
+                const int32_t hs0 = uniform_load(L.group_slot, gh), hs1 = uniform_load(L.group_slot, gh + 1);
+                const uint32_t b0 = (uint32_t)uniform_load(L.group_ptr, gh);
+                const uint32_t total = (uint32_t)uniform_load(L.group_ptr, gh + 1) - b0;
+                const int32_t len = hs0 + lane < hs1 ? (int32_t)L.seg_len[hs0 + lane] : 0;
+                int32_t *lens = sh_lens + wave * 64;
+                lens[lane] = len;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                int32_t cut_k;
+                uint32_t cut_pos;
+                cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)wave) / (uint32_t)kWaves), lane, cut_k, cut_pos);
+                if (lane == 0) { sh_cut_k[wave] = cut_k; sh_cut_pos[wave] = cut_pos; }
+                if (threadIdx.x == 0) { sh_cut_k[kWaves] = 0x10000; sh_cut_pos[kWaves] = total; }
+                __syncthreads();
+                const int32_t k_lo = sh_cut_k[wave], k_hi = sh_cut_k[wave + 1];
+                uint32_t pos = b0 + sh_cut_pos[wave];
+                T sum = T(0);
+                walk_rounds(pos, b0 + sh_cut_pos[wave + 1], min(len, k_hi), k_lo, sum);
+                __syncthreads();  // sh_route becomes the wavefronts' sums
+                T *const sums = reinterpret_cast<T *>(sh_route);
+                sums[threadIdx.x] = sum;
+                __syncthreads();
+                if (wave == 0 && hs0 + lane < hs1) {
+                    T total_sum = sums[lane];
+#pragma unroll
+                    for (int w = 1; w < kWaves; w++) total_sum += sums[w * 64 + lane];
+                    partial[hs0 + lane] = total_sum;
+                }
+                __syncthreads();  // the sums and the cuts are reused by the next heavy group
+            }
+            // Long groups: one wavefront each, whoever is free next.
+            const int32_t n_long = pass ? min(sh_long_n[1], kLongCap) : first_long ? sh_long_n[0] : 0;
+            while (n_long > 0) {
+                int32_t i = 0;
+                if (lane == 0) i = atomicAdd(&sh_long_next[pass], 1);
+                i = __builtin_amdgcn_readfirstlane(i);
+                if (i >= n_long) break;
+                const int32_t gl = __builtin_amdgcn_readfirstlane(pass ? sh_long[i] : g_begin + (int32_t)sh_first_long[i]);
+                const int32_t ls0 = uniform_load(L.group_slot, gl), ls1 = uniform_load(L.group_slot, gl + 1);
+                uint32_t pos = (uint32_t)uniform_load(L.group_ptr, gl);
+                const int32_t len = ls0 + lane < ls1 ? (int32_t)L.seg_len[ls0 + lane] : 0;
+                T sum = T(0);
+                walk_rounds(pos, (uint32_t)uniform_load(L.group_ptr, gl + 1), len, 0, sum);
+                if (ls0 + lane < ls1) partial[ls0 + lane] = sum;
+            }
+            if (pass == 1) break;
+        }
         int32_t e = 0, e1 = 0, e2 = 0;  // ends of the packs g, g1, g2: group g + q exists if it is below e
         int32_t g = draw_resolve(draw_issue(), e), g1 = draw_resolve(draw_issue(), e1), g2 = kNone;
         unsigned long long raw2 = draw_issue();
         int32_t s0[GP], s1[GP], n[GP], done_slot[GP];
         // The slot ranges and first positions of a pack's groups travel in one vector register per
-        // pack: lane l <= GP holds group_slot[first + l], lane 32 + l (l < GP) holds
+        // pack: lane l <= GP holds group_slot[first + l], lane 32 + l holds
         // group_ptr[first + l], zero where the pack has no such group; they are read out into
         // scalars where they are used.  (Loaded as scalars and carried three packs deep they did
         // not fit the scalar registers: the spills cost some fifty instructions per pack and made
@@ -474,7 +601,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             uint32_t m = 0;
             const int32_t l = lane & 31;
             const bool position = lane >= 32;
-            if (first != kNone && l <= GP && l < end - first + (position ? 0 : 1))
+            if (first != kNone && l <= GP && l <= end - first)
                 m = (uint32_t)(position ? L.group_ptr : L.group_slot)[first + l];
             return m;
         };
@@ -484,7 +611,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             to = there ? (int32_t)__builtin_amdgcn_readlane(m, q + 1) : 0;
         };
         auto meta_base = [&](uint32_t m, int32_t first, int32_t end, int q) __attribute__((always_inline)) {
-            return in_pack(first, end, q) ? (uint32_t)__builtin_amdgcn_readlane(m, 32 + q) : 0u;
+            return q == 0 || in_pack(first, end, q - 1) ? (uint32_t)__builtin_amdgcn_readlane(m, 32 + q) : 0u;
         };
         uint32_t meta = load_meta(g, e), meta_n = load_meta(g1, e1);  // of the packs g and g1
         // Packs of short rows have a path of their own in the fp64 kernels.  (In fp32 it measured
@@ -514,9 +641,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         }
         pack_longest = longest_in_pack(g, e);
         pack_longestn = longest_in_pack(g1, e1);
-        // the first packs' metadata is on its way while the slice of x is staged
+        // (without lists the slice starts here, behind the first packs' lengths: loads return in order, and in front of
+        // them it would delay them; 27-point grid of 67^3 29.6 against 28.6 us)
         if (bn != staged_bn) {
-            copy_slice(bn);
+            if (!HEAVY) copy_slice(bn);
+            wait_slice();
             __syncthreads();
             staged_bn = bn;
         }
@@ -529,23 +658,27 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 meta_slots(meta, g, e, q, s0[q], s1[q]);
                 base[q] = meta_base(meta, g, e, q);
             }
-            // A group with a row of more than heavy_rounds nonzeros would keep this wavefront busy
-            // long after the rest of the worker has run dry: it goes on the worker's heavy list and
-            // looks empty here (unless the list is full: then this wavefront walks it alone).  A
-            // group with a row of more than long_rounds goes on the long list: such groups come in
-            // runs (the last groups of a block), a pack would hand several of them to one
-            // wavefront to walk one after the other, and they are taken one per wavefront instead
-            // once the range's other groups are done.
+            // A group with a row of more than heavy_rounds nonzeros would keep this wavefront busy long
+            // after the rest of the worker has run dry, and groups with rows of more than long_rounds come
+            // in runs (the last groups of a block), of which a pack hands several to one wavefront to walk
+            // one after the other.  Those that the range began with have been walked before (unless they
+            // did not fit the lists) and look empty here; among the claimed ones the heavy ones go on the
+            // worker's heavy list, the long ones on the long list (unless it is full), which are walked
+            // when the range's other groups are done.
             if (HEAVY && (!kShortPacks || pack_longest > L.long_rounds)) {
 #pragma unroll
                 for (int q = 0; q < GP; q++) {
                     if (__ballot(n[q] > L.long_rounds)) {
                         const bool heavy = __ballot(n[q] > L.heavy_rounds) != 0;
-                        int32_t idx = 0;
-                        if (lane == 0) idx = atomicAdd(heavy ? &sh_heavy_n : &sh_long_n, 1);
-                        idx = __builtin_amdgcn_readfirstlane(idx);
-                        if (idx < (heavy ? kHeavyCap : kLongCap)) {
-                            if (lane == 0) (heavy ? sh_heavy : sh_long)[idx] = g + q;
+                        bool listed = heavy ? first_heavy : first_long;
+                        if (g + q >= g_end || !L.lists_first) {
+                            int32_t idx = 0;
+                            if (lane == 0) idx = atomicAdd(heavy ? &sh_heavy_n[1] : &sh_long_n[1], 1);
+                            idx = __builtin_amdgcn_readfirstlane(idx);
+                            listed = idx < (heavy ? kHeavyCap : kLongCap);
+                            if (listed && lane == 0) (heavy ? sh_heavy : sh_long)[idx] = g + q;
+                        }
+                        if (listed) {
                             n[q] = 0;
                             s1[q] = s0[q];
                         }
@@ -653,7 +786,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 for (int q = 0; q < GP; q++) {  // rows longer than U, one group at a time
                     // (the test keeps what the compiler hoists out of the walk's loops, a dozen
                     // values per group, off the path of the groups without such rows)
-                    if (__ballot(U < n[q])) walk_rounds(base[q], n[q], U, acc[q]);
+                    if (__ballot(U < n[q])) walk_rounds(base[q], meta_base(meta, g, e, q + 1), n[q], U, acc[q]);
                     slot[q] = s0[q] + lane < s1[q] ? s0[q] + lane : -1;
                 }
             }
@@ -673,59 +806,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         for (int q = 0; q < GP; q++)
             if (done_slot[q] >= 0) partial[done_slot[q]] = done_acc[q];
 
-        // Heavy groups of this range: all wavefronts of the worker walk each of them together.
-        // Wavefront w takes the rounds [k_w, k_{w+1}), where k_w is the first round that has
-        // w / kWaves of the group's nonzeros before it, and the per-lane sums of the wavefronts
-        // are added in LDS in wavefront order.
-        if constexpr (!HEAVY) return;
+        if constexpr (!HEAVY) break;
         __syncthreads();
-        // Long groups of this range: one wavefront each, whoever is free next.
-        const int32_t n_long = min(sh_long_n, kLongCap);
-        if (n_long > 0) {
-            for (;;) {
-                int32_t i = 0;
-                if (lane == 0) i = atomicAdd(&sh_long_next, 1);
-                i = __builtin_amdgcn_readfirstlane(i);
-                if (i >= n_long) break;
-                const int32_t gl = sh_long[i];
-                const int32_t ls0 = uniform_load(L.group_slot, gl), ls1 = uniform_load(L.group_slot, gl + 1);
-                uint32_t pos = (uint32_t)uniform_load(L.group_ptr, gl);
-                const int32_t len = ls0 + lane < ls1 ? (int32_t)L.seg_len[ls0 + lane] : 0;
-                T sum = T(0);
-                walk_rounds(pos, len, 0, sum);
-                if (ls0 + lane < ls1) partial[ls0 + lane] = sum;
-            }
-        }
-        const int32_t n_heavy = min(sh_heavy_n, kHeavyCap);
-        for (int32_t i = 0; i < n_heavy; i++) {
-            const int32_t gh = sh_heavy[i];
-            const int32_t hs0 = uniform_load(L.group_slot, gh), hs1 = uniform_load(L.group_slot, gh + 1);
-            const uint32_t b0 = (uint32_t)uniform_load(L.group_ptr, gh);
-            const uint32_t total = (uint32_t)uniform_load(L.group_ptr, gh + 1) - b0;
-            const int32_t len = hs0 + lane < hs1 ? (int32_t)L.seg_len[hs0 + lane] : 0;
-            int32_t *lens = sh_lens + wave * 64;
-            lens[lane] = len;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            int32_t cut_k;
-            uint32_t cut_pos;
-            cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)wave) / (uint32_t)kWaves), lane, cut_k, cut_pos);
-            if (lane == 0) { sh_cut_k[wave] = cut_k; sh_cut_pos[wave] = cut_pos; }
-            if (threadIdx.x == 0) sh_cut_k[kWaves] = 0x10000;
-            __syncthreads();
-            const int32_t k_lo = sh_cut_k[wave], k_hi = sh_cut_k[wave + 1];
-            uint32_t pos = b0 + sh_cut_pos[wave];
-            T sum = T(0);
-            walk_rounds(pos, min(len, k_hi), k_lo, sum);
-            sh_hand[threadIdx.x] = sum;
-            __syncthreads();
-            if (wave == 0 && hs0 + lane < hs1) {
-                T total_sum = sh_hand[lane];
-#pragma unroll
-                for (int w = 1; w < kWaves; w++) total_sum += sh_hand[w * 64 + lane];
-                partial[hs0 + lane] = total_sum;
-            }
-            __syncthreads();  // sh_hand and the cuts are reused by the next heavy group
         }
     };
 
@@ -742,17 +824,17 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     //     that were faster than theirs;
     //   phase 3 instead of 2, the paper's schedule: one ticket counter over the blocks that were not pre-assigned.
     const bool competitive = L.competitive != 0;
-    int32_t col = L.fixed_col[worker];
-    int32_t g_next = L.fixed_start[worker];
-    const int32_t g_stop = L.fixed_start[worker + 1];
-    const int32_t own_lo = L.comp_lo[worker];
+    int32_t col = uniform_load(L.fixed_col, worker);
+    int32_t g_next = uniform_load(L.fixed_start, worker);
+    const int32_t g_stop = uniform_load(L.fixed_start, worker + 1);
+    const int32_t own_lo = uniform_load(L.comp_lo, worker);
     for (int phase = 0;;) {
-        int32_t r_bn = 0, r_g0 = 0, r_g1 = 0, r_owner = worker;
+        int32_t r_bn = 0, r_g0 = 0, r_g1 = 0, r_owner = worker, r_lo = own_lo, r_end = g_stop;
         bool r_compete = true;
         if (phase == 0) {
             bool found = false;
             while (g_next < g_stop && !found) {
-                const int32_t c_end = L.col_group_ptr[col + 1];
+                const int32_t c_end = uniform_load(L.col_group_ptr, col + 1);
                 if (g_next >= c_end) { col++; continue; }  // columns without groups
                 const int32_t ge = min(g_stop, c_end), fe = max(g_next, min(ge, own_lo));
                 const bool last = ge == g_stop;
@@ -826,8 +908,10 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             __syncthreads();  // sh_next is rewritten in the next turn
             if (r_owner < 0) break;
             r_bn = L.comp_col[r_owner];
+            r_lo = L.comp_lo[r_owner];
+            r_end = L.fixed_start[r_owner + 1];
         }
-        run_range(r_bn, r_g0, r_g1, r_compete, r_owner);
+        run_range(r_bn, r_g0, r_g1, r_compete, r_owner, r_lo, r_end);
     }
     // Row blocks that the combine part cuts into several units are summed into y with atomic
     // adds: their rows of y start at zero.  (Done last: in front of the first range it delays
@@ -1314,7 +1398,7 @@ static int launch_part_t(const hbp_handle_s *h, const T *x, T *y, hipStream_t st
     const Layout L = hbp_view(h);
     if (h->flat_wpg) return launch_flat<T>(h, L, x, y, st, sc);
     // the kernel that can share heavy groups among a worker's wavefronts only where the matrix has one
-    if (h->longest_segment > long_rounds_of(h->heavy_rounds)) {
+    if (h->longest_segment > L.long_rounds) {
         if (h->threads == 1024) return launch_part_u<1024, true, T>(h, L, x, y, st, sc);
         if (h->threads == 512) return launch_part_u<512, true, T>(h, L, x, y, st, sc);
         return launch_part_u<256, true, T>(h, L, x, y, st, sc);

@@ -586,3 +586,26 @@ def test_small_matrices_without_workers(H, oracle, lens, n_cols, R, C, W, f64):
         assert np.array_equal(np.flatnonzero(~np.isfinite(y.cpu().numpy())), rows[m.col == c])
     finally:
         H.hbp_free(h)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rounds,threads", [(4, 256), (8, 512)])
+@pytest.mark.parametrize("workers,W,lens", [
+    (2, 1, [2] * 1990 + [60] * 40),                       # more long groups in a range than its list holds
+    (1, 2, [2] * 2000 + [1, 9, 70, 3] * 40 + [1] * 700),  # many groups per worker: the lists come last
+    (3, 2, [2] * 2000 + [1, 9, 70, 3] * 40 + [1] * 700),  # few: the lists come first
+    (2, 64, [3] * 32 + [8] * 31 + [196] + [3] * 63 + [196, 99] + [4] * 62),  # rests of 192 elements and around (96 in fp64)
+])
+def test_long_groups_before_and_after_the_others(H, oracle, workers, W, lens, rounds, threads, f64):
+    from workloads import CsrMatrix, widen_to_f64
+    rng = np.random.default_rng(workers + W)
+    n_cols = 400
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    m = CsrMatrix("lists", len(lens), n_cols, np.r_[0, np.cumsum(lens)].astype(np.int32), col,
+                  rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    if f64:
+        m = widen_to_f64(m)
+    for q8, heavy in ((256, 64), (100, 16), (0, 2048)):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=4096, cols_per_block=n_cols, group_width=W,
+                             rounds_per_batch=rounds, threads_per_worker=threads, num_workers=workers, fixed_fraction_q8=q8,
+                             heavy_group_rounds=heavy, slot_weight=0, group_weight=0, round_weight=0, column_weight=0)
