@@ -27,8 +27,7 @@ struct DeviceGuard {  // makes the handle's device current for the duration of a
 
 void free_arrays(hbp_handle_s *h)
 {
-    for (void *p : h->arena)
-        if (p) (void)hipFree(p);
+    for (int i = 0; i < 2; i++) hbp::release_block(h->device, h->arena[i], h->arena_bytes[i]);
 }
 
 }  // namespace
@@ -111,9 +110,10 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     if (p.heavy_group_rounds == 0) p.heavy_group_rounds = 2048;
     const int32_t max_r = value_bytes == 8 ? hbp::kMaxR64 : hbp::kMaxR, max_c = value_bytes == 8 ? hbp::kMaxC64 : hbp::kMaxC;
     if (p.rows_per_block < 0 || p.cols_per_block < 0 || p.rows_per_block > max_r || p.cols_per_block > max_c) return HBP_ERR_INVALID_ARGUMENT;
+    int64_t nnz = -1;  // not known yet
     {
         // whatever was left to the library is chosen from the matrix now (one sampling pass)
-        const int rc_choice = hbp::choose_block_parameters(csr_ptr, csr_col, n_rows, n_cols, value_bytes, p, (hipStream_t)stream);
+        const int rc_choice = hbp::choose_block_parameters(csr_ptr, csr_col, n_rows, n_cols, value_bytes, p, &nnz, (hipStream_t)stream);
         if (rc_choice != HBP_OK) return rc_choice;
     }
     if (p.rows_per_block < 1 || p.rows_per_block > max_r || p.cols_per_block < 1 || p.cols_per_block > max_c ||
@@ -131,7 +131,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     if (!h) return HBP_ERR_OUT_OF_MEMORY;
     std::memset(h, 0, sizeof *h);
     if (hipGetDevice(&h->device) != hipSuccess) { delete h; return HBP_ERR_HIP; }
-    h->n_rows = n_rows; h->n_cols = n_cols;
+    h->n_rows = n_rows; h->n_cols = n_cols; h->nnz = nnz;
     h->value_bytes = value_bytes;
     h->flags = p.flags;
     h->scheduled = scheduled;
@@ -157,32 +157,6 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     }
     if (rc != HBP_OK) {
         (void)hipStreamSynchronize((hipStream_t)stream);
-        free_arrays(h);
-        delete h;
-        return rc;
-    }
-    {
-        // Schedule weights, in units of one nonzero, where the caller left them open.  They are costs of
-        // the SpMV-part kernel on MI355X, not properties of a matrix: measured over workers with very
-        // different mixes, a group costs a wavefront 18 ns, a round 3 ns, a slot 0.6 ns and entering a
-        // block column costs the worker 19 us, next to 0.03 ns per nonzero while the wavefront waits for
-        // its loads anyway (groups of a few hundred nonzeros).  Groups of 512 nonzeros and more are
-        // streamed at the worker's share of the memory bandwidth instead (0.3 ns per nonzero): the same
-        // costs are a tenth as many nonzeros there.
-        const bool streamed = h->G > 0 && h->nnz >= 512 * h->G;
-        h->slot_weight = p.slot_weight >= 0 ? p.slot_weight : streamed ? 2 : 20;
-        h->group_weight = p.group_weight >= 0 ? p.group_weight : streamed ? 60 : 600;
-        h->round_weight = p.round_weight >= 0 ? p.round_weight : streamed ? 10 : 100;
-        h->column_weight = p.column_weight >= 0 ? p.column_weight : streamed ? 60000 : 600000;
-    }
-    if (p.num_workers == 0) {
-        // device default: no more workers than the groups can keep busy, one group per wavefront
-        const int64_t waves = h->threads / hbp::kWave;
-        const int64_t useful = std::max<int64_t>(1, (h->G + waves - 1) / waves);
-        if (useful < h->P) h->P = (int32_t)useful;
-    }
-    rc = hbp::build_schedule(h, (hipStream_t)stream);
-    if (rc != HBP_OK) {
         free_arrays(h);
         delete h;
         return rc;

@@ -59,86 +59,107 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t *to
     return woff + inc - v;
 }
 
-// ------------------------------------------------------------------ device-wide exclusive scan
+// ------------------------------------------------------------------ device-wide exclusive scans
+//
+// Up to three scans of arrays of one length go through the same launches: the arrays are short (tens of
+// thousands of entries), so a scan costs its launches, some 5 us each, whatever it does.
 
-enum { kOpIdentity = 0, kOpCeilDivW = 1, kOpNonZero = 2 };
-template <int OP>
-__device__ __forceinline__ uint32_t scan_input(uint32_t v, uint32_t W)
+enum { kOpIdentity = 0, kOpCeilDivW = 1, kOpNonZero = 2, kOpAboveOne = 3 };
+__device__ __forceinline__ uint32_t scan_input(int32_t op, uint32_t v, uint32_t W)
 {
-    if (OP == kOpCeilDivW) return (v + W - 1) / W;
-    if (OP == kOpNonZero) return v ? 1u : 0u;
-    return v;
+    return op == kOpCeilDivW ? (v + W - 1) / W : op == kOpNonZero ? (v ? 1u : 0u) : op == kOpAboveOne ? (v > 1 ? 1u : 0u) : v;
 }
 
 constexpr int kScanTile = 2048;  // 256 threads x 8 consecutive items
 
-template <int OP>
-__global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t *__restrict__ in, int64_t n, uint32_t W,
-                                                     uint32_t *__restrict__ tile_sum)
+// out[0..n) = exclusive scan of op(in), out[n] = total.  `in` and `out` may alias where only one scan reads `in`.
+struct Scans {
+    const uint32_t *in[3];
+    uint32_t *out[3];
+    int32_t op[3];
+};
+
+__global__ __launch_bounds__(256) void k_scan_reduce(Scans s, int64_t n, uint32_t W, int64_t n_tiles, uint32_t *__restrict__ tile_sum)
 {
     __shared__ uint32_t sh[4];
+    const int a = blockIdx.y;
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * 8;
-    uint32_t s = 0;
+    uint32_t sum = 0;
 #pragma unroll
     for (int i = 0; i < 8; i++)
-        if (base + i < n) s += scan_input<OP>(in[base + i], W);
+        if (base + i < n) sum += scan_input(s.op[a], s.in[a][base + i], W);
     uint32_t total;
-    block_excl_scan_256(s, &total, sh);
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
+    block_excl_scan_256(sum, &total, sh);
+    if (threadIdx.x == 0) tile_sum[a * n_tiles + blockIdx.x] = total;
 }
 
-// One workgroup scans the tile sums in place (exclusive) and writes the grand total.
-__global__ __launch_bounds__(256) void k_scan_tiles(uint32_t *__restrict__ tile_sum, int64_t n_tiles,
-                                                    uint32_t *__restrict__ total_out)
+// One workgroup per scan turns the tile sums into prefix sums in place (for more tiles than every
+// workgroup of k_scan_down would want to add up by itself).
+__global__ __launch_bounds__(256) void k_scan_tiles(uint32_t *__restrict__ tile_sum, int64_t n_tiles)
 {
     __shared__ uint32_t sh[4];
+    uint32_t *sums = tile_sum + blockIdx.x * n_tiles;
     uint32_t carry = 0;
     for (int64_t base = 0; base < n_tiles; base += 256) {
         int64_t i = base + threadIdx.x;
-        uint32_t v = i < n_tiles ? tile_sum[i] : 0u, total;
+        uint32_t v = i < n_tiles ? sums[i] : 0u, total;
         uint32_t ex = block_excl_scan_256(v, &total, sh);
-        if (i < n_tiles) tile_sum[i] = carry + ex;
+        if (i < n_tiles) sums[i] = carry + ex;
         carry += total;
     }
-    if (threadIdx.x == 0) *total_out = carry;
 }
 
-template <int OP>
-__global__ __launch_bounds__(256) void k_scan_down(const uint32_t *__restrict__ in, int64_t n, uint32_t W,
-                                                   const uint32_t *__restrict__ tile_off, uint32_t *__restrict__ out)
+__global__ __launch_bounds__(256) void k_scan_down(Scans s, int64_t n, uint32_t W, int64_t n_tiles, int32_t prefixed,
+                                                   const uint32_t *__restrict__ tile_sum)
 {
     __shared__ uint32_t sh[4];
+    const int a = blockIdx.y;
+    const uint32_t *sums = tile_sum + a * n_tiles;
+    uint32_t before = 0;
+    if (prefixed) {
+        before = sums[blockIdx.x];
+    } else if (blockIdx.x > 0) {
+        uint32_t part = 0;
+        for (int64_t i = threadIdx.x; i < blockIdx.x; i += 256) part += sums[i];
+        block_excl_scan_256(part, &before, sh);
+    }
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * 8;
-    uint32_t v[8], s = 0;
+    uint32_t v[8], sum = 0;
 #pragma unroll
     for (int i = 0; i < 8; i++) {
-        v[i] = base + i < n ? scan_input<OP>(in[base + i], W) : 0u;
-        s += v[i];
+        v[i] = base + i < n ? scan_input(s.op[a], s.in[a][base + i], W) : 0u;
+        sum += v[i];
     }
     uint32_t total;
-    uint32_t run = tile_off[blockIdx.x] + block_excl_scan_256(s, &total, sh);
+    uint32_t run = before + block_excl_scan_256(sum, &total, sh);
 #pragma unroll
     for (int i = 0; i < 8; i++) {
-        if (base + i < n) out[base + i] = run;
+        if (base + i < n) s.out[a][base + i] = run;
         run += v[i];
     }
+    if (blockIdx.x == n_tiles - 1 && threadIdx.x == 0) s.out[a][n] = before + total;
 }
 
-// out[0..n) = exclusive scan of OP(in), out[n] = total.  `in` and `out` may alias.
-// tile_tmp must hold ceil(n / 2048) entries.
-template <int OP>
-int exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t W, uint32_t *tile_tmp, hipStream_t st)
+// tile_tmp must hold `count` * ceil(n / 2048) entries.
+int exclusive_scans(const Scans &s, int count, int64_t n, uint32_t W, uint32_t *tile_tmp, hipStream_t st)
 {
     if (n <= 0) {
-        HBP_HIP(hipMemsetAsync(out, 0, sizeof(uint32_t), st));
+        for (int a = 0; a < count; a++) HBP_HIP(hipMemsetAsync(s.out[a], 0, sizeof(uint32_t), st));
         return HBP_OK;
     }
     const int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    k_scan_reduce<OP><<<dim3((unsigned)tiles), 256, 0, st>>>(in, n, W, tile_tmp);
-    k_scan_tiles<<<1, 256, 0, st>>>(tile_tmp, tiles, out + n);
-    k_scan_down<OP><<<dim3((unsigned)tiles), 256, 0, st>>>(in, n, W, tile_tmp, out);
+    const dim3 grid((unsigned)tiles, (unsigned)count);
+    const bool prefixed = tiles > 4096;
+    k_scan_reduce<<<grid, 256, 0, st>>>(s, n, W, tiles, tile_tmp);
+    if (prefixed) k_scan_tiles<<<dim3((unsigned)count), 256, 0, st>>>(tile_tmp, tiles);
+    k_scan_down<<<grid, 256, 0, st>>>(s, n, W, tiles, prefixed ? 1 : 0, tile_tmp);
     HBP_HIP(hipGetLastError());
     return HBP_OK;
+}
+
+int exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tile_tmp, hipStream_t st)
+{
+    return exclusive_scans(Scans{{in}, {out}, {kOpIdentity}}, 1, n, 1, tile_tmp, st);
 }
 
 // ------------------------------------------------------------------ Section 3.2: hash
@@ -160,9 +181,9 @@ __device__ __forceinline__ uint32_t hash_key(uint32_t n, uint32_t a, uint32_t b,
 // counts the sampled segments with at least kLongSegment nonzeros (block sizes are chosen by it).
 constexpr int kLongSegment = 6;
 __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                                                     int64_t n_rows, int64_t nnz, int32_t C, int32_t S,
-                                                     uint32_t *__restrict__ hist)
+                                                     int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist)
 {
+    const int64_t nnz = ptr[n_rows];
     __shared__ uint32_t sh_hist[15];  // [14]: sampled segments with kLongSegment or more nonzeros
     if (threadIdx.x < 15) sh_hist[threadIdx.x] = 0;
     __syncthreads();
@@ -440,27 +461,57 @@ __global__ __launch_bounds__(256) void k_compact_blocks(const uint32_t *__restri
     blk_group_ptr[b] = (int32_t)group_off[d];
 }
 
-// Combine index: thread bm walks its row of the block table left to right (coalesced over bm).
-__global__ __launch_bounds__(256) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC,
-                                                      uint32_t *__restrict__ stripe_cnt)
+// Combine index.  A workgroup takes 64 row blocks (a wavefront reads 64 neighbouring entries of a row of the block
+// table) and deals the block columns out to its 16 wavefronts in contiguous slices.  (One thread per row
+// block walking all block columns: 15 + 33 us for 512 x 64 blocks in 2 workgroups.)
+constexpr int kStripeSlices = 16;
+
+__device__ __forceinline__ uint32_t stripe_slice_count(const uint32_t *__restrict__ dense_cnt, int64_t bm, int32_t NBR, int32_t NBC,
+                                                       int32_t &bn0, int32_t &bn1)
 {
-    const int64_t bm = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (bm >= NBR) return;
+    const int32_t slice = threadIdx.x >> 6;
+    bn0 = (int32_t)(((int64_t)NBC * slice) / kStripeSlices);
+    bn1 = (int32_t)(((int64_t)NBC * (slice + 1)) / kStripeSlices);
     uint32_t n = 0;
-    for (int64_t bn = 0; bn < NBC; bn++) n += dense_cnt[bn * NBR + bm] ? 1u : 0u;
+    if (bm < NBR) {
+#pragma unroll 8
+        for (int64_t bn = bn0; bn < bn1; bn++) n += dense_cnt[bn * NBR + bm] ? 1u : 0u;
+    }
+    return n;
+}
+
+__global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC,
+                                                       uint32_t *__restrict__ stripe_cnt)
+{
+    __shared__ uint32_t sh[kStripeSlices * 64];
+    const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+    int32_t bn0, bn1;
+    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1);
+    __syncthreads();
+    if (threadIdx.x >= 64 || bm >= NBR) return;
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < kStripeSlices; i++) n += sh[i * 64 + threadIdx.x];
     stripe_cnt[bm] = n;
 }
 
-__global__ __launch_bounds__(256) void k_stripe_fill(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ blk_id,
-                                                     const int32_t *__restrict__ stripe_ptr, int32_t NBR, int32_t NBC,
-                                                     int32_t *__restrict__ stripe_blk)
+__global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ blk_id,
+                                                      const int32_t *__restrict__ stripe_ptr, int32_t NBR, int32_t NBC,
+                                                      int32_t *__restrict__ stripe_blk)
 {
-    const int64_t bm = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    __shared__ uint32_t sh[kStripeSlices * 64];
+    const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+    int32_t bn0, bn1;
+    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1);
+    __syncthreads();
     if (bm >= NBR) return;
     int32_t k = stripe_ptr[bm];
-    for (int64_t bn = 0; bn < NBC; bn++) {
+    for (uint32_t i = threadIdx.x & 63; i < threadIdx.x; i += 64) k += (int32_t)sh[i];
+#pragma unroll 8
+    for (int64_t bn = bn0; bn < bn1; bn++) {
         const int64_t d = bn * NBR + bm;
-        if (dense_cnt[d]) stripe_blk[k++] = (int32_t)blk_id[d];
+        const int32_t id = (int32_t)blk_id[d];
+        if (dense_cnt[d]) stripe_blk[k++] = id;
     }
 }
 
@@ -1050,13 +1101,6 @@ __global__ __launch_bounds__(256) void k_unit_count(const int32_t *__restrict__ 
     units[bm] = (uint32_t)(u < 1 ? 1 : u);
 }
 
-// multi[bm] = 1 when the row block has more than one unit (input of the scan that numbers them)
-__global__ __launch_bounds__(256) void k_unit_multi(const uint32_t *__restrict__ units, int32_t NBR, uint32_t *__restrict__ multi)
-{
-    const int64_t bm = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (bm < NBR) multi[bm] = units[bm] > 1 ? 1u : 0u;
-}
-
 __global__ __launch_bounds__(256) void k_unit_fill(const int32_t *__restrict__ stripe_ptr, const uint32_t *__restrict__ cum,
                                                    const int32_t *__restrict__ unit_ptr, const uint32_t *__restrict__ multi_idx,
                                                    int32_t NBR, int32_t B, int32_t *__restrict__ unit_stripe,
@@ -1097,105 +1141,110 @@ struct Weights {
     }
 };
 
-__global__ __launch_bounds__(256) void k_col_group_ptr(const int32_t *__restrict__ col_blk_ptr, const int32_t *__restrict__ blk_group_ptr,
-                                                       int32_t NBC, int32_t *__restrict__ col_group_ptr)
+// col_group_ptr[c]: first group of block column c; col_rank[c], c in 0..NBC: block columns before c that hold a
+// group.  One workgroup: every thread counts a contiguous piece, the pieces' counts are scanned, every
+// thread writes its piece.
+__global__ __launch_bounds__(256) void k_col_groups(const int32_t *__restrict__ col_blk_ptr, const int32_t *__restrict__ blk_group_ptr,
+                                                    int32_t NBC, int32_t *__restrict__ col_group_ptr, int32_t *__restrict__ col_rank)
 {
-    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c <= NBC) col_group_ptr[c] = blk_group_ptr[col_blk_ptr[c]];
-}
-
-// comp_lo[w]: first group of worker w's range left to competition: the first g in the range whose
-// preceding weight inside the range reaches fixed_q8/256 of the range's weight, but not before
-// the first group of the block column that holds the range's last group (comp_col[w]), so that
-// the competitive groups of a range need one segment of the vector.
-__global__ __launch_bounds__(256) void k_comp_lo(const int32_t *__restrict__ col_group_ptr, Weights wt, int32_t NBC, int32_t P,
-                                                 int32_t fixed_q8, const int32_t *__restrict__ fixed_start,
-                                                 const int32_t *__restrict__ fixed_col, int32_t *__restrict__ comp_lo,
-                                                 int32_t *__restrict__ comp_col)
-{
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w >= P) return;
-    const int32_t g0 = fixed_start[w], g1 = fixed_start[w + 1];
-    const int64_t w0 = wt.before(g0);
-    const int64_t need = (wt.before(g1) - w0) * fixed_q8;
-    int32_t lo = g0, hi = g1;  // smallest g in [g0, g1] with (Wt(g) - w0) * 256 >= need
-    while (lo < hi) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        if ((wt.before(mid) - w0) * 256 >= need) hi = mid; else lo = mid + 1;
-    }
-    int32_t c = fixed_col[w];
-    if (g1 > g0) {
-        int32_t c_lo = 0, c_hi = NBC - 1;  // largest c with col_group_ptr[c] <= g1 - 1
-        while (c_lo < c_hi) {
-            const int32_t mid = c_lo + ((c_hi - c_lo + 1) >> 1);
-            if (col_group_ptr[mid] <= g1 - 1) c_lo = mid; else c_hi = mid - 1;
-        }
-        c = c_lo;
-        lo = max(lo, col_group_ptr[c]);
-    }
-    comp_lo[w] = lo;
-    comp_col[w] = c;
-}
-
-// col_rank[c], c in 0..NBC: block columns before c that hold a group.  One workgroup: every thread
-// counts a contiguous piece, the pieces' counts are scanned in LDS, every thread writes its piece.
-__global__ __launch_bounds__(256) void k_col_rank(const int32_t *__restrict__ col_group_ptr, int32_t NBC, int32_t *__restrict__ col_rank)
-{
-    __shared__ int32_t piece_sum[256];
+    __shared__ uint32_t sh[4];
+    for (int32_t c = threadIdx.x; c <= NBC; c += 256) col_group_ptr[c] = blk_group_ptr[col_blk_ptr[c]];
+    __syncthreads();
     const int32_t per = (NBC + 255) / 256, c0 = min(NBC, (int32_t)threadIdx.x * per), c1 = min(NBC, c0 + per);
-    int32_t mine = 0;
+    uint32_t mine = 0, total;
     for (int32_t c = c0; c < c1; c++) mine += col_group_ptr[c + 1] > col_group_ptr[c];
-    piece_sum[threadIdx.x] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int32_t run = 0;
-        for (int i = 0; i < 256; i++) { const int32_t v = piece_sum[i]; piece_sum[i] = run; run += v; }
-    }
-    __syncthreads();
-    int32_t run = piece_sum[threadIdx.x];
+    uint32_t run = block_excl_scan_256(mine, &total, sh);
     for (int32_t c = c0; c < c1; c++) {
-        col_rank[c] = run;
+        col_rank[c] = (int32_t)run;
         run += col_group_ptr[c + 1] > col_group_ptr[c];
     }
-    if (c1 == NBC && c0 < NBC) col_rank[NBC] = run;  // the thread that holds the last column
+    if (threadIdx.x == 0) col_rank[NBC] = (int32_t)total;
 }
 
+// Smallest i in [lo, hi] for which reached(i) holds, given that reached(hi) does: the lanes of a wavefront ask
+// for 64 candidates at once, so that a million groups take four dependent steps instead of twenty.
+template <typename F>
+__device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reached)
+{
+    const int lane = threadIdx.x & 63;
+    while (lo < hi) {  // wave-uniform
+        const int32_t step = (int32_t)(((int64_t)hi - lo + 63) / 64);
+        const int32_t i = (int32_t)min((int64_t)hi, lo + (int64_t)lane * step);
+        const uint64_t yes = __ballot(reached(i));
+        if (yes & 1) return lo;
+        if (yes == 0) {  // behind the last candidate below hi
+            lo = (int32_t)min((int64_t)hi, lo + 63 * (int64_t)step + 1);
+        } else {
+            const int f = __builtin_ctzll(yes);
+            hi = (int32_t)min((int64_t)hi, lo + (int64_t)f * step);
+            lo = (int32_t)(lo + (int64_t)(f - 1) * step + 1);
+        }
+    }
+    return lo;
+}
+
+// One wavefront per worker w.
 // fixed_start[w]: first g with Wc(g) * P >= w * Wc(G) (P contiguous ranges of equal weight), where
 // Wc(g) = Wt(g) + CW * (block columns with a group that start before g): entering a block column
 // costs a worker the fetch of its vector segment, charged to the column's first group;
 // fixed_col[w]: the last block column that starts at or before that group.
-__global__ __launch_bounds__(256) void k_fixed_start(const int32_t *__restrict__ col_group_ptr, Weights wt,
-                                                     const int32_t *__restrict__ col_rank, int64_t CW, int32_t NBC, int32_t G,
-                                                     int32_t P, int32_t *__restrict__ fixed_start, int32_t *__restrict__ fixed_col)
+// comp_lo[w]: first group of worker w's range left to competition: the first g in the range whose
+// preceding weight inside the range reaches fixed_q8/256 of the range's weight, but not before
+// the first group of the block column that holds the range's last group (comp_col[w]), so that
+// the competitive groups of a range need one segment of the vector.
+__global__ __launch_bounds__(256) void k_schedule(const int32_t *__restrict__ col_group_ptr, Weights wt,
+                                                  const int32_t *__restrict__ col_rank, int64_t CW, int32_t NBC, int32_t G, int32_t P,
+                                                  int32_t fixed_q8, int32_t *__restrict__ fixed_start, int32_t *__restrict__ fixed_col,
+                                                  int32_t *__restrict__ comp_lo, int32_t *__restrict__ comp_col)
 {
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr int kKept = 2048;  // block columns whose first groups are kept in LDS
+    __shared__ int32_t sh_first[kKept + 1];
+    const bool kept = NBC <= kKept;
+    if (kept)
+        for (int32_t c = threadIdx.x; c <= NBC; c += 256) sh_first[c] = col_group_ptr[c];
+    __syncthreads();
+    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (w > P) return;
+    auto first_group = [&](int32_t c) { return kept ? sh_first[c] : col_group_ptr[c]; };
     auto before = [&](int32_t g) {
         int64_t v = wt.before(g);
         if (CW) {
             int32_t c_lo = 0, c_hi = NBC;  // first c in 0..NBC with col_group_ptr[c] >= g (col_group_ptr[NBC] = G)
             while (c_lo < c_hi) {
                 const int32_t mid = c_lo + ((c_hi - c_lo) >> 1);
-                if (col_group_ptr[mid] >= g) c_hi = mid; else c_lo = mid + 1;
+                if (first_group(mid) >= g) c_hi = mid; else c_lo = mid + 1;
             }
             v += CW * col_rank[c_lo];
         }
         return v;
     };
-    const int64_t need = w * before(G);
-    int32_t lo = 0, hi = G;
-    while (lo < hi) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        if (before(mid) * P >= need) hi = mid; else lo = mid + 1;
-    }
-    fixed_start[w] = lo;
+    auto column_of = [&](int32_t g) {  // largest c with col_group_ptr[c] <= g
+        int32_t c_lo = 0, c_hi = NBC - 1;
+        while (c_lo < c_hi) {
+            const int32_t mid = c_lo + ((c_hi - c_lo + 1) >> 1);
+            if (first_group(mid) <= g) c_lo = mid; else c_hi = mid - 1;
+        }
+        return c_lo;
+    };
+    const int64_t all = before(G);
+    auto start = [&](int64_t worker) { return first_reached(0, G, [&](int32_t g) { return before(g) * P >= worker * all; }); };
+    const int32_t g0 = start(w);
+    const bool writes = (threadIdx.x & 63) == 0;
+    if (writes) fixed_start[w] = g0;
     if (w == P) return;
-    int32_t c_lo = 0, c_hi = NBC - 1;  // largest c with col_group_ptr[c] <= lo
-    while (c_lo < c_hi) {
-        const int32_t mid = c_lo + ((c_hi - c_lo + 1) >> 1);
-        if (col_group_ptr[mid] <= lo) c_lo = mid; else c_hi = mid - 1;
+    const int32_t g1 = start(w + 1), col0 = column_of(g0);
+    const int64_t w0 = wt.before(g0), need = (wt.before(g1) - w0) * fixed_q8;
+    int32_t lo = first_reached(g0, g1, [&](int32_t g) { return (wt.before(g) - w0) * 256 >= need; });
+    int32_t c = col0;
+    if (g1 > g0) {
+        c = column_of(g1 - 1);
+        lo = max(lo, first_group(c));
     }
-    fixed_col[w] = c_lo;
+    if (writes) {
+        fixed_col[w] = col0;
+        comp_lo[w] = lo;
+        comp_col[w] = c;
+    }
 }
 
 // The paper's schedule (Section 3.3 read literally): worker w is pre-assigned the F blocks
@@ -1253,6 +1302,90 @@ int workspace_get(int device, int slot, size_t bytes, void **out)
     return HBP_OK;
 }
 
+// Allocations of freed handles, kept for the next ones: a program that rebuilds its matrix (time stepping,
+// Newton) otherwise pays milliseconds per build for hipMalloc and hipFree of hundreds of megabytes
+// (mapping and unmapping; stencil 128^3: 4.0 of 5.2 ms).  Bounded per device by kCacheBytes and
+// kCacheBlocks, given back by hbp_release_workspace() and when an allocation fails.  hbp_free waits
+// for the device before a block comes here, so whatever stream gets it next finds it idle.
+constexpr size_t kCacheBytes = size_t(4) << 30;
+constexpr size_t kCacheBlocks = 16;
+struct CachedBlock { void *base; size_t bytes; };
+struct BlockCache {
+    CachedBlock at[kCacheBlocks];  // oldest first
+    size_t count = 0, bytes = 0;
+    CachedBlock take(size_t i)
+    {
+        const CachedBlock c = at[i];
+        for (size_t j = i + 1; j < count; j++) at[j - 1] = at[j];
+        count--;
+        bytes -= c.bytes;
+        return c;
+    }
+};
+BlockCache g_cache[kWorkspaceDevices];
+std::mutex g_cache_mutex[kWorkspaceDevices];
+
+// sizes in steps of an eighth of the power of two below, so that matrices of much the same size share blocks
+size_t cache_size_of(size_t bytes)
+{
+    size_t step = 256;
+    while (bytes > 16 * step) step *= 2;
+    return (bytes + step - 1) / step * step;
+}
+
+int drop_cached_blocks(int device)
+{
+    int rc = HBP_OK;
+    std::lock_guard<std::mutex> lock(g_cache_mutex[device]);
+    BlockCache &cache = g_cache[device];
+    while (cache.count > 0)
+        if (hipFree(cache.take(0).base) != hipSuccess) rc = HBP_ERR_HIP;
+    return rc;
+}
+
+int block_get(int device, size_t bytes, void **out, size_t *got)
+{
+    const size_t want = cache_size_of(bytes);
+    if (device >= 0 && device < kWorkspaceDevices) {
+        std::lock_guard<std::mutex> lock(g_cache_mutex[device]);
+        BlockCache &cache = g_cache[device];
+        for (size_t i = cache.count; i-- > 0;)
+            if (cache.at[i].bytes == want) {
+                *out = cache.take(i).base;
+                *got = want;
+                return HBP_OK;
+            }
+    }
+    hipError_t e = hipMalloc(out, want);
+    if (e == hipErrorOutOfMemory && device >= 0 && device < kWorkspaceDevices) {
+        (void)hipGetLastError();
+        (void)drop_cached_blocks(device);
+        e = hipMalloc(out, want);
+    }
+    HBP_HIP(e);
+    *got = want;
+    return HBP_OK;
+}
+
+// A few words that kernels write for the host: one synchronisation instead of a blocking copy per word.
+constexpr int kReadback = 32;
+uint32_t *g_readback[kWorkspaceDevices];  // pinned; guarded by the device's workspace lock
+
+int readback_get(int device, uint32_t **out)
+{
+    if (device < 0 || device >= kWorkspaceDevices) return HBP_ERR_INTERNAL;
+    if (!g_readback[device]) HBP_HIP(hipHostMalloc((void **)&g_readback[device], kReadback * sizeof(uint32_t), hipHostMallocDefault));
+    *out = g_readback[device];
+    return HBP_OK;
+}
+
+struct Words { const void *at[kReadback]; };
+__global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host)
+{
+    const int i = threadIdx.x;
+    if (i < count) host[i] = *static_cast<const uint32_t *>(words.at[i]);
+}
+
 // One device allocation carved into 256-byte aligned arrays: reserve() every array first,
 // commit() allocates once and hands out the pointers.  hipMalloc/hipFree calls are a large part
 // of the preprocessing time otherwise (each hipFree synchronises the device).  An arena is
@@ -1276,7 +1409,8 @@ public:
     int commit()
     {
         if (keep_) {
-            HBP_HIP(hipMalloc(&base_, total_ ? total_ : 256));
+            const int rc = block_get(device_, total_ ? total_ : 256, &base_, &bytes_);
+            if (rc != HBP_OK) return rc;
         } else if (device_ < 0 || device_ >= kWorkspaceDevices || slot_ < 0 || slot_ >= kWorkspaceSlots) {
             HBP_HIP(hipMalloc(&base_, total_ ? total_ : 256));  // no workspace slot for it: freed when the build ends
             free_at_end_ = true;
@@ -1288,11 +1422,13 @@ public:
         return HBP_OK;
     }
     void *base() const { return base_; }
+    size_t bytes() const { return bytes_; }
+    size_t total() const { return total_; }
 
 private:
     struct Slot { void **out; size_t offset; };
     std::vector<Slot> slots_;
-    size_t total_ = 0;
+    size_t total_ = 0, bytes_ = 0;  // bytes_: of the block, where the caller keeps it
     void *base_ = nullptr;
     bool keep_, free_at_end_ = false;
     int device_, slot_;
@@ -1317,7 +1453,7 @@ inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + pe
 //         rounds with four groups in flight.  Both thresholds are measured on MI355X.
 // The sampled shift is written back into p.hash_shift, so that the build does not sample again.
 int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int64_t n_rows, int64_t n_cols, int32_t value_bytes,
-                            hbp_params_t &p, hipStream_t st)
+                            hbp_params_t &p, int64_t *nnz_out, hipStream_t st)
 {
     const int32_t max_c = value_bytes == 8 ? kMaxC64 : kMaxC;
     if (p.cols_per_block == 0) p.cols_per_block = (int32_t)std::min<int64_t>(max_c, n_cols);
@@ -1327,35 +1463,77 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
     int device = 0;
     HBP_HIP(hipGetDevice(&device));
     std::lock_guard<std::mutex> workspace_lock(workspace_mutex(device));
-    int32_t ends[2] = {0, 0};
-    HBP_HIP(hipMemcpyAsync(&ends[0], csr_ptr, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&ends[1], csr_ptr + n_rows, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    uint32_t *host = nullptr;
+    HBP_TRY(readback_get(device, &host));
+    void *buf = nullptr;
+    HBP_TRY(workspace_get(device, 1, 256, &buf));
+    uint32_t *hist = static_cast<uint32_t *>(buf);
+    int32_t *d_a = reinterpret_cast<int32_t *>(hist + 16);
+    HBP_HIP(hipMemsetAsync(hist, 0, 17 * sizeof(uint32_t), st));
+    const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
+    k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, p.cols_per_block, S_rows, hist);
+    k_pick_shift<<<1, 64, 0, st>>>(hist, d_a);
+    Words words;
+    for (int i = 0; i < 16; i++) words.at[i] = hist + i;
+    words.at[16] = d_a;
+    words.at[17] = csr_ptr;
+    words.at[18] = csr_ptr + n_rows;
+    k_publish<<<1, 64, 0, st>>>(words, 19, host);
+    HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
-    if (ends[0] != 0 || ends[1] < 0) return HBP_ERR_BAD_CSR_PTR;
-    const int64_t nnz = ends[1];
-    uint32_t host[16] = {0};
-    int32_t a = 0;
-    if (nnz > 0) {
-        void *buf = nullptr;
-        const int rc = workspace_get(device, 1, 256, &buf);
-        if (rc != HBP_OK) return rc;
-        uint32_t *hist = static_cast<uint32_t *>(buf);
-        int32_t *d_a = reinterpret_cast<int32_t *>(hist + 16);
-        HBP_HIP(hipMemsetAsync(hist, 0, 17 * sizeof(uint32_t), st));
-        const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
-        k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, p.cols_per_block, S_rows, hist);
-        k_pick_shift<<<1, 64, 0, st>>>(hist, d_a);
-        HBP_HIP(hipGetLastError());
-        HBP_HIP(hipMemcpyAsync(host, hist, sizeof host, hipMemcpyDeviceToHost, st));
-        HBP_HIP(hipMemcpyAsync(&a, d_a, sizeof a, hipMemcpyDeviceToHost, st));
-        HBP_HIP(hipStreamSynchronize(st));
-    }
+    const int32_t a = (int32_t)host[16], first = (int32_t)host[17];
+    *nnz_out = (int32_t)host[18];
+    if (first != 0 || *nnz_out < 0) return HBP_ERR_BAD_CSR_PTR;
+    const int64_t nnz = *nnz_out;
     uint64_t segments = 0;
     for (int i = 0; i < 14; i++) segments += host[i];
     const bool long_segments = segments > 0 && 2 * (uint64_t)host[14] >= segments;
     if (p.rows_per_block == 0) p.rows_per_block = long_segments ? 512 : 2048;
     if (p.rounds_per_batch == 0) p.rounds_per_batch = long_segments ? 8 : 4;
     if (p.hash_shift < 0 && nnz > 0) p.hash_shift = a;
+    return HBP_OK;
+}
+
+// Schedule weights, in units of one nonzero, where the caller left them open.  They are costs of
+// the SpMV-part kernel on MI355X, not properties of a matrix: measured over workers with very
+// different mixes, a group costs a wavefront 18 ns, a round 3 ns, a slot 0.6 ns and entering a
+// block column costs the worker 19 us, next to 0.03 ns per nonzero while the wavefront waits for
+// its loads anyway (groups of a few hundred nonzeros).  Groups of 512 nonzeros and more are
+// streamed at the worker's share of the memory bandwidth instead (0.3 ns per nonzero): the same
+// costs are a tenth as many nonzeros there.  And the device default of the workers: no more than
+// the groups can keep busy, one group per wavefront.
+static void choose_schedule(hbp_handle_s *h, const hbp_params_t &p)
+{
+    const bool streamed = h->G > 0 && h->nnz >= 512 * h->G;
+    h->slot_weight = p.slot_weight >= 0 ? p.slot_weight : streamed ? 2 : 20;
+    h->group_weight = p.group_weight >= 0 ? p.group_weight : streamed ? 60 : 600;
+    h->round_weight = p.round_weight >= 0 ? p.round_weight : streamed ? 10 : 100;
+    h->column_weight = p.column_weight >= 0 ? p.column_weight : streamed ? 60000 : 600000;
+    if (p.num_workers == 0) {
+        const int64_t waves = h->threads / kWave;
+        const int64_t useful = std::max<int64_t>(1, (h->G + waves - 1) / waves);
+        if (useful < h->P) h->P = (int32_t)useful;
+    }
+}
+
+// Section 3.3: which groups are pre-assigned to which worker and which are left to competition.
+static int launch_schedule(hbp_handle_s *h, hipStream_t st)
+{
+    const int32_t NBC = (int32_t)h->NBC;
+    k_col_groups<<<1, 256, 0, st>>>(h->col_blk_ptr, h->blk_group_ptr, NBC, h->col_group_ptr, h->col_rank);
+    if (h->flags & HBP_FLAG_PAPER_SCHEDULE) {
+        const int64_t F = (h->B * (int64_t)h->fixed_q8) / (256 * (int64_t)h->P);
+        h->first_ticket_block = F * h->P;
+        k_paper_schedule<<<blocks_for((int64_t)h->P + 1, 256), 256, 0, st>>>(h->blk_group_ptr, h->blk_bn, F, (int32_t)h->B, NBC, h->P,
+                                                                             h->fixed_start, h->fixed_col, h->comp_lo, h->comp_col);
+    } else {
+        const Weights wt{h->group_ptr, h->group_slot, h->group_rounds, (int64_t)h->slot_weight, (int64_t)h->round_weight,
+                         (int64_t)h->group_weight};
+        k_schedule<<<blocks_for((int64_t)h->P + 1, 4), 256, 0, st>>>(h->col_group_ptr, wt, h->col_rank, (int64_t)h->column_weight, NBC,
+                                                                     (int32_t)h->G, h->P, h->fixed_q8, h->fixed_start, h->fixed_col,
+                                                                     h->comp_lo, h->comp_col);
+    }
+    HBP_HIP(hipGetLastError());
     return HBP_OK;
 }
 
@@ -1380,18 +1558,21 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const int32_t R = h->R, C = h->C, W = h->W;
     const int64_t NBR = h->NBR, NBC = h->NBC, D = NBR * NBC;
 
+    uint32_t *host = nullptr;
+    HBP_TRY(readback_get(h->device, &host));
     // nnz and csr_ptr[0] are needed on the host before anything can be sized
-    int32_t ends[2] = {0, 0};
-    HBP_HIP(hipMemcpyAsync(&ends[0], csr_ptr, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&ends[1], csr_ptr + n_rows, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipStreamSynchronize(st));
-    if (ends[0] != 0 || ends[1] < 0) return HBP_ERR_BAD_CSR_PTR;
-    const int64_t nnz = ends[1];
+    if (h->nnz < 0) {
+        k_publish<<<1, 64, 0, st>>>(Words{{csr_ptr, csr_ptr + n_rows}}, 2, host);
+        HBP_HIP(hipGetLastError());
+        HBP_HIP(hipStreamSynchronize(st));
+        if (host[0] != 0 || (int32_t)host[1] < 0) return HBP_ERR_BAD_CSR_PTR;
+        h->nnz = host[1];
+    }
+    const int64_t nnz = h->nnz;
     if (nnz >= (int64_t(1) << 31) - 64) return HBP_ERR_TOO_LARGE;
-    h->nnz = nnz;
 
     // arrays whose size does not depend on the matrix content
-    Arena own0(true);
+    Arena own0(true, h->device);
     own0.reserve(&h->col_blk_ptr, NBC + 1);
     own0.reserve(&h->stripe_ptr, NBR + 1);
     own0.reserve(&h->ticket, (int64_t)h->P);
@@ -1403,20 +1584,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own0.reserve(&h->unit_ptr, NBR + 1);
     own0.reserve(&h->col_rank, NBC + 1);
     HBP_TRY(own0.commit());
-    h->arena[0] = own0.base();
-    HBP_HIP(hipMemsetAsync(h->ticket, 0, sizeof(uint32_t) * (size_t)h->P, st));
-    HBP_HIP(hipMemsetAsync(h->col_blk_ptr, 0, sizeof(int32_t) * (size_t)(NBC + 1), st));
-    HBP_HIP(hipMemsetAsync(h->stripe_ptr, 0, sizeof(int32_t) * (size_t)(NBR + 1), st));
-    HBP_HIP(hipMemsetAsync(h->comp_lo, 0, sizeof(int32_t) * (size_t)h->P, st));
-    HBP_HIP(hipMemsetAsync(h->comp_col, 0, sizeof(int32_t) * (size_t)h->P, st));
-    HBP_HIP(hipMemsetAsync(h->col_group_ptr, 0, sizeof(int32_t) * (size_t)(NBC + 1), st));
-    HBP_HIP(hipMemsetAsync(h->fixed_start, 0, sizeof(int32_t) * (size_t)(h->P + 1), st));
-    HBP_HIP(hipMemsetAsync(h->fixed_col, 0, sizeof(int32_t) * (size_t)h->P, st));
+    h->arena[0] = own0.base(); h->arena_bytes[0] = own0.bytes();
+    HBP_HIP(hipMemsetAsync(own0.base(), 0, own0.total(), st));
 
     if (nnz == 0) {  // empty matrix: no blocks; the combine part alone writes y = 0
         h->B = h->S = h->G = 0;
         h->a = p.hash_shift >= 0 ? p.hash_shift : 0;
-        Arena own1(true);
+        Arena own1(true, h->device);
         own1.reserve(&h->blk_bm, 1); own1.reserve(&h->blk_bn, 1); own1.reserve(&h->slot_ptr, 1);
         own1.reserve(&h->blk_group_ptr, 1); own1.reserve(&h->stripe_blk, 1); own1.reserve(&h->group_ptr, 1);
         own1.reserve(&h->group_slot, 1); own1.reserve(&h->group_rounds, 1); own1.reserve(&h->group_blk, 1);
@@ -1424,13 +1598,14 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         own1.reserve(&h->col_local, 1); own1.reserve_bytes(&h->data, 8); own1.reserve_bytes(&h->partial, 8);
         own1.reserve(&h->unit_stripe, NBR + 1); own1.reserve(&h->unit_k, NBR + 2); own1.reserve(&h->multi_stripes, 1);
         HBP_TRY(own1.commit());
-        h->arena[1] = own1.base();
+        h->arena[1] = own1.base(); h->arena_bytes[1] = own1.bytes();
         h->U = NBR; h->NM = 0;
         if (h->unit_slots == 0) h->unit_slots = 16384;
         k_iota_units<<<blocks_for(NBR + 1, 256), 256, 0, st>>>(h->unit_ptr, h->unit_stripe, h->unit_k, (int32_t)NBR);
         HBP_HIP(hipMemsetAsync(h->slot_ptr, 0, 4, st)); HBP_HIP(hipMemsetAsync(h->blk_group_ptr, 0, 4, st));
         HBP_HIP(hipMemsetAsync(h->group_ptr, 0, 4, st)); HBP_HIP(hipMemsetAsync(h->group_slot, 0, 4, st));
         HBP_HIP(hipMemsetAsync(h->group_rounds, 0, 4, st));
+        choose_schedule(h, p);
         HBP_HIP(hipStreamSynchronize(st));
         return HBP_OK;
     }
@@ -1441,7 +1616,11 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint32_t *row_bits, *seg_cnt, *word_off, *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
     uint64_t *seg_bits;
     int32_t *word_row, *seg_j, *seg_row, *seg_bn, *d_a, *d_err;
+    // the arrays that start at zero side by side: one fill
     tmp.reserve(&row_bits, (nnz + 31) / 32 + 1);
+    tmp.reserve(&dense_cnt, D);
+    tmp.reserve(&hist, 16);
+    tmp.reserve(&d_err, 1);
     tmp.reserve(&seg_bits, n_words);
     tmp.reserve(&seg_cnt, n_words);
     tmp.reserve(&word_off, n_words + 1);
@@ -1449,27 +1628,21 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&seg_j, nnz + 1);     // S <= nnz: sized by the bound, no host round trip needed
     tmp.reserve(&seg_row, nnz);
     tmp.reserve(&seg_bn, nnz);
-    tmp.reserve(&dense_cnt, D);
     tmp.reserve(&slot_off, D + 1);
     tmp.reserve(&group_off, D + 1);
     tmp.reserve(&blk_id, D + 1);
     tmp.reserve(&stripe_cnt, NBR);
-    tmp.reserve(&scan_tmp, scan_n / kScanTile + 2);
-    tmp.reserve(&hist, 16);
+    tmp.reserve(&scan_tmp, 3 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
-    tmp.reserve(&d_err, 1);
     HBP_TRY(tmp.commit());
-    HBP_HIP(hipMemsetAsync(row_bits, 0, sizeof(uint32_t) * (size_t)((nnz + 31) / 32 + 1), st));
-    HBP_HIP(hipMemsetAsync(dense_cnt, 0, sizeof(uint32_t) * (size_t)D, st));
-    HBP_HIP(hipMemsetAsync(hist, 0, sizeof(uint32_t) * 16, st));
-    HBP_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), st));
+    HBP_HIP(hipMemsetAsync(row_bits, 0, (size_t)((char *)seg_bits - (char *)row_bits), st));
 
     // Section 3.2: shift a, sampled or given
     if (p.hash_shift >= 0) {
         k_set_i32<<<1, 64, 0, st>>>(d_a, p.hash_shift);
     } else {
         const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
-        k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, C, S_rows, hist);
+        k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, C, S_rows, hist);
         k_pick_shift<<<1, 64, 0, st>>>(hist, d_a);
     }
 
@@ -1481,34 +1654,29 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         if (C == (int32_t(1) << b)) shift_c = b;
     k_seg_flags<<<blocks_for(n_words, 4 * kWordsPerWave), 256, 0, st>>>(csr_col, row_bits, nnz, n_cols, C, shift_c, n_words,
                                                                        (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, seg_bits, seg_cnt, d_err);
-    HBP_TRY(exclusive_scan<kOpIdentity>(seg_cnt, word_off, n_words, 1, scan_tmp, st));
+    HBP_TRY(exclusive_scan(seg_cnt, word_off, n_words, scan_tmp, st));
     k_seg_emit<<<blocks_for(n_words, 4 * kWordsPerWave), 256, 0, st>>>(csr_ptr, csr_col, seg_bits, word_off, word_row, nnz, n_cols, R, C,
                                                                       shift_c, (int32_t)NBR, n_words, seg_j, seg_row, seg_bn);
     k_count_blocks<<<blocks_for(nnz, kTileSegs), 256, 0, st>>>(seg_row, seg_bn, word_off + n_words, d_err, R, (int32_t)NBR, (int32_t)NBC,
                                                                dense_cnt);
     // step 4: scans over the block table
-    HBP_TRY(exclusive_scan<kOpIdentity>(dense_cnt, slot_off, D, 1, scan_tmp, st));
-    HBP_TRY(exclusive_scan<kOpCeilDivW>(dense_cnt, group_off, D, (uint32_t)W, scan_tmp, st));
-    HBP_TRY(exclusive_scan<kOpNonZero>(dense_cnt, blk_id, D, 1, scan_tmp, st));
-    k_stripe_count<<<blocks_for(NBR, 256), 256, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, stripe_cnt);
-    HBP_TRY(exclusive_scan<kOpIdentity>(stripe_cnt, (uint32_t *)h->stripe_ptr, NBR, 1, scan_tmp, st));
+    HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
+                            D, (uint32_t)W, scan_tmp, st));
+    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, stripe_cnt);
+    HBP_TRY(exclusive_scan(stripe_cnt, (uint32_t *)h->stripe_ptr, NBR, scan_tmp, st));
     HBP_HIP(hipGetLastError());
 
     // the one host round trip of the build: totals (and the error word)
-    uint32_t totals[3];
-    int32_t err = 0, a = 0;
-    HBP_HIP(hipMemcpyAsync(&totals[0], slot_off + D, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&totals[1], group_off + D, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&totals[2], blk_id + D, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&err, d_err, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&a, d_a, 4, hipMemcpyDeviceToHost, st));
+    k_publish<<<1, 64, 0, st>>>(Words{{slot_off + D, group_off + D, blk_id + D, d_err, d_a}}, 5, host);
+    HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
+    const int32_t err = (int32_t)host[3], a = (int32_t)host[4];
     if (err & kErrPtr) return HBP_ERR_BAD_CSR_PTR;
     if (err & kErrCol) return HBP_ERR_BAD_CSR_COL;
-    const int64_t S = totals[0], G = totals[1], B = totals[2];
+    const int64_t S = host[0], G = host[1], B = host[2];
     h->S = S; h->G = G; h->B = B; h->a = a;
 
-    Arena own1(true);
+    Arena own1(true, h->device);
     own1.reserve(&h->blk_bm, B + 1); own1.reserve(&h->blk_bn, B + 1);
     own1.reserve(&h->slot_ptr, B + 1); own1.reserve(&h->blk_group_ptr, B + 1);
     own1.reserve(&h->stripe_blk, B + 1);
@@ -1531,7 +1699,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own1.reserve(&h->unit_stripe, max_units); own1.reserve(&h->unit_k, max_units + 1);
     own1.reserve(&h->multi_stripes, NBR);
     HBP_TRY(own1.commit());
-    h->arena[1] = own1.base();
+    h->arena[1] = own1.base(); h->arena_bytes[1] = own1.bytes();
     Arena tmp2(false, h->device, 1);
     uint32_t *stripe_cum, *unit_cnt, *multi_idx;
     tmp2.reserve(&stripe_cum, B + 1); tmp2.reserve(&unit_cnt, NBR + 1); tmp2.reserve(&multi_idx, NBR + 1);
@@ -1539,23 +1707,21 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     int32_t *bucket_j;
     int32_t *slot_j;
     tmp2.reserve(&bucket_len_row, S); tmp2.reserve(&bucket_j, S);
-    tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 1); tmp2.reserve(&d_n_long, 1);
+    tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 2);
     HBP_TRY(tmp2.commit());
-    HBP_HIP(hipMemsetAsync(longest_all, 0, sizeof(uint32_t), st));
-    HBP_HIP(hipMemsetAsync(d_n_long, 0, sizeof(uint32_t), st));
+    d_n_long = longest_all + 1;
+    HBP_HIP(hipMemsetAsync(longest_all, 0, 2 * sizeof(uint32_t), st));
 
     k_compact_blocks<<<blocks_for(std::max<int64_t>(D, NBC) + 1, 256), 256, 0, st>>>(
         dense_cnt, slot_off, group_off, blk_id, D, (int32_t)NBR, (int32_t)NBC, h->blk_bm, h->blk_bn, h->slot_ptr,
         h->blk_group_ptr, h->col_blk_ptr);
-    k_stripe_fill<<<blocks_for(NBR, 256), 256, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, (int32_t)NBR, (int32_t)NBC,
+    k_stripe_fill<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, (int32_t)NBR, (int32_t)NBC,
                                                        h->stripe_blk);
     // combine work units
     k_stripe_sizes<<<blocks_for(B, 256), 256, 0, st>>>(h->stripe_blk, h->slot_ptr, (int32_t)B, stripe_cum);
-    HBP_TRY(exclusive_scan<kOpIdentity>(stripe_cum, stripe_cum, B, 1, scan_tmp, st));
+    HBP_TRY(exclusive_scan(stripe_cum, stripe_cum, B, scan_tmp, st));
     k_unit_count<<<blocks_for(NBR, 256), 256, 0, st>>>(h->stripe_ptr, stripe_cum, (int32_t)NBR, h->unit_slots, unit_cnt);
-    k_unit_multi<<<blocks_for(NBR, 256), 256, 0, st>>>(unit_cnt, (int32_t)NBR, multi_idx);
-    HBP_TRY(exclusive_scan<kOpIdentity>(unit_cnt, (uint32_t *)h->unit_ptr, NBR, 1, scan_tmp, st));
-    HBP_TRY(exclusive_scan<kOpIdentity>(multi_idx, multi_idx, NBR, 1, scan_tmp, st));
+    HBP_TRY(exclusive_scans(Scans{{unit_cnt, unit_cnt}, {(uint32_t *)h->unit_ptr, multi_idx}, {kOpIdentity, kOpAboveOne}}, 2, NBR, 1, scan_tmp, st));
     k_unit_fill<<<blocks_for(NBR, 256), 256, 0, st>>>(h->stripe_ptr, stripe_cum, h->unit_ptr, multi_idx, (int32_t)NBR, (int32_t)B,
                                                      h->unit_stripe, h->unit_k, h->multi_stripes);
     // steps 5-6 (slot_off doubles as the per-block cursor from here on)
@@ -1582,8 +1748,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                             h->row_local, h->seg_len, slot_j, group_nnz, group_longest, h->group_slot,
                                                             h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all,
                                                             d_n_long, h->long_groups, h->flat_wpg, reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);
-    HBP_TRY(exclusive_scan<kOpIdentity>(group_nnz, (uint32_t *)h->group_ptr, G, 1, scan_tmp, st));
-    HBP_TRY(exclusive_scan<kOpIdentity>(group_longest, (uint32_t *)h->group_rounds, G, 1, scan_tmp, st));
+    HBP_TRY(exclusive_scans(Scans{{group_nnz, group_longest}, {(uint32_t *)h->group_ptr, (uint32_t *)h->group_rounds}, {kOpIdentity, kOpIdentity}}, 2,
+                            G, 1, scan_tmp, st));
     k_set_i32<<<1, 64, 0, st>>>(h->group_slot + G, (int32_t)S);
     // step 7
     // the padding behind the last group is read (and its products dropped) by lanes without an element
@@ -1608,42 +1774,30 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                    h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, static_cast<float *>(h->data));
     }
     HBP_HIP(hipGetLastError());
-    uint32_t n_units = 0, n_multi = 0, longest = 0, n_long = 0;
-    HBP_HIP(hipMemcpyAsync(&n_long, d_n_long, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&longest, longest_all, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&n_units, h->unit_ptr + NBR, 4, hipMemcpyDeviceToHost, st));
-    HBP_HIP(hipMemcpyAsync(&n_multi, multi_idx + NBR, 4, hipMemcpyDeviceToHost, st));
+    choose_schedule(h, p);
+    HBP_TRY(launch_schedule(h, st));
+    k_publish<<<1, 64, 0, st>>>(Words{{h->unit_ptr + NBR, multi_idx + NBR, longest_all, d_n_long}}, 4, host);
+    HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
-    h->U = n_units; h->NM = n_multi; h->n_long = (int32_t)n_long;
-    h->longest_segment = (int32_t)longest;  // 0 unless it makes a group long
+    h->U = host[0]; h->NM = host[1];
+    h->longest_segment = (int32_t)host[2];  // 0 unless it makes a group long
+    h->n_long = (int32_t)host[3];
     return HBP_OK;
 }
 
-// Section 3.3: which groups are pre-assigned to which worker and which are left to competition.
-int build_schedule(hbp_handle_s *h, hipStream_t st)
+// Takes back an allocation of a handle.  Nothing on the device uses it any more.
+void release_block(int device, void *base, size_t bytes)
 {
-    h->first_ticket_block = -1;
-    if (h->G > 0 && (h->flags & HBP_FLAG_PAPER_SCHEDULE)) {
-        const int32_t NBC = (int32_t)h->NBC;
-        const int64_t F = (h->B * (int64_t)h->fixed_q8) / (256 * (int64_t)h->P);
-        h->first_ticket_block = F * h->P;
-        k_col_group_ptr<<<blocks_for(h->NBC + 1, 256), 256, 0, st>>>(h->col_blk_ptr, h->blk_group_ptr, NBC, h->col_group_ptr);
-        k_paper_schedule<<<blocks_for((int64_t)h->P + 1, 256), 256, 0, st>>>(h->blk_group_ptr, h->blk_bn, F, (int32_t)h->B, NBC, h->P,
-                                                                             h->fixed_start, h->fixed_col, h->comp_lo, h->comp_col);
-    } else if (h->G > 0) {
-        const int32_t NBC = (int32_t)h->NBC;
-        k_col_group_ptr<<<blocks_for(h->NBC + 1, 256), 256, 0, st>>>(h->col_blk_ptr, h->blk_group_ptr, NBC, h->col_group_ptr);
-        const Weights wt{h->group_ptr, h->group_slot, h->group_rounds, (int64_t)h->slot_weight, (int64_t)h->round_weight,
-                         (int64_t)h->group_weight};
-        k_col_rank<<<1, 256, 0, st>>>(h->col_group_ptr, NBC, h->col_rank);
-        k_fixed_start<<<blocks_for((int64_t)h->P + 1, 256), 256, 0, st>>>(h->col_group_ptr, wt, h->col_rank, (int64_t)h->column_weight,
-                                                                          NBC, (int32_t)h->G, h->P, h->fixed_start, h->fixed_col);
-        k_comp_lo<<<blocks_for((int64_t)h->P, 256), 256, 0, st>>>(h->col_group_ptr, wt, NBC, h->P, h->fixed_q8, h->fixed_start,
-                                                                  h->fixed_col, h->comp_lo, h->comp_col);
+    if (!base) return;
+    if (device < 0 || device >= kWorkspaceDevices || bytes > kCacheBytes) {
+        (void)hipFree(base);
+        return;
     }
-    HBP_HIP(hipGetLastError());
-    HBP_HIP(hipStreamSynchronize(st));
-    return HBP_OK;
+    std::lock_guard<std::mutex> lock(g_cache_mutex[device]);
+    BlockCache &cache = g_cache[device];
+    while (cache.count == kCacheBlocks || cache.bytes + bytes > kCacheBytes) (void)hipFree(cache.take(0).base);
+    cache.at[cache.count++] = {base, bytes};
+    cache.bytes += bytes;
 }
 
 int release_workspace()
@@ -1656,6 +1810,9 @@ int release_workspace()
             w.base = nullptr;
             w.bytes = 0;
         }
+        if (g_readback[device] && hipHostFree(g_readback[device]) != hipSuccess) rc = HBP_ERR_HIP;
+        g_readback[device] = nullptr;
+        if (drop_cached_blocks(device) != HBP_OK) rc = HBP_ERR_HIP;
     }
     return rc;
 }

@@ -84,6 +84,7 @@ struct hbp_handle_s {
     // device arrays (owned): views into two allocations, arena[0] sized before the matrix is
     // looked at, arena[1] after the segment, group and block counts are known
     void *arena[2];
+    size_t arena_bytes[2];
     int32_t *blk_bm, *blk_bn, *slot_ptr, *blk_group_ptr, *col_blk_ptr, *stripe_ptr, *stripe_blk;
     int32_t *group_ptr, *group_slot;
     int32_t *col_group_ptr, *comp_lo, *comp_col, *fixed_start, *fixed_col;
@@ -129,12 +130,12 @@ void set_last_hip_error(hipError_t e);
 // build (hbp_build.hip)
 int build_layout(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
                  const hbp_params_t &p, hipStream_t stream);
-int build_schedule(hbp_handle_s *h, hipStream_t stream);
 int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int64_t n_rows, int64_t n_cols, int32_t value_bytes,
-                            hbp_params_t &p, hipStream_t stream);
+                            hbp_params_t &p, int64_t *nnz, hipStream_t stream);  // *nnz: unchanged where the matrix was not looked at
 int derive_add_sign(const hbp_handle_s *h, int32_t *d_out, hipStream_t stream);
 int hash_keys(const uint32_t *n, int64_t count, int32_t a, int32_t R, uint32_t *keys, hipStream_t stream);
 int release_workspace();
+void release_block(int device, void *base, size_t bytes);  // a handle's allocation, idle
 
 // spmv (hbp_spmv.hip)
 Layout hbp_view(const hbp_handle_s *h);

@@ -49,9 +49,9 @@ Layout hbp_view(const hbp_handle_s *h)
 // on the device at once given the LDS a vector segment takes.
 int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_wanted, int32_t *threads_out, int32_t *workers_out)
 {
-    hipDeviceProp_t prop;
-    HBP_HIP(hipGetDeviceProperties(&prop, device));
-    const int cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    int cus = 0;
+    HBP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+    if (cus <= 0) cus = 256;
     const size_t lds = (size_t)C * (size_t)value_bytes + 64;
     const int threads = threads_wanted ? threads_wanted : (lds > 80 * 1024 ? 1024 : 512);
     int per_cu = (int)((160 * 1024) / lds);

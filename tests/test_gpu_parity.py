@@ -609,3 +609,14 @@ def test_long_groups_before_and_after_the_others(H, oracle, workers, W, lens, ro
         check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=4096, cols_per_block=n_cols, group_width=W,
                              rounds_per_batch=rounds, threads_per_worker=threads, num_workers=workers, fixed_fraction_q8=q8,
                              heavy_group_rounds=heavy, slot_weight=0, group_weight=0, round_weight=0, column_weight=0)
+
+
+def test_rebuilds_reuse_memory_of_freed_handles(H, oracle):
+    """A build after a free may get the freed handle's memory; the layouts and products are those of fresh memory,
+    with handles of other sizes and of the other value type in between, and after the memory was given back."""
+    from workloads import widen_to_f64
+    a, b = random_csr(3000, 2000, 0.01, 81, empty_row_frac=0.1), random_csr(900, 5000, 0.02, 82)
+    for m in (a, b, a, widen_to_f64(a), b, a):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=256, cols_per_block=512, num_workers=9)
+    H.hbp_release_workspace()
+    check_against_oracle(H, oracle, a, check_add_sign=False, rows_per_block=256, cols_per_block=512, num_workers=9)
