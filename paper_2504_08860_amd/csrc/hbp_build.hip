@@ -3,14 +3,13 @@
 // The paper's Algorithm 2 walks one matrix row per thread and inserts rows into a per-block
 // hash table with atomics.  Here the same quantities are produced with coalesced passes
 // over the CSR arrays and a deterministic placement:
-//   1. row-start bits      one bit per nonzero marking the first nonzero of a row
-//   2. segment flags       a nonzero starts a segment when it starts a row or its column
+//   1-3. segments, counted the row pointers are checked; a nonzero starts a segment when it starts a row or its column
 //                          block differs from its left neighbour's (Algorithm 2's inner
-//                          while loop, evaluated for all nonzeros at once)
-//   3. segment records     (first nonzero, row, column block) in CSR order via a scan
-//   4. block table         count of segments per (column block, row block); scans give each
-//                          non-empty block its slot range, group range and list position
-//   5. bucketed scatter    every segment drops (hash key, local row, segment id) into its
+//                          while loop, evaluated for all nonzeros at once); segments per
+//                          (column block, row block)
+//   4. block table         scans give each non-empty block its slot range, group range and
+//                          list position
+//   5. segments, again     every segment drops (length, local row, first nonzero) into its
 //                          block's slot range through an atomic cursor
 //   6. block ordering      each block's range is ordered by (key, local row) in LDS; the
 //                          pair is unique inside a block, so the result does not depend on
@@ -294,8 +293,17 @@ __global__ void k_set_i32(int32_t *p, int32_t v)
 
 // ------------------------------------------------------------------ steps 1-3: segments
 
-__global__ __launch_bounds__(256) void k_row_bits(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz,
-                                                  uint32_t *__restrict__ row_bits, int32_t *__restrict__ err)
+__device__ __forceinline__ int32_t block_column(int32_t c, int32_t C, int32_t shift_c)
+{
+    return shift_c >= 0 ? c >> shift_c : c / C;
+}
+
+constexpr int kTile = 4096, kTileThreads = 512, kTileWords = kTile / 64, kWordsPerWave = kTileWords / (kTileThreads / 64);
+constexpr int kTileCounters = 4096;  // 16 KB of LDS
+
+// Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).
+__global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t *__restrict__ tile_row,
+                                                   int32_t *__restrict__ err)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (r >= n_rows) return;
@@ -304,134 +312,226 @@ __global__ __launch_bounds__(256) void k_row_bits(const int32_t *__restrict__ pt
         atomicOr(err, kErrPtr);
         return;
     }
-    if (p1 > p0) atomicOr(&row_bits[p0 >> 5], 1u << (p0 & 31));
+    for (int64_t t = (p0 + kTile - 1) / kTile; t * kTile < p1; t++) tile_row[t] = (int32_t)r;
 }
 
-// word_row[w] = the row that holds nonzero 64 w (largest r with ptr[r] <= 64 w); word_row[n_words] = n_rows - 1.
-__global__ __launch_bounds__(256) void k_word_rows(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t n_words,
-                                                   int32_t *__restrict__ word_row)
-{
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w > n_words) return;
-    if (w == n_words) { word_row[w] = (int32_t)(n_rows - 1); return; }
-    const int64_t j = w * 64;
-    int64_t lo = 0, hi = n_rows - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (ptr[mid] <= j) lo = mid; else hi = mid - 1;
-    }
-    word_row[w] = (int32_t)lo;
-}
-
-// A wavefront takes kWordsPerWave words of 64 consecutive nonzeros each, all loads issued before
-// the first use: segment-start bits of every word and their count.  (One word per wavefront
-// left the kernel waiting on a single load per lane.)  shift_c >= 0: C = 2^shift_c.
-constexpr int kWordsPerWave = 4;
-
-__device__ __forceinline__ int32_t block_column(int32_t c, int32_t C, int32_t shift_c)
-{
-    return shift_c >= 0 ? c >> shift_c : c / C;
-}
-
-__global__ __launch_bounds__(256) void k_seg_flags(const int32_t *__restrict__ col, const uint32_t *__restrict__ row_bits,
-                                                   int64_t nnz, int64_t n_cols, int32_t C, int32_t shift_c, int64_t n_words,
-                                                   int validate, uint64_t *__restrict__ seg_bits,
-                                                   uint32_t *__restrict__ seg_cnt, int32_t *__restrict__ err)
+// Wave-aggregated fetch-add: lanes of the wavefront that target the same counter are served by
+// one atomic (neighbouring segments mostly fall into the same block, and same-address atomics
+// serialise).  Returns, for an active lane, the value its own atomicAdd(&counters[key], 1) would
+// have returned in some serial order.  After a few distinct keys the rest go one by one.
+__device__ __forceinline__ uint32_t aggregated_add(uint32_t *counters, int64_t key, bool active)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kWordsPerWave;
-    if (w0 >= n_words) return;
-    int32_t c[kWordsPerWave];
-    uint32_t bits[kWordsPerWave];
-#pragma unroll
-    for (int u = 0; u < kWordsPerWave; u++) {
-        const int64_t j = (w0 + u) * 64 + lane;
-        c[u] = j < nnz ? col[j] : 0;
-        bits[u] = j < nnz ? row_bits[j >> 5] : 0u;
+    uint64_t todo = __ballot(active);
+    uint32_t result = 0;
+    for (int it = 0; todo && it < 8; it++) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const int64_t k = __shfl(key, leader);
+        const uint64_t same = __ballot(active && key == k) & todo;
+        uint32_t base = 0;
+        if (lane == leader) base = atomicAdd(&counters[k], (uint32_t)__popcll(same));
+        base = __shfl(base, leader);
+        if ((same >> lane) & 1ull) result = base + (uint32_t)lanes_below(same);
+        todo &= ~same;
     }
-    int32_t before = -1;  // the nonzero in front of this wavefront's first
-    if (lane == 0 && w0 > 0) before = col[w0 * 64 - 1];
+    if ((todo >> lane) & 1ull) result = atomicAdd(&counters[key], 1u);
+    return result;
+}
+
+// Smallest i in [lo, hi] for which reached(i) holds, given that reached(hi) does: the lanes of a wavefront ask
+// for 64 candidates at once, so that a million entries take four dependent steps instead of twenty.
+template <typename F>
+__device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reached)
+{
+    const int lane = threadIdx.x & 63;
+    while (lo < hi) {  // wave-uniform
+        const int32_t step = (int32_t)(((int64_t)hi - lo + 63) / 64);
+        const int32_t i = (int32_t)min((int64_t)hi, lo + (int64_t)lane * step);
+        const uint64_t yes = __ballot(reached(i));
+        if (yes & 1) return lo;
+        if (yes == 0) {  // behind the last candidate below hi
+            lo = (int32_t)min((int64_t)hi, lo + 63 * (int64_t)step + 1);
+        } else {
+            const int f = __builtin_ctzll(yes);
+            hi = (int32_t)min((int64_t)hi, lo + (int64_t)f * step);
+            lo = (int32_t)(lo + (int64_t)(f - 1) * step + 1);
+        }
+    }
+    return lo;
+}
+
+// The segments of kTile consecutive nonzeros per workgroup: a nonzero starts one when it starts a row or
+// its block column differs from its left neighbour's.  The rows that start inside the tile are read from
+// csr_ptr (empty rows own no position) into an LDS table by position; a segment's row is the last one
+// that starts at or before it.  Two passes over the matrix (bound by reading csr_col, 4 bytes per nonzero, and in the
+// second pass by writing 8 bytes per segment), with the scans over the block table between them:
+//   EMIT false  counts the segments of every block (cursor: the block table) and notes every tile's first
+//               segment start;
+//   EMIT true   drops (length << 16 | local row, first nonzero) of every segment into its block's slot range
+//               (cursor: the blocks' next free slots), in no particular order: k_order_block sorts them.
+// A tile's rows are neighbours, so it touches the blocks of a few row blocks only: (bm_hi - bm_lo + 1) * NBC
+// counters.  When those fit in LDS the tile counts there (LDS integer atomics are two orders of magnitude
+// faster than scattered global ones) and goes to global memory once per counter it has touched;
+// otherwise every segment goes to global memory with wave-aggregated atomics.
+// (Before: row-start bits by global atomics, segment flags, a scan, segment records with a binary search per
+// segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
+// on the 4M x 1M lognormal matrix, 555 now; 300 and 300 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
+// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.)
+// the value of the lane below; lane 0 gets `first`
+__device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false); }
+
+template <bool EMIT>
+__global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col, int64_t n_rows,
+                                                           int64_t nnz, int64_t n_cols, int32_t R, int32_t shift_r, int32_t C, int32_t shift_c,
+                                                           int32_t NBR, int32_t NBC, int validate, const int32_t *__restrict__ tile_row,
+                                                           int32_t *__restrict__ tile_first, uint32_t *__restrict__ cursor,
+                                                           uint2 *__restrict__ bucket, int32_t *err)
+{
+    __shared__ uint32_t cnt[kTileCounters];
+    __shared__ __align__(16) int32_t row_at[kTile];  // row that starts at a position, counted from the tile's first row; -1: none
+    __shared__ int32_t word_last[kTileWords], word_first[kTileWords];  // last row start, first segment start of a word; -1, kTile: none
+    __shared__ int32_t sh_row, sh_next;
+    if (*err & kErrPtr) return;  // k_check_ptr's finding: the rows below would not ascend
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t j0 = (int64_t)blockIdx.x * kTile;
+    const int32_t count = (int32_t)min((int64_t)kTile, nnz - j0);
+    const int32_t first_word = wave * kWordsPerWave;
+    int32_t c[kWordsPerWave], before = -1;  // before: the nonzero in front of this wavefront's first
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
-        const int64_t w = w0 + u;
-        if (w >= n_words) break;  // wave-uniform
-        const int64_t j = w * 64 + lane;
-        const bool valid = j < nnz;
-        int32_t c_prev = __shfl_up(c[u], 1);
-        const int32_t last_of_prev = u > 0 ? __shfl(c[u > 0 ? u - 1 : 0], 63) : before;
-        if (lane == 0) c_prev = last_of_prev;
-        const bool row_start = valid && ((bits[u] >> (j & 31)) & 1u);
+        const int32_t i = (first_word + u) * 64 + lane;
+        c[u] = i < count ? col[j0 + i] : 0;
+    }
+    if (lane == 0 && j0 + first_word * 64 > 0 && first_word * 64 < count) before = col[j0 + first_word * 64 - 1];
+    for (int i = threadIdx.x; i < kTile / 4; i += kTileThreads) reinterpret_cast<int4 *>(row_at)[i] = int4{-1, -1, -1, -1};
+    if (EMIT && wave == 0) {  // where the segment that is open at the tile's end ends: a segment has fewer than 2^16 nonzeros, 16 tiles
+        const int64_t tiles = (nnz + kTile - 1) / kTile, t = (int64_t)blockIdx.x + 1 + lane;
+        const int32_t f = t < tiles ? tile_first[t] : (int32_t)nnz;
+        const uint64_t there = __ballot(f >= 0);
+        const int32_t next = there ? __shfl(f, __builtin_ctzll(there)) : (int32_t)nnz;
+        if (lane == 0) sh_next = next;
+    }
+    __syncthreads();
+    const int32_t row_lo = tile_row[blockIdx.x];
+    for (int64_t r0 = row_lo;;) {
+        const int64_t r = r0 + threadIdx.x;
+        int64_t p0 = nnz, p1 = nnz;
+        if (r < n_rows) { p0 = ptr[r]; p1 = ptr[r + 1]; }
+        const bool starts = p1 > p0 && p0 >= j0 && p0 < j0 + count;
+        if (starts) row_at[p0 - j0] = (int32_t)(r - row_lo);
+        // more rows start in the tile if the last of these starts in it; none of these did: a gap, jump over it
+        const bool go_on = __syncthreads_or(threadIdx.x == kTileThreads - 1 && p0 < j0 + count);
+        if (!go_on) break;
+        r0 += kTileThreads;
+        if (!__syncthreads_or(starts)) {
+            if (wave == 0) {
+                const int64_t p = ptr[r0];
+                int32_t next = (int32_t)n_rows;
+                if (p < j0 + count) next = first_reached((int32_t)r0, (int32_t)n_rows, [&](int32_t i) { return i >= n_rows || ptr[i + 1] > p; });
+                if (lane == 0) sh_row = next;
+            }
+            __syncthreads();
+            r0 = sh_row;
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    uint64_t rows_here[kWordsPerWave];
+#pragma unroll
+    for (int u = 0; u < kWordsPerWave; u++) {
+        const int32_t w = first_word + u, r = row_at[w * 64 + lane];
+        rows_here[u] = __ballot(r >= 0);
+        const int32_t last = rows_here[u] ? __builtin_amdgcn_readlane(r, 63 - __clzll((long long)rows_here[u])) : -1;
+        if (lane == 0) word_last[w] = last;
+    }
+    __syncthreads();
+    // lane w: the last row that starts in the words 0 .. w (rows ascend)
+    int32_t last_row = max(0, word_last[lane]);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t up = __shfl_up(last_row, d);
+        if (lane >= d) last_row = max(last_row, up);
+    }
+    auto row_block = [&](int32_t row) { return shift_r >= 0 ? row >> shift_r : row / R; };
+    const int32_t bm_lo = row_block(row_lo), bm_hi = row_block(row_lo + __builtin_amdgcn_readlane(last_row, 63));
+    const int64_t counters = (int64_t)(bm_hi - bm_lo + 1) * NBC;
+    const bool in_lds = counters <= kTileCounters;
+    if (in_lds) {
+        for (int i = threadIdx.x; i < (int)counters; i += kTileThreads) cnt[i] = 0u;
+        __syncthreads();
+    }
+    int32_t row[kWordsPerWave], local[kWordsPerWave];
+    uint32_t rank[kWordsPerWave];
+    uint64_t starts[kWordsPerWave];
+    int32_t last_bn = 0;  // block column of the last nonzero of the word before
+#pragma unroll
+    for (int u = 0; u < kWordsPerWave; u++) {
+        const int32_t w = first_word + u, i = w * 64 + lane;
+        const bool valid = i < count;
+        const uint64_t up_to_me = rows_here[u] & ((2ull << lane) - 1ull);
+        const int32_t carried = w > 0 ? __builtin_amdgcn_readlane(last_row, w > 0 ? w - 1 : 0) : 0;
+        row[u] = row_lo + (up_to_me ? row_at[w * 64 + 63 - __clzll((long long)up_to_me)] : carried);
+        const bool row_start = (rows_here[u] >> lane) & 1ull;
+        const int32_t c_prev = lane_below(c[u], u > 0 ? __builtin_amdgcn_readlane(c[u > 0 ? u - 1 : 0], 63) : __builtin_amdgcn_readfirstlane(before));
         const bool in_range = c[u] >= 0 && c[u] < n_cols;
-        if (valid && !in_range) atomicOr(err, kErrCol);
-        if (validate && valid && !row_start && c[u] <= c_prev) atomicOr(err, kErrCol);
-        const bool start = valid && (row_start || block_column(c[u], C, shift_c) != block_column(c_prev, C, shift_c));
-        const uint64_t mask = __ballot(start);
-        if (lane == 0) {
-            seg_bits[w] = mask;
-            seg_cnt[w] = (uint32_t)__popcll(mask);
+        if (!EMIT && valid && (!in_range || (validate && !row_start && c[u] <= c_prev))) atomicOr(err, kErrCol);
+        const int32_t bn = block_column(c[u], C, shift_c);
+        const int32_t bn_prev = lane_below(bn, u > 0 ? last_bn : block_column(__builtin_amdgcn_readfirstlane(before), C, shift_c));
+        last_bn = __builtin_amdgcn_readlane(bn, 63);
+        const bool start = valid && (row_start || bn != bn_prev);
+        starts[u] = __ballot(start);
+        if (lane == 0) word_first[w] = starts[u] ? w * 64 + __builtin_ctzll(starts[u]) : kTile;
+        local[u] = -1;
+        rank[u] = 0;
+        const bool mine = start && in_range;  // (a column out of range has been reported; never index with it)
+        if (in_lds) {
+            if (mine) {
+                local[u] = (row_block(row[u]) - bm_lo) * NBC + bn;
+                rank[u] = atomicAdd(&cnt[local[u]], 1u);
+            }
+        } else {
+            rank[u] = aggregated_add(cursor, mine ? (int64_t)bn * NBR + row_block(row[u]) : 0, mine);
+            if (mine) local[u] = 0;
         }
     }
-}
-
-// Segment list: every set bit of seg_bits becomes a segment (first nonzero, row, block column).
-// A wavefront takes kWordsPerWave words; the row of a segment start is found by a binary search
-// over the rows its word spans, the searches of the wavefront's words advancing together so that
-// their loads overlap.
-__global__ __launch_bounds__(256) void k_seg_emit(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                                                  const uint64_t *__restrict__ seg_bits, const uint32_t *__restrict__ word_off,
-                                                  const int32_t *__restrict__ word_row, int64_t nnz, int64_t n_cols,
-                                                  int32_t R, int32_t C, int32_t shift_c, int32_t NBR, int64_t n_words,
-                                                  int32_t *__restrict__ seg_j, int32_t *__restrict__ seg_row,
-                                                  int32_t *__restrict__ seg_bn)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kWordsPerWave;
-    if (w0 >= n_words) return;
-    uint64_t mask[kWordsPerWave];
-    int32_t c[kWordsPerWave], lo[kWordsPerWave], hi[kWordsPerWave];
-    uint32_t off[kWordsPerWave];
-    bool mine[kWordsPerWave];
-#pragma unroll
-    for (int u = 0; u < kWordsPerWave; u++) {
-        const int64_t w = min(w0 + u, n_words - 1);
-        mask[u] = w0 + u < n_words ? seg_bits[w] : 0ull;
-        off[u] = word_off[w];
-        lo[u] = word_row[w];
-        hi[u] = word_row[w + 1];
-    }
-    if (w0 + kWordsPerWave >= n_words && lane == 0) seg_j[word_off[n_words]] = (int32_t)nnz;  // sentinel: end of the last segment
-#pragma unroll
-    for (int u = 0; u < kWordsPerWave; u++) {
-        mine[u] = (mask[u] >> lane) & 1ull;
-        c[u] = mine[u] ? col[(w0 + u) * 64 + lane] : 0;
-        if (c[u] < 0 || c[u] >= n_cols) mine[u] = false;  // already reported; never index with it
-        if (!mine[u]) hi[u] = lo[u];
-    }
-    for (;;) {  // largest row with ptr[row] <= j, for all words at once
-        bool any = false;
-        int32_t mid[kWordsPerWave], p[kWordsPerWave];
-#pragma unroll
-        for (int u = 0; u < kWordsPerWave; u++) {
-            mid[u] = lo[u] + ((hi[u] - lo[u] + 1) >> 1);
-            any |= lo[u] < hi[u];
-        }
-        if (!__ballot(any)) break;
-#pragma unroll
-        for (int u = 0; u < kWordsPerWave; u++) p[u] = ptr[mid[u]];
-#pragma unroll
-        for (int u = 0; u < kWordsPerWave; u++) {
-            if (lo[u] < hi[u]) {
-                if (p[u] <= (w0 + u) * 64 + lane) lo[u] = mid[u]; else hi[u] = mid[u] - 1;
+    __syncthreads();
+    if (in_lds) {
+        for (int i = threadIdx.x; i < (int)counters; i += kTileThreads) {
+            const uint32_t n = cnt[i];
+            if (n) {
+                const uint32_t at = atomicAdd(&cursor[(int64_t)(i % NBC) * NBR + bm_lo + i / NBC], n);
+                if (EMIT) cnt[i] = at;
             }
         }
     }
+    if constexpr (!EMIT) {
+        if (wave == 0) {
+            const int32_t f = word_first[lane];
+            const uint64_t there = __ballot(f < kTile);
+            const int32_t first = there ? __shfl(f, __builtin_ctzll(there)) : -1;
+            if (lane == 0) tile_first[blockIdx.x] = first < 0 ? -1 : (int32_t)(j0 + first);
+        }
+    } else {
+        __syncthreads();
+        // lane w: the first segment start in the words w .. 63
+        int32_t next_start = word_first[lane];
 #pragma unroll
-    for (int u = 0; u < kWordsPerWave; u++) {
-        if (!mine[u]) continue;
-        const uint32_t s = off[u] + (uint32_t)lanes_below(mask[u]);
-        seg_j[s] = (int32_t)((w0 + u) * 64 + lane);
-        seg_row[s] = lo[u];
-        seg_bn[s] = block_column(c[u], C, shift_c);
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t down = __shfl_down(next_start, d);
+            if (lane + d < 64) next_start = min(next_start, down);
+        }
+#pragma unroll
+        for (int u = 0; u < kWordsPerWave; u++) {
+            const int32_t w = first_word + u, i = w * 64 + lane;
+            const uint64_t above = starts[u] & ~((2ull << lane) - 1ull);
+            const int32_t later = w < kTileWords - 1 ? __builtin_amdgcn_readlane(next_start, w < kTileWords - 1 ? w + 1 : 0) : kTile;
+            const int32_t j = (int32_t)(j0 + i);
+            const int32_t end = above ? (int32_t)(j0 + w * 64) + __builtin_ctzll(above) : later < kTile ? (int32_t)(j0 + later) : sh_next;
+            if (local[u] < 0) continue;
+            const uint32_t pos = rank[u] + (in_lds ? cnt[local[u]] : 0u);
+            bucket[pos] = {((uint32_t)(end - j) << 16) | (uint32_t)(row[u] - row_block(row[u]) * R), (uint32_t)j};  // length <= C <= 32768
+        }
     }
 }
 
@@ -517,145 +617,6 @@ __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict
 
 // ------------------------------------------------------------------ steps 5-6: hash + placement
 
-// Wave-aggregated fetch-add: lanes of the wavefront that target the same counter are served by
-// one atomic (neighbouring segments mostly fall into the same block, and same-address atomics
-// serialise).  Returns, for an active lane, the value its own atomicAdd(&counters[key], 1) would
-// have returned in some serial order.  After a few distinct keys the rest go one by one.
-__device__ __forceinline__ uint32_t aggregated_add(uint32_t *counters, int64_t key, bool active)
-{
-    const int lane = threadIdx.x & 63;
-    uint64_t todo = __ballot(active);
-    uint32_t result = 0;
-    for (int it = 0; todo && it < 8; it++) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int64_t k = __shfl(key, leader);
-        const uint64_t same = __ballot(active && key == k) & todo;
-        uint32_t base = 0;
-        if (lane == leader) base = atomicAdd(&counters[k], (uint32_t)__popcll(same));
-        base = __shfl(base, leader);
-        if ((same >> lane) & 1ull) result = base + (uint32_t)lanes_below(same);
-        todo &= ~same;
-    }
-    if ((todo >> lane) & 1ull) result = atomicAdd(&counters[key], 1u);
-    return result;
-}
-
-// Tiles for the two passes that touch a per-block counter for every segment.  A workgroup takes
-// kTileSegs consecutive segments.  They are in CSR order, so their rows ascend and the tile
-// touches the blocks of a few neighbouring row blocks only: (bm_hi - bm_lo + 1) * NBC counters.
-// When those fit in LDS the tile counts there (LDS integer atomics are two orders of magnitude
-// faster than scattered global ones) and goes to global memory once per counter it has
-// touched; otherwise every segment goes to global memory with wave-aggregated atomics.
-constexpr int kTileSegs = 2048;      // 256 threads x 8 segments
-constexpr int kTileCounters = 8192;  // 32 KB of LDS
-
-struct Tile {
-    int64_t base, S;
-    int32_t bm_lo, span;  // span = 0: the counters do not fit
-};
-
-__device__ __forceinline__ Tile tile_of(const int32_t *__restrict__ seg_row, int64_t S, int32_t R, int32_t NBC)
-{
-    Tile t;
-    t.S = S;
-    t.base = (int64_t)blockIdx.x * kTileSegs;
-    t.bm_lo = 0;
-    t.span = 0;
-    if (t.base < S) {
-        const int64_t last = min(t.base + kTileSegs, S) - 1;
-        t.bm_lo = seg_row[t.base] / R;
-        const int64_t span = (int64_t)(seg_row[last] / R - t.bm_lo + 1) * NBC;
-        t.span = span <= kTileCounters ? (int32_t)span : 0;
-    }
-    return t;
-}
-
-// Segments per block of the (column block, row block) table.
-// The segment count is still on the device (last entry of the scan) and the records of a
-// malformed matrix are incomplete, hence S_ptr and err.
-__global__ __launch_bounds__(256) void k_count_blocks(const int32_t *__restrict__ seg_row, const int32_t *__restrict__ seg_bn,
-                                                      const uint32_t *__restrict__ S_ptr, const int32_t *__restrict__ err,
-                                                      int32_t R, int32_t NBR, int32_t NBC, uint32_t *__restrict__ dense_cnt)
-{
-    __shared__ uint32_t cnt[kTileCounters];
-    if (*err) return;
-    const Tile t = tile_of(seg_row, (int64_t)*S_ptr, R, NBC);
-    if (t.base >= t.S) return;
-    if (t.span == 0) {
-        for (int i = 0; i < kTileSegs / 256; i++) {
-            const int64_t s = t.base + i * 256 + threadIdx.x;
-            const bool active = s < t.S;
-            const int64_t d = active ? (int64_t)seg_bn[s] * NBR + seg_row[s] / R : 0;
-            aggregated_add(dense_cnt, d, active);
-        }
-        return;
-    }
-    for (int i = threadIdx.x; i < t.span; i += 256) cnt[i] = 0u;
-    __syncthreads();
-    for (int i = 0; i < kTileSegs / 256; i++) {
-        const int64_t s = t.base + i * 256 + threadIdx.x;
-        if (s < t.S) atomicAdd(&cnt[(seg_row[s] / R - t.bm_lo) * NBC + seg_bn[s]], 1u);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < t.span; i += 256) {
-        const uint32_t c = cnt[i];
-        if (c) atomicAdd(&dense_cnt[(int64_t)(i % NBC) * NBR + t.bm_lo + i / NBC], c);
-    }
-}
-
-// Bucketed scatter: (length << 16 | local row, first nonzero) of every segment into its block's
-// slot range.  The order in which the segments of a block arrive is arbitrary (k_order_block
-// computes the keys and sorts them).
-__global__ __launch_bounds__(256) void k_bucket(const int32_t *__restrict__ seg_j, const int32_t *__restrict__ seg_row,
-                                                const int32_t *__restrict__ seg_bn, int64_t S, int32_t R, int32_t NBR, int32_t NBC,
-                                                uint32_t *__restrict__ cursor, uint32_t *__restrict__ bucket_len_row, int32_t *__restrict__ bucket_j)
-{
-    __shared__ uint32_t cnt[kTileCounters];  // per counter of the tile: segments seen, then their first position
-    const Tile t = tile_of(seg_row, S, R, NBC);
-    if (t.base >= t.S) return;
-    auto emit = [&](int64_t s, int32_t row, uint32_t pos) {
-        const int32_t j0 = seg_j[s];
-        bucket_len_row[pos] = ((uint32_t)(seg_j[s + 1] - j0) << 16) | (uint32_t)(row % R);  // length <= C <= 32768
-        bucket_j[pos] = j0;
-    };
-    if (t.span == 0) {
-        for (int i = 0; i < kTileSegs / 256; i++) {
-            const int64_t s = t.base + i * 256 + threadIdx.x;
-            const bool active = s < t.S;
-            const int32_t row = active ? seg_row[s] : 0;
-            const int64_t d = active ? (int64_t)seg_bn[s] * NBR + row / R : 0;
-            const uint32_t pos = aggregated_add(cursor, d, active);
-            if (active) emit(s, row, pos);
-        }
-        return;
-    }
-    for (int i = threadIdx.x; i < t.span; i += 256) cnt[i] = 0u;
-    __syncthreads();
-    int32_t row[kTileSegs / 256], local[kTileSegs / 256];
-    uint32_t rank[kTileSegs / 256];
-#pragma unroll
-    for (int i = 0; i < kTileSegs / 256; i++) {
-        const int64_t s = t.base + i * 256 + threadIdx.x;
-        row[i] = 0; local[i] = 0; rank[i] = 0;
-        if (s < t.S) {
-            row[i] = seg_row[s];
-            local[i] = (row[i] / R - t.bm_lo) * NBC + seg_bn[s];
-            rank[i] = atomicAdd(&cnt[local[i]], 1u);
-        }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < t.span; i += 256) {
-        const uint32_t c = cnt[i];
-        if (c) cnt[i] = atomicAdd(&cursor[(int64_t)(i % NBC) * NBR + t.bm_lo + i / NBC], c);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kTileSegs / 256; i++) {
-        const int64_t s = t.base + i * 256 + threadIdx.x;
-        if (s < t.S) emit(s, row[i], cnt[local[i]] + rank[i]);
-    }
-}
-
 // Which blocks a workgroup of k_fill takes.  The kernel gathers from arrays in CSR order (columns,
 // values), where the pieces that the blocks of one row block need lie side by side in the same
 // 128-byte lines.  Taken in the layout's column-major order every block fetches those lines anew
@@ -724,7 +685,7 @@ __device__ __forceinline__ void scan_in_lds(uint32_t *a, int n, uint32_t *sh_wav
 // sum over (digit, tile) turns the counts into positions.  As many passes as the block's largest
 // key has hex digits.  Smaller blocks (the passes would still walk all R rows): a bitonic network
 // over (key, row, length, position) words.
-__global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict__ bucket_len_row, const int32_t *__restrict__ bucket_j,
+__global__ __launch_bounds__(256) void k_order_block(const uint2 *__restrict__ bucket,
                                                      const int32_t *__restrict__ slot_ptr, const int32_t *__restrict__ blk_group_ptr,
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,
                                                      int32_t *__restrict__ slot_j, uint32_t *__restrict__ group_nnz, uint32_t *__restrict__ group_longest,
@@ -737,7 +698,7 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
     extern __shared__ __align__(8) uint32_t order_lds[];  // two arrays of cap entries, then 16 counters per tile of 64
     __shared__ uint32_t sh_hist[14];
     __shared__ int32_t sh_shift;
-    __shared__ uint32_t sh_max_key, sh_wave[4], sh_long_n, sh_long_at;
+    __shared__ uint32_t sh_max_key, sh_wave[4], sh_long_n, sh_long_at, sh_longest;
     constexpr uint32_t kHole = 0xffffffffu;
     constexpr int kSmallBlock = 256;  // slots: one entry per thread
     const int cap = (int)((R + 63u) & ~63u);
@@ -752,12 +713,13 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
     if (threadIdx.x == 0) {
         sh_max_key = 0u;
         sh_long_n = 0u;
+        sh_longest = 0u;
         sh_shift = *a_ptr;
     }
     __syncthreads();
     if (reorder == 3) {
         for (int i = threadIdx.x; i < m; i += 256) {
-            const uint32_t n = bucket_len_row[s0 + i] >> 16;
+            const uint32_t n = bucket[s0 + i].x >> 16;
             int a = 0;
             while (a < 13 && n >= (9u << a)) a++;
             atomicAdd(&sh_hist[a], 1u);
@@ -778,6 +740,14 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
     auto key_of = [&](uint32_t n) __attribute__((always_inline)) {
         return reorder == 0 ? 0u : reorder == 2 ? n : hash_key(n, shift_a, band, R);
     };
+    // What the slots are sorted by.  The hash is b = d bands of class (n >> a, 8 at most) and inside them ascends with n
+    // mod 2^a; where a band is wide enough to keep all 2^a remainders apart, class and remainder put side by
+    // side give the same order and the same ties in 4 + a bits instead of the key's 11 (R = 2048): one pass over
+    // the block instead of three at a = 0 (4M x 1M lognormal matrix 732 -> 529 us).
+    const bool compact = (reorder == 1 || reorder == 3) && R >= 9u && band >= (1u << shift_a);
+    auto sort_key = [&](uint32_t n) __attribute__((always_inline)) {
+        return compact ? (min(n >> shift_a, 8u) << shift_a) | (n & ((1u << shift_a) - 1u)) : key_of(n);
+    };
     if (threadIdx.x == 0) blk_shift[b] = (int32_t)shift_a;
     if (small) {
         uint64_t *wide = reinterpret_cast<uint64_t *>(order_lds);  // 2 cap words: room for cap >= m entries
@@ -786,8 +756,8 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
         for (int i = threadIdx.x; i < n2; i += 256) {
             uint64_t e = ~0ull;
             if (i < m) {
-                const uint32_t lr = bucket_len_row[s0 + i];
-                e = ((uint64_t)key_of(lr >> 16) << 48) | ((uint64_t)(lr & 0xffffu) << 32) | (lr & 0xffff0000u) | (uint32_t)i;
+                const uint32_t lr = bucket[s0 + i].x;
+                e = ((uint64_t)sort_key(lr >> 16) << 48) | ((uint64_t)(lr & 0xffffu) << 32) | (lr & 0xffff0000u) | (uint32_t)i;
             }
             wide[i] = e;
         }
@@ -809,15 +779,15 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
             const uint32_t n = (uint32_t)(e >> 16) & 0xffffu;
             row_local[s0 + i] = (uint16_t)((e >> 32) & 0xffffu);
             seg_len[s0 + i] = (uint16_t)n;
-            if (slot_key) slot_key[s0 + i] = (uint32_t)(e >> 48);
-            slot_j[s0 + i] = bucket_j[s0 + (int32_t)(e & 0xffffu)];  // a gather inside the block's own range
+            if (slot_key) slot_key[s0 + i] = key_of(n);
+            slot_j[s0 + i] = (int32_t)bucket[s0 + (int32_t)(e & 0xffffu)].y;  // a gather inside the block's own range
             to[i] = n;
         }
     } else {
         uint32_t most = 0;
         for (int i = threadIdx.x; i < m; i += 256) {
-            const uint32_t lr = bucket_len_row[s0 + i];
-            const uint32_t key = key_of(lr >> 16);
+            const uint32_t lr = bucket[s0 + i].x;
+            const uint32_t key = sort_key(lr >> 16);
             from[lr & 0xffffu] = (key << 16) | (uint32_t)i;
             most = max(most, key);
         }
@@ -888,11 +858,12 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
         for (int i = threadIdx.x; i < m; i += 256) {
             const uint32_t e = from[i];
             const int32_t at = s0 + (int32_t)(e & 0xffffu);  // the segment's place in the block's bucket (gathers inside the block's own range)
-            const uint32_t lr = bucket_len_row[at];
+            const uint2 entry = bucket[at];
+            const uint32_t lr = entry.x;
             row_local[s0 + i] = (uint16_t)(lr & 0xffffu);
             seg_len[s0 + i] = (uint16_t)(lr >> 16);
-            if (slot_key) slot_key[s0 + i] = e >> 16;
-            slot_j[s0 + i] = bucket_j[at];
+            if (slot_key) slot_key[s0 + i] = key_of(lr >> 16);
+            slot_j[s0 + i] = (int32_t)entry.y;
             to[i] = lr >> 16;
         }
     }
@@ -911,15 +882,16 @@ __global__ __launch_bounds__(256) void k_order_block(const uint32_t *__restrict_
         if (lane == 0) {
             group_nnz[g0 + gi] = sum;
             group_longest[g0 + gi] = longest;
-            // only that long rows matter to the caller; most of them are not the longest so far
-            if (longest > heavy_rounds && longest > *(volatile uint32_t *)longest_all) atomicMax(longest_all, longest);
+            // only that long rows matter to the caller
+            if (longest > heavy_rounds) atomicMax(&sh_longest, longest);
             group_slot[g0 + gi] = s0 + gi * W;
             group_blk[g0 + gi] = b;
             if (long_groups && is_long_group((int32_t)sum, (int32_t)longest, flat_wpg)) listed[atomicAdd(&sh_long_n, 1u)] = g0 + gi;
         }
     }
-    if (!long_groups) return;
     __syncthreads();
+    if (threadIdx.x == 0 && sh_longest) atomicMax(longest_all, sh_longest);
+    if (!long_groups) return;
     const uint32_t found = sh_long_n;
     if (found == 0) return;
     if (threadIdx.x == 0) sh_long_at = atomicAdd(n_long, found);
@@ -1159,28 +1131,6 @@ __global__ __launch_bounds__(256) void k_col_groups(const int32_t *__restrict__ 
         run += col_group_ptr[c + 1] > col_group_ptr[c];
     }
     if (threadIdx.x == 0) col_rank[NBC] = (int32_t)total;
-}
-
-// Smallest i in [lo, hi] for which reached(i) holds, given that reached(hi) does: the lanes of a wavefront ask
-// for 64 candidates at once, so that a million groups take four dependent steps instead of twenty.
-template <typename F>
-__device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reached)
-{
-    const int lane = threadIdx.x & 63;
-    while (lo < hi) {  // wave-uniform
-        const int32_t step = (int32_t)(((int64_t)hi - lo + 63) / 64);
-        const int32_t i = (int32_t)min((int64_t)hi, lo + (int64_t)lane * step);
-        const uint64_t yes = __ballot(reached(i));
-        if (yes & 1) return lo;
-        if (yes == 0) {  // behind the last candidate below hi
-            lo = (int32_t)min((int64_t)hi, lo + 63 * (int64_t)step + 1);
-        } else {
-            const int f = __builtin_ctzll(yes);
-            hi = (int32_t)min((int64_t)hi, lo + (int64_t)f * step);
-            lo = (int32_t)(lo + (int64_t)(f - 1) * step + 1);
-        }
-    }
-    return lo;
 }
 
 // One wavefront per worker w.
@@ -1611,23 +1561,16 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     }
 
     Arena tmp(false, h->device, 0);
-    const int64_t n_words = (nnz + 63) / 64;
-    const int64_t scan_n = std::max<int64_t>(std::max<int64_t>(n_words, D), std::max<int64_t>(NBR, nnz / W + D)) + 1;
-    uint32_t *row_bits, *seg_cnt, *word_off, *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
-    uint64_t *seg_bits;
-    int32_t *word_row, *seg_j, *seg_row, *seg_bn, *d_a, *d_err;
+    const int64_t n_tiles = (nnz + kTile - 1) / kTile;
+    const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
+    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
+    int32_t *tile_row, *tile_first, *d_a, *d_err;
     // the arrays that start at zero side by side: one fill
-    tmp.reserve(&row_bits, (nnz + 31) / 32 + 1);
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, 16);
     tmp.reserve(&d_err, 1);
-    tmp.reserve(&seg_bits, n_words);
-    tmp.reserve(&seg_cnt, n_words);
-    tmp.reserve(&word_off, n_words + 1);
-    tmp.reserve(&word_row, n_words + 1);
-    tmp.reserve(&seg_j, nnz + 1);     // S <= nnz: sized by the bound, no host round trip needed
-    tmp.reserve(&seg_row, nnz);
-    tmp.reserve(&seg_bn, nnz);
+    tmp.reserve(&tile_first, n_tiles);
+    tmp.reserve(&tile_row, n_tiles);
     tmp.reserve(&slot_off, D + 1);
     tmp.reserve(&group_off, D + 1);
     tmp.reserve(&blk_id, D + 1);
@@ -1635,7 +1578,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&scan_tmp, 3 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
     HBP_TRY(tmp.commit());
-    HBP_HIP(hipMemsetAsync(row_bits, 0, (size_t)((char *)seg_bits - (char *)row_bits), st));
+    HBP_HIP(hipMemsetAsync(dense_cnt, 0, (size_t)((char *)tile_first - (char *)dense_cnt), st));
 
     // Section 3.2: shift a, sampled or given
     if (p.hash_shift >= 0) {
@@ -1647,18 +1590,15 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     }
 
     // steps 1-3
-    k_row_bits<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, row_bits, d_err);
-    k_word_rows<<<blocks_for(n_words + 1, 256), 256, 0, st>>>(csr_ptr, n_rows, n_words, word_row);
-    int32_t shift_c = -1;  // C = 2^shift_c, or -1
-    for (int32_t b = 0; b < 31; b++)
+    int32_t shift_c = -1, shift_r = -1;  // C = 2^shift_c, R = 2^shift_r, or -1
+    for (int32_t b = 0; b < 31; b++) {
         if (C == (int32_t(1) << b)) shift_c = b;
-    k_seg_flags<<<blocks_for(n_words, 4 * kWordsPerWave), 256, 0, st>>>(csr_col, row_bits, nnz, n_cols, C, shift_c, n_words,
-                                                                       (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, seg_bits, seg_cnt, d_err);
-    HBP_TRY(exclusive_scan(seg_cnt, word_off, n_words, scan_tmp, st));
-    k_seg_emit<<<blocks_for(n_words, 4 * kWordsPerWave), 256, 0, st>>>(csr_ptr, csr_col, seg_bits, word_off, word_row, nnz, n_cols, R, C,
-                                                                      shift_c, (int32_t)NBR, n_words, seg_j, seg_row, seg_bn);
-    k_count_blocks<<<blocks_for(nnz, kTileSegs), 256, 0, st>>>(seg_row, seg_bn, word_off + n_words, d_err, R, (int32_t)NBR, (int32_t)NBC,
-                                                               dense_cnt);
+        if (R == (int32_t(1) << b)) shift_r = b;
+    }
+    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tile_row, d_err);
+    k_segments<false><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
+                                                                        (int32_t)NBC, (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, tile_row,
+                                                                        tile_first, dense_cnt, nullptr, d_err);
     // step 4: scans over the block table
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
@@ -1703,10 +1643,10 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     Arena tmp2(false, h->device, 1);
     uint32_t *stripe_cum, *unit_cnt, *multi_idx;
     tmp2.reserve(&stripe_cum, B + 1); tmp2.reserve(&unit_cnt, NBR + 1); tmp2.reserve(&multi_idx, NBR + 1);
-    uint32_t *bucket_len_row, *group_nnz, *group_longest, *longest_all, *d_n_long;
-    int32_t *bucket_j;
+    uint2 *bucket;
+    uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
-    tmp2.reserve(&bucket_len_row, S); tmp2.reserve(&bucket_j, S);
+    tmp2.reserve(&bucket, S);
     tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 2);
     HBP_TRY(tmp2.commit());
     d_n_long = longest_all + 1;
@@ -1726,8 +1666,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                      h->unit_stripe, h->unit_k, h->multi_stripes);
     // steps 5-6 (slot_off doubles as the per-block cursor from here on)
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
-    k_bucket<<<blocks_for(S, kTileSegs), 256, 0, st>>>(seg_j, seg_row, seg_bn, S, R, (int32_t)NBR, (int32_t)NBC, slot_off,
-                                                       bucket_len_row, bucket_j);
+    k_segments<true><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
+                                                                       (int32_t)NBC, 0, tile_row, tile_first, slot_off, bucket, d_err);
     // The order in which k_fill takes the blocks (see stripe_walk).  Row block by
     // row block pays where a row segment is a small part of the 128-byte lines it is gathered from
     // (fewer than 4 nonzeros on average) and the blocks are large enough to keep a workgroup busy
@@ -1744,7 +1684,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const size_t order_lds = std::max(sizeof(uint32_t) * (2 * order_cap + 16 * (order_cap / 64)),  // two entry arrays, 16 counters per tile
                                       sizeof(uint64_t) * small_n2);
     HBP_HIP(hipFuncSetAttribute((const void *)k_order_block, hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds));
-    k_order_block<<<dim3((unsigned)B), 256, order_lds, st>>>(bucket_len_row, bucket_j, h->slot_ptr, h->blk_group_ptr, W,
+    k_order_block<<<dim3((unsigned)B), 256, order_lds, st>>>(bucket, h->slot_ptr, h->blk_group_ptr, W,
                                                             h->row_local, h->seg_len, slot_j, group_nnz, group_longest, h->group_slot,
                                                             h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all,
                                                             d_n_long, h->long_groups, h->flat_wpg, reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);

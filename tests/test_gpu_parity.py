@@ -620,3 +620,23 @@ def test_rebuilds_reuse_memory_of_freed_handles(H, oracle):
         check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=256, cols_per_block=512, num_workers=9)
     H.hbp_release_workspace()
     check_against_oracle(H, oracle, a, check_add_sign=False, rows_per_block=256, cols_per_block=512, num_workers=9)
+
+
+@pytest.mark.parametrize("lens,n_cols,R,C", [
+    ([4095], 5000, 16, 4096), ([4096], 5000, 16, 5000), ([4096, 1], 5000, 16, 5000), ([1] * 4095 + [2], 3, 4096, 3),
+    ([8192, 8192], 8192, 1, 8192),                                     # segments longer than a tile, cut at its ends
+    ([20000, 3, 0, 0, 9000], 20000, 8, 20000),
+    ([2] * 2000 + [0] * 5000 + [3] * 40 + [0] * 30000 + [1] * 700, 600, 512, 128),   # gaps of empty rows inside a tile
+    ([0] * 3000 + [1, 0, 0, 0] * 1200 + [0] * 3000, 5000, 7, 100),     # few rows that start in a tile, many blocks
+])
+def test_segments_at_the_ends_of_tiles(H, oracle, lens, n_cols, R, C):
+    """The build finds the segments in tiles of 4096 nonzeros: sizes around one, rows and segments across several,
+    and rows without a nonzero between the rows of a tile."""
+    from workloads import CsrMatrix
+    rng = np.random.default_rng(len(lens))
+    lens = np.asarray(lens)
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    m = CsrMatrix("tiles", len(lens), n_cols, np.r_[0, np.cumsum(lens)].astype(np.int32), col,
+                  rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C)
+    check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C, hash_shift=5)   # bands narrower than 2^a
