@@ -182,6 +182,9 @@ constexpr int kLongSegment = 6;
 __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
                                                      int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist)
 {
+    // Pointers that do not start at 0 (a row slice of a larger matrix) are refused when the host has them; until then
+    // csr_col is not read through them: it has ptr[n_rows] entries at most if they do start at 0.
+    if (ptr[0] != 0) return;
     const int64_t nnz = ptr[n_rows];
     __shared__ uint32_t sh_hist[15];  // [14]: sampled segments with kLongSegment or more nonzeros
     if (threadIdx.x < 15) sh_hist[threadIdx.x] = 0;
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
     if (k < S) {
         const int64_t r = ((int64_t)k * n_rows) / S;
         int64_t j0 = ptr[r], j1 = ptr[r + 1];
-        if (j0 < 0 || j1 > nnz || j1 < j0) j1 = j0;  // malformed ptr is reported by the row-bit pass
+        if (j0 < 0 || j1 > nnz || j1 < j0) j1 = j0;  // malformed ptr is reported by k_check_ptr
         int64_t open = -1;                            // start of the segment whose end is not yet seen
         int bn_left = -1;                             // column block of the nonzero left of this chunk
         // A long row that spans few column blocks (R-MAT has rows of 10^5 nonzeros; walking one

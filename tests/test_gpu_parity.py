@@ -190,6 +190,24 @@ def test_invalid_inputs_are_errors(H):
     assert e.value.status == -4
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("params", [dict(), dict(rows_per_block=512, rounds_per_batch=8)])
+@pytest.mark.parametrize("first_row,n_rows", [(7, 5000), (4999, 1), (3000, 2000)])
+def test_row_slices_without_rebased_pointers_are_errors(H, first_row, n_rows, params, f64):
+    """The pointers of a row slice, not rebased, with the slice's own columns: ptr[0] = b, ptr[n] = b + nnz, nnz
+    columns.  Refused, with the parameters chosen from the matrix (a sampling pass) or given."""
+    m = random_csr(first_row + n_rows, 700, 0.05, 3)
+    ptr, col, val, _ = to_dev(m)
+    b, e = int(m.ptr[first_row]), int(m.ptr[-1])
+    assert b > 0
+    build = H.hbp_build_f64 if f64 else H.hbp_build
+    with pytest.raises(H.HbpError) as err:
+        build(ptr[first_row:].clone(), col[b:e].clone(), (val.double() if f64 else val)[b:e].clone(), n_rows, m.n_cols, **params)
+    assert err.value.status == -2
+    h = build((ptr[first_row:] - b).contiguous(), col[b:e].clone(), (val.double() if f64 else val)[b:e].clone(), n_rows, m.n_cols, **params)
+    H.hbp_free(h)
+
+
 @pytest.mark.parametrize("kind", [0, 1, 2, 4, 8, 16, 32])
 def test_csr_baselines(H, oracle, kind):
     import torch
