@@ -25,9 +25,10 @@ struct DeviceGuard {  // makes the handle's device current for the duration of a
     ~DeviceGuard() { if (prev >= 0) (void)hipSetDevice(prev); }
 };
 
-void free_arrays(hbp_handle_s *h)
+// `idle`: the caller has waited, successfully, for everything on the device that uses the handle
+void free_arrays(hbp_handle_s *h, bool idle)
 {
-    for (int i = 0; i < 2; i++) hbp::release_block(h->device, h->arena[i], h->arena_bytes[i]);
+    for (int i = 0; i < 2; i++) hbp::release_block(h->device, h->arena[i], h->arena_bytes[i], idle);
 }
 
 }  // namespace
@@ -156,8 +157,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
         rc = hbp::build_layout(h, csr_ptr, csr_col, csr_val, p, (hipStream_t)stream);
     }
     if (rc != HBP_OK) {
-        (void)hipStreamSynchronize((hipStream_t)stream);
-        free_arrays(h);
+        free_arrays(h, hipStreamSynchronize((hipStream_t)stream) == hipSuccess);
         delete h;
         return rc;
     }
@@ -221,8 +221,10 @@ int hbp_free(hbp_handle_t h)
 {
     if (!h) return HBP_OK;
     DeviceGuard guard(h->device);
-    (void)hipDeviceSynchronize();
-    free_arrays(h);
+    // The wait can be refused (while a stream of this process is being captured, for one), or may have gone to
+    // another device: products with this handle may then still be in flight.
+    const bool idle = guard.ok && hipDeviceSynchronize() == hipSuccess;
+    free_arrays(h, idle);
     delete h;
     return HBP_OK;
 }

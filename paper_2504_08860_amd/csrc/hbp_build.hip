@@ -1258,8 +1258,8 @@ int workspace_get(int device, int slot, size_t bytes, void **out)
 // Allocations of freed handles, kept for the next ones: a program that rebuilds its matrix (time stepping,
 // Newton) otherwise pays milliseconds per build for hipMalloc and hipFree of hundreds of megabytes
 // (mapping and unmapping; stencil 128^3: 4.0 of 5.2 ms).  Bounded per device by kCacheBytes and
-// kCacheBlocks, given back by hbp_release_workspace() and when an allocation fails.  hbp_free waits
-// for the device before a block comes here, so whatever stream gets it next finds it idle.
+// kCacheBlocks, given back by hbp_release_workspace() and when an allocation fails.  A block comes here only
+// after a wait for everything that used it has succeeded, so whatever stream gets it next finds it idle.
 constexpr size_t kCacheBytes = size_t(4) << 30;
 constexpr size_t kCacheBlocks = 16;
 struct CachedBlock { void *base; size_t bytes; };
@@ -1728,11 +1728,11 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     return HBP_OK;
 }
 
-// Takes back an allocation of a handle.  Nothing on the device uses it any more.
-void release_block(int device, void *base, size_t bytes)
+// Memory that may still be in use goes back to the driver, which does not hand it out before its users are done.
+void release_block(int device, void *base, size_t bytes, bool idle)
 {
     if (!base) return;
-    if (device < 0 || device >= kWorkspaceDevices || bytes > kCacheBytes) {
+    if (!idle || device < 0 || device >= kWorkspaceDevices || bytes > kCacheBytes) {
         (void)hipFree(base);
         return;
     }

@@ -135,7 +135,8 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
 int derive_add_sign(const hbp_handle_s *h, int32_t *d_out, hipStream_t stream);
 int hash_keys(const uint32_t *n, int64_t count, int32_t a, int32_t R, uint32_t *keys, hipStream_t stream);
 int release_workspace();
-void release_block(int device, void *base, size_t bytes);  // a handle's allocation, idle
+// takes back a handle's allocation; idle: nothing on the device uses it any more
+void release_block(int device, void *base, size_t bytes, bool idle);
 
 // spmv (hbp_spmv.hip)
 Layout hbp_view(const hbp_handle_s *h);

@@ -1,0 +1,124 @@
+"""What becomes of a handle's device memory, with a HIP runtime of the test's own in front of the real one: device
+memory is host memory of a stated capacity, kernels do nothing (so every matrix is an empty one) and a wait can be
+made to fail.  Runs on the CPU, in a process of its own."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+RUNTIME = r"""
+#include <stdlib.h>
+#include <string.h>
+#include <stddef.h>
+enum { kMax = 4096 };
+static void *at[kMax];
+static size_t size_of[kMax], live, capacity = (size_t)1 << 30;
+static int frees, refuse_waits;
+void set_capacity(size_t bytes) { capacity = bytes; }
+void set_refuse_waits(int yes) { refuse_waits = yes; }
+size_t live_bytes(void) { return live; }
+int free_calls(void) { return frees; }
+int hipMalloc(void **out, size_t bytes)
+{
+    if (live + bytes > capacity) return 2;  /* hipErrorOutOfMemory */
+    for (int i = 0; i < kMax; i++)
+        if (!at[i]) {
+            at[i] = *out = calloc(1, bytes);
+            size_of[i] = bytes;
+            live += bytes;
+            return 0;
+        }
+    abort();
+}
+int hipFree(void *p)
+{
+    for (int i = 0; i < kMax; i++)
+        if (p && at[i] == p) {
+            live -= size_of[i];
+            free(p);
+            at[i] = 0;
+            frees++;
+            return 0;
+        }
+    return 1;
+}
+int hipHostMalloc(void **out, size_t bytes, unsigned flags) { (void)flags; *out = calloc(1, bytes); return 0; }
+int hipHostFree(void *p) { free(p); return 0; }
+int hipMemsetAsync(void *p, int v, size_t n, void *s) { (void)s; memset(p, v, n); return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipSetDevice(int d) { (void)d; return 0; }
+int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
+int hipDeviceSynchronize(void) { return refuse_waits ? 900 : 0; }  /* hipErrorStreamCaptureUnsupported */
+int hipStreamSynchronize(void *s) { (void)s; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
+typedef struct { unsigned x, y, z; } dim3_;
+int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t lds, void *s)
+{
+    (void)f; (void)g; (void)b; (void)args; (void)lds; (void)s;
+    return 0;
+}
+"""
+
+PROGRAM = r"""
+import ctypes, sys
+rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # in front of the real runtime for what it defines
+lib = ctypes.CDLL(sys.argv[2])
+rt.live_bytes.restype = ctypes.c_size_t
+rt.set_capacity.argtypes = [ctypes.c_size_t]
+lib.hbp_build.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int64] * 2 + [ctypes.c_void_p] * 3
+lib.hbp_free.argtypes = [ctypes.c_void_p]
+word = ctypes.create_string_buffer(64)
+def build(n_rows, params=None):
+    h = ctypes.c_void_p()
+    rc = lib.hbp_build(word, word, word, n_rows, 100, params, None, ctypes.byref(h))
+    return rc, h
+"""
+
+
+def run(tmp_path, body):
+    import paper_2504_08860_amd as H
+    if not os.path.exists(H.LIB_PATH):
+        from paper_2504_08860_amd.build import build_library
+        build_library()
+    source, runtime = tmp_path / "runtime.c", tmp_path / "runtime.so"
+    source.write_text(RUNTIME)
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", str(source), "-o", str(runtime)])
+    program = tmp_path / "program.py"
+    program.write_text(PROGRAM + textwrap.dedent(body))
+    res = subprocess.run([sys.executable, str(program), str(runtime), H.LIB_PATH], capture_output=True, text=True, cwd=ROOT, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_memory_is_kept_after_a_wait_and_given_back(tmp_path):
+    run(tmp_path, """
+        rc, h = build(10**6)
+        assert rc == 0
+        held = rt.live_bytes()
+        assert lib.hbp_free(h) == 0
+        assert rt.live_bytes() == held and rt.free_calls() == 0        # kept
+        rc, h = build(10**6)
+        assert rc == 0 and rt.live_bytes() == held                     # and taken again
+        assert lib.hbp_free(h) == 0
+        assert lib.hbp_release_workspace() == 0 and rt.live_bytes() == 0
+    """)
+
+
+def test_memory_whose_wait_failed_is_not_handed_out_again(tmp_path):
+    run(tmp_path, """
+        rc, h = build(10**6)
+        assert rc == 0
+        before = rt.live_bytes()
+        rt.set_refuse_waits(1)
+        assert lib.hbp_free(h) == 0
+        rt.set_refuse_waits(0)
+        assert rt.free_calls() == 2                                    # both of the handle's allocations
+        after = rt.live_bytes()
+        rc, h = build(10**6)                                           # allocates anew
+        assert rc == 0 and rt.live_bytes() == before and after < before
+        assert lib.hbp_free(h) == 0
+    """)
