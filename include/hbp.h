@@ -250,7 +250,11 @@ int hbp_spmv_f64(hbp_handle_t h, const double *x, double *y, void *stream);
  * streams, different handles) race and must be ordered by the caller. */
 int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stream);
 
-/* Frees the handle and its device arrays (synchronises the device first). NULL is allowed. */
+/* Frees the handle (synchronises the device first).  NULL is allowed.  The library keeps the handle's device
+ * memory for the next builds (a build of much the same size then allocates nothing): at most 4 GiB in 16
+ * allocations per device, the oldest given up first.  hbp_release_workspace() gives it back; until then other
+ * allocators of the process cannot have it.  The library gives it up by itself where an allocation of its own
+ * fails.  Memory whose wait failed (a stream of the process is being captured) is not kept. */
 int hbp_free(hbp_handle_t h);
 
 /* Sizes, parameters and byte counts of a handle.  *info HOST. */
@@ -288,7 +292,7 @@ int hbp_hash_keys(const uint32_t *n, int64_t count, int32_t a, int32_t rows_per_
 /* hbp_build keeps its scratch memory (a few hundred megabytes for the large workloads, per
  * device) for the next build instead of freeing it: freeing costs a good part of a build.
  * Builds of one process therefore run one at a time.  This call gives the memory back (no build
- * may be running). */
+ * may be running), and with it the memory of freed handles (see hbp_free), on every device. */
 int hbp_release_workspace(void);
 
 const char *hbp_status_string(int status);

@@ -233,6 +233,7 @@ def hbp_spmv_timed_f64(handle: int, x, y, iters: int, stream=None):
 
 
 def hbp_free(handle: int) -> None:
+    """Frees the handle; its device memory is kept for the next builds until hbp_release_workspace()."""
     _check(lib().hbp_free(handle), "hbp_free")
 
 
@@ -281,5 +282,5 @@ def hbp_hash_keys(n, a: int, rows_per_block: int, stream=None):
 
 
 def hbp_release_workspace() -> None:
-    """Gives back the scratch memory hbp_build keeps between builds."""
+    """Gives back the scratch memory hbp_build keeps between builds and the memory kept of freed handles (at most 4 GiB per device)."""
     _check(lib().hbp_release_workspace(), "hbp_release_workspace")

@@ -310,9 +310,10 @@ int hbp_export(hbp_handle_t h, int which, void *host_dst, size_t capacity, size_
     if (bytes == 0) return HBP_OK;
     HBP_HIP(hipDeviceSynchronize());
     if (which == HBP_ARRAY_ADD_SIGN) {
-        int32_t *tmp = nullptr;
-        HBP_HIP(hipMalloc((void **)&tmp, bytes));
-        int rc = hbp::derive_add_sign(h, tmp, nullptr);
+        void *tmp = nullptr;
+        int rc = hbp::device_alloc(h->device, bytes, &tmp);
+        if (rc != HBP_OK) return rc;
+        rc = hbp::derive_add_sign(h, static_cast<int32_t *>(tmp), nullptr);
         hipError_t e = rc == HBP_OK ? hipMemcpy(host_dst, tmp, bytes, hipMemcpyDeviceToHost) : hipSuccess;
         (void)hipFree(tmp);
         if (rc != HBP_OK) return rc;

@@ -1227,33 +1227,9 @@ __global__ __launch_bounds__(256) void k_hash_keys(const uint32_t *__restrict__ 
     if (i < count) keys[i] = hash_key(n[i], a, R / 9u ? R / 9u : 1u, R);
 }
 
-// Scratch memory of the build, kept between builds: freeing a few hundred megabytes costs a
-// quarter of a millisecond per allocation, a good part of a build.  Two slots per device (a
-// build has two scratch arenas alive at a time), grown when a build needs more, given back by
-// hbp_release_workspace().  The device's lock is held for the whole of build_layout: the builds
-// of one process on one device are serialised; builds on different devices are not.
-constexpr int kWorkspaceDevices = 64, kWorkspaceSlots = 2;
-struct Workspace { void *base = nullptr; size_t bytes = 0; };
-Workspace g_workspace[kWorkspaceDevices][kWorkspaceSlots];
-std::mutex g_workspace_mutex[kWorkspaceDevices];
+#define HBP_TRY(expr) do { int rc_ = (expr); if (rc_ != HBP_OK) return rc_; } while (0)
 
-std::mutex &workspace_mutex(int device) { return g_workspace_mutex[device >= 0 && device < kWorkspaceDevices ? device : 0]; }
-
-int workspace_get(int device, int slot, size_t bytes, void **out)
-{
-    if (device < 0 || device >= kWorkspaceDevices) return HBP_ERR_INTERNAL;
-    Workspace &w = g_workspace[device][slot];
-    if (w.bytes < bytes) {
-        if (w.base) (void)hipFree(w.base);
-        w.base = nullptr;
-        w.bytes = 0;
-        const size_t want = bytes + bytes / 8;  // some room, so that similar matrices do not reallocate
-        HBP_HIP(hipMalloc(&w.base, want));
-        w.bytes = want;
-    }
-    *out = w.base;
-    return HBP_OK;
-}
+constexpr int kWorkspaceDevices = 64;  // devices whose memory is kept
 
 // Allocations of freed handles, kept for the next ones: a program that rebuilds its matrix (time stepping,
 // Newton) otherwise pays milliseconds per build for hipMalloc and hipFree of hundreds of megabytes
@@ -1278,14 +1254,6 @@ struct BlockCache {
 BlockCache g_cache[kWorkspaceDevices];
 std::mutex g_cache_mutex[kWorkspaceDevices];
 
-// sizes in steps of an eighth of the power of two below, so that matrices of much the same size share blocks
-size_t cache_size_of(size_t bytes)
-{
-    size_t step = 256;
-    while (bytes > 16 * step) step *= 2;
-    return (bytes + step - 1) / step * step;
-}
-
 int drop_cached_blocks(int device)
 {
     int rc = HBP_OK;
@@ -1296,28 +1264,69 @@ int drop_cached_blocks(int device)
     return rc;
 }
 
-int block_get(int device, size_t bytes, void **out, size_t *got)
+}  // namespace
+
+int device_alloc(int device, size_t bytes, void **out)
 {
-    const size_t want = cache_size_of(bytes);
-    if (device >= 0 && device < kWorkspaceDevices) {
-        std::lock_guard<std::mutex> lock(g_cache_mutex[device]);
-        BlockCache &cache = g_cache[device];
-        for (size_t i = cache.count; i-- > 0;)
-            if (cache.at[i].bytes == want) {
-                *out = cache.take(i).base;
-                *got = want;
-                return HBP_OK;
-            }
-    }
-    hipError_t e = hipMalloc(out, want);
+    hipError_t e = hipMalloc(out, bytes);
     if (e == hipErrorOutOfMemory && device >= 0 && device < kWorkspaceDevices) {
         (void)hipGetLastError();
         (void)drop_cached_blocks(device);
-        e = hipMalloc(out, want);
+        e = hipMalloc(out, bytes);
     }
     HBP_HIP(e);
-    *got = want;
     return HBP_OK;
+}
+
+namespace {
+
+// Scratch memory of the build, kept between builds: freeing a few hundred megabytes costs a
+// quarter of a millisecond per allocation, a good part of a build.  Two slots per device (a
+// build has two scratch arenas alive at a time), grown when a build needs more, given back by
+// hbp_release_workspace().  The device's lock is held for the whole of build_layout: the builds
+// of one process on one device are serialised; builds on different devices are not.
+constexpr int kWorkspaceSlots = 2;
+struct Workspace { void *base = nullptr; size_t bytes = 0; };
+Workspace g_workspace[kWorkspaceDevices][kWorkspaceSlots];
+std::mutex g_workspace_mutex[kWorkspaceDevices];
+
+std::mutex &workspace_mutex(int device) { return g_workspace_mutex[device >= 0 && device < kWorkspaceDevices ? device : 0]; }
+
+int workspace_get(int device, int slot, size_t bytes, void **out)
+{
+    if (device < 0 || device >= kWorkspaceDevices) return HBP_ERR_INTERNAL;
+    Workspace &w = g_workspace[device][slot];
+    if (w.bytes < bytes) {
+        if (w.base) (void)hipFree(w.base);
+        w.base = nullptr;
+        w.bytes = 0;
+        const size_t want = bytes + bytes / 8;  // some room, so that similar matrices do not reallocate
+        HBP_TRY(device_alloc(device, want, &w.base));
+        w.bytes = want;
+    }
+    *out = w.base;
+    return HBP_OK;
+}
+
+// The smallest kept block that is large enough and not more than an eighth larger, or a new one of just the size.
+int block_get(int device, size_t bytes, void **out, size_t *got)
+{
+    if (device >= 0 && device < kWorkspaceDevices) {
+        std::lock_guard<std::mutex> lock(g_cache_mutex[device]);
+        BlockCache &cache = g_cache[device];
+        size_t best = cache.count;
+        for (size_t i = 0; i < cache.count; i++)
+            if (cache.at[i].bytes >= bytes && cache.at[i].bytes <= bytes + bytes / 8 && (best == cache.count || cache.at[i].bytes < cache.at[best].bytes))
+                best = i;
+        if (best < cache.count) {
+            const CachedBlock block = cache.take(best);
+            *out = block.base;
+            *got = block.bytes;
+            return HBP_OK;
+        }
+    }
+    *got = bytes;
+    return device_alloc(device, bytes, out);
 }
 
 // A few words that kernels write for the host: one synchronisation instead of a blocking copy per word.
@@ -1365,7 +1374,7 @@ public:
             const int rc = block_get(device_, total_ ? total_ : 256, &base_, &bytes_);
             if (rc != HBP_OK) return rc;
         } else if (device_ < 0 || device_ >= kWorkspaceDevices || slot_ < 0 || slot_ >= kWorkspaceSlots) {
-            HBP_HIP(hipMalloc(&base_, total_ ? total_ : 256));  // no workspace slot for it: freed when the build ends
+            HBP_TRY(device_alloc(device_, total_ ? total_ : 256, &base_));  // no workspace slot for it: freed when the build ends
             free_at_end_ = true;
         } else {
             const int rc = workspace_get(device_, slot_, total_ ? total_ : 256, &base_);
@@ -1388,8 +1397,6 @@ private:
 };
 
 inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
-
-#define HBP_TRY(expr) do { int rc_ = (expr); if (rc_ != HBP_OK) return rc_; } while (0)
 
 }  // namespace
 

@@ -135,6 +135,7 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
 int derive_add_sign(const hbp_handle_s *h, int32_t *d_out, hipStream_t stream);
 int hash_keys(const uint32_t *n, int64_t count, int32_t a, int32_t R, uint32_t *keys, hipStream_t stream);
 int release_workspace();
+int device_alloc(int device, size_t bytes, void **out);  // hipMalloc; where memory is short, after giving back what freed handles left
 // takes back a handle's allocation; idle: nothing on the device uses it any more
 void release_block(int device, void *base, size_t bytes, bool idle);
 

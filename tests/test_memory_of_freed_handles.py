@@ -90,7 +90,8 @@ def run(tmp_path, body):
     subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", str(source), "-o", str(runtime)])
     program = tmp_path / "program.py"
     program.write_text(PROGRAM + textwrap.dedent(body))
-    res = subprocess.run([sys.executable, str(program), str(runtime), H.LIB_PATH], capture_output=True, text=True, cwd=ROOT, timeout=120)
+    res = subprocess.run([sys.executable, str(program), str(runtime), H.LIB_PATH], capture_output=True, text=True, cwd=ROOT, timeout=120,
+                         env=dict(os.environ, PYTHONPATH=ROOT))
     assert res.returncode == 0, res.stdout + res.stderr
 
 
@@ -120,5 +121,57 @@ def test_memory_whose_wait_failed_is_not_handed_out_again(tmp_path):
         after = rt.live_bytes()
         rc, h = build(10**6)                                           # allocates anew
         assert rc == 0 and rt.live_bytes() == before and after < before
+        assert lib.hbp_free(h) == 0
+    """)
+
+
+def test_kept_memory_is_given_up_where_a_build_is_short_of_it(tmp_path):
+    run(tmp_path, """
+        import paper_2504_08860_amd as H
+        given = H.hbp_params_t(512, 64, 64, 0, -1, 0, 0, 0, 8, -1, -1, 0, -1, 0, 1, -1)   # no sampling pass, no scratch memory
+        rc, h = build(10**6, ctypes.byref(given))
+        assert rc == 0 and lib.hbp_free(h) == 0
+        held = rt.live_bytes()
+        assert held > 0
+        rt.set_capacity(held + 100)                                    # the scratch memory of a build does not fit beside it
+        rc, h = build(1000)
+        assert rc == 0 and rt.free_calls() == 2
+        assert lib.hbp_free(h) == 0
+        # nor do a larger handle's own arrays
+        assert lib.hbp_release_workspace() == 0
+        rt.set_capacity(1 << 30)
+        rc, h = build(2 * 10**6, ctypes.byref(given))
+        assert rc == 0
+        needs = rt.live_bytes()
+        assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0 and rt.live_bytes() == 0
+        rt.set_capacity(needs)
+        rc, h = build(10**6, ctypes.byref(given))
+        assert rc == 0 and lib.hbp_free(h) == 0
+        rc, h = build(2 * 10**6, ctypes.byref(given))
+        assert rc == 0 and rt.live_bytes() == needs
+        assert lib.hbp_free(h) == 0
+    """)
+
+
+def test_a_handle_takes_no_more_than_it_needs(tmp_path):
+    """New memory is of the size that is needed; kept memory is taken by handles of about its size only."""
+    run(tmp_path, """
+        import paper_2504_08860_amd as H
+        given = ctypes.byref(H.hbp_params_t(1, 64, 64, 1, -1, 0, 0, 0, 8, -1, -1, 0, -1, 0, 1, -1))
+        n = 10**6 + 77777                                              # one row per block: 4 bytes of four arrays per row
+        rt.set_capacity(4 * 4 * n + 8 * 1024)
+        rc, h = build(n, given)
+        assert rc == 0
+        held = rt.live_bytes()
+        assert lib.hbp_free(h) == 0 and rt.live_bytes() == held
+        rt.set_capacity(1 << 30)
+        rc, h = build(n - n // 10, given)                              # in the kept memory
+        assert rc == 0 and rt.live_bytes() == held
+        rc, other = build(n // 2, given)                               # the rest of it gone, beside it
+        assert rc == 0 and held < rt.live_bytes() < 1.51 * held
+        assert lib.hbp_free(h) == 0 and lib.hbp_free(other) == 0
+        held = rt.live_bytes()
+        rc, h = build(3 * n // 4, given)                               # kept: one too large, one too small
+        assert rc == 0 and rt.live_bytes() > 1.4 * held
         assert lib.hbp_free(h) == 0
     """)
