@@ -39,8 +39,8 @@ struct Batch {
     int rounds;  // rounds of the batch in which some lane has a nonzero (they are the leading ones)
 };
 
-// a * b + c in one instruction (the value of a lane without an element in the round is zeroed
-// before it, one select instead of a select between a multiply and an add)
+// a * b + c in one instruction (a lane without an element in the round drops the whole sum: a zero in place
+// of the value alone would make NaN of an infinity in x that belongs to another row)
 __device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -87,7 +87,10 @@ __device__ __forceinline__ T consume_batch(const Batch<U, T> &b, const T *xs, in
 #pragma unroll
                 for (int u = 0; u < Q; u++) xv[u] = xs[b.c[q0 + u]];
 #pragma unroll
-                for (int u = 0; u < Q; u++) acc = fma_of(k + q0 + u < n ? b.v[q0 + u] : T(0), xv[u], acc);
+                for (int u = 0; u < Q; u++) {
+                    const T more = fma_of(b.v[q0 + u], xv[u], acc);
+                    acc = k + q0 + u < n ? more : acc;
+                }
             }
         }
     } else {
@@ -95,7 +98,10 @@ __device__ __forceinline__ T consume_batch(const Batch<U, T> &b, const T *xs, in
 #pragma unroll
         for (int u = 0; u < U; u++) xv[u] = xs[b.c[u]];
 #pragma unroll
-        for (int u = 0; u < U; u++) acc = fma_of(k + u < n ? b.v[u] : T(0), xv[u], acc);
+        for (int u = 0; u < U; u++) {
+            const T more = fma_of(b.v[u], xv[u], acc);
+            acc = k + u < n ? more : acc;
+        }
     }
     return acc;
 }

@@ -607,6 +607,40 @@ def test_small_matrices_without_workers(H, oracle, lens, n_cols, R, C, W, f64):
 
 
 @pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("heavy", [0, 64, 700])
+@pytest.mark.parametrize("rounds,threads", [(2, 256), (4, 512), (8, 1024), (9, 256), (16, 512)])
+def test_infinities_and_nan_stay_in_their_rows(H, rounds, threads, heavy, f64):
+    """An infinity or NaN in x reaches the rows that hold its column and no other, through every walk of the
+    workers' kernel (a small matrix without workers: test_small_matrices_without_workers)."""
+    import torch
+    from workloads import widen_to_f64
+    m = _mixed_matrix(seed=19)
+    if f64:
+        m = widen_to_f64(m)
+    ptr, cols, val, x = to_dev(m)
+    rows = np.repeat(np.arange(m.n_rows), np.diff(m.ptr))
+    used = np.bincount(m.col, minlength=m.n_cols)
+    rare = np.argsort(used, kind="stable")[:3]                  # columns of few rows
+    build, spmv = (H.hbp_build_f64, H.hbp_spmv_f64) if f64 else (H.hbp_build, H.hbp_spmv)
+    for C in (m.n_cols, 2048):
+        h = build(ptr, cols, val, m.n_rows, m.n_cols, rows_per_block=2048, cols_per_block=C, rounds_per_batch=rounds,
+                  threads_per_worker=threads, num_workers=5, heavy_group_rounds=heavy)
+        try:
+            # each column block's first column is what lanes without an element read
+            for bad in ({int(rare[0]): float("inf")}, {int(rare[1]): float("nan"), int(rare[2]): float("-inf")},
+                        {c: float("inf") for c in range(0, m.n_cols, C)}):
+                xb = x.clone()
+                for c, v in bad.items():
+                    xb[c] = v
+                y = torch.zeros(m.n_rows, device="cuda", dtype=x.dtype)
+                spmv(h, xb, y)
+                hit = np.unique(rows[np.isin(m.col, list(bad))])
+                assert np.array_equal(np.flatnonzero(~np.isfinite(y.cpu().numpy())), hit), (C, bad)
+        finally:
+            H.hbp_free(h)
+
+
+@pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("rounds,threads", [(4, 256), (8, 512)])
 @pytest.mark.parametrize("workers,W,lens", [
     (2, 1, [2] * 1990 + [60] * 40),                       # more long groups in a range than its list holds
