@@ -183,9 +183,9 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
                                                      int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist)
 {
     // Pointers that do not start at 0 (a row slice of a larger matrix) are refused when the host has them; until then
-    // csr_col is not read through them: it has ptr[n_rows] entries at most if they do start at 0.
-    if (ptr[0] != 0) return;
-    const int64_t nnz = ptr[n_rows];
+    // csr_col is not read through them: every row counts as empty.  (Both words are read before either is looked at.)
+    const int32_t first = ptr[0], last = ptr[n_rows];
+    const int64_t nnz = first == 0 ? last : 0;
     __shared__ uint32_t sh_hist[15];  // [14]: sampled segments with kLongSegment or more nonzeros
     if (threadIdx.x < 15) sh_hist[threadIdx.x] = 0;
     __syncthreads();
@@ -1308,7 +1308,8 @@ int workspace_get(int device, int slot, size_t bytes, void **out)
     return HBP_OK;
 }
 
-// The smallest kept block that is large enough and not more than an eighth larger, or a new one of just the size.
+// The smallest kept block that is large enough and not more than an eighth larger (the latest of several), or a new one of just
+// the size.
 int block_get(int device, size_t bytes, void **out, size_t *got)
 {
     if (device >= 0 && device < kWorkspaceDevices) {
@@ -1316,7 +1317,7 @@ int block_get(int device, size_t bytes, void **out, size_t *got)
         BlockCache &cache = g_cache[device];
         size_t best = cache.count;
         for (size_t i = 0; i < cache.count; i++)
-            if (cache.at[i].bytes >= bytes && cache.at[i].bytes <= bytes + bytes / 8 && (best == cache.count || cache.at[i].bytes < cache.at[best].bytes))
+            if (cache.at[i].bytes >= bytes && cache.at[i].bytes <= bytes + bytes / 8 && (best == cache.count || cache.at[i].bytes <= cache.at[best].bytes))
                 best = i;
         if (best < cache.count) {
             const CachedBlock block = cache.take(best);
