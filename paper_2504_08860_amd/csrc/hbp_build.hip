@@ -303,6 +303,9 @@ __device__ __forceinline__ int32_t block_column(int32_t c, int32_t C, int32_t sh
 
 constexpr int kTile = 4096, kTileThreads = 512, kTileWords = kTile / 64, kWordsPerWave = kTileWords / (kTileThreads / 64);
 constexpr int kTileCounters = 4096;  // 16 KB of LDS
+// A tile with as many rows and more between its first and its last has its nonzeros look for their rows instead of walking
+// them all.  Whole builds, us, walked / looked for, rows per tile: 16 K 514 / 540, 41 K 411 / 400, 64 K 481 / 500, 128 K 731 / 714.
+constexpr int kTileRowsWalked = 64 * kTileThreads;
 
 // Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).
 __global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t *__restrict__ tile_row,
@@ -365,8 +368,8 @@ __device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reach
 
 // The segments of kTile consecutive nonzeros per workgroup: a nonzero starts one when it starts a row or
 // its block column differs from its left neighbour's.  The rows that start inside the tile are read from
-// csr_ptr (empty rows own no position) into an LDS table by position; a segment's row is the last one
-// that starts at or before it.  Two passes over the matrix (bound by reading csr_col, 4 bytes per nonzero, and in the
+// csr_ptr (empty rows own no position) into an LDS table by position, or looked for from the nonzeros where most
+// rows are empty; a segment's row is the last one that starts at or before it.  Two passes over the matrix (bound by reading csr_col, 4 bytes per nonzero, and in the
 // second pass by writing 8 bytes per segment), with the scans over the block table between them:
 //   EMIT false  counts the segments of every block (cursor: the block table) and notes every tile's first
 //               segment start;
@@ -379,7 +382,9 @@ __device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reach
 // (Before: row-start bits by global atomics, segment flags, a scan, segment records with a binary search per
 // segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
 // on the 4M x 1M lognormal matrix, 555 now; 300 and 300 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
-// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.)
+// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.
+// Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
+// jump over the gaps 3260 / 20900.)
 // the value of the lane below; lane 0 gets `first`
 __device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false); }
 
@@ -393,7 +398,7 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
     __shared__ uint32_t cnt[kTileCounters];
     __shared__ __align__(16) int32_t row_at[kTile];  // row that starts at a position, counted from the tile's first row; -1: none
     __shared__ int32_t word_last[kTileWords], word_first[kTileWords];  // last row start, first segment start of a word; -1, kTile: none
-    __shared__ int32_t sh_row, sh_next;
+    __shared__ int32_t sh_next;
     if (*err & kErrPtr) return;  // k_check_ptr's finding: the rows below would not ascend
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -416,27 +421,39 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
         if (lane == 0) sh_next = next;
     }
     __syncthreads();
+    // the rows that can start in the tile: from the one that holds its first nonzero to the one that holds the next tile's
     const int32_t row_lo = tile_row[blockIdx.x];
-    for (int64_t r0 = row_lo;;) {
-        const int64_t r = r0 + threadIdx.x;
-        int64_t p0 = nnz, p1 = nnz;
-        if (r < n_rows) { p0 = ptr[r]; p1 = ptr[r + 1]; }
-        const bool starts = p1 > p0 && p0 >= j0 && p0 < j0 + count;
-        if (starts) row_at[p0 - j0] = (int32_t)(r - row_lo);
-        // more rows start in the tile if the last of these starts in it; none of these did: a gap, jump over it
-        const bool go_on = __syncthreads_or(threadIdx.x == kTileThreads - 1 && p0 < j0 + count);
-        if (!go_on) break;
-        r0 += kTileThreads;
-        if (!__syncthreads_or(starts)) {
-            if (wave == 0) {
-                const int64_t p = ptr[r0];
-                int32_t next = (int32_t)n_rows;
-                if (p < j0 + count) next = first_reached((int32_t)r0, (int32_t)n_rows, [&](int32_t i) { return i >= n_rows || ptr[i + 1] > p; });
-                if (lane == 0) sh_row = next;
+    const int32_t row_hi = j0 + count < nnz ? tile_row[blockIdx.x + 1] : (int32_t)(n_rows - 1);
+    if (row_hi - row_lo < kTileRowsWalked) {
+        for (int64_t r = (int64_t)row_lo + threadIdx.x; r <= row_hi; r += kTileThreads) {
+            const int64_t p0 = ptr[r], p1 = ptr[r + 1];
+            if (p1 > p0 && p0 >= j0 && p0 < j0 + count) row_at[p0 - j0] = (int32_t)(r - row_lo);
+        }
+    } else {
+        // Empty rows by the thousand: every nonzero looks for its row, the last one that starts at or before it, a lane's
+        // kAtOnce searches side by side (all eight would take the registers of the whole kernel from 66 to 100).
+        constexpr int kAtOnce = 4;
+#pragma unroll 1
+        for (int u0 = 0; u0 < kWordsPerWave; u0 += kAtOnce) {
+            int32_t r[kAtOnce];
+            uint32_t p[kAtOnce];
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++) r[u] = row_lo;
+            const int32_t i0 = (first_word + u0) * 64 + lane;
+            const uint32_t j = (uint32_t)(j0 + i0);  // (behind the last nonzero: beyond 2^31, not beyond 2^32)
+#pragma unroll 1
+            for (int32_t step = 1 << (31 - __clz(row_hi - row_lo)); step > 0; step >>= 1) {
+#pragma unroll
+                for (int u = 0; u < kAtOnce; u++) p[u] = step <= row_hi - r[u] ? (uint32_t)ptr[r[u] + step] : 0xffffffffu;
+#pragma unroll
+                for (int u = 0; u < kAtOnce; u++)
+                    if (p[u] <= j + 64 * u) r[u] += step;
             }
-            __syncthreads();
-            r0 = sh_row;
-            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++) p[u] = (uint32_t)ptr[r[u]];
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++)
+                if (i0 + 64 * u < count && p[u] == j + 64 * u) row_at[i0 + 64 * u] = r[u] - row_lo;
         }
     }
     __syncthreads();

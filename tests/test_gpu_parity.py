@@ -680,6 +680,11 @@ def test_rebuilds_reuse_memory_of_freed_handles(H, oracle):
     ([20000, 3, 0, 0, 9000], 20000, 8, 20000),
     ([2] * 2000 + [0] * 5000 + [3] * 40 + [0] * 30000 + [1] * 700, 600, 512, 128),   # gaps of empty rows inside a tile
     ([0] * 3000 + [1, 0, 0, 0] * 1200 + [0] * 3000, 5000, 7, 100),     # few rows that start in a tile, many blocks
+    # rows looked for from the nonzeros (32768 rows and more between a tile's first and its last): all tiles, the last one
+    # for the empty rows behind it, around the limit, a row and a segment across tiles in between
+    (([1] + [0] * 20) * 5000, 300, 512, 64), ([3] * 3000 + [0] * 40000, 300, 512, 64),
+    ([4096] + [2] * 100 + [0] * 32567 + [1] * 3995, 5000, 512, 5000), ([4096] + [2] * 100 + [0] * 32568 + [1] * 3995, 5000, 512, 5000),
+    ([0] * 50000 + [2] * 1000 + [0] * 20000 + [9000] + [0] * 35000 + [1, 0] * 1500 + [0] * 7, 10000, 2048, 700),
 ])
 def test_segments_at_the_ends_of_tiles(H, oracle, lens, n_cols, R, C):
     """The build finds the segments in tiles of 4096 nonzeros: sizes around one, rows and segments across several,
