@@ -13,6 +13,10 @@ constexpr int kMaxR = 8192;          // rows per block: one block's slots are or
 constexpr int kMaxC = 32768;         // columns per block: fp32 vector segment of 128 KB in LDS
 constexpr int kMaxC64 = 16384;       // the same 128 KB with fp64 values
 constexpr int kMaxR64 = 4096;        // fp64: the combine part keeps four copies of a y slice in LDS
+// LDS of a k_spmv_part workgroup next to its slice of x, at most (the kernel checks its arrays against it)
+constexpr int kLdsPerCu = 160 * 1024;
+constexpr int part_static_lds(int threads) { return 28 * threads + threads / 8 + 3648; }
+static_assert(kMaxC * 4 + part_static_lds(1024) <= kLdsPerCu && kMaxC64 * 8 == kMaxC * 4, "the largest slice has to fit beside the kernel's own arrays");
 constexpr int64_t kMaxDense = int64_t(1) << 27;  // NBR * NBC table entries
 // Rows longer than long_rounds_of (and up to heavy_group_rounds) make their group a "long" one.  Where a worker has
 // few groups they are walked first, so that the others fill up the wavefronts that are done with theirs; the worker's

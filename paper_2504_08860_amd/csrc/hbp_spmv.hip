@@ -15,6 +15,8 @@
 // block's blocks into an LDS copy of the y slice and writes it out, zeros included.
 #include "hbp_spmv_impl.h"
 
+#include <algorithm>
+
 namespace hbp {
 
 Layout hbp_view(const hbp_handle_s *h)
@@ -45,19 +47,21 @@ Layout hbp_view(const hbp_handle_s *h)
     return L;
 }
 
-// Workers the schedule is built for when the caller does not say: as many workgroups as fit
-// on the device at once given the LDS a vector segment takes.
+// Workers the schedule is built for when the caller does not say: as many workgroups as fit on the device at once,
+// given the LDS that a vector segment and the kernel's own arrays take and the 16 wavefronts of 128 registers per lane
+// (the kernel's launch bounds) that a CU holds.  Two workers of 512 threads per CU where they fit, else one of 1024: workers
+// that were planned and did not fit ran as a second wave behind the others' fixed parts.  (Of the kernel's two variants, with
+// lists of long groups and without, the larger one counts: which one a matrix needs is known when it is built.)
+// Measured, us per product, planned by the slice alone / by what fits: 1M lognormal rows over 8000 columns (4 planned per CU,
+// 2 fit) 112 / 59, 16384 (2, 1) 93 / 66, fp64 8192 101 / 83; 3M rows of 1 to 5 nonzeros over 18000 columns (2, 1) 69 / 45.
 int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_wanted, int32_t *threads_out, int32_t *workers_out)
 {
     int cus = 0;
     HBP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
     if (cus <= 0) cus = 256;
-    const size_t lds = (size_t)C * (size_t)value_bytes + 64;
-    const int threads = threads_wanted ? threads_wanted : (lds > 80 * 1024 ? 1024 : 512);
-    int per_cu = (int)((160 * 1024) / lds);
-    const int by_threads = 2048 / threads;
-    if (per_cu > by_threads) per_cu = by_threads;
-    if (per_cu < 1) per_cu = 1;
+    const int slice = C * value_bytes;
+    const int threads = threads_wanted ? threads_wanted : 2 * (slice + part_static_lds(512)) > kLdsPerCu ? 1024 : 512;
+    const int per_cu = std::max(1, std::min(kLdsPerCu / (slice + part_static_lds(threads)), 1024 / threads));
     *threads_out = threads;
     *workers_out = cus * per_cu;
     return HBP_OK;

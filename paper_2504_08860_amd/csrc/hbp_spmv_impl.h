@@ -245,6 +245,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_lens[THREADS];  // per wavefront: segment lengths of the heavy group being cut
     __shared__ int32_t sh_cut_k[THREADS / 64 + 1];   // heavy group: first round of every wavefront's share
     __shared__ uint32_t sh_cut_pos[THREADS / 64 + 1];  // and the nonzeros before that round
+    static_assert(sizeof sh_route + sizeof sh_heavy + sizeof sh_long + sizeof sh_first_heavy + sizeof sh_first_long + sizeof sh_lens +
+                      sizeof sh_cut_k + sizeof sh_cut_pos + 128 <= part_static_lds(THREADS), "part_static_lds is out of date");
     constexpr int kWaves = THREADS / 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -663,6 +663,34 @@ def test_long_groups_before_and_after_the_others(H, oracle, workers, W, lens, ro
                              heavy_group_rounds=heavy, slot_weight=0, group_weight=0, round_weight=0, column_weight=0)
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("threads", [0, 256, 512, 1024])
+@pytest.mark.parametrize("slice_bytes", [400, 32000, 48000, 63800, 65536, 72000, 81920, 100000, 131072])
+def test_planned_workers_fit_the_device(H, slice_bytes, threads, f64):
+    """The workers that the library plans are on the device at once: their slices of x and the kernel's own arrays (bytes
+    as the compiler reports them for the variant with lists) fit the 160 KB of a CU, their wavefronts its 16 of 128
+    registers per lane; and where two workers of 512 threads fit a CU there are two, else one of 1024."""
+    import torch
+    own = {256: 10736, 512: 17936, 1024: 32336}
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    vb = 8 if f64 else 4
+    n = 16 * cus + 100                        # a group per row: no fewer groups than wavefronts
+    ptr = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    col = torch.zeros(n, dtype=torch.int32, device="cuda")
+    val = torch.ones(n, dtype=torch.float64 if f64 else torch.float32, device="cuda")
+    build = H.hbp_build_f64 if f64 else H.hbp_build
+    h = build(ptr, col, val, n, 10**6, group_width=1, cols_per_block=slice_bytes // vb, threads_per_worker=threads)
+    try:
+        info = H.hbp_get_info(h)
+        T, per_cu = info.threads_per_worker, info.num_workers // cus
+        assert info.num_workers == per_cu * cus and per_cu >= 1
+        assert per_cu * (slice_bytes + own[T]) <= 160 * 1024 and per_cu * T <= 1024
+        if threads == 0:
+            assert (T, per_cu) == ((512, 2) if 2 * (slice_bytes + own[512]) <= 160 * 1024 else (1024, 1))
+    finally:
+        H.hbp_free(h)
+
+
 def test_rebuilds_reuse_memory_of_freed_handles(H, oracle):
     """A build after a free may get the freed handle's memory; the layouts and products are those of fresh memory,
     with handles of other sizes and of the other value type in between, and after the memory was given back."""
