@@ -1369,8 +1369,10 @@ static int launch_part(const hbp_handle_s *h, const Layout &L, const T *x, T *y,
 template <int THREADS, bool HEAVY, typename T>
 static int launch_part_u(const hbp_handle_s *h, const Layout &L, const T *x, T *y, hipStream_t st, SpmvScratch sc)
 {
-    // fp64 at 1024 threads (128 registers per lane): half as many groups at once, or the batches spill
-    constexpr int kHalf = sizeof(T) == 8 && THREADS == 1024 ? 2 : 1;
+    // fp64: half as many groups at once, or the batches spill (128 registers per lane whatever the workgroup size).
+    // (256 and 512 threads with all eight or four: 64 to 196 registers spilled; 3M rows of 1 to 5 nonzeros over 7900 columns 96 against
+    // 58 us, 1M lognormal rows in blocks of 7900 columns 472 against 155.)
+    constexpr int kHalf = sizeof(T) == 8 ? 2 : 1;
     switch (h->unroll) {  // rounds per batch; short batches walk several groups at once
     case 2: return launch_part<THREADS, 2, 8 / kHalf, HEAVY, T>(h, L, x, y, st, sc);
     case 4: return launch_part<THREADS, 4, 4 / kHalf, HEAVY, T>(h, L, x, y, st, sc);
