@@ -150,7 +150,8 @@ typedef struct {
                                   its nonzeros, instead of by one: >= 1; 0 = default 2048.  A group with a row of
                                   more than a 64th of this is walked by a wavefront of its own, like the heavy ones
                                   before the worker's other groups; with 1024 groups per worker and more: with a
-                                  row of more than an eighth, after them                            */
+                                  row of more than an eighth, after them.  With the default, rows that are not much
+                                  longer than the groups' average are left out of that                 */
     uint32_t flags;            /* HBP_FLAG_*                                                    */
     int32_t column_weight;     /* schedule weight of entering a block column (the worker fetches its segment
                                   of x), in nonzeros, charged to the column's first group when the group list

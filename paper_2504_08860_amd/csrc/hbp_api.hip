@@ -108,7 +108,8 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
                            p.column_weight >= 0 || p.heavy_group_rounds != 0 || (p.flags & HBP_FLAG_PAPER_SCHEDULE);
     if (p.group_width == 0) p.group_width = 64;
     if (p.fixed_fraction_q8 < 0) p.fixed_fraction_q8 = 240;
-    if (p.heavy_group_rounds == 0) p.heavy_group_rounds = 2048;
+    const bool heavy_chosen = p.heavy_group_rounds == 0;
+    if (heavy_chosen) p.heavy_group_rounds = 2048;
     const int32_t max_r = value_bytes == 8 ? hbp::kMaxR64 : hbp::kMaxR, max_c = value_bytes == 8 ? hbp::kMaxC64 : hbp::kMaxC;
     if (p.rows_per_block < 0 || p.cols_per_block < 0 || p.rows_per_block > max_r || p.cols_per_block > max_c) return HBP_ERR_INVALID_ARGUMENT;
     int64_t nnz = -1;  // not known yet
@@ -136,6 +137,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     h->value_bytes = value_bytes;
     h->flags = p.flags;
     h->scheduled = scheduled;
+    h->heavy_chosen = heavy_chosen;
     h->first_ticket_block = -1;
     h->R = p.rows_per_block; h->C = p.cols_per_block; h->W = p.group_width;
     h->NBR = (n_rows + h->R - 1) / h->R;

@@ -31,6 +31,18 @@ inline int32_t long_rounds_of(int32_t heavy_rounds, bool long_first)
     return rounds > 0 ? rounds : 1;
 }
 
+// Long is only what is longer than the others: a listed group is walked without the next one's loads on their way, which
+// costs more than the order brings where all groups are of about one length (`mean` rounds on average).  Up to three
+// times the mean, or 96 rounds, or a quarter more than the mean, is not; where the caller gives heavy_group_rounds, that alone
+// counts.  Measured, SpMV part in us, from 32 rounds on / with this line / never below 256 rounds: bands of 48 nonzeros per row 68 / 60 /
+// 64, of 200 69 / 61 / 61 (fp64 93 / 79 / 82); rows of 60 random nonzeros 48 / 42 / 42, of 1 to 79 44 / 36 / 36, of 1 to 299 64 /
+// 61 / 85; lognormal rows of 111 on average 154 / 152 / 180 (fp64, 55 per column block: 168 / 170 / 163).
+inline int32_t long_rounds_beside(int64_t mean)
+{
+    const int64_t rounds = mean + mean / 4 > 96 ? mean + mean / 4 : 3 * mean < 96 ? 3 * mean : 96;
+    return rounds < (1 << 16) ? (int32_t)rounds : 1 << 16;
+}
+
 // Matrices small enough for k_spmv_flat (one group after the other across the grid, x read from L2) in
 // place of k_spmv_part (persistent workers with x staged in LDS): the wavefronts it gives a group, or 0.
 // The workers spend 5-7 us before the first product and have at most a pack or two per wavefront here;
@@ -102,6 +114,7 @@ struct hbp_handle_s {
     int64_t U, NM;       // combine work units, row blocks cut into several units
     int32_t unit_slots;  // target slots per combine unit
     int32_t heavy_rounds;  // groups with a longer row are shared by a worker's wavefronts
+    bool heavy_chosen;     // by the library
     int32_t group_weight;  // schedule weight of a group as such
     int32_t longest_segment;  // longest row segment of the matrix (0 unless it makes a group long)
     int32_t round_weight;  // schedule weight of a group on top of its nonzeros and slots

@@ -664,6 +664,28 @@ def test_long_groups_before_and_after_the_others(H, oracle, workers, W, lens, ro
 
 
 @pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("lens", [
+    [60] * 700,                                   # all of one length: none is long, whatever that length
+    [60] * 700 + [200, 300] * 5,                  # and where a few are longer
+    [32] * 640 + [33, 96, 97] * 20,               # around a 64th of 2048 and around three times the mean
+    [300] * 256 + [380, 2047, 2048, 2049] * 3,    # a quarter more than the mean, heavy ones
+])
+def test_long_groups_beside_the_average(H, oracle, lens, f64):
+    from workloads import CsrMatrix, widen_to_f64
+    rng = np.random.default_rng(len(lens))
+    n_cols = 3000
+    lens = rng.permutation(np.asarray(lens))
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    m = CsrMatrix("beside", len(lens), n_cols, np.r_[0, np.cumsum(lens)].astype(np.int32), col,
+                  rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    if f64:
+        m = widen_to_f64(m)
+    for workers, q8, rounds in ((1, 256, 8), (3, 100, 4)):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=512, cols_per_block=n_cols, num_workers=workers,
+                             fixed_fraction_q8=q8, rounds_per_batch=rounds)
+
+
+@pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("threads", [0, 256, 512, 1024])
 @pytest.mark.parametrize("slice_bytes", [400, 32000, 48000, 63800, 65536, 72000, 81920, 100000, 131072])
 def test_planned_workers_fit_the_device(H, slice_bytes, threads, f64):
