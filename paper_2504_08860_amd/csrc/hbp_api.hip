@@ -113,9 +113,10 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     const int32_t max_r = value_bytes == 8 ? hbp::kMaxR64 : hbp::kMaxR, max_c = value_bytes == 8 ? hbp::kMaxC64 : hbp::kMaxC;
     if (p.rows_per_block < 0 || p.cols_per_block < 0 || p.rows_per_block > max_r || p.cols_per_block > max_c) return HBP_ERR_INVALID_ARGUMENT;
     int64_t nnz = -1;  // not known yet
+    hbp::RowStats rows{0, 0};
     {
         // whatever was left to the library is chosen from the matrix now (one sampling pass)
-        const int rc_choice = hbp::choose_block_parameters(csr_ptr, csr_col, n_rows, n_cols, value_bytes, p, &nnz, (hipStream_t)stream);
+        const int rc_choice = hbp::choose_block_parameters(csr_ptr, csr_col, n_rows, n_cols, value_bytes, p, &nnz, &rows, (hipStream_t)stream);
         if (rc_choice != HBP_OK) return rc_choice;
     }
     if (p.rows_per_block < 1 || p.rows_per_block > max_r || p.cols_per_block < 1 || p.cols_per_block > max_c ||
@@ -137,6 +138,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     h->value_bytes = value_bytes;
     h->flags = p.flags;
     h->scheduled = scheduled;
+    h->rows = rows;
     h->heavy_chosen = heavy_chosen;
     h->first_ticket_block = -1;
     h->R = p.rows_per_block; h->C = p.cols_per_block; h->W = p.group_width;

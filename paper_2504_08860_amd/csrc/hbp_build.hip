@@ -178,9 +178,12 @@ __device__ __forceinline__ uint32_t hash_key(uint32_t n, uint32_t a, uint32_t b,
 // Sampling of the shift a: histogram, over the segments of up to 4096 evenly spaced rows, of
 // the smallest a in 0..12 with n < 9 * 2^a.  One wavefront walks one sampled row.  hist[14] also
 // counts the sampled segments with at least kLongSegment nonzeros (block sizes are chosen by it).
+// row_stats (or null): kStatsCopies copies that add up to the statistics of all rows, where they matter.
 constexpr int kLongSegment = 6;
+constexpr int kStatsCopies = 16;  // so that the workgroups do not queue up for one address
 __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
-                                                     int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist)
+                                                     int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist,
+                                                     RowStats *__restrict__ row_stats)
 {
     // Pointers that do not start at 0 (a row slice of a larger matrix) are refused when the host has them; until then
     // csr_col is not read through them: every row counts as empty.  (Both words are read before either is looked at.)
@@ -190,6 +193,29 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
     if (threadIdx.x < 15) sh_hist[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
+    if (row_stats && rows_matter(nnz, n_rows)) {
+        const int64_t per = (n_rows + gridDim.x - 1) / gridDim.x, r0 = (int64_t)blockIdx.x * per, r1 = min(n_rows, r0 + per);
+        const int64_t cap = max((int64_t)1, 64 * nnz / n_rows);
+        uint32_t rows = 0;
+        unsigned long long skew = 0;
+        for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
+            const int64_t n = (int64_t)ptr[r + 1] - ptr[r];
+            if (n > 0) {
+                rows++;
+                skew += (unsigned long long)(n * min(n, cap));
+            }
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            rows += __shfl_xor(rows, d);
+            skew += __shfl_xor(skew, d);
+        }
+        if (lane == 0 && rows) {
+            RowStats *const mine = row_stats + blockIdx.x % kStatsCopies;
+            atomicAdd(&mine->rows, rows);
+            atomicAdd(&mine->skew, skew);
+        }
+    }
     const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
     auto tally = [&](int n) {
         int a = 0;
@@ -263,9 +289,17 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
 }
 
 // a = smallest shift for which at least 15/16 of the sampled segments aggregate into 0..8.
-__global__ void k_pick_shift(const uint32_t *__restrict__ hist, int32_t *__restrict__ a_out)
+__global__ void k_pick_shift(const uint32_t *__restrict__ hist, int32_t *__restrict__ a_out, RowStats *__restrict__ row_stats)
 {
     if (threadIdx.x || blockIdx.x) return;
+    if (row_stats) {  // the copies' sum goes to the first
+        RowStats all = row_stats[0];
+        for (int i = 1; i < kStatsCopies; i++) {
+            all.rows += row_stats[i].rows;
+            all.skew += row_stats[i].skew;
+        }
+        row_stats[0] = all;
+    }
     uint64_t total = 0, below = 0;
     for (int i = 0; i < 14; i++) total += hist[i];
     int a = 0;
@@ -1431,7 +1465,7 @@ inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + pe
 //         rounds with four groups in flight.  Both thresholds are measured on MI355X.
 // The sampled shift is written back into p.hash_shift, so that the build does not sample again.
 int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int64_t n_rows, int64_t n_cols, int32_t value_bytes,
-                            hbp_params_t &p, int64_t *nnz_out, hipStream_t st)
+                            hbp_params_t &p, int64_t *nnz_out, RowStats *rows_out, hipStream_t st)
 {
     const int32_t max_c = value_bytes == 8 ? kMaxC64 : kMaxC;
     if (p.cols_per_block == 0) p.cols_per_block = (int32_t)std::min<int64_t>(max_c, n_cols);
@@ -1444,23 +1478,29 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
     uint32_t *host = nullptr;
     HBP_TRY(readback_get(device, &host));
     void *buf = nullptr;
-    HBP_TRY(workspace_get(device, 1, 256, &buf));
+    HBP_TRY(workspace_get(device, 1, 1024, &buf));
     uint32_t *hist = static_cast<uint32_t *>(buf);
     int32_t *d_a = reinterpret_cast<int32_t *>(hist + 16);
-    HBP_HIP(hipMemsetAsync(hist, 0, 17 * sizeof(uint32_t), st));
+    RowStats *row_stats = reinterpret_cast<RowStats *>(hist + 32);
+    HBP_HIP(hipMemsetAsync(hist, 0, 32 * sizeof(uint32_t) + kStatsCopies * sizeof(RowStats), st));
     const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
-    k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, p.cols_per_block, S_rows, hist);
-    k_pick_shift<<<1, 64, 0, st>>>(hist, d_a);
+    k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, p.cols_per_block, S_rows, hist, row_stats);
+    k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, row_stats);
     Words words;
     for (int i = 0; i < 16; i++) words.at[i] = hist + i;
     words.at[16] = d_a;
     words.at[17] = csr_ptr;
     words.at[18] = csr_ptr + n_rows;
-    k_publish<<<1, 64, 0, st>>>(words, 19, host);
+    words.at[19] = &row_stats->rows;
+    words.at[20] = &row_stats->skew;
+    words.at[21] = reinterpret_cast<uint32_t *>(&row_stats->skew) + 1;
+    k_publish<<<1, 64, 0, st>>>(words, 22, host);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     const int32_t a = (int32_t)host[16], first = (int32_t)host[17];
     *nnz_out = (int32_t)host[18];
+    rows_out->rows = host[19];
+    rows_out->skew = host[20] | (unsigned long long)host[21] << 32;
     if (first != 0 || *nnz_out < 0) return HBP_ERR_BAD_CSR_PTR;
     const int64_t nnz = *nnz_out;
     uint64_t segments = 0;
@@ -1613,8 +1653,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         k_set_i32<<<1, 64, 0, st>>>(d_a, p.hash_shift);
     } else {
         const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
-        k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, C, S_rows, hist);
-        k_pick_shift<<<1, 64, 0, st>>>(hist, d_a);
+        k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, C, S_rows, hist, nullptr);
+        k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, nullptr);
     }
 
     // steps 1-3
@@ -1650,7 +1690,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own1.reserve(&h->stripe_blk, B + 1);
     own1.reserve(&h->group_ptr, G + 1); own1.reserve(&h->group_slot, G + 1); own1.reserve(&h->group_rounds, G + 1);
     own1.reserve(&h->group_blk, G + 1);
-    h->flat_wpg = h->scheduled ? 0 : flat_wavefronts(nnz, S, n_rows, NBC);
+    h->flat_wpg = h->scheduled ? 0 : flat_wavefronts(nnz, S, NBC, h->value_bytes, h->rows);
     if (h->flat_wpg) own1.reserve(&h->long_groups, G + 1);
     own1.reserve(&h->row_local, S + 1); own1.reserve(&h->seg_len, S + 1);
     own1.reserve(&h->blk_shift, B + 1);

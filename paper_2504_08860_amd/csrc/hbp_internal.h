@@ -43,21 +43,45 @@ inline int32_t long_rounds_beside(int64_t mean)
     return rounds < (1 << 16) ? (int32_t)rounds : 1 << 16;
 }
 
+// What choose_block_parameters finds out about the rows of a matrix that flat_wavefronts may ask for (zeros: not looked at).
+struct RowStats {
+    uint32_t rows;            // with a nonzero
+    unsigned long long skew;  // sum over the rows of length * min(length, 64 * mean length)
+};
+constexpr int64_t kFlatLeast = 1000000, kFlatMost = 12000000;  // nonzeros: flat whatever the rows are like, never flat
+__host__ __device__ inline bool rows_matter(int64_t nnz, int64_t n_rows) { return nnz > kFlatLeast && nnz <= kFlatMost && n_rows <= 4 * nnz; }
+
 // Matrices small enough for k_spmv_flat (one group after the other across the grid, x read from L2) in
 // place of k_spmv_part (persistent workers with x staged in LDS): the wavefronts it gives a group, or 0.
 // The workers spend 5-7 us before the first product and have at most a pack or two per wavefront here;
-// against that x comes out of L2 at some 100 G random elements/s for the whole chip (rows that each stay in a block
-// column or two of several, as a grid operator's, read neighbouring elements and are not held up by that).
-// Measured, us per product, workers / flat: 20K nonzeros in one block column 20.5 / 3.8; random columns 1.2M
-// 43 / 19, 2.4M (fp64) 45 / 47, 4.2M 26.6 / 32, 9.7M 70 / 91; R-MAT 3.9M 89 / 59; 5-point grid 5M 37 / 25, 11M
-// 56 / 46; 27-point grid 2.4M 22 / 13.6, 7.9M 27.8 / 30.
+// against that x comes out of L2 at some 100 G random elements/s for the whole chip.  Not held up by that are rows that each
+// stay in a block column or two of several (a grid operator's, which read neighbouring elements), and less so rows of
+// very uneven length (a graph's, whose columns are as uneven: an average nonzero lies in a row of 8 times the average
+// length and more, rows of over 64 times the average counted as that; lognormal rows 4, R-MAT 12 to 14), which the workers in turn
+// wait for.  The rest is the sooner too large the more block columns and bytes of x there are; over four block columns and more
+// the workers cope better with uneven rows than with even ones.
+// Measured, us per product, workers / flat, fp32 (fp64):
+//   5-point grid     1M 27 / 13 (27 / 15)    4M 33 / 22 (38 / 27)    12M 59 / 50 (80 / 69)    20M 77 / 70 (110 / 116)
+//   27-point grid    2M 20 / 13 (23 / 16)    2.9M 21 / 14 (25 / 20)  3.9M 22 / 20 (27 / 24)   5.6M 23 / 24 (29 / 31)
+//   R-MAT            1M 67 / 43 (62 / 43)    2M 62 / 55 (78 / 46)    3.9M 67 / 57 (88 / 62)   8M 80 / 79 (92 / 96)
+//   random columns, one block column: rows of 20    3M 19 / 17 (21 / 19)   4M 20 / 22 (22 / 25); lognormal rows 3M 42 / 28, 4M -
+//     two or three: lognormal rows 2M 38 / 30 (36 / 32)   2.5M (36 / 40)   4M 40 / 48 (44 / 52); rows of 32 2M 20 / 19   3M 23 / 32
+//     more: rows of 4 1M 23 / 16 (27 / 22)   2M 28 / 28 (33 / 36)   3M 34 / 39 (41 / 50)
+//           lognormal rows 1M 34 / 35 (34 / 36)   1.5M 32 / 37 (39 / 38)   2M 33 / 40 (39 / 40)
+//           10 in every third row 1M 22 / 14 (24 / 20)   2M 24 / 21 (32 / 33)   3M 27 / 28 (35 / 43)   10M 45 / 80
 // Segments of 8 nonzeros and more on average get four wavefronts per group, shorter ones would leave three idle:
 // 27-point grid 0.75M 17.9 (one) / 7.3 (four); 5-point grid 5M 25 / 51.
-inline int flat_wavefronts(int64_t nnz, int64_t S, int64_t n_rows, int64_t NBC)
+inline int flat_wavefronts(int64_t nnz, int64_t S, int64_t NBC, int32_t value_bytes, RowStats rows)
 {
     const bool short_segments = nnz < 8 * S;
-    const bool local = NBC >= 4 && S <= 2 * n_rows && nnz >= 2 * S;
-    const int64_t most = !local ? 3000000 : short_segments ? 12000000 : 4000000;
+    const bool local = 2 * S <= (NBC < 4 ? NBC : 4) * (int64_t)rows.rows && nnz >= 2 * S;
+    const double uneven = (double)rows.skew * (double)rows.rows / ((double)nnz * (double)nnz);
+    const int64_t most = local && short_segments ? kFlatMost
+                         : local || uneven >= 8  ? 4000000
+                         : NBC == 1              ? 3000000
+                         : NBC <= 3              ? 2250000
+                         : value_bytes == 4 && uneven < 2 ? 2000000
+                                                          : kFlatLeast;
     return nnz > most ? 0 : short_segments ? 1 : 4;
 }
 // whether k_spmv_flat with `wpg` wavefronts per group gives a group a workgroup of its own: one wavefront
@@ -110,6 +134,7 @@ struct hbp_handle_s {
     int32_t n_long;
     int32_t flat_wpg;                    // wavefronts per group of k_spmv_flat; 0: k_spmv_part runs
     bool scheduled;                      // the caller chose something about the workers or their schedule
+    hbp::RowStats rows;
     int32_t *unit_ptr, *unit_stripe, *unit_k, *multi_stripes;
     int64_t U, NM;       // combine work units, row blocks cut into several units
     int32_t unit_slots;  // target slots per combine unit
@@ -147,8 +172,9 @@ void set_last_hip_error(hipError_t e);
 // build (hbp_build.hip)
 int build_layout(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
                  const hbp_params_t &p, hipStream_t stream);
+// *nnz, *rows: unchanged where the matrix was not looked at
 int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int64_t n_rows, int64_t n_cols, int32_t value_bytes,
-                            hbp_params_t &p, int64_t *nnz, hipStream_t stream);  // *nnz: unchanged where the matrix was not looked at
+                            hbp_params_t &p, int64_t *nnz, RowStats *rows, hipStream_t stream);
 int derive_add_sign(const hbp_handle_s *h, int32_t *d_out, hipStream_t stream);
 int hash_keys(const uint32_t *n, int64_t count, int32_t a, int32_t R, uint32_t *keys, hipStream_t stream);
 int release_workspace();
