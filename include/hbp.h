@@ -165,7 +165,7 @@ typedef struct {
     int32_t hash_b;              /* b = d = max(1, R / 9)                                       */
     int64_t row_blocks, col_blocks;       /* NBR, NBC                                           */
     int64_t blocks, slots, groups;        /* B, S, G                                            */
-    int32_t num_workers;         /* P                                                           */
+    int32_t num_workers;         /* P, also where a small matrix runs without them (see hbp_spmv)  */
     int32_t fixed_fraction_q8;   /* share of the work that is pre-assigned, in 1/256            */
     int32_t claim_chunk;
     int32_t threads_per_worker;  /* workgroup size of the SpMV-part kernel                      */
@@ -180,9 +180,11 @@ typedef struct {
     int64_t split_row_blocks;    /* NM: row blocks cut into more than one unit                  */
     int32_t value_bytes;         /* 4: fp32 handle, 8: fp64 handle                              */
     int64_t first_ticket_block;  /* HBP_FLAG_PAPER_SCHEDULE: first block of the competitive part (P F); else -1 */
-    int64_t bytes_layout;        /* device bytes of all layout arrays                           */
+    int64_t bytes_layout;        /* device bytes of the block, group, slot and nonzero arrays (without the schedule,
+                                    the combine units and what the kernels keep beside them)    */
     int64_t bytes_spmv_part;     /* algorithmic bytes one SpMV-part launch moves                 */
-    int64_t bytes_combine;       /* algorithmic bytes one combine launch moves                  */
+    int64_t bytes_combine;       /* algorithmic bytes one combine launch moves; 0 where there is none (see hbp_spmv): the
+                                    other launch then writes y                                  */
     double build_ms;             /* wall time of hbp_build, allocation and synchronisation included */
 } hbp_info_t;
 
@@ -222,10 +224,15 @@ int hbp_build(const int32_t *csr_ptr, const int32_t *csr_col, const float *csr_v
  * per slot; the combine part adds the partial sums of each row and writes y.
  *   x DEVICE float [n_cols], read only;  y DEVICE float [n_rows], overwritten (both kernels
  *   write it: x and y must not overlap).
+ * A small matrix (up to 1 to 12 million nonzeros, by what its rows are like) whose schedule was left to the
+ * library runs without workers: one wavefront or a few per group across the whole device, with x read through
+ * the caches; with one block column that kernel writes y itself and there is no combine part.  A handle built with any
+ * of num_workers, fixed_fraction_q8, claim_chunk, threads_per_worker, rounds_per_batch, heavy_group_rounds, a schedule
+ * weight or HBP_FLAG_PAPER_SCHEDULE given has workers whatever its size.  The results are the same but for the order of sums.
  * Asynchronous on `stream`.  A handle supports one SpMV in flight at a time: calls on the
  * same stream serialise by themselves; calls on different streams must be ordered by the
  * caller (they share the partial-sum buffer and the ticket counter).  The call allocates
- * nothing and launches two kernels, no memset or copy: after one ordinary call on the device
+ * nothing and launches two kernels (one where there is no combine part), no memset or copy: after one ordinary call on the device
  * (which configures the kernels) it may be recorded into a HIP graph by stream capture. */
 int hbp_spmv(hbp_handle_t h, const float *x, float *y, void *stream);
 
@@ -246,7 +253,8 @@ int hbp_spmv_f64(hbp_handle_t h, const double *x, double *y, void *stream);
  * of the library (32 MiB per device, held until the process ends) instead of the handle's buffers:
  * 256 KiB of claim counters and at most 8,323,072 slots (S * 4 bytes <= 32 MiB - 256 KiB).  A handle
  * with more slots or more than 65536 workers is refused with HBP_ERR_TOO_LARGE.  The call allocates
- * nothing, launches three kernels (the first clears the counters), and is asynchronous on `stream`.
+ * nothing, launches three kernels (the first clears the counters; small matrices without workers: not that one), and is
+ * asynchronous on `stream`.
  * All calls on one device share the one array: calls that overlap in time on one device (different
  * streams, different handles) race and must be ordered by the caller. */
 int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stream);
@@ -267,7 +275,7 @@ int hbp_get_info(hbp_handle_t h, hbp_info_t *info);
 int hbp_export(hbp_handle_t h, int which, void *host_dst, size_t capacity, size_t *bytes_out);
 
 /* Times `iters` back-to-back hbp_spmv calls with HIP events recorded on `stream` around
- * each of the two kernels.  HOST outputs: average milliseconds of the SpMV-part kernel,
+ * each of the two kernels (an empty span where there is no combine part).  HOST outputs: average milliseconds of the SpMV-part kernel,
  * of the combine kernel, and of a whole call (event before the first kernel to event
  * after the second).  Synchronises the stream. */
 int hbp_spmv_timed(hbp_handle_t h, const float *x, float *y, void *stream, int iters,

@@ -265,6 +265,10 @@ int hbp_get_info(hbp_handle_t h, hbp_info_t *info)
     info->bytes_spmv_part = (2 + vb) * h->nnz + 2 * h->S + grp + 4 * (2 * (h->B + 1) + h->NBC + 1) + vb * h->n_cols + vb * h->S;
     // combine: partial sum + row_local per slot, stripe index and slot_ptr, y written once.
     info->bytes_combine = (2 + vb) * h->S + 4 * ((h->NBR + 1) + 2 * h->B + 1) + vb * h->n_rows;
+    if (h->flat_wpg && h->NBC == 1) {  // k_spmv_flat writes y, for which it reads row_local
+        info->bytes_spmv_part += 2 * h->S + vb * h->n_rows;
+        info->bytes_combine = 0;
+    }
     info->build_ms = h->build_ms;
     return HBP_OK;
 }

@@ -589,7 +589,8 @@ def test_small_matrices_without_workers(H, oracle, lens, n_cols, R, C, W, f64):
                   rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
     if f64:
         m = widen_to_f64(m)
-    check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C, group_width=W)
+    info = check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C, group_width=W)
+    assert (info.bytes_combine == 0) == (info.col_blocks == 1)     # y written by the one launch there is
     # an infinity in x reaches the rows that hold its column and no other
     import torch
     ptr, cols, val, x = to_dev(m)
