@@ -520,12 +520,7 @@ def test_two_handles_on_two_streams(H, oracle):
             H.hbp_free(h)
 
 
-@pytest.mark.parametrize("rounds,threads", [(4, 512), (8, 1024)])
-def test_long_group_list_overflows(H, oracle, rounds, threads):
-    """Groups with a row above heavy_group_rounds / 8 wait on a per-range list for a wavefront of
-    their own.  Here nearly every group is such a group and a single worker holds hundreds of them:
-    the list (256 entries) overflows and the rest are walked where they were drawn; a few rows are
-    long enough for the cooperative heavy path as well."""
+def _short_rows_with_a_few_long_ones():
     from workloads import CsrMatrix
     rng = np.random.default_rng(12)
     n_cols = 3000
@@ -533,12 +528,57 @@ def test_long_group_list_overflows(H, oracle, rounds, threads):
     rng.shuffle(lens)
     col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
     ptr = np.r_[0, np.cumsum(lens)].astype(np.int32)
-    m = CsrMatrix("long_list", len(lens), n_cols, ptr, col, rng.standard_normal(len(col)).astype(np.float32),
-                  rng.uniform(-1, 1, n_cols).astype(np.float32))
+    return CsrMatrix("long_list", len(lens), n_cols, ptr, col, rng.standard_normal(len(col)).astype(np.float32),
+                     rng.uniform(-1, 1, n_cols).astype(np.float32))
+
+
+@pytest.mark.parametrize("rounds,threads", [(4, 512), (8, 1024)])
+def test_long_group_list_overflows(H, oracle, rounds, threads):
+    """Nearly every group has a row of more than heavy_group_rounds / 64 nonzeros and the workers have fewer than 1024
+    groups each: a range's own long groups wait on a list (1024 entries, enough here) and go first, the claimed ones on
+    another one (256 entries); a few rows are long enough for the cooperative heavy path as well.  Lists that do
+    overflow: test_full_lists_of_long_groups."""
+    m = _short_rows_with_a_few_long_ones()
     for workers, q8 in ((1, 256), (3, 128)):
         check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=4096, cols_per_block=4096,
                              rounds_per_batch=rounds, threads_per_worker=threads, num_workers=workers,
                              fixed_fraction_q8=q8, heavy_group_rounds=16)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rounds,threads", [(4, 512), (8, 1024)])
+@pytest.mark.parametrize("workers,W,q8", [
+    (1, 64, 0),      # lists first: all groups are claimed, more long ones than the list of claimed groups holds
+    (1, 2, 256),     # lists last (1024 groups and more per worker): more long ones in the range than the list holds
+    (3, 2, 100),     # the same, in the fixed parts and among the claimed groups
+    (20, 2, 256),    # lists first: ranges with few long groups and with many
+])
+def test_full_lists_of_long_groups(H, oracle, workers, W, q8, rounds, threads, f64):
+    """Long groups that do not fit their list are walked where they were drawn."""
+    from workloads import widen_to_f64
+    m = _short_rows_with_a_few_long_ones()
+    if f64:
+        m = widen_to_f64(m)
+    heavy, params = 16, dict(rows_per_block=4096, cols_per_block=4096, group_width=W, rounds_per_batch=rounds, threads_per_worker=threads,
+                             num_workers=workers, fixed_fraction_q8=q8, heavy_group_rounds=16)
+    ptr, col, val, _ = to_dev(m)
+    h = (H.hbp_build_f64 if f64 else H.hbp_build)(ptr, col, val, m.n_rows, m.n_cols, **params)
+    try:
+        longest = np.diff(H.hbp_export(h, "group_rounds"))
+        start, comp = H.hbp_export(h, "fixed_start"), H.hbp_export(h, "comp_lo")
+    finally:
+        H.hbp_free(h)
+    first = len(longest) < 1024 * workers
+    is_long = (longest > max(1, heavy // (64 if first else 8))) & (longest <= heavy)
+    own = [int(is_long[a:b].sum()) for a, b in zip(start[:-1], comp)]                 # fixed parts
+    claimed = [int(is_long[a:b].sum()) for a, b in zip(comp, start[1:])]
+    if workers == 1 and q8 == 0:
+        assert first and claimed[0] > 256
+    elif workers < 20:
+        assert not first and max(own) > 256
+    else:
+        assert first and max(own) > 256
+    check_against_oracle(H, oracle, m, check_add_sign=False, **params)
 
 
 def test_release_workspace(H, oracle):
