@@ -739,7 +739,9 @@ __device__ __forceinline__ void scan_in_lds(uint32_t *a, int n, uint32_t *sh_wav
 // sum over (digit, tile) turns the counts into positions.  As many passes as the block's largest
 // key has hex digits.  Smaller blocks (the passes would still walk all R rows): a bitonic network
 // over (key, row, length, position) words.
-__global__ __launch_bounds__(256) void k_order_block(const uint2 *__restrict__ bucket,
+// (second launch bound: all eight workgroups of small blocks to a CU, which 105 scalar registers had made seven; with a
+// barrier less at the end, 1.9M blocks of 9 slots 4725 -> 3450 us, 3880 before long rows were counted per block.)
+__global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict__ bucket,
                                                      const int32_t *__restrict__ slot_ptr, const int32_t *__restrict__ blk_group_ptr,
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,
                                                      int32_t *__restrict__ slot_j, uint32_t *__restrict__ group_nnz, uint32_t *__restrict__ group_longest,
@@ -752,7 +754,7 @@ __global__ __launch_bounds__(256) void k_order_block(const uint2 *__restrict__ b
     extern __shared__ __align__(8) uint32_t order_lds[];  // two arrays of cap entries, then 16 counters per tile of 64
     __shared__ uint32_t sh_hist[14];
     __shared__ int32_t sh_shift;
-    __shared__ uint32_t sh_max_key, sh_wave[4], sh_long_n, sh_long_at, sh_longest;
+    __shared__ uint32_t sh_max_key, sh_wave[4], sh_long_n, sh_long_at;
     constexpr uint32_t kHole = 0xffffffffu;
     constexpr int kSmallBlock = 256;  // slots: one entry per thread
     const int cap = (int)((R + 63u) & ~63u);
@@ -767,7 +769,6 @@ __global__ __launch_bounds__(256) void k_order_block(const uint2 *__restrict__ b
     if (threadIdx.x == 0) {
         sh_max_key = 0u;
         sh_long_n = 0u;
-        sh_longest = 0u;
         sh_shift = *a_ptr;
     }
     __syncthreads();
@@ -936,16 +937,16 @@ __global__ __launch_bounds__(256) void k_order_block(const uint2 *__restrict__ b
         if (lane == 0) {
             group_nnz[g0 + gi] = sum;
             group_longest[g0 + gi] = longest;
-            // only that long rows matter to the caller
-            if (longest > heavy_rounds) atomicMax(&sh_longest, longest);
+            // only that long rows matter to the caller; one that has been beaten already need not queue up for the counter
+            if (longest > heavy_rounds && longest > __hip_atomic_load(longest_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(longest_all, longest);
             group_slot[g0 + gi] = s0 + gi * W;
             group_blk[g0 + gi] = b;
             if (long_groups && is_long_group((int32_t)sum, (int32_t)longest, flat_wpg)) listed[atomicAdd(&sh_long_n, 1u)] = g0 + gi;
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0 && sh_longest) atomicMax(longest_all, sh_longest);
     if (!long_groups) return;
+    __syncthreads();
     const uint32_t found = sh_long_n;
     if (found == 0) return;
     if (threadIdx.x == 0) sh_long_at = atomicAdd(n_long, found);
