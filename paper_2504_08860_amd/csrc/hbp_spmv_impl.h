@@ -1374,7 +1374,7 @@ static int launch_part_u(const hbp_handle_s *h, const Layout &L, const T *x, T *
     // 58 us, 1M lognormal rows in blocks of 7900 columns 472 against 155.)
     constexpr int kHalf = sizeof(T) == 8 ? 2 : 1;
     switch (h->unroll) {  // rounds per batch; short batches walk several groups at once
-    case 2: return launch_part<THREADS, 2, 8 / kHalf, HEAVY, T>(h, L, x, y, st, sc);
+    case 2: return launch_part<THREADS, 2, 4 / kHalf, HEAVY, T>(h, L, x, y, st, sc);  // (eight: up to 45 registers spilled, 119 against 80 us)
     case 4: return launch_part<THREADS, 4, 4 / kHalf, HEAVY, T>(h, L, x, y, st, sc);
     case 9: return launch_part<THREADS, 9, 1, HEAVY, T>(h, L, x, y, st, sc);
     case 16: return launch_part<THREADS, 16, 1, HEAVY, T>(h, L, x, y, st, sc);
