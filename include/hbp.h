@@ -148,9 +148,9 @@ typedef struct {
     int32_t heavy_group_rounds;/* a group with a row of more nonzeros than this (inside the block) is walked
                                   by all wavefronts of its worker together, each taking an equal share of
                                   its nonzeros, instead of by one: >= 1; 0 = default 2048.  A group with a row of
-                                  more than a 64th of this is walked by a wavefront of its own, like the heavy ones
-                                  before the worker's other groups; with 1024 groups per worker and more: with a
-                                  row of more than an eighth, after them.  With the default, rows that are not much
+                                  more than a 64th of this (an eighth, up to 32 nonzeros, if that is more) is walked by
+                                  a wavefront of its own, like the heavy ones before the worker's other groups; with
+                                  1024 groups per worker and more: with a row of more than an eighth, after them.  With the default, rows that are not much
                                   longer than the groups' average are left out of that                 */
     uint32_t flags;            /* HBP_FLAG_*                                                    */
     int32_t column_weight;     /* schedule weight of entering a block column (the worker fetches its segment

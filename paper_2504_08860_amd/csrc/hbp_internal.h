@@ -23,11 +23,13 @@ constexpr int64_t kMaxDense = int64_t(1) << 27;  // NBR * NBC table entries
 // start then waits for its slice of x (2 us), and where it has many groups the long ones are lost among them.
 // Measured, us per product, after the others from 256 rounds on / first from 32 rounds on (groups per worker): lognormal rows
 // 400K x 100K (72) 70 / 46, fp64 (120) 66 / 57, 1.2M x 300K (473) 103 / 92, 4M x 1M (3037) 285 / 297; R-MAT 2^20 (241)
-// 120 / 114, fp64 (340) 119.6 / 121.5, 2^22 (1785) 299 / 309.
+// 120 / 114, fp64 (340) 119.6 / 121.5, 2^22 (1785) 299 / 309.  (For heavy_group_rounds given as 64, 1M x 1M lognormal rows: first from 1 round on
+// 118, from 8 on, an eighth of it, 92.)
 inline bool walk_long_first(int64_t G, int64_t P) { return G < 1024 * P; }
 inline int32_t long_rounds_of(int32_t heavy_rounds, bool long_first)
 {
-    const int32_t rounds = heavy_rounds / (long_first ? 64 : 8);
+    const int32_t eighth = heavy_rounds / 8, few = eighth < 32 ? eighth : 32;
+    const int32_t rounds = !long_first ? eighth : heavy_rounds / 64 > few ? heavy_rounds / 64 : few;
     return rounds > 0 ? rounds : 1;
 }
 

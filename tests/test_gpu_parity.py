@@ -534,7 +534,7 @@ def _short_rows_with_a_few_long_ones():
 
 @pytest.mark.parametrize("rounds,threads", [(4, 512), (8, 1024)])
 def test_long_group_list_overflows(H, oracle, rounds, threads):
-    """Nearly every group has a row of more than heavy_group_rounds / 64 nonzeros and the workers have fewer than 1024
+    """Nearly every group has a row of more than heavy_group_rounds / 8 nonzeros and the workers have fewer than 1024
     groups each: a range's own long groups wait on a list (1024 entries, enough here) and go first, the claimed ones on
     another one (256 entries); a few rows are long enough for the cooperative heavy path as well.  Lists that do
     overflow: test_full_lists_of_long_groups."""
@@ -569,7 +569,7 @@ def test_full_lists_of_long_groups(H, oracle, workers, W, q8, rounds, threads, f
     finally:
         H.hbp_free(h)
     first = len(longest) < 1024 * workers
-    is_long = (longest > max(1, heavy // (64 if first else 8))) & (longest <= heavy)
+    is_long = (longest > max(1, heavy // 64, min(heavy // 8, 32)) if first else longest > heavy // 8) & (longest <= heavy)
     own = [int(is_long[a:b].sum()) for a, b in zip(start[:-1], comp)]                 # fixed parts
     claimed = [int(is_long[a:b].sum()) for a, b in zip(comp, start[1:])]
     if workers == 1 and q8 == 0:
