@@ -178,9 +178,11 @@ __device__ __forceinline__ uint32_t hash_key(uint32_t n, uint32_t a, uint32_t b,
 // Sampling of the shift a: histogram, over the segments of up to 4096 evenly spaced rows, of
 // the smallest a in 0..12 with n < 9 * 2^a.  One wavefront walks one sampled row.  hist[14] also
 // counts the sampled segments with at least kLongSegment nonzeros (block sizes are chosen by it).
-// row_stats (or null): kStatsCopies copies that add up to the statistics of all rows, where they matter.
+// row_stats: kStatsCopies copies that add up to the statistics of all rows, where they matter (and the grid has the workgroups).
+// (Every wavefront of the sampling workgroups counting its share of the rows into 16 copies: 15 to 20 us more per build.)
 constexpr int kLongSegment = 6;
-constexpr int kStatsCopies = 16;  // so that the workgroups do not queue up for one address
+constexpr int kStatsCopies = 64;  // so that the workgroups do not queue up for one address
+constexpr int kStatsGroups = 1024;
 __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
                                                      int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist,
                                                      RowStats *__restrict__ row_stats)
@@ -193,28 +195,33 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
     if (threadIdx.x < 15) sh_hist[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    if (row_stats && rows_matter(nnz, n_rows)) {
-        const int64_t per = (n_rows + gridDim.x - 1) / gridDim.x, r0 = (int64_t)blockIdx.x * per, r1 = min(n_rows, r0 + per);
+    const int32_t sampling = (S + 3) / 4;  // workgroups; kStatsGroups more look at all rows (beside them: they wait for loads too)
+    if ((int32_t)blockIdx.x >= sampling) {
+        if (!rows_matter(nnz, n_rows)) return;
+        const int64_t per = (n_rows + kStatsGroups - 1) / kStatsGroups, r0 = (int64_t)(blockIdx.x - sampling) * per, r1 = min(n_rows, r0 + per);
         const int64_t cap = max((int64_t)1, 64 * nnz / n_rows);
         uint32_t rows = 0;
         unsigned long long skew = 0;
+#pragma unroll 4
         for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
             const int64_t n = (int64_t)ptr[r + 1] - ptr[r];
-            if (n > 0) {
-                rows++;
-                skew += (unsigned long long)(n * min(n, cap));
-            }
+            rows += n > 0 ? 1u : 0u;
+            skew += n > 0 ? (unsigned long long)(n * min(n, cap)) : 0ull;
         }
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) {
             rows += __shfl_xor(rows, d);
             skew += __shfl_xor(skew, d);
         }
-        if (lane == 0 && rows) {
+        __shared__ RowStats sh_stats[4];
+        if (lane == 0) sh_stats[threadIdx.x >> 6] = {rows, skew};
+        __syncthreads();
+        if (threadIdx.x == 0) {
             RowStats *const mine = row_stats + blockIdx.x % kStatsCopies;
-            atomicAdd(&mine->rows, rows);
-            atomicAdd(&mine->skew, skew);
+            atomicAdd(&mine->rows, sh_stats[0].rows + sh_stats[1].rows + sh_stats[2].rows + sh_stats[3].rows);
+            atomicAdd(&mine->skew, sh_stats[0].skew + sh_stats[1].skew + sh_stats[2].skew + sh_stats[3].skew);
         }
+        return;
     }
     const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
     auto tally = [&](int n) {
@@ -289,17 +296,18 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
 }
 
 // a = smallest shift for which at least 15/16 of the sampled segments aggregate into 0..8.
-__global__ void k_pick_shift(const uint32_t *__restrict__ hist, int32_t *__restrict__ a_out, RowStats *__restrict__ row_stats)
+__global__ __launch_bounds__(64) void k_pick_shift(const uint32_t *__restrict__ hist, int32_t *__restrict__ a_out, RowStats *__restrict__ row_stats)
 {
-    if (threadIdx.x || blockIdx.x) return;
     if (row_stats) {  // the copies' sum goes to the first
-        RowStats all = row_stats[0];
-        for (int i = 1; i < kStatsCopies; i++) {
-            all.rows += row_stats[i].rows;
-            all.skew += row_stats[i].skew;
+        RowStats all = row_stats[threadIdx.x];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            all.rows += __shfl_xor(all.rows, d);
+            all.skew += __shfl_xor(all.skew, d);
         }
-        row_stats[0] = all;
+        if (threadIdx.x == 0) row_stats[0] = all;
     }
+    if (threadIdx.x || blockIdx.x) return;
     uint64_t total = 0, below = 0;
     for (int i = 0; i < 14; i++) total += hist[i];
     int a = 0;
@@ -1479,13 +1487,13 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
     uint32_t *host = nullptr;
     HBP_TRY(readback_get(device, &host));
     void *buf = nullptr;
-    HBP_TRY(workspace_get(device, 1, 1024, &buf));
+    HBP_TRY(workspace_get(device, 1, 2048, &buf));
     uint32_t *hist = static_cast<uint32_t *>(buf);
     int32_t *d_a = reinterpret_cast<int32_t *>(hist + 16);
     RowStats *row_stats = reinterpret_cast<RowStats *>(hist + 32);
     HBP_HIP(hipMemsetAsync(hist, 0, 32 * sizeof(uint32_t) + kStatsCopies * sizeof(RowStats), st));
     const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
-    k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, p.cols_per_block, S_rows, hist, row_stats);
+    k_sample_hist<<<blocks_for(S_rows, 4) + kStatsGroups, 256, 0, st>>>(csr_ptr, csr_col, n_rows, p.cols_per_block, S_rows, hist, row_stats);
     k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, row_stats);
     Words words;
     for (int i = 0; i < 16; i++) words.at[i] = hist + i;
