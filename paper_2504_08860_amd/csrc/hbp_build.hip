@@ -423,7 +423,7 @@ __device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reach
 // otherwise every segment goes to global memory with wave-aggregated atomics.
 // (Before: row-start bits by global atomics, segment flags, a scan, segment records with a binary search per
 // segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
-// on the 4M x 1M lognormal matrix, 555 now; 300 and 300 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
+// on the 4M x 1M lognormal matrix, 535 now; 300 and 288 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
 // tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.
 // Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
 // jump over the gaps 3260 / 20900.)
@@ -748,7 +748,8 @@ __device__ __forceinline__ void scan_in_lds(uint32_t *a, int n, uint32_t *sh_wav
 // key has hex digits.  Smaller blocks (the passes would still walk all R rows): a bitonic network
 // over (key, row, length, position) words.
 // (second launch bound: all eight workgroups of small blocks to a CU, which 105 scalar registers had made seven; with a
-// barrier less at the end, 1.9M blocks of 9 slots 4725 -> 3450 us, 3880 before long rows were counted per block.)
+// barrier less at the end, 1.9M blocks of 9 slots 4725 -> 3450 us, 3880 before long rows were counted per block;
+// 4M x 1M lognormal matrix 529 -> 475.)
 __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict__ bucket,
                                                      const int32_t *__restrict__ slot_ptr, const int32_t *__restrict__ blk_group_ptr,
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,

@@ -265,8 +265,9 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
 
     // Starts the copy of the vector segment of block column bn into LDS: 16-byte loads that write LDS
     // themselves (no registers, nothing to wait for here) when the slice is 16-byte aligned.
-    // The caller waits (wait_slice) and orders it with barriers.  (R-MAT 2^22 309 -> 300 us against loads
-    // into registers and stores to LDS.)
+    // The caller waits (wait_slice) and orders it with barriers.  (Against loads into registers and
+    // stores to LDS, us per product: 27-point grid of 67^3 28.3 -> 27.8, lognormal 150001 x 400009 38.5 -> 36.9, 27-point grid of 128^3
+    // 84.3 -> 83.6, R-MAT 2^22 and lognormal 4M x 1M as they were.)
     auto copy_slice = [&](int32_t bn) __attribute__((always_inline)) {
         const int64_t c0 = (int64_t)bn * L.C;
         const int32_t width = (int32_t)min((int64_t)L.C, L.n_cols - c0);
