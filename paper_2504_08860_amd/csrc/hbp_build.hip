@@ -33,6 +33,39 @@ __device__ __forceinline__ int lanes_below(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Element i of an array whose address is the same in all lanes: the array's address stays in scalar registers, the element's offset is
+// a 32-bit vector register (an index added to a pointer costs 64-bit vector arithmetic per access).  sizeof(T) i < 2^32.
+template <typename T>
+__device__ __forceinline__ T &lane_at(T *uniform, uint32_t i)
+{
+    return *reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(uniform) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
+// Sum and maximum over the wavefront, the same in all lanes (row shifts and broadcasts inside the vector ALU: six instructions each, no
+// LDS).  All lanes have to be active.
+template <int kControl, int kRows>
+__device__ __forceinline__ uint32_t lanes_moved(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kControl, kRows, 0xf, false); }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    v += lanes_moved<0x111, 0xf>(v);  // from 1, 2, 4, 8 lanes below in the row of 16 (0 where there is none)
+    v += lanes_moved<0x112, 0xf>(v);
+    v += lanes_moved<0x114, 0xf>(v);
+    v += lanes_moved<0x118, 0xf>(v);
+    v += lanes_moved<0x142, 0xa>(v);  // lane 15 of a row to the next row: rows 1 and 3
+    v += lanes_moved<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    v = max(v, lanes_moved<0x111, 0xf>(v));
+    v = max(v, lanes_moved<0x112, 0xf>(v));
+    v = max(v, lanes_moved<0x114, 0xf>(v));
+    v = max(v, lanes_moved<0x118, 0xf>(v));
+    v = max(v, lanes_moved<0x142, 0xa>(v));
+    v = max(v, lanes_moved<0x143, 0xc>(v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Exclusive scan of one value per thread over a 256-thread workgroup; *total is the
 // workgroup sum.  sh needs 4 entries.
 __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t *total, uint32_t *sh)
@@ -750,6 +783,9 @@ __device__ __forceinline__ void scan_in_lds(uint32_t *a, int n, uint32_t *sh_wav
 // (second launch bound: all eight workgroups of small blocks to a CU, which 105 scalar registers had made seven; with a
 // barrier less at the end, 1.9M blocks of 9 slots 4725 -> 3450 us, 3880 before long rows were counted per block;
 // 4M x 1M lognormal matrix 529 -> 475.)
+// Bound by its vector instructions: 253M of them per launch there, 4 cycles each on 1024 SIMDs, were all of 467 us.  With the wavefront's
+// number and the arrays' addresses in scalar registers, sums over a wavefront without LDS and the lanes of a digit found by two
+// instructions per half and bit: 190M, 361 us; 27-point grid of 128^3 54 -> 36 us, R-MAT 2^20 146 -> 124 us.
 __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict__ bucket,
                                                      const int32_t *__restrict__ slot_ptr, const int32_t *__restrict__ blk_group_ptr,
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,
@@ -768,10 +804,14 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
     constexpr int kSmallBlock = 256;  // slots: one entry per thread
     const int cap = (int)((R + 63u) & ~63u);
     uint32_t *from = order_lds, *to = order_lds + cap, *cnt = order_lds + 2 * cap;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b = blockIdx.x;
     const int s0 = slot_ptr[b], m = slot_ptr[b + 1] - s0;
     const bool small = m <= kSmallBlock;
+    const uint2 *const mine = bucket + s0;
+    uint16_t *const out_row = row_local + s0, *const out_len = seg_len + s0;
+    int32_t *const out_j = slot_j + s0;
+    uint32_t *const out_key = slot_key ? slot_key + s0 : nullptr;
     if (!small)
         for (int i = threadIdx.x; i < cap; i += 256) from[i] = kHole;
     if (threadIdx.x < 14) sh_hist[threadIdx.x] = 0u;
@@ -783,7 +823,7 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
     __syncthreads();
     if (reorder == 3) {
         for (int i = threadIdx.x; i < m; i += 256) {
-            const uint32_t n = bucket[s0 + i].x >> 16;
+            const uint32_t n = lane_at(mine, i).x >> 16;
             int a = 0;
             while (a < 13 && n >= (9u << a)) a++;
             atomicAdd(&sh_hist[a], 1u);
@@ -820,7 +860,7 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
         for (int i = threadIdx.x; i < n2; i += 256) {
             uint64_t e = ~0ull;
             if (i < m) {
-                const uint32_t lr = bucket[s0 + i].x;
+                const uint32_t lr = lane_at(mine, i).x;
                 e = ((uint64_t)sort_key(lr >> 16) << 48) | ((uint64_t)(lr & 0xffffu) << 32) | (lr & 0xffff0000u) | (uint32_t)i;
             }
             wide[i] = e;
@@ -841,21 +881,22 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
         __syncthreads();  // `to` may overlap `wide`
         if (i < m) {
             const uint32_t n = (uint32_t)(e >> 16) & 0xffffu;
-            row_local[s0 + i] = (uint16_t)((e >> 32) & 0xffffu);
-            seg_len[s0 + i] = (uint16_t)n;
-            if (slot_key) slot_key[s0 + i] = key_of(n);
-            slot_j[s0 + i] = (int32_t)bucket[s0 + (int32_t)(e & 0xffffu)].y;  // a gather inside the block's own range
+            lane_at(out_row, i) = (uint16_t)((e >> 32) & 0xffffu);
+            lane_at(out_len, i) = (uint16_t)n;
+            if (out_key) lane_at(out_key, i) = key_of(n);
+            lane_at(out_j, i) = (int32_t)lane_at(mine, (uint32_t)(e & 0xffffu)).y;  // a gather inside the block's own range
             to[i] = n;
         }
     } else {
         uint32_t most = 0;
         for (int i = threadIdx.x; i < m; i += 256) {
-            const uint32_t lr = bucket[s0 + i].x;
+            const uint32_t lr = lane_at(mine, i).x;
             const uint32_t key = sort_key(lr >> 16);
             from[lr & 0xffffu] = (key << 16) | (uint32_t)i;
             most = max(most, key);
         }
-        if (most) atomicMax(&sh_max_key, most);
+        most = wave_max(most);
+        if (most && lane == 0) atomicMax(&sh_max_key, most);
         __syncthreads();
         const uint32_t max_key = sh_max_key;
         const int passes = max_key ? (35 - __clz(max_key)) / 4 : 1;  // hex digits of the largest key; one pass at least: it closes the holes
@@ -870,13 +911,17 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
                 e = i < len ? from[i] : kHole;
                 const bool valid = e != kHole;
                 digit = (e >> shift) & 15u;
-                same = __ballot(valid);
+                const uint64_t there = __ballot(valid);
+                uint32_t same_lo = (uint32_t)there, same_hi = (uint32_t)(there >> 32);
 #pragma unroll
                 for (int bit = 0; bit < 4; bit++) {
-                    const bool set = (digit >> bit) & 1u;
-                    const uint64_t with = __ballot(valid && set);
-                    same &= set ? with : ~with;
+                    // (holes may count as whatever they hold: they are not in `same` to begin with)
+                    const uint32_t set = (uint32_t)((int32_t)(digit << (31 - bit)) >> 31);  // all ones or zero
+                    const uint64_t with = __ballot(set != 0u);
+                    same_lo &= ~((uint32_t)with ^ set);
+                    same_hi &= ~((uint32_t)(with >> 32) ^ set);
                 }
+                same = (uint64_t)same_hi << 32 | same_lo;
                 return valid;
             };
             // the first kKeep tiles of a wavefront (all of them up to R = 2048) keep their entry,
@@ -892,9 +937,9 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
                     uint32_t digit;
                     uint64_t same;
                     const bool valid = classify(tile, kept_e[t], digit, same);
-                    const uint32_t rank = (uint32_t)lanes_below(same);
-                    if (valid && rank == 0) cnt[digit * tiles + tile] = (uint32_t)__popcll(same);
-                    kept_at[t] = ((digit * (uint32_t)tiles + (uint32_t)tile) << 6) | rank;
+                    const uint32_t rank = (uint32_t)lanes_below(same), at = __umul24(digit, (uint32_t)tiles) + (uint32_t)tile;
+                    if (valid && rank == 0) cnt[at] = (uint32_t)__popcll(same);
+                    kept_at[t] = (at << 6) | rank;
                 }
             }
             for (int tile = wave + 4 * kKeep; tile < tiles; tile += 4) {
@@ -921,13 +966,12 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
         // `from` holds the m entries in (key, local row) order; `to` is free: the lengths go there
         for (int i = threadIdx.x; i < m; i += 256) {
             const uint32_t e = from[i];
-            const int32_t at = s0 + (int32_t)(e & 0xffffu);  // the segment's place in the block's bucket (gathers inside the block's own range)
-            const uint2 entry = bucket[at];
+            const uint2 entry = lane_at(mine, e & 0xffffu);  // the segment's place in the block's bucket (gathers inside the block's own range)
             const uint32_t lr = entry.x;
-            row_local[s0 + i] = (uint16_t)(lr & 0xffffu);
-            seg_len[s0 + i] = (uint16_t)(lr >> 16);
-            if (slot_key) slot_key[s0 + i] = key_of(lr >> 16);
-            slot_j[s0 + i] = (int32_t)entry.y;
+            lane_at(out_row, i) = (uint16_t)(lr & 0xffffu);
+            lane_at(out_len, i) = (uint16_t)(lr >> 16);
+            if (out_key) lane_at(out_key, i) = key_of(lr >> 16);
+            lane_at(out_j, i) = (int32_t)entry.y;
             to[i] = lr >> 16;
         }
     }
@@ -937,12 +981,7 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
     int32_t *listed = reinterpret_cast<int32_t *>(from);  // the block's long groups (as many as groups at most)
     for (int gi = wave; gi < ng; gi += 4) {
         const int i = gi * W + lane;
-        uint32_t sum = lane < W && i < m ? to[i] : 0u, longest = sum;
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            sum += __shfl_xor(sum, d);
-            longest = max(longest, __shfl_xor(longest, d));
-        }
+        const uint32_t n = lane < W && i < m ? to[i] : 0u, sum = wave_sum(n), longest = wave_max(n);
         if (lane == 0) {
             group_nnz[g0 + gi] = sum;
             group_longest[g0 + gi] = longest;
