@@ -457,9 +457,22 @@ __device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reach
 // (Before: row-start bits by global atomics, segment flags, a scan, segment records with a binary search per
 // segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
 // on the 4M x 1M lognormal matrix, 535 now; 300 and 288 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
-// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.
+// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.  Then, with a nonzero's row found by a maximum over the lanes
+// up to it in place of a bit search and an LDS read: first pass 197 -> 187 us there, 115 -> 103 us on the 27-point grid.
 // Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
 // jump over the gaps 3260 / 20900.)
+// inclusive maximum over the lanes up to this one, of values from -1 up (all lanes active; six vector instructions)
+template <int kControl, int kRows>
+__device__ __forceinline__ int32_t highest_moved(int32_t v) { return max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, kControl, kRows, 0xf, false)); }
+__device__ __forceinline__ int32_t highest_up_to_lane(int32_t v)
+{
+    v = highest_moved<0x111, 0xf>(v);
+    v = highest_moved<0x112, 0xf>(v);
+    v = highest_moved<0x114, 0xf>(v);
+    v = highest_moved<0x118, 0xf>(v);
+    v = highest_moved<0x142, 0xa>(v);
+    return highest_moved<0x143, 0xc>(v);
+}
 // the value of the lane below; lane 0 gets `first`
 __device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false); }
 
@@ -533,11 +546,13 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
     }
     __syncthreads();
     uint64_t rows_here[kWordsPerWave];
+    int32_t latest[kWordsPerWave];  // the last row that starts in the word, up to this lane; -1: none
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
         const int32_t w = first_word + u, r = row_at[w * 64 + lane];
-        rows_here[u] = __ballot(r >= 0);
-        const int32_t last = rows_here[u] ? __builtin_amdgcn_readlane(r, 63 - __clzll((long long)rows_here[u])) : -1;
+        rows_here[u] = __builtin_amdgcn_ballot_w64(r >= 0);
+        latest[u] = highest_up_to_lane(r);
+        const int32_t last = __builtin_amdgcn_readlane(latest[u], 63);
         if (lane == 0) word_last[w] = last;
     }
     __syncthreads();
@@ -559,30 +574,30 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
     int32_t row[kWordsPerWave], local[kWordsPerWave];
     uint32_t rank[kWordsPerWave];
     uint64_t starts[kWordsPerWave];
+    const uint32_t cols = (uint32_t)n_cols;  // below 2^31
     int32_t last_bn = 0;  // block column of the last nonzero of the word before
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
         const int32_t w = first_word + u, i = w * 64 + lane;
         const bool valid = i < count;
-        const uint64_t up_to_me = rows_here[u] & ((2ull << lane) - 1ull);
         const int32_t carried = w > 0 ? __builtin_amdgcn_readlane(last_row, w > 0 ? w - 1 : 0) : 0;
-        row[u] = row_lo + (up_to_me ? row_at[w * 64 + 63 - __clzll((long long)up_to_me)] : carried);
+        row[u] = row_lo + max(latest[u], carried);  // (rows ascend)
         const bool row_start = (rows_here[u] >> lane) & 1ull;
         const int32_t c_prev = lane_below(c[u], u > 0 ? __builtin_amdgcn_readlane(c[u > 0 ? u - 1 : 0], 63) : __builtin_amdgcn_readfirstlane(before));
-        const bool in_range = c[u] >= 0 && c[u] < n_cols;
+        const bool in_range = (uint32_t)c[u] < cols;
         if (!EMIT && valid && (!in_range || (validate && !row_start && c[u] <= c_prev))) atomicOr(err, kErrCol);
         const int32_t bn = block_column(c[u], C, shift_c);
         const int32_t bn_prev = lane_below(bn, u > 0 ? last_bn : block_column(__builtin_amdgcn_readfirstlane(before), C, shift_c));
         last_bn = __builtin_amdgcn_readlane(bn, 63);
         const bool start = valid && (row_start || bn != bn_prev);
-        starts[u] = __ballot(start);
+        starts[u] = __builtin_amdgcn_ballot_w64(start);
         if (lane == 0) word_first[w] = starts[u] ? w * 64 + __builtin_ctzll(starts[u]) : kTile;
         local[u] = -1;
         rank[u] = 0;
         const bool mine = start && in_range;  // (a column out of range has been reported; never index with it)
         if (in_lds) {
             if (mine) {
-                local[u] = (row_block(row[u]) - bm_lo) * NBC + bn;
+                local[u] = (int32_t)__umul24((uint32_t)(row_block(row[u]) - bm_lo), (uint32_t)NBC) + bn;  // (below kTileCounters)
                 rank[u] = atomicAdd(&cnt[local[u]], 1u);
             }
         } else {
