@@ -21,6 +21,7 @@
 
 #include <chrono>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace hbp {
@@ -382,18 +383,32 @@ constexpr int kTileCounters = 4096;  // 16 KB of LDS
 // them all.  Whole builds, us, walked / looked for, rows per tile: 16 K 514 / 540, 41 K 411 / 400, 64 K 481 / 500, 128 K 731 / 714.
 constexpr int kTileRowsWalked = 64 * kTileThreads;
 
-// Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).
+// Rounds of a group that one wavefront fills where the groups are cut (step 7).  A wavefront copies 8 to 32 rounds per memory round trip:
+// left to one, the longest row segment of R-MAT 2^20 (fp64) is on its way for 320 us.
+constexpr int kFillRounds = 128;
+
+constexpr int kLongRow = 4 * kFillRounds;
+
+// Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).  longest_rows: the longest row, where
+// it has more than kLongRow nonzeros, in copies apart from each other (one word for all: 101 us in place of 10 where one row in 40
+// asks for it).
+constexpr int kLongestCopies = 64, kLongestStride = 16;
 __global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t *__restrict__ tile_row,
-                                                   int32_t *__restrict__ err)
+                                                   int32_t *__restrict__ err, uint32_t *__restrict__ longest_rows)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r >= n_rows) return;
-    const int64_t p0 = ptr[r], p1 = ptr[r + 1];
-    if (p0 < 0 || p1 < p0 || p1 > nnz) {
-        atomicOr(err, kErrPtr);
-        return;
+    uint32_t length = 0;
+    if (r < n_rows) {
+        const int64_t p0 = ptr[r], p1 = ptr[r + 1];
+        if (p0 < 0 || p1 < p0 || p1 > nnz) {
+            atomicOr(err, kErrPtr);
+        } else {
+            for (int64_t t = (p0 + kTile - 1) / kTile; t * kTile < p1; t++) tile_row[t] = (int32_t)r;
+            length = (uint32_t)(p1 - p0);
+        }
     }
-    for (int64_t t = (p0 + kTile - 1) / kTile; t * kTile < p1; t++) tile_row[t] = (int32_t)r;
+    const uint32_t longest = wave_max(length);
+    if (longest > (uint32_t)kLongRow && (threadIdx.x & 63) == 0) atomicMax(&longest_rows[blockIdx.x % kLongestCopies * kLongestStride], longest);
 }
 
 // Wave-aggregated fetch-add: lanes of the wavefront that target the same counter are served by
@@ -1021,17 +1036,18 @@ __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict_
 
 // One group, one wavefront.  Round k stores the k-th nonzero of every lane that still has one,
 // lanes in slot order; rows keep their CSR (ascending column) order.  col0 is the first column of
-// the group's block column.
-template <typename T>
-__device__ __forceinline__ void fill_group(int32_t g, int32_t col0, int lane, int64_t nnz, const int32_t *__restrict__ csr_col,
+// the group's block column.  CUT: the rounds k0 .. k0 + kFillRounds - 1 alone.
+template <bool CUT, typename T>
+__device__ __forceinline__ void fill_group(int32_t g, int32_t k0, int32_t col0, int lane, int64_t nnz, const int32_t *__restrict__ csr_col,
                                            const T *__restrict__ csr_val, const int32_t *__restrict__ group_ptr,
                                            const int32_t *__restrict__ group_slot, const uint16_t *__restrict__ seg_len,
                                            const int32_t *__restrict__ slot_j, uint16_t *__restrict__ col_local, T *__restrict__ data)
 {
     const int s0 = group_slot[g], cnt = group_slot[g + 1] - s0;
-    const int n = lane < cnt ? seg_len[s0 + lane] : 0;
+    const int len = lane < cnt ? seg_len[s0 + lane] : 0, n = CUT ? min(len, k0 + kFillRounds) : len;
     const int64_t j = lane < cnt ? slot_j[s0 + lane] : 0;
     uint32_t base = (uint32_t)group_ptr[g];
+    if (CUT && k0 > 0) base += wave_sum((uint32_t)min(len, k0));
     // Where the element of a lane goes in a round that begins at `at`: the round's place stays in the scalar part of the address,
     // the lane's rank among the live lanes is its vector part.  (With 64-bit vector addresses per lane and every round of a
     // batch gone through, k_fill took 1027 us on the 4M x 1M lognormal matrix, k_fill_flat 247 on the 27-point grid of 128^3 and 350 on
@@ -1045,7 +1061,7 @@ __device__ __forceinline__ void fill_group(int32_t g, int32_t col0, int lane, in
     };
     // eight rounds at a time: the sixteen loads are independent of each other and of the stores
     constexpr int kRounds = 8, kLongRounds = 32;
-    for (int k = 0; __ballot(k < n); k += kRounds) {
+    for (int k = CUT ? k0 : 0; __ballot(k < n); k += kRounds) {
         // Few rows left, each with at least kLongRounds more nonzeros: the set of live lanes does
         // not change over these rounds, so round k + u of a live lane lands at base + u * m + its
         // rank, and a lane copies kLongRounds of its row at a time.  (Eight rounds per memory
@@ -1139,12 +1155,12 @@ __global__ __launch_bounds__(256) void k_fill(const int32_t *__restrict__ stripe
         const int32_t col0 = blk_bn[b] * C;
         const int32_t g_end = blk_group_ptr[b + 1];
         for (int32_t g = blk_group_ptr[b] + wave; g < g_end; g += 4)
-            fill_group<T>(g, col0, lane, nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j, col_local, data);
+            fill_group<false, T>(g, 0, col0, lane, nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j, col_local, data);
     }
 }
 
-// The same with one wavefront per group, in the layout's own order.
-template <typename T>
+// The same with one wavefront per group, in the layout's own order.  CUT: the first kFillRounds rounds of a group alone.
+template <bool CUT, typename T>
 __global__ __launch_bounds__(256) void k_fill_flat(const int32_t *__restrict__ csr_col, const T *__restrict__ csr_val,
                                                    const int32_t *__restrict__ group_ptr, const int32_t *__restrict__ group_slot,
                                                    const int32_t *__restrict__ group_blk, const int32_t *__restrict__ blk_bn,
@@ -1153,8 +1169,50 @@ __global__ __launch_bounds__(256) void k_fill_flat(const int32_t *__restrict__ c
 {
     const int64_t g = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (g >= G) return;
-    fill_group<T>((int32_t)g, blk_bn[group_blk[g]] * C, (int)(threadIdx.x & 63), nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j,
+    fill_group<CUT, T>((int32_t)g, 0, blk_bn[group_blk[g]] * C, (int)(threadIdx.x & 63), nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j,
                   col_local, data);
+}
+
+// The rest of groups that are cut, entries (group, first round) of a list.  A workgroup of k_list_rest looks at 1024 groups and goes to
+// the list's counter once: same-address atomics serialise at some 30 ns (listed by k_order_block, block by block: 66 us on R-MAT 2^20).
+__global__ __launch_bounds__(256) void k_list_rest(const uint32_t *__restrict__ group_longest, int32_t G, int2 *__restrict__ rest,
+                                                   uint32_t *__restrict__ n_rest)
+{
+    constexpr int kPer = 4;
+    __shared__ uint32_t sh[4], sh_at;
+    uint32_t more[kPer], mine = 0, total;
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        const int64_t g = (int64_t)blockIdx.x * (256 * kPer) + 256 * u + threadIdx.x;
+        const uint32_t longest = g < G ? group_longest[g] : 0u;
+        more[u] = longest ? (longest - 1u) / kFillRounds : 0u;
+        mine += more[u];
+    }
+    uint32_t at = block_excl_scan_256(mine, &total, sh);
+    if (total == 0) return;
+    if (threadIdx.x == 0) sh_at = atomicAdd(n_rest, total);
+    __syncthreads();
+    at += sh_at;
+#pragma unroll
+    for (int u = 0; u < kPer; u++)
+        for (uint32_t t = 0; t < more[u]; t++)
+            rest[at++] = {(int32_t)(blockIdx.x * (256 * kPer) + 256 * u + threadIdx.x), (int32_t)((t + 1u) * kFillRounds)};
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_fill_rest(const int2 *__restrict__ rest, const uint32_t *__restrict__ n_rest,
+                                                   const int32_t *__restrict__ csr_col, const T *__restrict__ csr_val,
+                                                   const int32_t *__restrict__ group_ptr, const int32_t *__restrict__ group_slot,
+                                                   const int32_t *__restrict__ group_blk, const int32_t *__restrict__ blk_bn,
+                                                   const uint16_t *__restrict__ seg_len, const int32_t *__restrict__ slot_j,
+                                                   int32_t C, int64_t nnz, uint16_t *__restrict__ col_local, T *__restrict__ data)
+{
+    const uint32_t n = *n_rest;
+    for (uint32_t i = blockIdx.x * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < n; i += gridDim.x * 4u) {
+        const int32_t g = rest[i].x, k0 = rest[i].y;
+        fill_group<true, T>(g, k0, blk_bn[group_blk[g]] * C, (int)(threadIdx.x & 63), nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j,
+                            col_local, data);
+    }
 }
 
 // add_sign derived from seg_len (Section 3.2: distance to the row's next nonzero = nonzeros
@@ -1474,11 +1532,16 @@ int readback_get(int device, uint32_t **out)
 }
 
 struct Words { const void *at[kReadback]; };
-__global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host)
+// longest_rows: k_check_ptr's; the largest of its copies goes behind the words
+__global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host, const uint32_t *__restrict__ longest_rows)
 {
     const int i = threadIdx.x;
     if (i < count) host[i] = *static_cast<const uint32_t *>(words.at[i]);
+    if (!longest_rows) return;
+    const uint32_t longest = wave_max(longest_rows[i * kLongestStride]);
+    if (i == 0) host[count] = longest;
 }
+static_assert(kLongestCopies == 64, "a lane of k_publish per copy");
 
 // One device allocation carved into 256-byte aligned arrays: reserve() every array first,
 // commit() allocates once and hands out the pointers.  hipMalloc/hipFree calls are a large part
@@ -1574,7 +1637,7 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
     words.at[19] = &row_stats->rows;
     words.at[20] = &row_stats->skew;
     words.at[21] = reinterpret_cast<uint32_t *>(&row_stats->skew) + 1;
-    k_publish<<<1, 64, 0, st>>>(words, 22, host);
+    k_publish<<<1, 64, 0, st>>>(words, 22, host, nullptr);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     const int32_t a = (int32_t)host[16], first = (int32_t)host[17];
@@ -1660,7 +1723,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_TRY(readback_get(h->device, &host));
     // nnz and csr_ptr[0] are needed on the host before anything can be sized
     if (h->nnz < 0) {
-        k_publish<<<1, 64, 0, st>>>(Words{{csr_ptr, csr_ptr + n_rows}}, 2, host);
+        k_publish<<<1, 64, 0, st>>>(Words{{csr_ptr, csr_ptr + n_rows}}, 2, host, nullptr);
         HBP_HIP(hipGetLastError());
         HBP_HIP(hipStreamSynchronize(st));
         if (host[0] != 0 || (int32_t)host[1] < 0) return HBP_ERR_BAD_CSR_PTR;
@@ -1711,12 +1774,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     Arena tmp(false, h->device, 0);
     const int64_t n_tiles = (nnz + kTile - 1) / kTile;
     const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
-    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
+    uint32_t *longest_rows, *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
     int32_t *tile_row, *tile_first, *d_a, *d_err;
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, 16);
     tmp.reserve(&d_err, 1);
+    tmp.reserve(&longest_rows, kLongestCopies * kLongestStride);
     tmp.reserve(&tile_first, n_tiles);
     tmp.reserve(&tile_row, n_tiles);
     tmp.reserve(&slot_off, D + 1);
@@ -1743,7 +1807,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         if (C == (int32_t(1) << b)) shift_c = b;
         if (R == (int32_t(1) << b)) shift_r = b;
     }
-    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tile_row, d_err);
+    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tile_row, d_err, longest_rows);
     k_segments<false><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
                                                                         (int32_t)NBC, (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, tile_row,
                                                                         tile_first, dense_cnt, nullptr, d_err);
@@ -1755,13 +1819,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_HIP(hipGetLastError());
 
     // the one host round trip of the build: totals (and the error word)
-    k_publish<<<1, 64, 0, st>>>(Words{{slot_off + D, group_off + D, blk_id + D, d_err, d_a}}, 5, host);
+    k_publish<<<1, 64, 0, st>>>(Words{{slot_off + D, group_off + D, blk_id + D, d_err, d_a}}, 5, host, longest_rows);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     const int32_t err = (int32_t)host[3], a = (int32_t)host[4];
     if (err & kErrPtr) return HBP_ERR_BAD_CSR_PTR;
     if (err & kErrCol) return HBP_ERR_BAD_CSR_COL;
-    const int64_t S = host[0], G = host[1], B = host[2];
+    const int64_t S = host[0], G = host[1], B = host[2], longest_row = host[5];
     h->S = S; h->G = G; h->B = B; h->a = a;
 
     Arena own1(true, h->device);
@@ -1795,10 +1859,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
     tmp2.reserve(&bucket, S);
-    tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 2);
+    tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 3);
+    int2 *rest;  // an entry per kFillRounds nonzeros of a group's longest row at most
+    tmp2.reserve(&rest, nnz / kFillRounds + 1);
     HBP_TRY(tmp2.commit());
     d_n_long = longest_all + 1;
-    HBP_HIP(hipMemsetAsync(longest_all, 0, 2 * sizeof(uint32_t), st));
+    uint32_t *const d_n_rest = longest_all + 2;
+    HBP_HIP(hipMemsetAsync(longest_all, 0, 3 * sizeof(uint32_t), st));
 
     k_compact_blocks<<<blocks_for(std::max<int64_t>(D, NBC) + 1, 256), 256, 0, st>>>(
         dense_cnt, slot_off, group_off, blk_id, D, (int32_t)NBR, (int32_t)NBC, h->blk_bm, h->blk_bn, h->slot_ptr,
@@ -1843,28 +1910,32 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // the padding behind the last group is read (and its products dropped) by lanes without an element
     HBP_HIP(hipMemsetAsync(h->col_local + nnz, 0, 256 * sizeof(uint16_t), st));
     HBP_HIP(hipMemsetAsync((char *)h->data + (size_t)nnz * h->value_bytes, 0, 256 * (size_t)h->value_bytes, st));
-    if (parts == 0) {
-        if (h->value_bytes == 8)
-            k_fill_flat<double><<<blocks_for(G, 4), 256, 0, st>>>(csr_col, static_cast<const double *>(csr_val), h->group_ptr, h->group_slot,
-                                                                  h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C, nnz, h->col_local,
-                                                                  static_cast<double *>(h->data));
-        else
-            k_fill_flat<float><<<blocks_for(G, 4), 256, 0, st>>>(csr_col, static_cast<const float *>(csr_val), h->group_ptr, h->group_slot,
-                                                                 h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C, nnz, h->col_local,
-                                                                 static_cast<float *>(h->data));
-    } else if (h->value_bytes == 8) {
-        k_fill<double><<<stripe_grid, 256, 0, st>>>(h->stripe_ptr, h->stripe_blk, (int32_t)NBR, (int32_t)B, parts, csr_col,
-                                                    static_cast<const double *>(csr_val), h->group_ptr, h->group_slot, h->blk_group_ptr,
-                                                    h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, static_cast<double *>(h->data));
-    } else {
-        k_fill<float><<<stripe_grid, 256, 0, st>>>(h->stripe_ptr, h->stripe_blk, (int32_t)NBR, (int32_t)B, parts, csr_col,
-                                                   static_cast<const float *>(csr_val), h->group_ptr, h->group_slot, h->blk_group_ptr,
-                                                   h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, static_cast<float *>(h->data));
-    }
+    // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
+    // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us); where
+    // all rows are long nothing waits.  R-MAT 2^20 (fp64) 322 us whole; cut 224, 5 for the list and 39 for the rest.  Not for
+    // k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
+    const bool cut = parts == 0 && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
+    auto fill = [&](const auto *val, auto *data) {
+        using T = std::remove_reference_t<decltype(*data)>;
+        if (parts > 0) {
+            k_fill<T><<<stripe_grid, 256, 0, st>>>(h->stripe_ptr, h->stripe_blk, (int32_t)NBR, (int32_t)B, parts, csr_col, val, h->group_ptr,
+                                                   h->group_slot, h->blk_group_ptr, h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, data);
+            return;
+        }
+        const auto flat = cut ? k_fill_flat<true, T> : k_fill_flat<false, T>;
+        flat<<<blocks_for(G, 4), 256, 0, st>>>(csr_col, val, h->group_ptr, h->group_slot, h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C,
+                                               nnz, h->col_local, data);
+        if (!cut) return;
+        k_list_rest<<<blocks_for(G, 1024), 256, 0, st>>>(group_longest, (int32_t)G, rest, d_n_rest);
+        k_fill_rest<T><<<dim3(2048), 256, 0, st>>>(rest, d_n_rest, csr_col, val, h->group_ptr, h->group_slot, h->group_blk, h->blk_bn, h->seg_len,
+                                                   slot_j, C, nnz, h->col_local, data);
+    };
+    if (h->value_bytes == 8) fill(static_cast<const double *>(csr_val), static_cast<double *>(h->data));
+    else fill(static_cast<const float *>(csr_val), static_cast<float *>(h->data));
     HBP_HIP(hipGetLastError());
     choose_schedule(h, p);
     HBP_TRY(launch_schedule(h, st));
-    k_publish<<<1, 64, 0, st>>>(Words{{h->unit_ptr + NBR, multi_idx + NBR, longest_all, d_n_long}}, 4, host);
+    k_publish<<<1, 64, 0, st>>>(Words{{h->unit_ptr + NBR, multi_idx + NBR, longest_all, d_n_long}}, 4, host, nullptr);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     h->U = host[0]; h->NM = host[1];

@@ -788,3 +788,25 @@ def test_segments_at_the_ends_of_tiles(H, oracle, lens, n_cols, R, C):
                   rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
     check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C)
     check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=C, hash_shift=5)   # bands narrower than 2^a
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("long,W", [
+    ([512], 64), ([513], 64),                                  # the longest row with its group filled as a whole, the shortest with it cut
+    ([127, 128, 129, 255, 256, 257, 513, 640, 641], 64),       # ends of rows at the cuts, after 128 rounds each
+    ([640] * 70 + [641] * 3, 64), ([3000, 1, 700] * 5, 5),     # whole groups that go on together, narrow groups
+    ([9000], 1),
+])
+def test_groups_cut_where_rows_are_much_longer(H, oracle, long, W, f64):
+    """A row of more than 512 nonzeros among short ones: several wavefronts fill a group, 128 rounds each."""
+    from workloads import CsrMatrix, widen_to_f64
+    rng = np.random.default_rng(len(long) + W)
+    n_cols = 10000
+    lens = rng.permutation(np.r_[rng.integers(0, 4, 4000), long])
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    m = CsrMatrix("cut", len(lens), n_cols, np.r_[0, np.cumsum(lens)].astype(np.int32), col,
+                  rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    if f64:
+        m = widen_to_f64(m)
+    check_against_oracle(H, oracle, m, rows_per_block=1024, cols_per_block=10000, group_width=W)
+    check_against_oracle(H, oracle, m, rows_per_block=2048, cols_per_block=1700, group_width=W)
