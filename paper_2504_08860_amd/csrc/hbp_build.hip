@@ -42,20 +42,20 @@ __device__ __forceinline__ T &lane_at(T *uniform, uint32_t i)
     return *reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(uniform) + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
-// Sum and maximum over the wavefront, the same in all lanes (row shifts and broadcasts inside the vector ALU: six instructions each, no
+// Inclusive sum over the lanes; sum and maximum over the wavefront, the same in all lanes (row shifts and broadcasts inside the vector ALU: six instructions each, no
 // LDS).  All lanes have to be active.
 template <int kControl, int kRows>
 __device__ __forceinline__ uint32_t lanes_moved(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kControl, kRows, 0xf, false); }
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+__device__ __forceinline__ uint32_t sum_up_to_lane(uint32_t v)
 {
     v += lanes_moved<0x111, 0xf>(v);  // from 1, 2, 4, 8 lanes below in the row of 16 (0 where there is none)
     v += lanes_moved<0x112, 0xf>(v);
     v += lanes_moved<0x114, 0xf>(v);
     v += lanes_moved<0x118, 0xf>(v);
     v += lanes_moved<0x142, 0xa>(v);  // lane 15 of a row to the next row: rows 1 and 3
-    v += lanes_moved<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    return v + lanes_moved<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
 }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)sum_up_to_lane(v), 63); }
 __device__ __forceinline__ uint32_t wave_max(uint32_t v)
 {
     v = max(v, lanes_moved<0x111, 0xf>(v));
@@ -173,11 +173,52 @@ __global__ __launch_bounds__(256) void k_scan_down(Scans s, int64_t n, uint32_t 
     if (blockIdx.x == n_tiles - 1 && threadIdx.x == 0) s.out[a][n] = before + total;
 }
 
+// Short scans in one launch in place of two: a workgroup per scan, 8192 items at a time.  A launch costs some 5 us whatever it does,
+// 8192 items here 3 us; three of a build's five scans are as short on large matrices, all of them on small ones.
+constexpr int64_t kScanAlone = 16384;
+__global__ __launch_bounds__(1024) void k_scan_alone(Scans s, int64_t n, uint32_t W)
+{
+    __shared__ uint32_t sh[16];
+    const int a = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t carry = 0;
+    for (int64_t base0 = 0; base0 < n; base0 += 1024 * 8) {
+        const int64_t base = base0 + (int64_t)threadIdx.x * 8;
+        uint32_t v[8], sum = 0;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            v[i] = base + i < n ? scan_input(s.op[a], s.in[a][base + i], W) : 0u;
+            sum += v[i];
+        }
+        const uint32_t incl = sum_up_to_lane(sum);
+        if (lane == 63) sh[wave] = incl;
+        __syncthreads();
+        uint32_t run = carry + incl - sum;
+#pragma unroll
+        for (int w = 0; w < 16; w++) {
+            const uint32_t t = sh[w];
+            if (w < wave) run += t;
+            carry += t;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            if (base + i < n) s.out[a][base + i] = run;
+            run += v[i];
+        }
+    }
+    if (threadIdx.x == 0) s.out[a][n] = carry;
+}
+
 // tile_tmp must hold `count` * ceil(n / 2048) entries.
 int exclusive_scans(const Scans &s, int count, int64_t n, uint32_t W, uint32_t *tile_tmp, hipStream_t st)
 {
     if (n <= 0) {
         for (int a = 0; a < count; a++) HBP_HIP(hipMemsetAsync(s.out[a], 0, sizeof(uint32_t), st));
+        return HBP_OK;
+    }
+    if (n <= kScanAlone) {
+        k_scan_alone<<<dim3(1, (unsigned)count), 1024, 0, st>>>(s, n, W);
+        HBP_HIP(hipGetLastError());
         return HBP_OK;
     }
     const int64_t tiles = (n + kScanTile - 1) / kScanTile;
