@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void k_scan_down(Scans s, int64_t n, uint32_t 
 }
 
 // Short scans in one launch in place of two: a workgroup per scan, 8192 items at a time.  A launch costs some 5 us whatever it does,
-// 8192 items here 3 us; three of a build's five scans are as short on large matrices, all of them on small ones.
+// one of this kernel 6 us; three of a build's five scans are as short on large matrices, all of them on small ones.
 constexpr int64_t kScanAlone = 16384;
 __global__ __launch_bounds__(1024) void k_scan_alone(Scans s, int64_t n, uint32_t W)
 {
@@ -514,7 +514,8 @@ __device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reach
 // segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
 // on the 4M x 1M lognormal matrix, 535 now; 300 and 288 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
 // tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.  Then, with a nonzero's row found by a maximum over the lanes
-// up to it in place of a bit search and an LDS read: first pass 197 -> 187 us there, 115 -> 103 us on the 27-point grid.
+// up to it in place of a bit search and an LDS read and the scans over a tile's words without LDS: first pass 197 -> 181 us there, 115 -> 97 us on
+// the 27-point grid, second pass 167 -> 129 us on the grid (66 -> 62 registers: all four tiles of a CU).
 // Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
 // jump over the gaps 3260 / 20900.)
 // inclusive maximum over the lanes up to this one, of values from -1 up (all lanes active; six vector instructions)
@@ -613,12 +614,7 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
     }
     __syncthreads();
     // lane w: the last row that starts in the words 0 .. w (rows ascend)
-    int32_t last_row = max(0, word_last[lane]);
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t up = __shfl_up(last_row, d);
-        if (lane >= d) last_row = max(last_row, up);
-    }
+    const int32_t last_row = highest_up_to_lane(max(0, word_last[lane]));
     auto row_block = [&](int32_t row) { return shift_r >= 0 ? row >> shift_r : row / R; };
     const int32_t bm_lo = row_block(row_lo), bm_hi = row_block(row_lo + __builtin_amdgcn_readlane(last_row, 63));
     const int64_t counters = (int64_t)(bm_hi - bm_lo + 1) * NBC;
@@ -680,18 +676,13 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
         }
     } else {
         __syncthreads();
-        // lane w: the first segment start in the words w .. 63
-        int32_t next_start = word_first[lane];
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int32_t down = __shfl_down(next_start, d);
-            if (lane + d < 64) next_start = min(next_start, down);
-        }
+        // lane 63 - w: the first segment start in the words w .. 63, counted back from the tile's end (0: none)
+        const int32_t next_start = highest_up_to_lane(kTile - word_first[63 - lane]);
 #pragma unroll
         for (int u = 0; u < kWordsPerWave; u++) {
             const int32_t w = first_word + u, i = w * 64 + lane;
             const uint64_t above = starts[u] & ~((2ull << lane) - 1ull);
-            const int32_t later = w < kTileWords - 1 ? __builtin_amdgcn_readlane(next_start, w < kTileWords - 1 ? w + 1 : 0) : kTile;
+            const int32_t later = w < kTileWords - 1 ? kTile - __builtin_amdgcn_readlane(next_start, w < kTileWords - 1 ? kTileWords - 2 - w : 0) : kTile;
             const int32_t j = (int32_t)(j0 + i);
             const int32_t end = above ? (int32_t)(j0 + w * 64) + __builtin_ctzll(above) : later < kTile ? (int32_t)(j0 + later) : sh_next;
             if (local[u] < 0) continue;
