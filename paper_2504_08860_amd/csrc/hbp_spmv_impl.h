@@ -1420,6 +1420,7 @@ static int launch_part_t(const hbp_handle_s *h, const T *x, T *y, hipStream_t st
 }
 
 constexpr int kCombineLds = 4 * kMaxR * (int)sizeof(float);
+constexpr int kCombineStaticLds = 1280;  // its array of slot ranges, in the units LDS is given out in
 
 template <typename T>
 static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScratch sc)
@@ -1449,9 +1450,16 @@ static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScr
         // per CU) or two of them (up to 512) have on a CU.  Whole products, us, four wavefronts per unit / now: 3.6M nonzeros
         // in 74 units 51.6 / 47.0, 12.8M in 196 units 56.3 / 50.2; fp64 3.7M in 74 units 50.8 / 47.3.  (One workgroup
         // of eight per CU for 489 fp64 units: combine part 12.1 / 17.7, hence the second bound.)
+        // Three wavefronts where four would leave some units for a second round and three do not (a unit's time is that of its wavefronts'
+        // loads, so a nearly empty second round doubles the kernel).  Whole products, us, four / three: fp64 (513 to 768 units) lognormal rows 1.2M
+        // 137.5 / 128.9, 1.5M 186.7 / 172.5, 1.1M 108.3 / 102.5, R-MAT 2^20 136.9 / 132.5; fp32 (1025 to 1536 units) 2.5M 175.9 / 168.6, 2.2M
+        // 132.4 / 129.7, R-MAT 2^21 166.1 / 157.5.
         const int64_t copy = (int64_t)h->R * (int64_t)sizeof(T);
+        // units that the device holds at a time with `wavefronts` for each
+        auto at_once = [&](int64_t wavefronts) { return 256 * (kLdsPerCu / (wavefronts * copy + kCombineStaticLds)); };
         const int rc = h->U <= 256 && 16 * copy <= kCombineLds  ? pick(std::integral_constant<int, 1024>{})
                        : (h->U <= 256 && 8 * copy <= kCombineLds) || (h->U <= 512 && 16 * copy <= kCombineLds) ? pick(std::integral_constant<int, 512>{})
+                       : h->U > at_once(4) && h->U <= at_once(3)             ? pick(std::integral_constant<int, 192>{})
                                                                 : pick(std::integral_constant<int, 256>{});
         if (rc != HBP_OK) return rc;
     }

@@ -810,3 +810,22 @@ def test_groups_cut_where_rows_are_much_longer(H, oracle, long, W, f64):
         m = widen_to_f64(m)
     check_against_oracle(H, oracle, m, rows_per_block=1024, cols_per_block=10000, group_width=W)
     check_against_oracle(H, oracle, m, rows_per_block=2048, cols_per_block=1700, group_width=W)
+
+
+@pytest.mark.parametrize("f64,units", [(True, 512), (True, 513), (True, 768), (True, 769), (False, 1025), (False, 1536)])
+def test_combine_with_three_wavefronts(H, oracle, units, f64):
+    """The numbers of combine units around those that three wavefronts each, but not four, have on the device at once."""
+    from workloads import CsrMatrix, widen_to_f64
+    rng = np.random.default_rng(units)
+    n_rows, n_cols = 2048 * units - 7, 40000
+    lens = np.where(rng.random(n_rows) < 0.3, rng.integers(1, 3, n_rows), 0)
+    first = rng.integers(0, n_cols // 2, n_rows)                  # at most two nonzeros, half of the columns apart
+    ptr = np.r_[0, np.cumsum(lens)].astype(np.int32)
+    col = np.empty(ptr[-1], np.int32)
+    col[ptr[:-1][lens > 0]] = first[lens > 0]
+    col[ptr[:-1][lens > 1] + 1] = first[lens > 1] + n_cols // 2
+    m = CsrMatrix("units", n_rows, n_cols, ptr, col, rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    if f64:
+        m = widen_to_f64(m)
+    info = check_against_oracle(H, oracle, m, rows_per_block=2048, cols_per_block=10000)
+    assert info.combine_units == units
