@@ -34,12 +34,16 @@ __device__ __forceinline__ int lanes_below(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Element i of an array whose address is the same in all lanes: the array's address stays in scalar registers, the element's offset is
-// a 32-bit vector register (an index added to a pointer costs 64-bit vector arithmetic per access).  sizeof(T) i < 2^32.
+// Element i of an array whose address is the same in all lanes: an access by the array's address in scalar registers and a 32-bit offset in a
+// vector register (an index added to a pointer costs 64-bit vector arithmetic per access), but for stores in loops, whose vector address
+// the compiler steps on.  By way of bytes, not of an integer: an address that has been an integer may be LDS for all the compiler knows,
+// and a flat access has no scalar address and waits with the LDS ones (k_order_block, 13 of its accesses flat / none: lognormal 4M x 1M 365 / 360
+// us, R-MAT 2^20 in fp64 126 / 124.5, 27-point grid of 128^3 35.9 / 35.4).  sizeof(T) i < 2^32.
 template <typename T>
 __device__ __forceinline__ T &lane_at(T *uniform, uint32_t i)
 {
-    return *reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(uniform) + (uint32_t)(i * (uint32_t)sizeof(T)));
+    using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return *reinterpret_cast<T *>(reinterpret_cast<Byte *>(uniform) + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
 // Inclusive sum over the lanes; sum and maximum over the wavefront, the same in all lanes (row shifts and broadcasts inside the vector ALU: six instructions each, no
@@ -846,8 +850,8 @@ __device__ __forceinline__ void scan_in_lds(uint32_t *a, int n, uint32_t *sh_wav
 // barrier less at the end, 1.9M blocks of 9 slots 4725 -> 3450 us, 3880 before long rows were counted per block;
 // 4M x 1M lognormal matrix 529 -> 475.)
 // Bound by its vector instructions: 253M of them per launch there, 4 cycles each on 1024 SIMDs, were all of 467 us.  With the wavefront's
-// number and the arrays' addresses in scalar registers, sums over a wavefront without LDS and the lanes of a digit found by two
-// instructions per half and bit: 190M, 361 us; 27-point grid of 128^3 54 -> 36 us, R-MAT 2^20 146 -> 124 us.
+// number and most of the arrays' addresses in scalar registers, sums over a wavefront without LDS and the lanes of a digit found by two
+// instructions per half and bit: 188M (350 us of issue), 360 us; 27-point grid of 128^3 54 -> 35 us, R-MAT 2^20 146 -> 124 us.
 __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict__ bucket,
                                                      const int32_t *__restrict__ slot_ptr, const int32_t *__restrict__ blk_group_ptr,
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,
