@@ -150,7 +150,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     int rc = HBP_OK;
     if (h->NBR * h->NBC > hbp::kMaxDense) rc = HBP_ERR_TOO_LARGE;
     int32_t threads = 0, workers = 0;
-    if (rc == HBP_OK) rc = hbp::default_workers(h->device, h->C, value_bytes, p.threads_per_worker, &threads, &workers);
+    if (rc == HBP_OK) rc = hbp::default_workers(h->device, h->C, value_bytes, p.threads_per_worker, &threads, &workers, &h->cus);
     if (rc == HBP_OK) {
         h->threads = threads;
         h->unroll = p.rounds_per_batch ? p.rounds_per_batch : 8;

@@ -90,6 +90,33 @@ inline int flat_wavefronts(int64_t nnz, int64_t S, int64_t NBC, int32_t value_by
 // takes 8 rounds, up to 512 nonzeros, per memory round trip
 __host__ __device__ inline bool is_long_group(int32_t nnz, int32_t longest, int wpg) { return nnz > 2048 || (wpg > 1 && longest > 64); }
 
+// Combine part, blocks of more than 1024 rows: wavefronts of a workgroup, each with its own copy of the unit's slice of y in LDS.
+constexpr int kCombineLds = 4 * kMaxR * (int)sizeof(float);  // all copies, at most
+constexpr int kCombineStaticLds = 1024;                       // the kernel's own array (checked there)
+constexpr int kLdsStep = 1280, kWavesPerCu = 32;              // LDS is given out in these units; wavefronts on a compute unit (the kernel keeps to 64 registers)
+inline int64_t combine_units_by_lds(int64_t copy_bytes, int wavefronts)  // on a compute unit at a time
+{
+    return kLdsPerCu / ((wavefronts * copy_bytes + kCombineStaticLds + kLdsStep - 1) / kLdsStep * kLdsStep);
+}
+// Few units: more wavefronts for each, as many as the copies' LDS lets one workgroup (up to a unit per compute unit, 256 units) or two of
+// them (up to 512) have on a CU.  Whole products, us, four wavefronts per unit / now: 3.6M nonzeros in 74 units 51.6 / 47.0, 12.8M in 196
+// units 56.3 / 50.2; fp64 3.7M in 74 units 50.8 / 47.3.  (One workgroup of eight per CU for 489 fp64 units: combine part 12.1 / 17.7,
+// hence the second bound.)
+// Three wavefronts where four would leave some units for a second round and three do not (a unit's time is that of its wavefronts'
+// loads, so a nearly empty second round doubles the kernel).  Whole products, us, four / three, R = 2048: fp64 (513 to 768 units) lognormal
+// rows 1.2M 137.5 / 128.9, 1.5M 186.7 / 172.5, 1.1M 108.3 / 102.5, R-MAT 2^20 136.9 / 132.5; fp32 (1025 to 1536 units) 2.5M 175.9 /
+// 168.6, 2.2M 132.4 / 129.7, R-MAT 2^21 166.1 / 157.5.  Whether they do counts the wavefronts a compute unit holds, too; where these alone keep
+// four from one round, three wait for as long.  Combine part, us, four / three, fp32: R = 1025 (LDS for 9 and 11 units, wavefronts for 8 and
+// 10) 2100 units 26.8 / 27.1, 2250 27.8 / 28.2, 2600 29.7 / 33.3, 2900 32.3 / 34.2; R = 1200 (LDS for 8 and 9) 2320 units 30.9 / 34.3.
+inline int combine_wavefronts(int64_t cus, int64_t units, int64_t R, int32_t value_bytes)
+{
+    const int64_t copy = R * value_bytes;
+    if (units <= cus && 16 * copy <= kCombineLds) return 16;
+    if ((units <= cus && 8 * copy <= kCombineLds) || (units <= 2 * cus && 16 * copy <= kCombineLds)) return 8;
+    const int64_t by_lds = combine_units_by_lds(copy, 3), by_waves = kWavesPerCu / 3;
+    return units > cus * combine_units_by_lds(copy, 4) && units <= cus * (by_lds < by_waves ? by_lds : by_waves) ? 3 : 4;
+}
+
 // Device-side view of the layout, passed by value to kernels.
 struct Layout {
     int32_t R, C, W;
@@ -121,6 +148,7 @@ struct hbp_handle_s {
     int32_t R, C, W, a;
     int64_t NBR, NBC, B, S, G;
     int32_t P, fixed_q8, slot_weight, claim_chunk, threads;
+    int32_t cus;         // compute units of the device
     int32_t unroll;      // rounds taken per batch by the SpMV-part kernel
     double build_ms;
     // device arrays (owned): views into two allocations, arena[0] sized before the matrix is
@@ -186,7 +214,8 @@ void release_block(int device, void *base, size_t bytes, bool idle);
 
 // spmv (hbp_spmv.hip)
 Layout hbp_view(const hbp_handle_s *h);
-int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_wanted, int32_t *threads_out, int32_t *workers_out);
+int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_wanted, int32_t *threads_out, int32_t *workers_out,
+                    int32_t *cus_out);
 // x, y (and val): arrays of the handle's value type (value_bytes for the CSR baselines)
 // where one SpMV keeps its per-slot partial sums (S values of the handle's type) and its claim counters (P)
 struct SpmvScratch {

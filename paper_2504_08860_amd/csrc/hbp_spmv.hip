@@ -55,7 +55,8 @@ Layout hbp_view(const hbp_handle_s *h)
 // lists of long groups and without, the larger one counts: which one a matrix needs is known when it is built.)
 // Measured, us per product, planned by the slice alone / by what fits: 1M lognormal rows over 8000 columns (4 planned per CU,
 // 2 fit) 112 / 59, 16384 (2, 1) 93 / 66, fp64 8192 101 / 83; 3M rows of 1 to 5 nonzeros over 18000 columns (2, 1) 69 / 45.
-int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_wanted, int32_t *threads_out, int32_t *workers_out)
+int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_wanted, int32_t *threads_out, int32_t *workers_out,
+                    int32_t *cus_out)
 {
     int cus = 0;
     HBP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
@@ -65,6 +66,7 @@ int default_workers(int device, int32_t C, int32_t value_bytes, int32_t threads_
     const int per_cu = std::max(1, std::min(kLdsPerCu / (slice + part_static_lds(threads)), 1024 / threads));
     *threads_out = threads;
     *workers_out = cus * per_cu;
+    *cus_out = cus;
     return HBP_OK;
 }
 

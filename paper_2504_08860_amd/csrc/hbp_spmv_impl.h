@@ -1117,6 +1117,7 @@ __global__ __launch_bounds__(THREADS) void k_combine(Layout L, const T *__restri
     T *const ys_all = reinterpret_cast<T *>(dyn_lds);  // kWaves copies of R values
     constexpr int kPass = 128, kWaves = THREADS / 64;
     __shared__ int32_t range[2 * kPass];
+    static_assert(kRing == 0 || sizeof(range) == kCombineStaticLds, "what combine_units_by_lds counts for it");
     // One workgroup per combine unit: entries [unit_k[j], unit_k[j + 1]) of stripe_blk, all of row
     // block bm.  A row block with a single unit is stored; the units of a split row block add
     // their sums into y, which the SpMV part has zeroed.
@@ -1419,9 +1420,6 @@ static int launch_part_t(const hbp_handle_s *h, const T *x, T *y, hipStream_t st
     return launch_part_u<256, false, T>(h, L, x, y, st, sc);
 }
 
-constexpr int kCombineLds = 4 * kMaxR * (int)sizeof(float);
-constexpr int kCombineStaticLds = 1280;  // its array of slot ranges, in the units LDS is given out in
-
 template <typename T>
 static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScratch sc)
 {
@@ -1446,21 +1444,13 @@ static int launch_combine_t(const hbp_handle_s *h, T *y, hipStream_t st, SpmvScr
             return h->S < 128 * h->B ? go(kt, std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{})
                                      : go(kt, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
         };
-        // Few units: more wavefronts for each, as many as the copies' LDS lets one workgroup (up to 256 units, one
-        // per CU) or two of them (up to 512) have on a CU.  Whole products, us, four wavefronts per unit / now: 3.6M nonzeros
-        // in 74 units 51.6 / 47.0, 12.8M in 196 units 56.3 / 50.2; fp64 3.7M in 74 units 50.8 / 47.3.  (One workgroup
-        // of eight per CU for 489 fp64 units: combine part 12.1 / 17.7, hence the second bound.)
-        // Three wavefronts where four would leave some units for a second round and three do not (a unit's time is that of its wavefronts'
-        // loads, so a nearly empty second round doubles the kernel).  Whole products, us, four / three: fp64 (513 to 768 units) lognormal rows 1.2M
-        // 137.5 / 128.9, 1.5M 186.7 / 172.5, 1.1M 108.3 / 102.5, R-MAT 2^20 136.9 / 132.5; fp32 (1025 to 1536 units) 2.5M 175.9 / 168.6, 2.2M
-        // 132.4 / 129.7, R-MAT 2^21 166.1 / 157.5.
-        const int64_t copy = (int64_t)h->R * (int64_t)sizeof(T);
-        // units that the device holds at a time with `wavefronts` for each
-        auto at_once = [&](int64_t wavefronts) { return 256 * (kLdsPerCu / (wavefronts * copy + kCombineStaticLds)); };
-        const int rc = h->U <= 256 && 16 * copy <= kCombineLds  ? pick(std::integral_constant<int, 1024>{})
-                       : (h->U <= 256 && 8 * copy <= kCombineLds) || (h->U <= 512 && 16 * copy <= kCombineLds) ? pick(std::integral_constant<int, 512>{})
-                       : h->U > at_once(4) && h->U <= at_once(3)             ? pick(std::integral_constant<int, 192>{})
-                                                                : pick(std::integral_constant<int, 256>{});
+        int rc = HBP_OK;
+        switch (combine_wavefronts(h->cus, h->U, h->R, (int32_t)sizeof(T))) {
+        case 16: rc = pick(std::integral_constant<int, 1024>{}); break;
+        case 8: rc = pick(std::integral_constant<int, 512>{}); break;
+        case 3: rc = pick(std::integral_constant<int, 192>{}); break;
+        default: rc = pick(std::integral_constant<int, 256>{}); break;
+        }
         if (rc != HBP_OK) return rc;
     }
     HBP_HIP(hipGetLastError());

@@ -1,0 +1,164 @@
+"""Which kernels a build and a product launch, and how much memory they take, for sizes that no matrix has to be made for:
+the library on the CPU with the HIP runtime of test_memory_of_freed_handles.py in front of the real one, which here also
+notes kernels by name and hands the build scripted totals where it reads them back from the device."""
+import ast
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+from test_memory_of_freed_handles import ROOT, RUNTIME
+
+NOTES = r"""
+#undef hipMalloc
+#undef hipHostMalloc
+#undef hipStreamSynchronize
+#undef hipLaunchKernel
+static struct { const void *f; const char *name; } kernels[kMax];
+static int n_kernels, n_launched, n_allocated, n_waits;
+static const char *launched[kMax];
+static size_t allocated[kMax];
+static unsigned *readback, script[8][8];
+void __hipRegisterFunction(void **module, const void *f, char *device_f, const char *name, unsigned limit, void *a, void *b, void *c, void *d, int *e)
+{
+    (void)module; (void)device_f; (void)limit; (void)a; (void)b; (void)c; (void)d; (void)e;
+    if (n_kernels == kMax) abort();
+    kernels[n_kernels].f = f;
+    kernels[n_kernels++].name = name;
+}
+unsigned __hipPushCallConfiguration(dim3_ g, dim3_ b, size_t lds, void *s) { (void)g; (void)b; (void)lds; (void)s; return 0; }
+int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *lds, void **s) { *g = *b = (dim3_){1, 1, 1}; *lds = 0; *s = 0; return 0; }
+int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t lds, void *s)
+{
+    (void)g; (void)b; (void)args; (void)lds; (void)s;
+    int i = 0;
+    while (i < n_kernels && kernels[i].f != f) i++;
+    if (i == n_kernels || n_launched == kMax) abort();
+    launched[n_launched++] = kernels[i].name;
+    return 0;
+}
+int hipMalloc(void **out, size_t bytes)
+{
+    if (n_allocated == kMax) abort();
+    allocated[n_allocated++] = bytes;
+    return quiet_hipMalloc(out, bytes);
+}
+int hipHostMalloc(void **out, size_t bytes, unsigned flags)
+{
+    const int rc = quiet_hipHostMalloc(out, bytes, flags);
+    readback = *out;
+    return rc;
+}
+int hipStreamSynchronize(void *s)
+{
+    (void)s;
+    if (readback && n_waits < 8) memcpy(readback, script[n_waits], sizeof script[0]);
+    n_waits++;
+    return 0;
+}
+void begin(void) { n_launched = n_allocated = n_waits = 0; }
+void set_word(int wait, int i, unsigned value) { script[wait][i] = value; }
+int launches(void) { return n_launched; }
+const char *launch(int i) { return launched[i]; }
+int allocations(void) { return n_allocated; }
+size_t allocation(int i) { return allocated[i]; }
+"""
+
+PROGRAM = r"""
+import ctypes, json, sys
+import paper_2504_08860_amd as H
+rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # in front of the real runtime for what it defines
+lib = ctypes.CDLL(sys.argv[2])
+rt.launch.restype = ctypes.c_char_p
+rt.allocation.restype = ctypes.c_size_t
+for f in (lib.hbp_build, lib.hbp_build_f64):
+    f.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int64] * 2 + [ctypes.c_void_p] * 3
+for f in (lib.hbp_spmv, lib.hbp_spmv_f64):
+    f.argtypes = [ctypes.c_void_p] * 4
+lib.hbp_free.argtypes = [ctypes.c_void_p]
+word = ctypes.create_string_buffer(64)
+
+def noted():
+    return [rt.launch(i).decode() for i in range(rt.launches())], [rt.allocation(i) for i in range(rt.allocations())]
+
+def build(f64, n_rows, n_cols, R, C, nnz, S, G, B, counts, U):
+    # (given block parameters: no sampling pass; a given shift: no sampled one; given rounds: workers)
+    p = H.hbp_params_t()
+    assert lib.hbp_default_params(ctypes.byref(p)) == 0
+    p.rows_per_block, p.cols_per_block, p.rounds_per_batch, p.hash_shift = R, C, 4, 4
+    for wait, words in enumerate([[0, nnz], [S, G, B, 0, 4, *counts], [U, 0, 0, 0]]):
+        for i, w in enumerate(words):
+            rt.set_word(wait, i, w)
+    rt.begin()
+    h = ctypes.c_void_p()
+    rc = (lib.hbp_build_f64 if f64 else lib.hbp_build)(word, word, word, n_rows, n_cols, ctypes.byref(p), None, ctypes.byref(h))
+    assert rc == 0, rc
+    return h
+
+def product(f64, h):
+    rt.begin()
+    rc = (lib.hbp_spmv_f64 if f64 else lib.hbp_spmv)(h, word, word, None)
+    assert rc == 0, rc
+    return noted()[0]
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    """Runs a program against the noting runtime; returns the value that it prints."""
+    import paper_2504_08860_amd as H
+    if not os.path.exists(H.LIB_PATH):
+        from paper_2504_08860_amd.build import build_library
+        build_library()
+    at = tmp_path_factory.mktemp("launches")
+    source, runtime = at / "runtime.c", at / "runtime.so"
+    source.write_text("".join(f"#define {f} quiet_{f}\n" for f in ("hipMalloc", "hipHostMalloc", "hipStreamSynchronize", "hipLaunchKernel"))
+                      + RUNTIME + NOTES)
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", str(source), "-o", str(runtime)])
+
+    def program(body):
+        text = at / "program.py"
+        text.write_text(PROGRAM + textwrap.dedent(body))
+        res = subprocess.run([sys.executable, str(text), str(runtime), H.LIB_PATH], capture_output=True, text=True, cwd=ROOT, timeout=120,
+                             env=dict(os.environ, PYTHONPATH=ROOT))
+        assert res.returncode == 0, res.stdout + res.stderr
+        return ast.literal_eval(res.stdout)
+    return program
+
+
+# rows per block, units and the combine part's wavefronts per unit: on a compute unit fit as many units as their copies of the
+# slice and 1024 bytes, in steps of 1280, let into 160 KB, and as their wavefronts let into 32 (in comments: of four and of three wavefronts)
+COMBINE = {
+    False: [(2048, [(256, 16), (257, 8), (512, 8), (513, 4), (1024, 4), (1025, 3), (1536, 3), (1537, 4)]),   # 4 and 6 units
+            (1025, [(2048, 4), (2049, 4), (2304, 4), (2305, 3), (2560, 3), (2561, 4)]),                      # 8 (LDS: 9) and 10 (LDS: 11)
+            (1200, [(2048, 4), (2049, 3), (2304, 3), (2305, 4)]),                                            # 8 and 9
+            (8192, [(256, 4), (257, 4)])],                                                                   # 1 and 1
+    True: [(2048, [(256, 8), (257, 4), (512, 4), (513, 3), (768, 3), (769, 4)]),                             # 2 and 3
+           (1037, [(1024, 4), (1025, 3), (1536, 3), (1537, 4)]),                                             # 4 and 6
+           (4096, [(256, 4), (257, 4)])],                                                                    # 1 and 1
+}
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_wavefronts_of_the_combine_part(run, f64):
+    got = run(f"""
+        out = []
+        for R, units in {[(R, [u for u, _ in units]) for R, units in COMBINE[f64]]}:
+            for U in units:
+                for slots in (127, 128):                  # on average, per block: short chunks below 128, longer ones from there on
+                    h = build({f64}, R * U, 1000, R, 1000, 1000 * U, slots * U, 3 * U, U, [0] * 2, U)
+                    out.append((R, U, slots, [k for k in product({f64}, h) if "k_combine" in k]))
+                    assert lib.hbp_free(h) == 0
+                    assert lib.hbp_release_workspace() == 0
+        print(out)
+    """)
+    want = []
+    for R, units in COMBINE[f64]:
+        for U, wavefronts in units:
+            for slots in (127, 128):
+                want.append((R, U, slots, "k_combineILi%dE%sLi%dELi%dE" % (64 * wavefronts, "d" if f64 else "f", *((8, 2) if slots == 127 else (4, 4)))))
+    assert len(got) == len(want)
+    wrong = [(g, w) for g, w in zip(got, want) if g[:3] != w[:3] or len(g[3]) != 1 or w[3] not in g[3][0]]
+    assert not wrong, wrong
