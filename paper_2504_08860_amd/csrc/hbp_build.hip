@@ -434,26 +434,33 @@ constexpr int kFillRounds = 128;
 
 constexpr int kLongRow = 4 * kFillRounds;
 
-// Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).  longest_rows: the longest row, where
-// it has more than kLongRow nonzeros, in copies apart from each other (one word for all: 101 us in place of 10 where one row in 40
-// asks for it).
-constexpr int kLongestCopies = 64, kLongestStride = 16;
+// What k_check_ptr and k_segments find out, zeros to begin with: what is wrong; the longest row, where it has more than kLongRow
+// nonzeros; whether a tile shows a long segment.  The last two in copies apart from each other (one word for all: 101 us for k_check_ptr in
+// place of 10 where one row in 40 has to be told), and all behind one pointer (another argument, two more scalar registers, and
+// a compute unit holds three tiles of k_segments<false> instead of four: 98 -> 114 us on the 27-point grid of 128^3).
+struct Findings {
+    int32_t err, apart[15];
+    struct { uint32_t longest_row, long_segment, apart[14]; } copy[64];
+};
+__device__ __forceinline__ auto &findings_of_workgroup(Findings *found) { return found->copy[blockIdx.x % 64]; }
+
+// Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).
 __global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t *__restrict__ tile_row,
-                                                   int32_t *__restrict__ err, uint32_t *__restrict__ longest_rows)
+                                                   Findings *__restrict__ found)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
     uint32_t length = 0;
     if (r < n_rows) {
         const int64_t p0 = ptr[r], p1 = ptr[r + 1];
         if (p0 < 0 || p1 < p0 || p1 > nnz) {
-            atomicOr(err, kErrPtr);
+            atomicOr(&found->err, kErrPtr);
         } else {
             for (int64_t t = (p0 + kTile - 1) / kTile; t * kTile < p1; t++) tile_row[t] = (int32_t)r;
             length = (uint32_t)(p1 - p0);
         }
     }
     const uint32_t longest = wave_max(length);
-    if (longest > (uint32_t)kLongRow && (threadIdx.x & 63) == 0) atomicMax(&longest_rows[blockIdx.x % kLongestCopies * kLongestStride], longest);
+    if (longest > (uint32_t)kLongRow && (threadIdx.x & 63) == 0) atomicMax(&findings_of_workgroup(found).longest_row, longest);
 }
 
 // Wave-aggregated fetch-add: lanes of the wavefront that target the same counter are served by
@@ -542,13 +549,13 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
                                                            int64_t nnz, int64_t n_cols, int32_t R, int32_t shift_r, int32_t C, int32_t shift_c,
                                                            int32_t NBR, int32_t NBC, int validate, const int32_t *__restrict__ tile_row,
                                                            int32_t *__restrict__ tile_first, uint32_t *__restrict__ cursor,
-                                                           uint2 *__restrict__ bucket, int32_t *err)
+                                                           uint2 *__restrict__ bucket, Findings *found)
 {
     __shared__ uint32_t cnt[kTileCounters];
     __shared__ __align__(16) int32_t row_at[kTile];  // row that starts at a position, counted from the tile's first row; -1: none
     __shared__ int32_t word_last[kTileWords], word_first[kTileWords];  // last row start, first segment start of a word; -1, kTile: none
     __shared__ int32_t sh_next;
-    if (*err & kErrPtr) return;  // k_check_ptr's finding: the rows below would not ascend
+    if (found->err & kErrPtr) return;  // k_check_ptr's finding: the rows below would not ascend
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t j0 = (int64_t)blockIdx.x * kTile;
@@ -641,7 +648,7 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
         const bool row_start = (rows_here[u] >> lane) & 1ull;
         const int32_t c_prev = lane_below(c[u], u > 0 ? __builtin_amdgcn_readlane(c[u > 0 ? u - 1 : 0], 63) : __builtin_amdgcn_readfirstlane(before));
         const bool in_range = (uint32_t)c[u] < cols;
-        if (!EMIT && valid && (!in_range || (validate && !row_start && c[u] <= c_prev))) atomicOr(err, kErrCol);
+        if (!EMIT && valid && (!in_range || (validate && !row_start && c[u] <= c_prev))) atomicOr(&found->err, kErrCol);
         const int32_t bn = block_column(c[u], C, shift_c);
         const int32_t bn_prev = lane_below(bn, u > 0 ? last_bn : block_column(__builtin_amdgcn_readfirstlane(before), C, shift_c));
         last_bn = __builtin_amdgcn_readlane(bn, 63);
@@ -677,6 +684,7 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
             const uint64_t there = __ballot(f < kTile);
             const int32_t first = there ? __shfl(f, __builtin_ctzll(there)) : -1;
             if (lane == 0) tile_first[blockIdx.x] = first < 0 ? -1 : (int32_t)(j0 + first);
+            if (lane == 0 && shows_long_segment(there, count)) findings_of_workgroup(found).long_segment = 1u;
         }
     } else {
         __syncthreads();
@@ -1568,16 +1576,18 @@ int readback_get(int device, uint32_t **out)
 }
 
 struct Words { const void *at[kReadback]; };
-// longest_rows: k_check_ptr's; the largest of its copies goes behind the words
-__global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host, const uint32_t *__restrict__ longest_rows)
+// found: the largest of the copies go behind the words
+__global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host, const Findings *__restrict__ found)
 {
     const int i = threadIdx.x;
     if (i < count) host[i] = *static_cast<const uint32_t *>(words.at[i]);
-    if (!longest_rows) return;
-    const uint32_t longest = wave_max(longest_rows[i * kLongestStride]);
-    if (i == 0) host[count] = longest;
+    if (!found) return;
+    const uint32_t longest = wave_max(found->copy[i].longest_row), segment = wave_max(found->copy[i].long_segment);
+    if (i == 0) {
+        host[count] = longest;
+        host[count + 1] = segment;
+    }
 }
-static_assert(kLongestCopies == 64, "a lane of k_publish per copy");
 
 // One device allocation carved into 256-byte aligned arrays: reserve() every array first,
 // commit() allocates once and hands out the pointers.  hipMalloc/hipFree calls are a large part
@@ -1810,13 +1820,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     Arena tmp(false, h->device, 0);
     const int64_t n_tiles = (nnz + kTile - 1) / kTile;
     const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
-    uint32_t *longest_rows, *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
-    int32_t *tile_row, *tile_first, *d_a, *d_err;
+    Findings *found;
+    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
+    int32_t *tile_row, *tile_first, *d_a;
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, 16);
-    tmp.reserve(&d_err, 1);
-    tmp.reserve(&longest_rows, kLongestCopies * kLongestStride);
+    tmp.reserve(&found, 1);
     tmp.reserve(&tile_first, n_tiles);
     tmp.reserve(&tile_row, n_tiles);
     tmp.reserve(&slot_off, D + 1);
@@ -1843,10 +1853,10 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         if (C == (int32_t(1) << b)) shift_c = b;
         if (R == (int32_t(1) << b)) shift_r = b;
     }
-    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tile_row, d_err, longest_rows);
+    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tile_row, found);
     k_segments<false><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
                                                                         (int32_t)NBC, (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, tile_row,
-                                                                        tile_first, dense_cnt, nullptr, d_err);
+                                                                        tile_first, dense_cnt, nullptr, found);
     // step 4: scans over the block table
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
@@ -1855,13 +1865,14 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_HIP(hipGetLastError());
 
     // the one host round trip of the build: totals (and the error word)
-    k_publish<<<1, 64, 0, st>>>(Words{{slot_off + D, group_off + D, blk_id + D, d_err, d_a}}, 5, host, longest_rows);
+    k_publish<<<1, 64, 0, st>>>(Words{{slot_off + D, group_off + D, blk_id + D, &found->err, d_a}}, 5, host, found);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     const int32_t err = (int32_t)host[3], a = (int32_t)host[4];
     if (err & kErrPtr) return HBP_ERR_BAD_CSR_PTR;
     if (err & kErrCol) return HBP_ERR_BAD_CSR_COL;
     const int64_t S = host[0], G = host[1], B = host[2], longest_row = host[5];
+    const bool long_segments = host[6] != 0;
     h->S = S; h->G = G; h->B = B; h->a = a;
 
     Arena own1(true, h->device);
@@ -1918,7 +1929,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // steps 5-6 (slot_off doubles as the per-block cursor from here on)
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
     k_segments<true><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
-                                                                       (int32_t)NBC, 0, tile_row, tile_first, slot_off, bucket, d_err);
+                                                                       (int32_t)NBC, 0, tile_row, tile_first, slot_off, bucket, found);
     // The order in which k_fill takes the blocks (see stripe_walk).  Row block by
     // row block pays where a row segment is a small part of the 128-byte lines it is gathered from
     // (fewer than 4 nonzeros on average) and the blocks are large enough to keep a workgroup busy
@@ -1947,10 +1958,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_HIP(hipMemsetAsync(h->col_local + nnz, 0, 256 * sizeof(uint16_t), st));
     HBP_HIP(hipMemsetAsync((char *)h->data + (size_t)nnz * h->value_bytes, 0, 256 * (size_t)h->value_bytes, st));
     // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
-    // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us); where
-    // all rows are long nothing waits.  R-MAT 2^20 (fp64) 322 us whole; cut 224, 5 for the list and 39 for the rest.  Not for
-    // k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
-    const bool cut = parts == 0 && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
+    // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us), nor
+    // where the long rows lie in short segments over many block columns (20 rows of 4000 over 123 and 31 of them: 27.0 -> 36.5 and 55.2 -> 63.8);
+    // where all rows are long nothing waits.  Fill kernels, us, whole / cut: R-MAT 2^20 (fp64) 322 / 267; 50 rows of 30000 beside rows of 40 506 /
+    // 108; 250 of 600 beside rows of 70 211 / 214; one row in 40 held, of 400, 50 of 2500 93 / 51; one in 10, of 100, 50 of 700 61 / 57; one in
+    // 100, of 600 44.5 / 51.5 (the average counts empty rows: groups so few that the device is not full gain by being cut as a rule).  Not
+    // for k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
+    const bool cut = parts == 0 && long_segments && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
     auto fill = [&](const auto *val, auto *data) {
         using T = std::remove_reference_t<decltype(*data)>;
         if (parts > 0) {

@@ -90,6 +90,16 @@ inline int flat_wavefronts(int64_t nnz, int64_t S, int64_t NBC, int32_t value_by
 // takes 8 rounds, up to 512 nonzeros, per memory round trip
 __host__ __device__ inline bool is_long_group(int32_t nnz, int32_t longest, int wpg) { return nnz > 2048 || (wpg > 1 && longest > 64); }
 
+// The build cuts groups with long segments where it can.  Whether a tile of 64 words of 64 nonzeros (`count` of them there) shows that a
+// segment has more than 192 nonzeros: three words in a row without a start of one (bit w: one starts in word w).  More than 512
+// nonzeros show in one of their tiles, wherever they begin: at least 256 in a row behind the start lie in one.
+__host__ __device__ inline bool shows_long_segment(uint64_t words_with_start, int32_t count)
+{
+    const int32_t full = count >> 6;
+    const uint64_t without = ~words_with_start & (full < 64 ? (1ull << full) - 1ull : ~0ull);
+    return (without & without >> 1 & without >> 2) != 0;
+}
+
 // Combine part, blocks of more than 1024 rows: wavefronts of a workgroup, each with its own copy of the unit's slice of y in LDS.
 constexpr int kCombineLds = 4 * kMaxR * (int)sizeof(float);  // all copies, at most
 constexpr int kCombineStaticLds = 1024;                       // the kernel's own array (checked there)

@@ -162,3 +162,72 @@ def test_wavefronts_of_the_combine_part(run, f64):
     assert len(got) == len(want)
     wrong = [(g, w) for g, w in zip(got, want) if g[:3] != w[:3] or len(g[3]) != 1 or w[3] not in g[3][0]]
     assert not wrong, wrong
+
+
+# rows, nonzeros, longest row, whether a tile showed a long segment, whether groups are cut
+CUT = [
+    (1 << 20, 16_000_000, 513, True, True),          # rows from 513 nonzeros on
+    (1 << 20, 16_000_000, 512, True, False),
+    (1 << 20, 16_000_000, 5000, True, True),
+    (1 << 20, 16_000_000, 5000, False, False),       # long rows in short segments
+    (10_000, 6_000_000, 4800, True, False),          # more than eight times the average
+    (10_000, 6_000_000, 4801, True, True),
+    (1, 9000, 9000, True, False),
+]
+
+
+def test_groups_cut_where_segments_are_long(run):
+    got = run(f"""
+        out = []
+        for n_rows, nnz, longest, segments, _ in {CUT}:
+            h = build(False, n_rows, 30000, 512, 30000, nnz, n_rows, (n_rows + 63) // 64, (n_rows + 511) // 512, [longest, int(segments)], 100)
+            out.append([k for k in noted()[0] if "k_fill" in k or "k_list_rest" in k])
+            assert lib.hbp_free(h) == 0
+            assert lib.hbp_release_workspace() == 0
+        print(out)
+    """)
+    for case, kernels in zip(CUT, got, strict=True):
+        want = ["k_fill_flatILb1Ef", "k_list_rest", "k_fill_restIf"] if case[4] else ["k_fill_flatILb0Ef"]
+        assert len(kernels) == len(want) and all(w in k for w, k in zip(want, kernels)), (case, kernels)
+
+
+def test_what_tiles_show_of_long_segments(tmp_path):
+    """A segment of 513 nonzeros shows in a tile wherever it begins and its matrix ends; segments of up to 192 never do."""
+    source, exe = tmp_path / "rule.cpp", tmp_path / "rule"
+    source.write_text(r"""
+#include <cstdio>
+#include <vector>
+#include "hbp_internal.h"
+static bool shown(const std::vector<char> &starts)   // starts[j]: a segment starts at nonzero j
+{
+    const size_t n = starts.size();
+    for (size_t j0 = 0; j0 < n; j0 += 4096) {
+        uint64_t words = 0;
+        for (size_t j = j0; j < n && j < j0 + 4096; j++) words |= (uint64_t)(starts[j] != 0) << ((j - j0) / 64);
+        if (hbp::shows_long_segment(words, (int32_t)(n - j0 < 4096 ? n - j0 : 4096))) return true;
+    }
+    return false;
+}
+int main()
+{
+    for (size_t at = 0; at < 4200; at++)
+        for (size_t behind : {0, 1, 63, 700}) {
+            std::vector<char> starts(at + 513 + behind, 1);
+            for (size_t j = at + 1; j < at + 513; j++) starts[j] = 0;
+            if (!shown(starts)) { std::printf("513 from %zu, %zu behind\n", at, behind); return 1; }
+        }
+    for (size_t length : {1, 64, 191, 192})
+        for (size_t at = 0; at < length; at++)
+            for (size_t n : {size_t(100), size_t(4096), size_t(8192), size_t(9001)}) {
+                std::vector<char> starts(n, 0);
+                for (size_t j = at; j < n; j += length) starts[j] = 1;
+                starts[0] = 1;
+                if (shown(starts)) { std::printf("%zu from %zu of %zu\n", length, at, n); return 1; }
+            }
+    return 0;
+}
+""")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2504_08860_amd", "csrc"), str(source), "-o", str(exe)])
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
