@@ -1899,6 +1899,23 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own1.reserve(&h->multi_stripes, NBR);
     HBP_TRY(own1.commit());
     h->arena[1] = own1.base(); h->arena_bytes[1] = own1.bytes();
+    // The order in which k_fill takes the blocks (see stripe_walk).  Row block by
+    // row block pays where a row segment is a small part of the 128-byte lines it is gathered from
+    // (fewer than 4 nonzeros on average) and the blocks are large enough to keep a workgroup busy
+    // (256 slots on average); measured: k_fill 2.30 -> 1.10 ms on the 4M x 1M matrix with 2 nonzeros
+    // per segment, 0.79 -> 0.37 ms on the 2^20 one with 1.6; with 13 nonzeros per segment (27-point
+    // stencil) or 86 slots per block (R-MAT, whose dense row blocks then also wait for a few
+    // workgroups) it is slower than the layout's own order with a wavefront per group.
+    const bool by_row_block = NBR >= 64 && nnz < 4 * S && S >= 256 * B;
+    const int32_t parts = !by_row_block ? 0 : (int32_t)std::min<int64_t>(32, std::max<int64_t>(1, (B + NBR - 1) / NBR));
+    // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
+    // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us), nor
+    // where the long rows lie in short segments over many block columns (20 rows of 4000 over 123 and 31 of them: 27.0 -> 36.5 and 55.2 -> 63.8);
+    // where all rows are long nothing waits.  Fill kernels, us, whole / cut: R-MAT 2^20 (fp64) 322 / 267; 50 rows of 30000 beside rows of 40 506 /
+    // 108; 250 of 600 beside rows of 70 211 / 214; one row in 40 held, of 400, 50 of 2500 93 / 51; one in 10, of 100, 50 of 700 61 / 57; one in
+    // 100, of 600 44.5 / 51.5 (the average counts empty rows: groups so few that the device is not full gain by being cut as a rule).  Not
+    // for k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
+    const bool cut = parts == 0 && long_segments && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
     Arena tmp2(false, h->device, 1);
     uint32_t *stripe_cum, *unit_cnt, *multi_idx;
     tmp2.reserve(&stripe_cum, B + 1); tmp2.reserve(&unit_cnt, NBR + 1); tmp2.reserve(&multi_idx, NBR + 1);
@@ -1907,8 +1924,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     int32_t *slot_j;
     tmp2.reserve(&bucket, S);
     tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 3);
-    int2 *rest;  // an entry per kFillRounds nonzeros of a group's longest row at most
-    tmp2.reserve(&rest, nnz / kFillRounds + 1);
+    int2 *rest = nullptr;  // an entry per kFillRounds nonzeros of a group's longest row at most
+    if (cut) tmp2.reserve(&rest, nnz / kFillRounds + 1);
     HBP_TRY(tmp2.commit());
     d_n_long = longest_all + 1;
     uint32_t *const d_n_rest = longest_all + 2;
@@ -1930,15 +1947,6 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
     k_segments<true><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
                                                                        (int32_t)NBC, 0, tile_row, tile_first, slot_off, bucket, found);
-    // The order in which k_fill takes the blocks (see stripe_walk).  Row block by
-    // row block pays where a row segment is a small part of the 128-byte lines it is gathered from
-    // (fewer than 4 nonzeros on average) and the blocks are large enough to keep a workgroup busy
-    // (256 slots on average); measured: k_fill 2.30 -> 1.10 ms on the 4M x 1M matrix with 2 nonzeros
-    // per segment, 0.79 -> 0.37 ms on the 2^20 one with 1.6; with 13 nonzeros per segment (27-point
-    // stencil) or 86 slots per block (R-MAT, whose dense row blocks then also wait for a few
-    // workgroups) it is slower than the layout's own order with a wavefront per group.
-    const bool by_row_block = NBR >= 64 && nnz < 4 * S && S >= 256 * B;
-    const int32_t parts = !by_row_block ? 0 : (int32_t)std::min<int64_t>(32, std::max<int64_t>(1, (B + NBR - 1) / NBR));
     const dim3 stripe_grid((unsigned)(8 * ((NBR + 7) / 8) * std::max(parts, 1)));
     const size_t order_cap = ((size_t)R + 63) & ~(size_t)63;
     size_t small_n2 = 1;  // the bitonic network of a small block: 8-byte words, the next power of two above min(R, 256) slots
@@ -1957,14 +1965,6 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // the padding behind the last group is read (and its products dropped) by lanes without an element
     HBP_HIP(hipMemsetAsync(h->col_local + nnz, 0, 256 * sizeof(uint16_t), st));
     HBP_HIP(hipMemsetAsync((char *)h->data + (size_t)nnz * h->value_bytes, 0, 256 * (size_t)h->value_bytes, st));
-    // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
-    // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us), nor
-    // where the long rows lie in short segments over many block columns (20 rows of 4000 over 123 and 31 of them: 27.0 -> 36.5 and 55.2 -> 63.8);
-    // where all rows are long nothing waits.  Fill kernels, us, whole / cut: R-MAT 2^20 (fp64) 322 / 267; 50 rows of 30000 beside rows of 40 506 /
-    // 108; 250 of 600 beside rows of 70 211 / 214; one row in 40 held, of 400, 50 of 2500 93 / 51; one in 10, of 100, 50 of 700 61 / 57; one in
-    // 100, of 600 44.5 / 51.5 (the average counts empty rows: groups so few that the device is not full gain by being cut as a rule).  Not
-    // for k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
-    const bool cut = parts == 0 && long_segments && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
     auto fill = [&](const auto *val, auto *data) {
         using T = std::remove_reference_t<decltype(*data)>;
         if (parts > 0) {

@@ -73,6 +73,7 @@ rt = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)      # in front of the re
 lib = ctypes.CDLL(sys.argv[2])
 rt.launch.restype = ctypes.c_char_p
 rt.allocation.restype = ctypes.c_size_t
+rt.set_capacity.argtypes = [ctypes.c_size_t]
 for f in (lib.hbp_build, lib.hbp_build_f64):
     f.argtypes = [ctypes.c_void_p] * 3 + [ctypes.c_int64] * 2 + [ctypes.c_void_p] * 3
 for f in (lib.hbp_spmv, lib.hbp_spmv_f64):
@@ -189,6 +190,25 @@ def test_groups_cut_where_segments_are_long(run):
     for case, kernels in zip(CUT, got, strict=True):
         want = ["k_fill_flatILb1Ef", "k_list_rest", "k_fill_restIf"] if case[4] else ["k_fill_flatILb0Ef"]
         assert len(kernels) == len(want) and all(w in k for w, k in zip(want, kernels)), (case, kernels)
+
+
+def test_scratch_memory_for_groups_that_are_cut(run):
+    """The list of their parts, 8 bytes per 128 nonzeros, is in the fourth allocation of builds that cut, and of no others."""
+    got = run("""
+        out = []
+        for nnz, longest in ((16_000_000, 512), (64_000_000, 512), (16_000_000, 513), (64_000_000, 513)):
+            rt.set_capacity(1 << 32)
+            h = build(False, 1 << 20, 30000, 512, 30000, nnz, 1 << 20, 1 << 14, 1 << 11, [longest, 1], 100)
+            out.append(noted()[1])
+            assert lib.hbp_free(h) == 0
+            assert lib.hbp_release_workspace() == 0
+        print(out)
+    """)
+    assert [len(sizes) for sizes in got] == [4] * 4
+    small, large, small_cut, large_cut = (sizes[3] for sizes in got)
+    assert small == large
+    for size, nnz in ((small_cut, 16_000_000), (large_cut, 64_000_000)):
+        assert 0 <= size - small - nnz // 16 <= nnz // 16 // 8 + 1024   # (an eighth more is taken than needed, in steps of 256)
 
 
 def test_what_tiles_show_of_long_segments(tmp_path):
