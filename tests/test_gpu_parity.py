@@ -812,13 +812,18 @@ def test_groups_cut_where_rows_are_much_longer(H, oracle, long, W, f64):
     check_against_oracle(H, oracle, m, rows_per_block=2048, cols_per_block=1700, group_width=W)
 
 
-@pytest.mark.parametrize("f64,units", [(True, 512), (True, 513), (True, 768), (True, 769), (False, 1025), (False, 1536)])
-def test_combine_with_three_wavefronts(H, oracle, units, f64):
-    """The numbers of combine units around those that three wavefronts each, but not four, have on the device at once."""
+@pytest.mark.parametrize("f64,units,R,share", [
+    (True, 512, 2048, 0.3), (True, 513, 2048, 0.3), (True, 768, 2048, 0.3), (True, 769, 2048, 0.3), (False, 1025, 2048, 0.3), (False, 1536, 2048, 0.3),
+    (False, 1024, 2048, 0.3), (False, 1537, 2048, 0.3), (True, 1025, 1037, 0.3), (False, 2305, 1025, 0.3), (False, 2304, 1200, 0.3),
+    (True, 513, 2048, 0.1), (True, 769, 2048, 0.1), (False, 1025, 2048, 0.1), (False, 2560, 1025, 0.1),   # blocks of fewer than 128 slots
+])
+def test_combine_with_three_wavefronts(H, oracle, units, f64, R, share):
+    """The numbers of combine units around those that three wavefronts each, but not four, have on the device at once (which of them
+    runs: test_wavefronts_of_the_combine_part), with blocks of many and of few slots."""
     from workloads import CsrMatrix, widen_to_f64
     rng = np.random.default_rng(units)
-    n_rows, n_cols = 2048 * units - 7, 40000
-    lens = np.where(rng.random(n_rows) < 0.3, rng.integers(1, 3, n_rows), 0)
+    n_rows, n_cols = R * units - 7, 40000
+    lens = np.where(rng.random(n_rows) < share, rng.integers(1, 3, n_rows), 0)
     first = rng.integers(0, n_cols // 2, n_rows)                  # at most two nonzeros, half of the columns apart
     ptr = np.r_[0, np.cumsum(lens)].astype(np.int32)
     col = np.empty(ptr[-1], np.int32)
@@ -827,5 +832,23 @@ def test_combine_with_three_wavefronts(H, oracle, units, f64):
     m = CsrMatrix("units", n_rows, n_cols, ptr, col, rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
     if f64:
         m = widen_to_f64(m)
-    info = check_against_oracle(H, oracle, m, rows_per_block=2048, cols_per_block=10000)
+    info = check_against_oracle(H, oracle, m, rows_per_block=R, cols_per_block=10000 if R > 1500 or share < 0.3 else 16000)
     assert info.combine_units == units
+    assert (info.slots < 128 * info.blocks) == (share < 0.3)
+
+
+@pytest.mark.parametrize("blocks", [8191, 8192, 8193, 16384, 16385])
+@pytest.mark.parametrize("empty", [0, 3])
+def test_scans_at_the_ends_of_a_workgroups_turns(H, oracle, blocks, empty):
+    """A row per block: the scans over the block table, the row blocks and the groups have as many entries, 8192 to a turn of the
+    workgroup that scans alone, and 16385 are for the two kernels; with empty rows the last two have fewer."""
+    from workloads import CsrMatrix
+    rng = np.random.default_rng(blocks)
+    lens = rng.integers(1, 4, blocks + empty)
+    lens[rng.choice(blocks + empty, empty, replace=False)] = 0
+    n_cols = 60
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    m = CsrMatrix("scans", len(lens), n_cols, np.r_[0, np.cumsum(lens)].astype(np.int32), col,
+                  rng.standard_normal(len(col)).astype(np.float32), rng.uniform(-1, 1, n_cols).astype(np.float32))
+    info = check_against_oracle(H, oracle, m, rows_per_block=1, cols_per_block=n_cols, group_width=2)
+    assert (info.blocks, info.groups) == (blocks, blocks)
