@@ -177,8 +177,9 @@ __global__ __launch_bounds__(256) void k_scan_down(Scans s, int64_t n, uint32_t 
     if (blockIdx.x == n_tiles - 1 && threadIdx.x == 0) s.out[a][n] = before + total;
 }
 
-// Short scans in one launch in place of two: a workgroup per scan, 8192 items at a time.  A launch costs some 5 us whatever it does,
-// one of this kernel 6 us; three of a build's five scans are as short on large matrices, all of them on small ones.
+// Short scans in one launch in place of two: a workgroup per scan, 8192 items at a time.  4 to 6 us in place of 4.5 to 5 each for
+// k_scan_reduce and k_scan_down; two of a build's five scans are as short on R-MAT 2^20 and the 4M x 1M lognormal matrix, three on the 27-point
+// grid of 128^3, all of them on small matrices.
 constexpr int64_t kScanAlone = 16384;
 __global__ __launch_bounds__(1024) void k_scan_alone(Scans s, int64_t n, uint32_t W)
 {
@@ -508,27 +509,6 @@ __device__ __forceinline__ int32_t first_reached(int32_t lo, int32_t hi, F reach
     return lo;
 }
 
-// The segments of kTile consecutive nonzeros per workgroup: a nonzero starts one when it starts a row or
-// its block column differs from its left neighbour's.  The rows that start inside the tile are read from
-// csr_ptr (empty rows own no position) into an LDS table by position, or looked for from the nonzeros where most
-// rows are empty; a segment's row is the last one that starts at or before it.  Two passes over the matrix (bound by reading csr_col, 4 bytes per nonzero, and in the
-// second pass by writing 8 bytes per segment), with the scans over the block table between them:
-//   EMIT false  counts the segments of every block (cursor: the block table) and notes every tile's first
-//               segment start;
-//   EMIT true   drops (length << 16 | local row, first nonzero) of every segment into its block's slot range
-//               (cursor: the blocks' next free slots), in no particular order: k_order_block sorts them.
-// A tile's rows are neighbours, so it touches the blocks of a few row blocks only: (bm_hi - bm_lo + 1) * NBC
-// counters.  When those fit in LDS the tile counts there (LDS integer atomics are two orders of magnitude
-// faster than scattered global ones) and goes to global memory once per counter it has touched;
-// otherwise every segment goes to global memory with wave-aggregated atomics.
-// (Before: row-start bits by global atomics, segment flags, a scan, segment records with a binary search per
-// segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
-// on the 4M x 1M lognormal matrix, 535 now; 300 and 288 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
-// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.  Then, with a nonzero's row found by a maximum over the lanes
-// up to it in place of a bit search and an LDS read and the scans over a tile's words without LDS: first pass 197 -> 181 us there, 115 -> 97 us on
-// the 27-point grid, second pass 167 -> 129 us on the grid (66 -> 62 registers: all four tiles of a CU).
-// Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
-// jump over the gaps 3260 / 20900.)
 // inclusive maximum over the lanes up to this one, of values from -1 up (all lanes active; six vector instructions)
 template <int kControl, int kRows>
 __device__ __forceinline__ int32_t highest_moved(int32_t v) { return max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, kControl, kRows, 0xf, false)); }
@@ -544,6 +524,28 @@ __device__ __forceinline__ int32_t highest_up_to_lane(int32_t v)
 // the value of the lane below; lane 0 gets `first`
 __device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false); }
 
+// The segments of kTile consecutive nonzeros per workgroup: a nonzero starts one when it starts a row or
+// its block column differs from its left neighbour's.  The rows that start inside the tile are read from
+// csr_ptr (empty rows own no position) into an LDS table by position, or looked for from the nonzeros where most
+// rows are empty; a segment's row is the last one that starts at or before it.  Two passes over the matrix (reading csr_col, 4 bytes per
+// nonzero, and in the second pass writing 8 bytes per segment), with the scans over the block table between them:
+//   EMIT false  counts the segments of every block (cursor: the block table) and notes every tile's first
+//               segment start and whether a tile shows a long segment;
+//   EMIT true   drops (length << 16 | local row, first nonzero) of every segment into its block's slot range
+//               (cursor: the blocks' next free slots), in no particular order: k_order_block sorts them.
+// A tile's rows are neighbours, so it touches the blocks of a few row blocks only: (bm_hi - bm_lo + 1) * NBC
+// counters.  When those fit in LDS the tile counts there (LDS integer atomics are two orders of magnitude
+// faster than scattered global ones) and goes to global memory once per counter it has touched;
+// otherwise every segment goes to global memory with wave-aggregated atomics.
+// (Before: row-start bits by global atomics, segment flags, a scan, segment records with a binary search per
+// segment, a counting pass and a bucket pass over the records, 20 bytes per segment written and read twice: 1239 us
+// on the 4M x 1M lognormal matrix, 535 in two passes; 300 and 288 on the 27-point grid of 128^3, 181 and 186 on R-MAT 2^20.  A
+// tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.  With a nonzero's row found by a maximum over the lanes up to
+// it in place of a bit search and an LDS read, and the scans over a tile's words without LDS, 517, 227 and 118: first pass 197 -> 182 us on the
+// lognormal matrix and 115 -> 98 us on the grid, second pass 160 -> 129 us on the grid by the scans alone (65 -> 62 registers: all four tiles of
+// a CU).  Issuing vector instructions takes 77 and 88 % of the passes' time on the grid, 73 and 59 % on the lognormal matrix.
+// Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
+// jump over the gaps 3260 / 20900.)
 template <bool EMIT>
 __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col, int64_t n_rows,
                                                            int64_t nnz, int64_t n_cols, int32_t R, int32_t shift_r, int32_t C, int32_t shift_c,
@@ -857,9 +859,9 @@ __device__ __forceinline__ void scan_in_lds(uint32_t *a, int n, uint32_t *sh_wav
 // (second launch bound: all eight workgroups of small blocks to a CU, which 105 scalar registers had made seven; with a
 // barrier less at the end, 1.9M blocks of 9 slots 4725 -> 3450 us, 3880 before long rows were counted per block;
 // 4M x 1M lognormal matrix 529 -> 475.)
-// Bound by its vector instructions: 253M of them per launch there, 4 cycles each on 1024 SIMDs, were all of 467 us.  With the wavefront's
+// Bound by its vector instructions: 253M of them per launch there, 4 cycles each on 1024 SIMDs, were nine tenths of 467 us.  With the wavefront's
 // number and most of the arrays' addresses in scalar registers, sums over a wavefront without LDS and the lanes of a digit found by two
-// instructions per half and bit: 188M (350 us of issue), 360 us; 27-point grid of 128^3 54 -> 35 us, R-MAT 2^20 146 -> 124 us.
+// instructions per half and bit: 188M (86 % of the time), 360 us; 27-point grid of 128^3 54 -> 35 us, R-MAT 2^20 146 -> 124 us.
 __global__ __launch_bounds__(256, 8) void k_order_block(const uint2 *__restrict__ bucket,
                                                      const int32_t *__restrict__ slot_ptr, const int32_t *__restrict__ blk_group_ptr,
                                                      int32_t W, uint16_t *__restrict__ row_local, uint16_t *__restrict__ seg_len,
@@ -1092,11 +1094,13 @@ __device__ __forceinline__ void fill_group(int32_t g, int32_t k0, int32_t col0, 
     const int64_t j = lane < cnt ? slot_j[s0 + lane] : 0;
     uint32_t base = (uint32_t)group_ptr[g];
     if (CUT && k0 > 0) base += wave_sum((uint32_t)min(len, k0));
-    // Where the element of a lane goes in a round that begins at `at`: the round's place stays in the scalar part of the address,
-    // the lane's rank among the live lanes is its vector part.  (With 64-bit vector addresses per lane and every round of a
+    // Where the element of a lane goes in a round that begins at `at`: in rounds that look for their live lanes the round's place is the
+    // scalar part of the address and the lane's rank among them its vector part; where the lanes stay the same over several rounds the compiler
+    // keeps base and rank in a 64-bit vector address and adds the round to it.  (With 64-bit vector addresses everywhere and every round of a
     // batch gone through, k_fill took 1027 us on the 4M x 1M lognormal matrix, k_fill_flat 247 on the 27-point grid of 128^3 and 350 on
-    // R-MAT 2^20 in fp64; now 874, 224 and 322.  What bounds k_fill since is L2: a 128-byte line per segment and array, 103M of
-    // them; k_fill_flat on the grid streams 780 MB at 3.5 TB/s.)
+    // R-MAT 2^20 in fp64; now 877, 225 and 322, or 267 where the groups are cut.  What bounds k_fill since is the latency of L2: a
+    // 128-byte line per segment and array, 103M of them, 300 cycles each, 59 on their way per compute unit, L1 held up by pending ones in 78 % of
+    // its cycles; their 15 TB/s are not what L2 could deliver.  k_fill_flat on the grid streams 780 MB at 3.5 TB/s.)
     auto put = [&](uint32_t at, uint32_t rank, int32_t c, T v) __attribute__((always_inline)) {
         char *const round_col = reinterpret_cast<char *>(col_local) + ((uint64_t)at << 1);
         char *const round_val = reinterpret_cast<char *>(data) + (uint64_t)at * sizeof(T);
