@@ -686,7 +686,8 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
             const uint64_t there = __ballot(f < kTile);
             const int32_t first = there ? __shfl(f, __builtin_ctzll(there)) : -1;
             if (lane == 0) tile_first[blockIdx.x] = first < 0 ? -1 : (int32_t)(j0 + first);
-            if (lane == 0 && shows_long_segment(there, count)) findings_of_workgroup(found).long_segment = 1u;
+            if (lane == 0 && shows_long_segment(there, count))  // (several workgroups may write it, side by side)
+                __hip_atomic_store(&findings_of_workgroup(found).long_segment, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     } else {
         __syncthreads();
