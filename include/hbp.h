@@ -253,10 +253,10 @@ int hbp_spmv_f64(hbp_handle_t h, const double *x, double *y, void *stream);
  * of the library (32 MiB per device, held until the process ends) instead of the handle's buffers:
  * 256 KiB of claim counters and at most 8,323,072 slots (S * 4 bytes <= 32 MiB - 256 KiB).  A handle
  * with more slots or more than 65536 workers is refused with HBP_ERR_TOO_LARGE.  The call allocates
- * nothing, launches three kernels (the first clears the counters; small matrices without workers: not that one), and is
- * asynchronous on `stream`.
+ * nothing, launches the kernels that hbp_spmv launches, and is asynchronous on `stream`.
  * All calls on one device share the one array: calls that overlap in time on one device (different
- * streams, different handles) race and must be ordered by the caller. */
+ * streams, different handles) race and must be ordered by the caller.  (A call leaves its claim counters zero for the next one, as
+ * hbp_spmv does in the handle.) */
 int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stream);
 
 /* Frees the handle (synchronises the device first).  NULL is allowed.  The library keeps the handle's device
