@@ -143,7 +143,7 @@ struct Layout {
     int32_t claim;  // competitive groups a worker claims from a range's counter at a time
     int32_t SW, RW, GW;  // schedule weights of a slot, a round, a group (a nonzero weighs 1)
     int32_t steal_min;   // weight a range's competitive part must have left for another worker to enter it
-    int32_t heavy_rounds;  // a group with a longer row is walked by all wavefronts of a worker together
+    int32_t heavy_rounds;  // a group with a longer row is walked by several wavefronts of a worker together
     int32_t long_rounds;   // a group with a longer row (up to heavy_rounds) gets a wavefront of its own
     int32_t lists_first;   // and is walked, like the heavy ones, before the other groups of its range
     const uint16_t *row_local, *seg_len, *col_local;

@@ -235,18 +235,15 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     constexpr int kRoute = sizeof(T) == 4 ? 192 : 96;
     __shared__ Routed<T> sh_route[THREADS / 64 * kRoute + 1];
     constexpr int kHeavyCap = 64;
-    __shared__ int32_t sh_heavy[kHeavyCap];  // heavy groups of the current range, left to the whole worker
+    __shared__ int32_t sh_heavy[kHeavyCap];  // heavy groups of the current range, each left to several wavefronts
     constexpr int kLongCap = 256;
     __shared__ int32_t sh_long[kLongCap];  // long groups of the current range, each left to the next free wavefront
     // the same for the groups the range begins with, as offsets from its first group: known before it is walked
     constexpr int kFirstHeavyCap = 64, kFirstLongCap = 1024;
     __shared__ uint16_t sh_first_heavy[kFirstHeavyCap], sh_first_long[kFirstLongCap];
     __shared__ int32_t sh_heavy_n[2], sh_long_n[2], sh_long_next[2];  // 0: known before, 1: found among the claimed groups
-    __shared__ int32_t sh_lens[THREADS];  // per wavefront: segment lengths of the heavy group being cut
-    __shared__ int32_t sh_cut_k[THREADS / 64 + 1];   // heavy group: first round of every wavefront's share
-    __shared__ uint32_t sh_cut_pos[THREADS / 64 + 1];  // and the nonzeros before that round
-    static_assert(sizeof sh_route + sizeof sh_heavy + sizeof sh_long + sizeof sh_first_heavy + sizeof sh_first_long + sizeof sh_lens +
-                      sizeof sh_cut_k + sizeof sh_cut_pos + 128 <= part_static_lds(THREADS), "part_static_lds is out of date");
+    static_assert(sizeof sh_route + sizeof sh_heavy + sizeof sh_long + sizeof sh_first_heavy + sizeof sh_first_long +
+                      128 <= part_static_lds(THREADS), "part_static_lds is out of date");
     constexpr int kWaves = THREADS / 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -543,41 +540,49 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         // (HEAVY: the listed groups, the others, what the claims brought)
         for (int pass = 0;; pass++) {
         if constexpr (HEAVY) {
-            // Heavy groups: all wavefronts of the worker walk each of them together.  Wavefront w takes
-            // the rounds [k_w, k_{w+1}), where k_w is the first round that has w / kWaves of the group's
-            // nonzeros before it, and the per-lane sums of the wavefronts are added in LDS in wavefront order.
+            // Heavy groups: the wavefronts of the worker walk up to four of them at a time, `share` wavefronts each.  The w-th of
+            // these takes the rounds [k_w, k_{w+1}), where k_w is the first round that has w / share of the group's nonzeros
+            // before it, and their per-lane sums are added in LDS in wavefront order.
+            // (Bound by memory round trips, a few for the group's numbers and one for every 1024 nonzeros of a wavefront.  All wavefronts on
+            // one group after the other: 15 us a group, however few nonzeros were left to each; R-MAT 2^22 has nine such groups in the
+            // first worker's range, which took 247 us where the average worker took 160.  Product 296 -> 267 us.)
             const int32_t n_heavy = pass ? min(sh_heavy_n[1], kHeavyCap) : first_heavy ? sh_heavy_n[0] : 0;
-            for (int32_t i = 0; i < n_heavy; i++) {
-                const int32_t gh = __builtin_amdgcn_readfirstlane(pass ? sh_heavy[i] : g_begin + (int32_t)sh_first_heavy[i]);
-                const int32_t hs0 = uniform_load(L.group_slot, gh), hs1 = uniform_load(L.group_slot, gh + 1);
-                const uint32_t b0 = (uint32_t)uniform_load(L.group_ptr, gh);
-                const uint32_t total = (uint32_t)uniform_load(L.group_ptr, gh + 1) - b0;
-                const int32_t len = hs0 + lane < hs1 ? (int32_t)L.seg_len[hs0 + lane] : 0;
-                int32_t *lens = sh_lens + wave * 64;
-                lens[lane] = len;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                int32_t cut_k;
-                uint32_t cut_pos;
-                cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)wave) / (uint32_t)kWaves), lane, cut_k, cut_pos);
-                if (lane == 0) { sh_cut_k[wave] = cut_k; sh_cut_pos[wave] = cut_pos; }
-                if (threadIdx.x == 0) { sh_cut_k[kWaves] = 0x10000; sh_cut_pos[kWaves] = total; }
+            const int log_at_once = n_heavy >= 4 ? 2 : n_heavy >= 2 ? 1 : 0, share = kWaves >> log_at_once;
+            for (int32_t i0 = 0; i0 < n_heavy; i0 += 1 << log_at_once) {
+                const int32_t i = i0 + wave / share, part = wave % share;
+                T *const sums = reinterpret_cast<T *>(sh_route + wave * kRoute);  // the wavefront's place: lengths, what the walk holds there, its sums
+                int32_t hs0 = 0, hs1 = 0;
+                if (i < n_heavy) {
+                    const int32_t gh = __builtin_amdgcn_readfirstlane(pass ? sh_heavy[i] : g_begin + (int32_t)sh_first_heavy[i]);
+                    hs0 = uniform_load(L.group_slot, gh);
+                    hs1 = uniform_load(L.group_slot, gh + 1);
+                    const uint32_t b0 = (uint32_t)uniform_load(L.group_ptr, gh);
+                    const uint32_t total = (uint32_t)uniform_load(L.group_ptr, gh + 1) - b0;
+                    const int32_t len = hs0 + lane < hs1 ? (int32_t)L.seg_len[hs0 + lane] : 0;
+                    int32_t *lens = reinterpret_cast<int32_t *>(sums);
+                    lens[lane] = len;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    int32_t k_lo, k_hi = 1 << 16;
+                    uint32_t lo, hi = total;
+                    cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)part) / (uint32_t)share), lane, k_lo, lo);
+                    if (part + 1 < share) cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)(part + 1)) / (uint32_t)share), lane, k_hi, hi);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    uint32_t pos = b0 + lo;
+                    T sum = T(0);
+                    walk_rounds(pos, b0 + hi, min(len, k_hi), k_lo, sum);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    sums[lane] = sum;
+                }
                 __syncthreads();
-                const int32_t k_lo = sh_cut_k[wave], k_hi = sh_cut_k[wave + 1];
-                uint32_t pos = b0 + sh_cut_pos[wave];
-                T sum = T(0);
-                walk_rounds(pos, b0 + sh_cut_pos[wave + 1], min(len, k_hi), k_lo, sum);
-                __syncthreads();  // sh_route becomes the wavefronts' sums
-                T *const sums = reinterpret_cast<T *>(sh_route);
-                sums[threadIdx.x] = sum;
-                __syncthreads();
-                if (wave == 0 && hs0 + lane < hs1) {
+                if (part == 0 && hs0 + lane < hs1) {
                     T total_sum = sums[lane];
-#pragma unroll
-                    for (int w = 1; w < kWaves; w++) total_sum += sums[w * 64 + lane];
+                    for (int w = 1; w < share; w++) total_sum += reinterpret_cast<const T *>(sh_route + (wave + w) * kRoute)[lane];
                     partial[hs0 + lane] = total_sum;
                 }
-                __syncthreads();  // the sums and the cuts are reused by the next heavy group
+                __syncthreads();  // the places are used again
             }
             // Long groups: one wavefront each, whoever is free next.
             const int32_t n_long = pass ? min(sh_long_n[1], kLongCap) : first_long ? sh_long_n[0] : 0;

@@ -295,6 +295,30 @@ def test_heavy_groups_shared_by_a_worker(H, oracle, heavy, rounds, threads):
                              num_workers=workers, heavy_group_rounds=heavy)
 
 
+def _matrix_of_lengths(lens, n_cols, seed):
+    from workloads import CsrMatrix
+    rng = np.random.default_rng(seed)
+    col = np.concatenate([np.sort(rng.choice(n_cols, n, replace=False)) for n in lens]).astype(np.int32)
+    ptr = np.r_[0, np.cumsum(lens)].astype(np.int32)
+    return CsrMatrix("lengths", len(lens), n_cols, ptr, col, rng.standard_normal(len(col)).astype(np.float32),
+                     rng.uniform(-1, 1, n_cols).astype(np.float32))
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("threads", [256, 1024])
+@pytest.mark.parametrize("groups", [1, 2, 3, 4, 5, 9])
+def test_heavy_groups_walked_side_by_side(H, oracle, groups, threads, f64):
+    """One, two or four heavy groups at a time, the last turn with fewer than that; known before the range is walked (first
+    case) and found among the claimed groups (second)."""
+    from workloads import widen_to_f64
+    m = _matrix_of_lengths(np.concatenate([np.arange(64 * groups) % 190 + 65, np.full(100, 3)]), 4000, seed=groups)
+    if f64:
+        m = widen_to_f64(m)
+    for q8 in (256, 0):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=1024, cols_per_block=4096, rounds_per_batch=4,
+                             threads_per_worker=threads, num_workers=1, fixed_fraction_q8=q8, heavy_group_rounds=64)
+
+
 @pytest.mark.parametrize("seed", range(int(os.environ.get("HBP_RANDOM_CASES", "24"))))  # more seeds for a soak run
 def test_random_parameters(H, oracle, seed):
     """Seeded random draws over matrix shape and every build parameter (block sizes, group
