@@ -107,7 +107,8 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
                            p.rounds_per_batch != 0 || p.slot_weight >= 0 || p.group_weight >= 0 || p.round_weight >= 0 ||
                            p.column_weight >= 0 || p.heavy_group_rounds != 0 || (p.flags & HBP_FLAG_PAPER_SCHEDULE);
     if (p.group_width == 0) p.group_width = 64;
-    if (p.fixed_fraction_q8 < 0) p.fixed_fraction_q8 = 240;
+    const bool share_chosen = p.fixed_fraction_q8 < 0;
+    if (share_chosen) p.fixed_fraction_q8 = 240;
     const bool heavy_chosen = p.heavy_group_rounds == 0;
     if (heavy_chosen) p.heavy_group_rounds = 2048;
     const int32_t max_r = value_bytes == 8 ? hbp::kMaxR64 : hbp::kMaxR, max_c = value_bytes == 8 ? hbp::kMaxC64 : hbp::kMaxC;
@@ -140,6 +141,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     h->scheduled = scheduled;
     h->rows = rows;
     h->heavy_chosen = heavy_chosen;
+    h->share_chosen = share_chosen;
     h->first_ticket_block = -1;
     h->R = p.rows_per_block; h->C = p.cols_per_block; h->W = p.group_width;
     h->NBR = (n_rows + h->R - 1) / h->R;

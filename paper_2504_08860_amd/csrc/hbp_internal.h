@@ -127,6 +127,10 @@ inline int combine_wavefronts(int64_t cus, int64_t units, int64_t R, int32_t val
     return units > cus * combine_units_by_lds(copy, 4) && units <= cus * (by_lds < by_waves ? by_lds : by_waves) ? 3 : 4;
 }
 
+// Weight that another worker's range must have left for a worker to enter it: what entering a block column costs (the fetch of
+// its slice of x), twice, counting the restart of the pipeline.
+__host__ __device__ inline int32_t steal_weight(int32_t column_weight) { return 2 * column_weight; }
+
 // Device-side view of the layout, passed by value to kernels.
 struct Layout {
     int32_t R, C, W;
@@ -138,6 +142,7 @@ struct Layout {
     const int32_t *blk_bm, *blk_bn, *slot_ptr, *blk_group_ptr, *col_blk_ptr, *stripe_ptr, *stripe_blk;
     const int32_t *group_ptr, *group_slot, *group_rounds, *group_blk, *long_groups;
     const int32_t *col_group_ptr, *comp_lo, *comp_col, *fixed_start, *fixed_col;  // schedule (Section 3.3)
+    const int32_t *own_end, *any_open;
     const int32_t *unit_ptr, *unit_stripe, *unit_k, *multi_stripes;               // combine work units
     int32_t NM;                                                        // row blocks with several units
     int32_t claim;  // competitive groups a worker claims from a range's counter at a time
@@ -168,6 +173,8 @@ struct hbp_handle_s {
     int32_t *blk_bm, *blk_bn, *slot_ptr, *blk_group_ptr, *col_blk_ptr, *stripe_ptr, *stripe_blk;
     int32_t *group_ptr, *group_slot;
     int32_t *col_group_ptr, *comp_lo, *comp_col, *fixed_start, *fixed_col;
+    int32_t *own_end;                    // [P] end of the groups that are a worker's own: comp_lo, or the range's end where nobody would enter it
+    int32_t *any_open;                   // is there a range that somebody would enter?
     int32_t *group_rounds;               // [G+1] prefix sums of the groups' longest rows
     int32_t *group_blk;                  // [G] block of each group
     int32_t *long_groups;                // [n_long] groups that k_spmv_flat gives a workgroup of their own
@@ -178,6 +185,7 @@ struct hbp_handle_s {
     int32_t *unit_ptr, *unit_stripe, *unit_k, *multi_stripes;
     int64_t U, NM;       // combine work units, row blocks cut into several units
     int32_t unit_slots;  // target slots per combine unit
+    bool share_chosen;     // fixed_q8, by the library
     int32_t heavy_rounds;  // groups with a longer row are shared by a worker's wavefronts
     bool heavy_chosen;     // by the library
     int32_t group_weight;  // schedule weight of a group as such

@@ -36,11 +36,12 @@ Layout hbp_view(const hbp_handle_s *h)
     L.row_local = h->row_local; L.seg_len = h->seg_len; L.col_local = h->col_local; L.data = h->data;
     L.col_group_ptr = h->col_group_ptr; L.comp_lo = h->comp_lo; L.comp_col = h->comp_col;
     L.fixed_start = h->fixed_start; L.fixed_col = h->fixed_col;
+    L.own_end = h->own_end; L.any_open = h->any_open;
     L.unit_ptr = h->unit_ptr; L.unit_stripe = h->unit_stripe; L.unit_k = h->unit_k; L.multi_stripes = h->multi_stripes;
     L.NM = (int32_t)h->NM;
     L.claim = h->claim_chunk * (h->threads / kWave);
     L.SW = h->slot_weight; L.RW = h->round_weight; L.GW = h->group_weight;
-    L.steal_min = 2 * h->column_weight;
+    L.steal_min = steal_weight(h->column_weight);
     L.heavy_rounds = h->heavy_rounds;
     L.lists_first = walk_long_first(h->G, h->P) ? 1 : 0;
     L.long_rounds = long_rounds_of(h->heavy_rounds, L.lists_first);

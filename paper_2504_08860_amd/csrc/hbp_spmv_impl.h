@@ -837,11 +837,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     //     has enough left to be worth entering.  So a range that takes longer than its weight said is finished by the workers
     //     that were faster than theirs;
     //   phase 3 instead of 2, the paper's schedule: one ticket counter over the blocks that were not pre-assigned.
-    const bool competitive = L.competitive != 0;
+    const bool competitive = L.competitive != 0 && uniform_load(L.any_open, 0) != 0;
     int32_t col = uniform_load(L.fixed_col, worker);
     int32_t g_next = uniform_load(L.fixed_start, worker);
     const int32_t g_stop = uniform_load(L.fixed_start, worker + 1);
-    const int32_t own_lo = uniform_load(L.comp_lo, worker);
+    const int32_t own_lo = uniform_load(L.ticket_b0 >= 0 ? L.comp_lo : L.own_end, worker);
     for (int phase = 0;;) {
         int32_t r_bn = 0, r_g0 = 0, r_g1 = 0, r_owner = worker, r_lo = own_lo, r_end = g_stop;
         bool r_compete = true;
@@ -852,13 +852,13 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 if (g_next >= c_end) { col++; continue; }  // columns without groups
                 const int32_t ge = min(g_stop, c_end), fe = max(g_next, min(ge, own_lo));
                 const bool last = ge == g_stop;
-                if (g_next < fe || (last && competitive)) {
+                if (g_next < fe || (last && competitive && own_lo < g_stop)) {
                     r_bn = col;
                     // (an empty fixed part is handed over as [0, 0): the ends of a worker's
                     // successive ranges must grow, and claimed ranges start at comp_lo)
                     r_g0 = g_next < fe ? g_next : 0;
                     r_g1 = g_next < fe ? fe : 0;
-                    r_compete = last && competitive;
+                    r_compete = last && competitive && own_lo < g_stop;
                     found = true;
                 }
                 g_next = ge;

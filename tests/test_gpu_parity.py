@@ -259,6 +259,16 @@ def test_kernel_variants(H, oracle, rounds, threads):
                              num_workers=workers, slot_weight=3)
 
 
+@pytest.mark.parametrize("column_weight", [0, 1, 100, 2000, -1])
+@pytest.mark.parametrize("workers", [1, 5])
+def test_ranges_worth_entering_and_not(H, oracle, column_weight, workers):
+    """The library's own share: competitive groups that weigh at least twice the column weight are claimed (all of them, those
+    of some ranges), the others are run like the fixed part."""
+    check_against_oracle(H, oracle, _mixed_matrix(), check_add_sign=False, rows_per_block=1024, cols_per_block=2048,
+                         rounds_per_batch=4, num_workers=workers, slot_weight=1, group_weight=10, round_weight=1,
+                         column_weight=column_weight)
+
+
 def test_many_columns_competition(H, oracle):
     """More block columns than a wavefront has lanes (the scan for the fullest column loops), tiny
     tickets, more workers than groups."""
