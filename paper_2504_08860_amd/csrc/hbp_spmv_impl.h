@@ -180,6 +180,46 @@ __device__ __forceinline__ void consume_wide(const WideBatch<CH, T> &b, const T 
     }
 }
 
+// Buffer resources: wave-uniform base and length in scalar registers, a lane's offset in one vector register.  Lanes at or
+// behind the length read zero or store nothing, so that no load or store of a pack stands behind a branch and the
+// compiler's counts of what is in flight stay exact.
+typedef __amdgpu_buffer_rsrc_t Window;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Window window_of(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00027000);
+}
+constexpr int kNonTemporal = 2;
+__device__ __forceinline__ uint32_t rank_from(uint64_t mask, uint32_t first)  // first + number of set lanes below this one
+{
+    return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, first));
+}
+template <typename T>
+struct Columns;  // of a lane's 16 bytes of values
+template <>
+struct Columns<float> {
+    typedef u32x2 type;
+    static __device__ __forceinline__ type load(Window w, int lane) { return __builtin_amdgcn_raw_buffer_load_b64(w, lane * 8, 0, kNonTemporal); }
+    static __device__ __forceinline__ void unpack(type c, uint32_t (&out)[4])
+    {
+        out[0] = c.x & 0xffffu; out[1] = c.x >> 16; out[2] = c.y & 0xffffu; out[3] = c.y >> 16;
+    }
+};
+template <>
+struct Columns<double> {
+    typedef uint32_t type;
+    static __device__ __forceinline__ type load(Window w, int lane) { return __builtin_amdgcn_raw_buffer_load_b32(w, lane * 4, 0, kNonTemporal); }
+    static __device__ __forceinline__ void unpack(type c, uint32_t (&out)[2]) { out[0] = c & 0xffffu; out[1] = c >> 16; }
+};
+__device__ __forceinline__ void store_word(float v, Window w, int lane)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), w, lane * 4, 0, 0);
+}
+__device__ __forceinline__ void store_word(double v, Window w, int lane)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), w, lane * 8, 0, 0);
+}
+
 // An element on its way to the lane of its row.
 template <typename T>
 struct alignas(2 * sizeof(T)) Routed {
@@ -216,7 +256,7 @@ __device__ __forceinline__ void cut_rounds(const int32_t *lens, uint32_t target,
     cut_k = lo + 1;
 }
 
-template <int THREADS, int U, int GP, bool HEAVY, typename T>
+template <int THREADS, int U, int GP, bool HEAVY, bool STEPS, typename T>
 // (second launch bound: four wavefronts per SIMD, i.e. at most 128 vector registers per lane
 // whatever the workgroup size; with more, two 512-thread workers no longer fit a CU together)
 __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
@@ -232,8 +272,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_lock;  // end of the last range reported as used up
     __shared__ int32_t sh_col[3];  // whose competitive part is being claimed, its first group, its end
     // per wavefront: elements (value, x) on their way to the lanes of their rows, or 64 sums
-    constexpr int kRoute = sizeof(T) == 4 ? 192 : 96;
-    __shared__ Routed<T> sh_route[THREADS / 64 * kRoute + 1];
+    constexpr int kRoute = sizeof(T) == 4 ? 224 : 112;
+    // STEPS: groups are taken in steps instead of packs (see run_range)
+    constexpr int E = 16 / (int)sizeof(T), kWindow = 64 * E;  // elements of a step per lane and in all
+    constexpr int kChunk = 8, kDepth = 3;  // groups of a draw at most, steps in flight (two to five measured within 3 % of each other)
+    __shared__ __align__(16) Routed<T> sh_route[THREADS / 64 * kRoute + 1];
     constexpr int kHeavyCap = 64;
     __shared__ int32_t sh_heavy[kHeavyCap];  // heavy groups of the current range, each left to several wavefronts
     constexpr int kLongCap = 256;
@@ -241,6 +284,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     // the same for the groups the range begins with, as offsets from its first group: known before it is walked
     constexpr int kFirstHeavyCap = 64, kFirstLongCap = 1024;
     __shared__ uint16_t sh_first_heavy[kFirstHeavyCap], sh_first_long[kFirstLongCap];
+    __shared__ __align__(16) T sh_nowhere[16 / sizeof(T)];
     __shared__ int32_t sh_heavy_n[2], sh_long_n[2], sh_long_next[2];  // 0: known before, 1: found among the claimed groups
     static_assert(sizeof sh_route + sizeof sh_heavy + sizeof sh_long + sizeof sh_first_heavy + sizeof sh_first_long +
                       128 <= part_static_lds(THREADS), "part_static_lds is out of date");
@@ -308,13 +352,16 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     constexpr int32_t kNone = 0x7fffffff;
     constexpr int kSpinLimit = 1 << 16;
     bool stop = false;  // this wavefront draws no more in the current range
+    int32_t per_draw = GP;  // groups of the next draw
     // does group g + q of the pack (g, its end e) exist?
     auto in_pack = [&](int32_t g, int32_t e, int q) __attribute__((always_inline)) {
         return GP == 1 ? g != kNone : q < e - g;
     };
+    // In steps: fewer groups a draw towards the end of a range, so that the wavefronts are done with it together.
+    auto draw_of = [&](int32_t left) __attribute__((always_inline)) { return max(min(left / (2 * kWaves), kChunk), 2); };
     auto draw_issue = [&]() __attribute__((always_inline)) {
         unsigned long long old = 0;  // reads as a used-up range
-        if (lane == 0 && !stop) old = atomicAdd(&sh_rng, (unsigned long long)GP);
+        if (lane == 0 && !stop) old = atomicAdd(&sh_rng, (unsigned long long)per_draw);
         return old;
     };
     auto draw_resolve = [&](unsigned long long old, int32_t &pack_end) __attribute__((always_inline)) {
@@ -358,11 +405,12 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             }
             if (stop) continue;
             unsigned long long again = 0;
-            if (lane == 0) again = atomicAdd(&sh_rng, (unsigned long long)GP);
+            if (lane == 0) again = atomicAdd(&sh_rng, (unsigned long long)per_draw);
             v = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)again);
             end = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(again >> 32));
         }
-        pack_end = GP == 1 ? v + 1 : min(v + GP, end);
+        pack_end = GP == 1 ? v + 1 : min(v + per_draw, end);
+        if constexpr (STEPS) per_draw = draw_of(end - pack_end);
         return v;
     };
     // The rest of a group, rounds from k on, `count` <= kRoute elements from `base` on: the wavefront reads them
@@ -601,6 +649,203 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             }
             if (pass == 1) break;
         }
+        if constexpr (STEPS) {
+            // In steps.  A step is a run of up to E groups whose rows all have one nonzero, or one other group.  Its elements lie
+            // side by side, so every lane loads E of them with one 16-byte and one 2E-byte load; where they begin and end follows
+            // from group_ptr alone, so the loads of kDepth steps are in flight, whatever the rows' lengths.  In a run of rows
+            // of one nonzero the products are the sums: no lengths are read, and E sums per lane are stored together.
+            // Otherwise values and gathered x go through LDS, and every lane picks the elements of its row there round by round.
+            // Groups of more than kRoute elements are walked after the others of a turn, as in the packs.
+            // (Bound by HBM where segments are short: 340 MB at 5.4 TB/s on 2^20 rows of 32 from templates, a quarter of it stores; half of the groups there and of
+            // 4M x 1M lognormal rows have rows of one nonzero.  Products, packs / steps: 107.5 / 104.9 us and 281 / 274; R-MAT 2^22 267 / 264.)
+            int32_t e = 0, e1 = 0;  // ends of the chunks g and g1 of groups
+            per_draw = draw_of(g_end - g_begin);
+            int32_t g = draw_resolve(draw_issue(), e), g1 = draw_resolve(draw_issue(), e1);
+            // Lane l: first slot and first element of the chunk's group l; from the chunk's end on the ends of its last group.
+            // (Of no chunk: those of group 0, so that it is empty.)
+            uint32_t chunk_slot, chunk_pos, chunk_slot_n, chunk_pos_n;  // of the chunks g and g1
+            auto chunk_at = [&](int32_t first, int32_t end) __attribute__((always_inline)) {
+                return (uint32_t)((first == kNone ? 0 : first) + min(lane, first == kNone ? 0 : end - first));
+            };
+            // Bit i: a step begins with the chunk's group i; the highest bit: behind the last group.
+            uint32_t starts = 0;
+            auto open_chunk = [&]() __attribute__((always_inline)) {
+                const int32_t count = g == kNone ? 0 : e - g;
+                const uint32_t slots = (uint32_t)__shfl_down((int)chunk_slot, 1) - chunk_slot;
+                const uint32_t elements = (uint32_t)__shfl_down((int)chunk_pos, 1) - chunk_pos;
+                const uint32_t ones = (uint32_t)__ballot(lane < count && slots == elements);
+                uint32_t run = ones;  // bit i: groups i - E .. i are all of such rows
+#pragma unroll
+                for (int t = 1; t <= E; t++) run &= ones << t;
+                starts = ~(ones & ones << 1);
+#pragma unroll
+                for (int t = E; t < kChunk; t += E) starts |= starts << E & run;
+                starts = (starts & ((1u << count) - 1u)) | 1u << count;
+            };
+            u32x4 v[kDepth];
+            typename Columns<T>::type c[kDepth];
+            uint32_t len[kDepth];
+            int32_t at[kDepth], slot[kDepth];   // the step's first group and slot
+            uint32_t pos[kDepth], slots[kDepth], count[kDepth];  // its first element, its slots and elements
+            auto fetch = [&](int d) __attribute__((always_inline)) {
+                const int i = __builtin_ctz(starts);
+                const uint32_t rest = starts & (starts - 1u);
+                const int j = rest ? __builtin_ctz(rest) : i;  // (nothing left: an empty step)
+                starts = rest ? rest : starts;
+                at[d] = g + i;
+                slot[d] = (int32_t)__builtin_amdgcn_readlane(chunk_slot, i);
+                pos[d] = (uint32_t)__builtin_amdgcn_readlane(chunk_pos, i);
+                slots[d] = (uint32_t)__builtin_amdgcn_readlane(chunk_slot, j) - (uint32_t)slot[d];
+                count[d] = (uint32_t)__builtin_amdgcn_readlane(chunk_pos, j) - pos[d];
+                const uint32_t n = count[d] <= (uint32_t)kWindow ? count[d] : 0u;
+                v[d] = __builtin_amdgcn_raw_buffer_load_b128(window_of(data + pos[d], n * (uint32_t)sizeof(T)), lane * 16, 0, kNonTemporal);
+                c[d] = Columns<T>::load(window_of(L.col_local + pos[d], ((n + 3u) & ~3u) * 2u), lane);  // (whole words; the arrays are padded)
+                len[d] = __builtin_amdgcn_raw_buffer_load_b16(window_of(L.seg_len + slot[d], count[d] == slots[d] ? 0u : slots[d] * 2u), lane * 2, 0, 0);
+            };
+            uint32_t next_at = chunk_at(g, e);
+            chunk_slot = (uint32_t)L.group_slot[next_at];
+            chunk_pos = (uint32_t)L.group_ptr[next_at];
+            next_at = chunk_at(g1, e1);
+            chunk_slot_n = (uint32_t)L.group_slot[next_at];
+            chunk_pos_n = (uint32_t)L.group_ptr[next_at];
+            open_chunk();
+            if (bn != staged_bn && !HEAVY) copy_slice(bn);
+#pragma unroll
+            for (int d = 0; d < kDepth; d++) fetch(d);
+            if (bn != staged_bn) {
+                wait_slice();
+                __syncthreads();
+                staged_bn = bn;
+            }
+            // (nothing in flight on any way into the loop: the compiler does not see that the copy to LDS, which counts as a load and as
+            // an LDS access, has always been waited for, and would wait for everything throughout)
+            __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+            // the wavefront's elements on their way to the lanes of their rows: kRoute values, then their x; where a lane's E go
+            // (lanes whose elements never count write where nothing is read)
+            T *const way_v = reinterpret_cast<T *>(sh_route + wave * kRoute), *const way_x = way_v + kRoute;
+            const bool counts = lane < kRoute / E;
+            T *const write_v = counts ? way_v + E * lane : sh_nowhere, *const write_x = counts ? way_x + E * lane : sh_nowhere;
+            uint32_t long_step = 0;  // lanes 4 d .. 4 d + 3: first slot, slots, first element and elements of a group to be walked
+            for (;;) {
+                const bool used_up = (starts & (starts - 1u)) == 0;
+                if (used_up && g != kNone) {
+                    // the next chunk; its numbers were asked for when this one was begun
+                    chunk_slot = chunk_slot_n;
+                    chunk_pos = chunk_pos_n;
+                    g = g1;
+                    e = e1;
+                    g1 = draw_resolve(draw_issue(), e1);
+                    asm volatile("" : "+v"(chunk_slot), "+v"(chunk_pos));
+                    next_at = chunk_at(g1, e1);
+                    open_chunk();
+                }
+                // (in every turn, although they change with the chunk only: loaded in the branch they would be copied to where the
+                // other way leaves them, and waited for right there)
+                chunk_slot_n = (uint32_t)L.group_slot[next_at];
+                chunk_pos_n = (uint32_t)L.group_ptr[next_at];
+                const bool last = g == kNone;  // (a wavefront that has drawn nothing draws nothing more)
+                uint32_t walked = 0;  // bit d: the group of step d is too long for its window
+                int32_t rest[kDepth];
+#pragma unroll
+                for (int d = 0; d < kDepth; d++) {
+                    T vv[E];
+                    __builtin_memcpy(vv, &v[d], 16);
+                    uint32_t cc[E];
+                    Columns<T>::unpack(c[d], cc);
+                    rest[d] = (int32_t)len[d];
+                    asm volatile("" : "+v"(rest[d]));  // (the value from here on: a copy made elsewhere would wait for loads just issued)
+                    const Window out = window_of(partial + slot[d], slots[d] * (uint32_t)sizeof(T));
+                    if (count[d] == slots[d]) {
+                        // rows of one nonzero: the products are the sums
+                        T xv[E], sum[E];
+#pragma unroll
+                        for (int t = 0; t < E; t++) xv[t] = xs[cc[t]];
+#pragma unroll
+                        for (int t = 0; t < E; t++) sum[t] = fma_of(vv[t], xv[t], T(0));
+                        u32x4 bits;
+                        __builtin_memcpy(&bits, sum, 16);
+                        __builtin_amdgcn_raw_buffer_store_b128(bits, out, lane * 16, 0, 0);
+                    } else {
+                        int32_t n = rest[d];
+                        T acc = T(0);
+                        bool stored = count[d] <= (uint32_t)kRoute;
+                        if constexpr (HEAVY) {
+                            // (see below: what the lists hold looks empty here)
+                            if (__ballot(n > L.long_rounds)) {
+                                const bool heavy = __ballot(n > L.heavy_rounds) != 0;
+                                bool listed = heavy ? first_heavy : first_long;
+                                if (at[d] >= g_end || !L.lists_first) {
+                                    int32_t idx = 0;
+                                    if (lane == 0) idx = atomicAdd(heavy ? &sh_heavy_n[1] : &sh_long_n[1], 1);
+                                    idx = __builtin_amdgcn_readfirstlane(idx);
+                                    listed = idx < (heavy ? kHeavyCap : kLongCap);
+                                    if (listed && lane == 0) (heavy ? sh_heavy : sh_long)[idx] = at[d];
+                                }
+                                if (listed) {
+                                    n = 0;
+                                    rest[d] = 0;
+                                    stored = false;
+                                }
+                            }
+                        }
+                        if (count[d] > (uint32_t)kRoute) {
+                            walked |= 1u << d;
+                            const int l = lane - 4 * d;
+                            long_step = l == 0 ? (uint32_t)slot[d] : l == 1 ? slots[d] : l == 2 ? pos[d] : l == 3 ? count[d] : long_step;
+                        } else {
+                            T xv[E];
+#pragma unroll
+                            for (int t = 0; t < E; t++) xv[t] = xs[cc[t]];
+                            __builtin_memcpy(write_v, vv, 16);
+                            __builtin_memcpy(write_x, xv, 16);
+                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
+                            // round 0 has every row, so a lane's element there is the lane-th
+                            uint32_t off = slots[d];
+                            uint64_t live = __ballot(n > 1);
+                            const uint32_t i1 = rank_from(live, off);
+                            const T v0 = way_v[lane], x0 = way_x[lane], v1 = way_v[i1], x1 = way_x[i1];
+                            off += (uint32_t)__popcll(live);
+                            acc = fma_of(v0, x0, T(0));
+                            const T two = fma_of(v1, x1, acc);
+                            acc = n > 1 ? two : acc;
+                            for (int32_t k = 2; (live = __ballot(k < n)) != 0; k += 2) {
+                                const uint32_t ia = rank_from(live, off);
+                                off += (uint32_t)__popcll(live);
+                                live = __ballot(k + 1 < n);
+                                const uint32_t ib = rank_from(live, off);
+                                off += (uint32_t)__popcll(live);
+                                const T va = way_v[ia], xa = way_x[ia], vb = way_v[ib], xb = way_x[ib];
+                                const T ma = fma_of(va, xa, acc);
+                                acc = k < n ? ma : acc;
+                                const T mb = fma_of(vb, xb, acc);
+                                acc = k + 1 < n ? mb : acc;
+                            }
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
+                        }
+                        store_word(acc, window_of(partial + slot[d], stored ? slots[d] * (uint32_t)sizeof(T) : 0u), lane);
+                    }
+                    fetch(d);
+                }
+                asm volatile("" : "+v"(chunk_slot_n), "+v"(chunk_pos_n));  // (waited for here, in front of whatever the walks load)
+                for (; walked; walked &= walked - 1) {
+                    const int d = __builtin_ctz(walked);
+                    int32_t n = rest[0];
+#pragma unroll
+                    for (int t = 1; t < kDepth; t++) n = d == t ? rest[t] : n;
+                    const int32_t s0 = (int32_t)__builtin_amdgcn_readlane(long_step, 4 * d), rows = (int32_t)__builtin_amdgcn_readlane(long_step, 4 * d + 1);
+                    uint32_t base = (uint32_t)__builtin_amdgcn_readlane(long_step, 4 * d + 2);
+                    const uint32_t end = base + (uint32_t)__builtin_amdgcn_readlane(long_step, 4 * d + 3);
+                    T acc = T(0);
+                    if (__ballot(n != 0)) {  // (else it is on a list)
+                        walk_rounds(base, end, n, 0, acc);
+                        if (lane < rows) partial[s0 + lane] = acc;
+                    }
+                }
+                if (last) break;
+            }
+        } else {
         int32_t e = 0, e1 = 0, e2 = 0;  // ends of the packs g, g1, g2: group g + q exists if it is below e
         int32_t g = draw_resolve(draw_issue(), e), g1 = draw_resolve(draw_issue(), e1), g2 = kNone;
         unsigned long long raw2 = draw_issue();
@@ -820,6 +1065,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         for (int q = 0; q < GP; q++)
             if (done_slot[q] >= 0) partial[done_slot[q]] = done_acc[q];
 
+        }
         if constexpr (!HEAVY) break;
         __syncthreads();
         }
@@ -1360,15 +1606,15 @@ static int raise_lds_cap(std::atomic<uint64_t> &done, int device, K kernel, int 
     return HBP_OK;
 }
 
-template <int THREADS, int U, int GP, bool HEAVY, typename T>
+template <int THREADS, int U, int GP, bool HEAVY, bool STEPS, typename T>
 static int launch_part(const hbp_handle_s *h, const Layout &L, const T *x, T *y, hipStream_t st, SpmvScratch sc)
 {
     const size_t lds = (size_t)h->C * sizeof(T);
     static std::atomic<uint64_t> configured{0};  // per instantiation
-    const int rc = raise_lds_cap(configured, h->device, k_spmv_part<THREADS, U, GP, HEAVY, T>,
+    const int rc = raise_lds_cap(configured, h->device, k_spmv_part<THREADS, U, GP, HEAVY, STEPS, T>,
                                  kMaxC * (int)sizeof(float));  // 128 KB: kMaxC floats or kMaxC64 doubles
     if (rc != HBP_OK) return rc;
-    k_spmv_part<THREADS, U, GP, HEAVY, T><<<dim3((unsigned)h->P), THREADS, lds, st>>>(L, x, static_cast<T *>(sc.partial), y, sc.ticket);
+    k_spmv_part<THREADS, U, GP, HEAVY, STEPS, T><<<dim3((unsigned)h->P), THREADS, lds, st>>>(L, x, static_cast<T *>(sc.partial), y, sc.ticket);
     HBP_HIP(hipGetLastError());
     return HBP_OK;
 }
@@ -1380,12 +1626,17 @@ static int launch_part_u(const hbp_handle_s *h, const Layout &L, const T *x, T *
     // (256 and 512 threads with all eight or four: 64 to 196 registers spilled; 3M rows of 1 to 5 nonzeros over 7900 columns 96 against
     // 58 us, 1M lognormal rows in blocks of 7900 columns 472 against 155.)
     constexpr int kHalf = sizeof(T) == 8 ? 2 : 1;
+    // Short batches of fp32 values in steps, where a worker has many groups.  (With few, 71 a worker on lognormal 150001 x 400009, the packs' four
+    // groups at once start sooner: 36.0 us a product against 38.3.  fp64 windows hold half as many elements, so half of the
+    // groups would be walked on their own: lognormal 1.2M x 300K 128 against 139 us.)
+    if constexpr (sizeof(T) == 4)
+        if (h->unroll <= 4 && L.lists_first == 0) return launch_part<THREADS, 4, 4, HEAVY, true, T>(h, L, x, y, st, sc);
     switch (h->unroll) {  // rounds per batch; short batches walk several groups at once
-    case 2: return launch_part<THREADS, 2, 4 / kHalf, HEAVY, T>(h, L, x, y, st, sc);  // (eight: up to 45 registers spilled, 119 against 80 us)
-    case 4: return launch_part<THREADS, 4, 4 / kHalf, HEAVY, T>(h, L, x, y, st, sc);
-    case 9: return launch_part<THREADS, 9, 1, HEAVY, T>(h, L, x, y, st, sc);
-    case 16: return launch_part<THREADS, 16, 1, HEAVY, T>(h, L, x, y, st, sc);
-    default: return launch_part<THREADS, 8, 1, HEAVY, T>(h, L, x, y, st, sc);
+    case 2: return launch_part<THREADS, 2, 4 / kHalf, HEAVY, false, T>(h, L, x, y, st, sc);  // (eight: up to 45 registers spilled, 119 against 80 us)
+    case 4: return launch_part<THREADS, 4, 4 / kHalf, HEAVY, false, T>(h, L, x, y, st, sc);
+    case 9: return launch_part<THREADS, 9, 1, HEAVY, false, T>(h, L, x, y, st, sc);
+    case 16: return launch_part<THREADS, 16, 1, HEAVY, false, T>(h, L, x, y, st, sc);
+    default: return launch_part<THREADS, 8, 1, HEAVY, false, T>(h, L, x, y, st, sc);
     }
 }
 

@@ -269,6 +269,22 @@ def test_ranges_worth_entering_and_not(H, oracle, column_weight, workers):
                          column_weight=column_weight)
 
 
+@pytest.mark.parametrize("threads", [256, 512, 1024])
+@pytest.mark.parametrize("q8", [256, 100])
+def test_steps_of_short_rows(H, oracle, threads, q8):
+    """1024 groups per worker and more, fp32, short batches: runs of groups with rows of one nonzero (longer than a step and
+    than a draw, full and not), groups that just fit the wavefront's place in LDS (224 elements) and that just do not,
+    a long row among short ones.  64 rows per block, so that the rows of a group are known."""
+    rows = lambda *parts: np.concatenate([np.full(n, v) for n, v in parts])
+    one = rows((64, 1))
+    pattern = [one] * 13 + [rows((64, 3)), one, rows((32, 3), (32, 4)), one, one, rows((33, 4), (31, 3)), rows((31, 4), (33, 3)),
+                            rows((1, 161), (63, 1)), rows((1, 162), (63, 1)), rows((5, 1), (59, 0)), rows((17, 2), (47, 0)), one,
+                            rows((64, 8)), rows((63, 1), (1, 2)), rows((64, 2)), rows((1, 300), (63, 3))]
+    m = _matrix_of_lengths(np.concatenate((pattern * 40)[:1061] + [np.full(37, 1)]), 4000, seed=threads)
+    check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
+                         threads_per_worker=threads, num_workers=1, fixed_fraction_q8=q8)
+
+
 def test_many_columns_competition(H, oracle):
     """More block columns than a wavefront has lanes (the scan for the fullest column loops), tiny
     tickets, more workers than groups."""
