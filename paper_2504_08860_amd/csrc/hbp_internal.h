@@ -33,6 +33,12 @@ inline int32_t long_rounds_of(int32_t heavy_rounds, bool long_first)
     return rounds > 0 ? rounds : 1;
 }
 
+// A long group of more nonzeros than this is heavy, however they are spread over its rows: one wavefront takes 2.5 us for every 1024 of
+// them while the rest of its worker runs dry.  Shared by several wavefronts it costs the worker about 5 us, which fewer nonzeros
+// are worth where the worker has few groups.  Products, us, by rows alone / from 32768 nonzeros on / 16384 / 8192 / 4096: R-MAT 2^20
+// (241 groups a worker) 119 / 118 / 92 / 90 / 94, fp64 117 / 117 / 115 / 109 / 105, 2^22 (1785) 253 / 253 / 253 / 278 / 320.
+inline int32_t heavy_elements_of(bool long_first) { return long_first ? 8192 : 16384; }
+
 // Long is only what is longer than the others: a listed group is walked without the next one's loads on their way, which
 // costs more than the order brings where all groups are of about one length (`mean` rounds on average).  Up to three
 // times the mean, or 96 rounds, or a quarter more than the mean, is not; where the caller gives heavy_group_rounds, that alone
@@ -149,6 +155,7 @@ struct Layout {
     int32_t SW, RW, GW;  // schedule weights of a slot, a round, a group (a nonzero weighs 1)
     int32_t steal_min;   // weight a range's competitive part must have left for another worker to enter it
     int32_t heavy_rounds;  // a group with a longer row is walked by several wavefronts of a worker together
+    int32_t heavy_elements;  // and so is a long group of more nonzeros
     int32_t long_rounds;   // a group with a longer row (up to heavy_rounds) gets a wavefront of its own
     int32_t lists_first;   // and is walked, like the heavy ones, before the other groups of its range
     const uint16_t *row_local, *seg_len, *col_local;

@@ -574,7 +574,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             for (int32_t i = g_begin + (int32_t)threadIdx.x; i < g_end; i += THREADS) {
                 const int32_t longest = L.group_rounds[i + 1] - L.group_rounds[i];
                 if (longest > L.long_rounds) {
-                    const bool heavy = longest > L.heavy_rounds;
+                    const bool heavy = longest > L.heavy_rounds || L.group_ptr[i + 1] - L.group_ptr[i] > L.heavy_elements;
                     const int32_t idx = atomicAdd(heavy ? &sh_heavy_n[0] : &sh_long_n[0], 1);
                     if (idx < (heavy ? kFirstHeavyCap : kFirstLongCap)) (heavy ? sh_first_heavy : sh_first_long)[idx] = (uint16_t)(i - g_begin);
                 }
@@ -772,7 +772,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                         if constexpr (HEAVY) {
                             // (see below: what the lists hold looks empty here)
                             if (__ballot(n > L.long_rounds)) {
-                                const bool heavy = __ballot(n > L.heavy_rounds) != 0;
+                                const bool heavy = __ballot(n > L.heavy_rounds) != 0 || count[d] > (uint32_t)L.heavy_elements;
                                 bool listed = heavy ? first_heavy : first_long;
                                 if (at[d] >= g_end || !L.lists_first) {
                                     int32_t idx = 0;
@@ -928,7 +928,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
 #pragma unroll
                 for (int q = 0; q < GP; q++) {
                     if (__ballot(n[q] > L.long_rounds)) {
-                        const bool heavy = __ballot(n[q] > L.heavy_rounds) != 0;
+                        const bool heavy = __ballot(n[q] > L.heavy_rounds) != 0 || meta_base(meta, g, e, q + 1) - base[q] > (uint32_t)L.heavy_elements;
                         bool listed = heavy ? first_heavy : first_long;
                         if (g + q >= g_end || !L.lists_first) {
                             int32_t idx = 0;

@@ -269,6 +269,21 @@ def test_ranges_worth_entering_and_not(H, oracle, column_weight, workers):
                          column_weight=column_weight)
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("rows,lens", [
+    (2000, [127, 128, 129, 130, 200]),       # lists first: heavy from 8192 nonzeros on
+    (67000, [255, 256, 257, 258, 300]),      # 1024 groups and more, lists last: from 16384 on
+])
+def test_groups_heavy_by_their_nonzeros(H, oracle, rows, lens, f64):
+    """Groups of 64 rows of up to heavy_group_rounds nonzeros, just under, at and over the line."""
+    from workloads import widen_to_f64
+    m = _matrix_of_lengths(np.concatenate([np.repeat(lens, 64), np.full(rows, 2)]), 4000, seed=rows)
+    if f64:
+        m = widen_to_f64(m)
+    check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
+                         num_workers=1, fixed_fraction_q8=256, heavy_group_rounds=1024)
+
+
 @pytest.mark.parametrize("threads", [256, 512, 1024])
 @pytest.mark.parametrize("q8", [256, 100])
 def test_steps_of_short_rows(H, oracle, threads, q8):
