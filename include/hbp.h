@@ -126,7 +126,9 @@ typedef struct {
     int32_t group_width;       /* W, 1..64 lanes per group; 0 = default 64 (one wavefront)      */
     int32_t num_workers;       /* P, persistent workgroups the schedule is built for, up to 65536; 0 = as many as
                                   fit on the device at once, but no more than one per threads_per_worker / 64 groups */
-    int32_t fixed_fraction_q8; /* share of every worker's range that is pre-assigned, in 1/256; -1 = default 240 */
+    int32_t fixed_fraction_q8; /* share of every worker's range that is pre-assigned, in 1/256; -1 = default 240, and
+                                  competitive groups that weigh less than twice column_weight, for which no other
+                                  worker enters the range, are run by its own without competition */
     int32_t hash_shift;        /* a, 0..12; -1 = sample it from the matrix (Section 3.2)        */
     int32_t claim_chunk;       /* competitive part: groups per wavefront that a worker claims from a
                                   block column at a time, 1..1024; 0 = default (a few draws per wavefront) */
@@ -146,8 +148,9 @@ typedef struct {
     int32_t round_weight;      /* schedule weight of one round of a group (its rounds = the length of
                                   its longest row), in nonzeros: 0..1024; -1 = default 100 (10)      */
     int32_t heavy_group_rounds;/* a group with a row of more nonzeros than this (inside the block) is walked
-                                  by all wavefronts of its worker together, each taking an equal share of
-                                  its nonzeros, instead of by one: >= 1; 0 = default 2048.  A group with a row of
+                                  by several wavefronts of its worker together, each taking an equal share of
+                                  its nonzeros, instead of by one: >= 1; 0 = default 2048 (a long group, see below, of
+                                  more than 16384 nonzeros, 8192 where these go first, is, too).  A group with a row of
                                   more than a 64th of this (an eighth, up to 32 nonzeros, if that is more) is walked by
                                   a wavefront of its own, like the heavy ones before the worker's other groups; with
                                   1024 groups per worker and more: with a row of more than an eighth, after them.  With the default, rows that are not much
