@@ -236,7 +236,8 @@ int hbp_build(const int32_t *csr_ptr, const int32_t *csr_col, const float *csr_v
  * same stream serialise by themselves; calls on different streams must be ordered by the
  * caller (they share the partial-sum buffer and the ticket counter).  The call allocates
  * nothing and launches two kernels (one where there is no combine part), no memset or copy: after one ordinary call on the device
- * (which configures the kernels) it may be recorded into a HIP graph by stream capture. */
+ * (which configures the kernels) it may be recorded into a HIP graph by stream capture.  An error that an earlier HIP call of
+ * the thread has left (hipGetLastError) is returned as HBP_ERR_HIP before anything is launched. */
 int hbp_spmv(hbp_handle_t h, const float *x, float *y, void *stream);
 
 /* The fp64 variant (Section 3.1 counts 8 bytes per stored value): hbp_build_f64 is hbp_build

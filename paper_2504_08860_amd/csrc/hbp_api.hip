@@ -172,15 +172,41 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     return HBP_OK;
 }
 
+// The claim counters are zero between products: the combine part zeroes those that the SpMV part in front of it has counted
+// with.  So no SpMV part is left without what follows it.  An error that an earlier call of this thread has left behind is
+// reported before anything is launched (behind the SpMV part's launch it would pass for that launch's own), and where the
+// combine part cannot be launched the counters are cleared in its place.
+static int pending_error()
+{
+    HBP_HIP(hipGetLastError());
+    return HBP_OK;
+}
+
+static int combine_or_clear(hbp_handle_t h, void *y, hipStream_t st, hbp::SpmvScratch scratch)
+{
+    const int rc = hbp::launch_combine(h, y, st, scratch);
+    if (rc != HBP_OK && h->flat_wpg == 0) {
+        k_clear_u32<<<dim3((unsigned)((h->P + 255) / 256)), 256, 0, st>>>(scratch.ticket, h->P);
+        HBP_HIP(hipGetLastError());
+    }
+    return rc;
+}
+
+static int product(hbp_handle_t h, const void *x, void *y, hipStream_t st, hbp::SpmvScratch scratch)
+{
+    int rc = pending_error();
+    if (rc != HBP_OK) return rc;
+    rc = hbp::launch_spmv_part(h, x, y, st, scratch);
+    if (rc != HBP_OK) return rc;
+    return combine_or_clear(h, y, st, scratch);
+}
+
 static int spmv_any(int32_t value_bytes, hbp_handle_t h, const void *x, void *y, void *stream)
 {
     if (!h || !x || !y || h->value_bytes != value_bytes) return HBP_ERR_INVALID_ARGUMENT;
     DeviceGuard guard(h->device);
     if (!guard.ok) return HBP_ERR_HIP;
-    const hbp::SpmvScratch own{h->partial, h->ticket};
-    int rc = hbp::launch_spmv_part(h, x, y, (hipStream_t)stream, own);
-    if (rc != HBP_OK) return rc;
-    return hbp::launch_combine(h, y, (hipStream_t)stream, own);
+    return product(h, x, y, (hipStream_t)stream, hbp::SpmvScratch{h->partial, h->ticket});
 }
 
 static int spmv_timed_any(int32_t value_bytes, hbp_handle_t h, const void *x, void *y, void *stream, int iters, float *ms_part,
@@ -195,16 +221,17 @@ static int spmv_timed_any(int32_t value_bytes, hbp_handle_t h, const void *x, vo
     // every HIP call goes through `check`, so that the events are destroyed on every way out
     hipError_t err = hipSuccess;
     auto check = [&](hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; return err == hipSuccess; };
-    int rc = HBP_OK;
+    int rc = pending_error();
+    if (rc != HBP_OK) return rc;
     const hbp::SpmvScratch own{h->partial, h->ticket};
     for (auto &e : ev)
         if (!check(hipEventCreate(&e))) break;
     for (int i = 0; i < iters && rc == HBP_OK && err == hipSuccess; i++) {
         if (!check(hipEventRecord(ev[0], st))) break;
         rc = hbp::launch_spmv_part(h, x, y, st, own);
-        if (!check(hipEventRecord(ev[1], st))) break;
-        if (rc == HBP_OK) rc = hbp::launch_combine(h, y, st, own);
-        if (!check(hipEventRecord(ev[2], st))) break;
+        const bool recorded = check(hipEventRecord(ev[1], st));
+        if (rc == HBP_OK) rc = combine_or_clear(h, y, st, own);
+        if (!recorded || !check(hipEventRecord(ev[2], st))) break;
         if (!check(hipEventSynchronize(ev[2])) || rc != HBP_OK) break;
         float a = 0, b = 0, c = 0;
         if (!check(hipEventElapsedTime(&a, ev[0], ev[1])) || !check(hipEventElapsedTime(&b, ev[1], ev[2])) ||
@@ -372,14 +399,9 @@ int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stre
     int rc = static_scratch_address(h->device, &base);
     if (rc != HBP_OK) return rc;
     const hbp::SpmvScratch fixed{static_cast<unsigned char *>(base) + kStaticTicketBytes, static_cast<uint32_t *>(base)};
-    // The counters are zero here: the array begins as zeros, and the combine part of every call zeroes those that its SpMV part
-    // has counted with, like a handle's own.  (A kernel in front that clears them: 27-point grid of 67^3 28.0 against 26.4 us a product.)
-    rc = hbp::launch_spmv_part(h, x, y, (hipStream_t)stream, fixed);
-    if (rc != HBP_OK) return rc;
-    rc = hbp::launch_combine(h, y, (hipStream_t)stream, fixed);
-    if (rc != HBP_OK && h->flat_wpg == 0)  // nothing will have zeroed them
-        k_clear_u32<<<dim3((unsigned)((h->P + 255) / 256)), 256, 0, (hipStream_t)stream>>>(fixed.ticket, h->P);
-    return rc;
+    // The counters are zero here: the array begins as zeros, and every call leaves them so (see product), like a handle's
+    // own.  (A kernel in front that clears them: 27-point grid of 67^3 28.0 against 26.4 us a product.)
+    return product(h, x, y, (hipStream_t)stream, fixed);
 }
 
 int hbp_spmv_timed(hbp_handle_t h, const float *x, float *y, void *stream, int iters, float *ms_part, float *ms_combine,

@@ -82,3 +82,41 @@ def test_static_scratch_limits():
         assert L.hbp_spmv_static_scratch(None, None, None, None) == -1
     finally:
         H.hbp_free(h)
+
+
+@pytest.mark.parametrize("entry", ["hbp_spmv", "hbp_spmv_static_scratch", "hbp_spmv_f64", "hbp_spmv_timed"])
+def test_error_left_by_an_earlier_call(entry):
+    """A HIP error that an earlier call of the thread has left is returned before anything is launched: an SpMV part without its
+    combine part would leave counted claims behind, and the next call would take their groups for done."""
+    import torch
+    import paper_2504_08860_amd as H
+    from workloads import widen_to_f64
+    L = H.lib()
+    m = make_config(5, 0.02)
+    if entry == "hbp_spmv_f64":
+        m = widen_to_f64(m)
+    ptr, col, val, x = _dev(m)
+    build = H.hbp_build_f64 if entry == "hbp_spmv_f64" else H.hbp_build
+    h = build(ptr, col, val, m.n_rows, m.n_cols, rows_per_block=512, cols_per_block=2048, fixed_fraction_q8=0, num_workers=48)
+    try:
+        assert H.hbp_get_info(h).split_row_blocks == 0      # every sum has one order
+        y_ref, y = (torch.full((m.n_rows,), float("nan"), device="cuda", dtype=x.dtype) for _ in range(2))
+        other = 2 * x   # (a part that ran all the same would leave this one's partial sums)
+
+        def call(x):
+            args = [ctypes.c_void_p(h), ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()),
+                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)]
+            if entry == "hbp_spmv_timed":
+                args += [ctypes.c_int(1), None, None, None]
+            return getattr(L, entry)(*args)
+        (H.hbp_spmv_f64 if entry == "hbp_spmv_f64" else H.hbp_spmv)(h, x, y_ref)
+        torch.cuda.synchronize()
+        assert L.hipSetDevice(ctypes.c_int(1 << 20)) != 0   # refused, and remembered
+        assert call(other) == -6 and "HIP" in H.hbp_status_string(-6)
+        torch.cuda.synchronize()
+        assert torch.isnan(y).all()
+        assert call(x) == 0                                 # reported once
+        torch.cuda.synchronize()
+        assert torch.equal(y, y_ref)
+    finally:
+        H.hbp_free(h)
