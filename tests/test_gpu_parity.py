@@ -360,6 +360,33 @@ def test_heavy_groups_walked_side_by_side(H, oracle, groups, threads, f64):
                              threads_per_worker=threads, num_workers=1, fixed_fraction_q8=q8, heavy_group_rounds=64)
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("threads", [256, 1024])
+def test_heavy_groups_have_one_order_whoever_claims_them(H, threads, f64):
+    """Every group competitive: how many heavy ones a worker claims depends on the number of workers and on timing, a group's sum
+    does not."""
+    import torch
+    from workloads import widen_to_f64
+    m = _matrix_of_lengths(np.concatenate([np.arange(64 * 40) % 190 + 65, np.full(3000, 3)]), 4000, seed=40)
+    if f64:
+        m = widen_to_f64(m)
+    ptr, col, val, x = to_dev(m)
+    build, spmv = (H.hbp_build_f64, H.hbp_spmv_f64) if f64 else (H.hbp_build, H.hbp_spmv)
+    first = None
+    for workers in (1, 40, 5):
+        h = build(ptr, col, val, m.n_rows, m.n_cols, rows_per_block=1024, cols_per_block=4096, rounds_per_batch=4, claim_chunk=1,
+                  threads_per_worker=threads, num_workers=workers, fixed_fraction_q8=0, heavy_group_rounds=64)
+        try:
+            assert H.hbp_get_info(h).split_row_blocks == 0
+            for rep in range(10):
+                y = torch.full((m.n_rows,), float("nan"), device="cuda", dtype=x.dtype)
+                spmv(h, x, y)
+                first = y if first is None else first
+                assert torch.equal(y, first), (workers, rep)
+        finally:
+            H.hbp_free(h)
+
+
 @pytest.mark.parametrize("seed", range(int(os.environ.get("HBP_RANDOM_CASES", "24"))))  # more seeds for a soak run
 def test_random_parameters(H, oracle, seed):
     """Seeded random draws over matrix shape and every build parameter (block sizes, group
