@@ -272,7 +272,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_lock;  // end of the last range reported as used up
     __shared__ int32_t sh_col[3];  // whose competitive part is being claimed, its first group, its end
     // per wavefront: elements (value, x) on their way to the lanes of their rows, or 64 sums
-    constexpr int kRoute = sizeof(T) == 4 ? 224 : 112;
+    // (Of packs 192, fp64 96; 224 and 112 for them: R-MAT 2^20 90.1 / 90.2 us a product, fp64 109.8 / 110.1, lognormal 1.2M x 300K 84.3 / 84.7, fp64 124.)
+    constexpr int kRoute = STEPS ? 224 : sizeof(T) == 4 ? 192 : 96;
     // STEPS: groups are taken in steps instead of packs (see run_range)
     constexpr int E = 16 / (int)sizeof(T), kWindow = 64 * E;  // elements of a step per lane and in all
     constexpr int kChunk = 8, kDepth = 3;  // groups of a draw at most, steps in flight (two to five measured within 3 % of each other)
