@@ -33,11 +33,23 @@ inline int32_t long_rounds_of(int32_t heavy_rounds, bool long_first)
     return rounds > 0 ? rounds : 1;
 }
 
-// A long group of more nonzeros than this is heavy, however they are spread over its rows: one wavefront takes 2.5 us for every 1024 of
-// them while the rest of its worker runs dry.  Shared by several wavefronts it costs the worker about 5 us, which fewer nonzeros
-// are worth where the worker has few groups.  Products, us, by rows alone / from 32768 nonzeros on / 16384 / 8192 / 4096: R-MAT 2^20
-// (241 groups a worker) 119 / 118 / 92 / 90 / 94, fp64 117 / 117 / 115 / 109 / 105, 2^22 (1785) 253 / 253 / 253 / 278 / 320.
-inline int32_t heavy_elements_of(bool long_first) { return long_first ? 8192 : 16384; }
+// Where the long groups go first, one of more nonzeros than this is heavy, however they are spread over its rows, if it outweighs the
+// other groups of its range: one wavefront takes 2.5 us for every 1024 of them while the rest of its worker runs dry.  Shared by several
+// wavefronts it costs the worker about 5 us, which fewer nonzeros are not worth.  Products, us, by rows alone / from 32768
+// nonzeros on / 16384 / 8192 / 4096: R-MAT 2^20 119 / 118 / 92 / 90 / 94, fp64 117 / 117 / 115 / 109 / 105.  (Where they go last, with 1024 groups
+// per worker and more, it gains nothing: 2^22 253 / 253 / 253 / 278 / 320.)
+constexpr int32_t kHeavyElements = 8192;
+
+// Does it?  Where the other wavefronts have as much to do, nobody waits for the one that walks it, and sharing it costs more.
+// Fewer than half as many groups as wavefronts can have more than twice a wavefront's share of the range's nonzeros.
+// Products, us, by rows alone / shared without this / from one wavefront's share on / two / four: rows of 150 and of 20 nonzeros in equal
+// parts, 300K 38.5 / 57.9 / 58.1 / 43.0 / 38.6, 1M 98 / 126 / 98 / 98 / 98, fp64 160 / 178 / 161 / 161 / 162; R-MAT, five of each, 2^19 81 / 62 / 62 / 64 /
+// 75, 2^20 116 / 91 / 91 / 94 / 115, fp64 115 / 112 / 112 / 104 / 115, 2^21 134 / 139 / 133 / 133 / 134.
+constexpr int kMaxOutweighing = 8;
+__host__ __device__ inline bool outweighs(uint32_t elements, uint32_t range_elements, int wavefronts)
+{
+    return (uint64_t)elements * (uint32_t)wavefronts > 2 * (uint64_t)range_elements;
+}
 
 // Long is only what is longer than the others: a listed group is walked without the next one's loads on their way, which
 // costs more than the order brings where all groups are of about one length (`mean` rounds on average).  Up to three
@@ -155,7 +167,7 @@ struct Layout {
     int32_t SW, RW, GW;  // schedule weights of a slot, a round, a group (a nonzero weighs 1)
     int32_t steal_min;   // weight a range's competitive part must have left for another worker to enter it
     int32_t heavy_rounds;  // a group with a longer row is walked by several wavefronts of a worker together
-    int32_t heavy_elements;  // and so is a long group of more nonzeros
+    int32_t heavy_elements;  // and so is, where lists_first, a long group of more nonzeros that outweighs the others of its range
     int32_t long_rounds;   // a group with a longer row (up to heavy_rounds) gets a wavefront of its own
     int32_t lists_first;   // and is walked, like the heavy ones, before the other groups of its range
     const uint16_t *row_local, *seg_len, *col_local;

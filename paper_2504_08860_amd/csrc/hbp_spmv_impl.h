@@ -272,7 +272,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_lock;  // end of the last range reported as used up
     __shared__ int32_t sh_col[3];  // whose competitive part is being claimed, its first group, its end
     // per wavefront: elements (value, x) on their way to the lanes of their rows, or 64 sums
-    // (Of packs 192, fp64 96; 224 and 112 for them: R-MAT 2^20 90.1 / 90.2 us a product, fp64 109.8 / 110.1, lognormal 1.2M x 300K 84.3 / 84.7, fp64 124.)
+    // (With 224 and 112 for the packs, too, R-MAT 2^20 takes 90.2 us a product against 90.1, fp64 110.1 against 109.8.)
     constexpr int kRoute = STEPS ? 224 : sizeof(T) == 4 ? 192 : 96;
     // STEPS: groups are taken in steps instead of packs (see run_range)
     constexpr int E = 16 / (int)sizeof(T), kWindow = 64 * E;  // elements of a step per lane and in all
@@ -284,9 +284,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_long[kLongCap];  // long groups of the current range, each left to the next free wavefront
     // the same for the groups the range begins with, as offsets from its first group: known before it is walked
     constexpr int kFirstHeavyCap = 64, kFirstLongCap = 1024;
-    __shared__ uint16_t sh_first_heavy[kFirstHeavyCap], sh_first_long[kFirstLongCap];
+    static_assert(THREADS / 64 <= 2 * kMaxOutweighing, "more groups could outweigh the others than have a place");
+    __shared__ uint16_t sh_first_heavy[kFirstHeavyCap + kMaxOutweighing], sh_first_long[kFirstLongCap];  // (the last heavy places: those that outweigh the others)
     __shared__ __align__(16) T sh_nowhere[16 / sizeof(T)];
     __shared__ int32_t sh_heavy_n[2], sh_long_n[2], sh_long_next[2];  // 0: known before, 1: found among the claimed groups
+    __shared__ int32_t sh_outweighing_n;
     static_assert(sizeof sh_route + sizeof sh_heavy + sizeof sh_long + sizeof sh_first_heavy + sizeof sh_first_long +
                       128 <= part_static_lds(THREADS), "part_static_lds is out of date");
     constexpr int kWaves = THREADS / 64;
@@ -561,6 +563,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             sh_dry = compete ? 0 : 1;
             sh_lock = -1;
             sh_heavy_n[0] = sh_heavy_n[1] = 0;
+            sh_outweighing_n = 0;
             sh_long_n[0] = sh_long_n[1] = 0;
             sh_long_next[0] = sh_long_next[1] = 0;
             sh_col[0] = owner;  // whose competitive groups are claimed from here on
@@ -572,19 +575,28 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         bool first_heavy = false, first_long = false;  // are the range's own heavy and long groups on the lists?
         if (HEAVY && bn != staged_bn) copy_slice(bn);
         if (HEAVY && L.lists_first) {
+            const uint32_t in_range = (uint32_t)uniform_load(L.group_ptr, g_end) - (uint32_t)uniform_load(L.group_ptr, g_begin);
             for (int32_t i = g_begin + (int32_t)threadIdx.x; i < g_end; i += THREADS) {
                 const int32_t longest = L.group_rounds[i + 1] - L.group_rounds[i];
                 if (longest > L.long_rounds) {
-                    const bool heavy = longest > L.heavy_rounds || L.group_ptr[i + 1] - L.group_ptr[i] > L.heavy_elements;
-                    const int32_t idx = atomicAdd(heavy ? &sh_heavy_n[0] : &sh_long_n[0], 1);
-                    if (idx < (heavy ? kFirstHeavyCap : kFirstLongCap)) (heavy ? sh_first_heavy : sh_first_long)[idx] = (uint16_t)(i - g_begin);
+                    const uint16_t offset = (uint16_t)(i - g_begin);
+                    const int32_t in_group = L.group_ptr[i + 1] - L.group_ptr[i];
+                    if (longest > L.heavy_rounds) {
+                        const int32_t idx = atomicAdd(&sh_heavy_n[0], 1);
+                        if (idx < kFirstHeavyCap) sh_first_heavy[idx] = offset;
+                    } else if (in_group > L.heavy_elements && outweighs((uint32_t)in_group, in_range, kWaves)) {
+                        sh_first_heavy[kFirstHeavyCap + atomicAdd(&sh_outweighing_n, 1)] = offset;
+                    } else {
+                        const int32_t idx = atomicAdd(&sh_long_n[0], 1);
+                        if (idx < kFirstLongCap) sh_first_long[idx] = offset;
+                    }
                 }
             }
             wait_slice();
             __syncthreads();
             staged_bn = bn;
             first_heavy = sh_heavy_n[0] <= kFirstHeavyCap && g_end - g_begin <= 65536;
-            first_long = sh_long_n[0] <= kFirstLongCap && g_end - g_begin <= 65536;
+            first_long = sh_long_n[0] <= kFirstLongCap && g_end - g_begin <= 65536;  // (those that outweigh the others with them)
         }
         // (HEAVY: the listed groups, the others, what the claims brought)
         for (int pass = 0;; pass++) {
@@ -595,7 +607,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             // (Bound by memory round trips, a few for the group's numbers and one for every 1024 nonzeros of a wavefront.  All wavefronts on
             // one group after the other: 15 us a group, however few nonzeros were left to each; R-MAT 2^22 has nine such groups in the
             // first worker's range, which took 247 us where the average worker took 160.  Product 296 -> 267 us.)
-            const int32_t n_heavy = pass ? min(sh_heavy_n[1], kHeavyCap) : first_heavy ? sh_heavy_n[0] : 0;
+            const int32_t n_by_row = pass ? min(sh_heavy_n[1], kHeavyCap) : first_heavy ? sh_heavy_n[0] : 0;
+            const int32_t n_heavy = n_by_row + (!pass && first_long ? sh_outweighing_n : 0);
             // Where the range competes, how many of them a worker has claimed differs from call to call, and a group's sum must not:
             // there a group has kWaves parts whatever runs beside it, `parts` successive ones to a wavefront, and the sums meet in fours.
             const bool same_cut = pass && compete;
@@ -606,7 +619,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 T *const sums = reinterpret_cast<T *>(sh_route + wave * kRoute);  // the wavefront's place: lengths, what the walk holds there, its sums
                 int32_t hs0 = 0, hs1 = 0;
                 if (i < n_heavy) {
-                    const int32_t gh = __builtin_amdgcn_readfirstlane(pass ? sh_heavy[i] : g_begin + (int32_t)sh_first_heavy[i]);
+                    const int32_t gh = __builtin_amdgcn_readfirstlane(
+                        pass ? sh_heavy[i] : g_begin + (int32_t)sh_first_heavy[i < n_by_row ? i : kFirstHeavyCap + i - n_by_row]);
                     hs0 = uniform_load(L.group_slot, gh);
                     hs1 = uniform_load(L.group_slot, gh + 1);
                     const uint32_t b0 = (uint32_t)uniform_load(L.group_ptr, gh);
@@ -785,7 +799,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                         if constexpr (HEAVY) {
                             // (see below: what the lists hold looks empty here)
                             if (__ballot(n > L.long_rounds)) {
-                                const bool heavy = __ballot(n > L.heavy_rounds) != 0 || count[d] > (uint32_t)L.heavy_elements;
+                                const bool heavy = __ballot(n > L.heavy_rounds) != 0;
                                 bool listed = heavy ? first_heavy : first_long;
                                 if (at[d] >= g_end || !L.lists_first) {
                                     int32_t idx = 0;
@@ -941,7 +955,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
 #pragma unroll
                 for (int q = 0; q < GP; q++) {
                     if (__ballot(n[q] > L.long_rounds)) {
-                        const bool heavy = __ballot(n[q] > L.heavy_rounds) != 0 || meta_base(meta, g, e, q + 1) - base[q] > (uint32_t)L.heavy_elements;
+                        const bool heavy = __ballot(n[q] > L.heavy_rounds) != 0;
                         bool listed = heavy ? first_heavy : first_long;
                         if (g + q >= g_end || !L.lists_first) {
                             int32_t idx = 0;

@@ -270,18 +270,37 @@ def test_ranges_worth_entering_and_not(H, oracle, column_weight, workers):
 
 
 @pytest.mark.parametrize("f64", [False, True])
-@pytest.mark.parametrize("rows,lens", [
-    (2000, [127, 128, 129, 130, 200]),       # lists first: heavy from 8192 nonzeros on
-    (67000, [255, 256, 257, 258, 300]),      # 1024 groups and more, lists last: from 16384 on
+@pytest.mark.parametrize("blocks,lens", [
+    (30, [127, 128, 129, 130, 200]),       # lists first: heavy from 8192 nonzeros on
+    (1100, [255, 256, 257, 258, 300]),     # 1024 groups and more, lists last: never
 ])
-def test_groups_heavy_by_their_nonzeros(H, oracle, rows, lens, f64):
-    """Groups of 64 rows of up to heavy_group_rounds nonzeros, just under, at and over the line."""
+def test_groups_heavy_by_their_nonzeros(H, oracle, blocks, lens, f64):
+    """Groups of 64 rows of up to heavy_group_rounds nonzeros, just under, at and over the line, among blocks of one nonzero: each
+    has more than an eighth of the range's nonzeros."""
     from workloads import widen_to_f64
-    m = _matrix_of_lengths(np.concatenate([np.repeat(lens, 64), np.full(rows, 2)]), 4000, seed=rows)
+    m = _matrix_of_lengths(np.concatenate([np.repeat(lens, 64), np.tile([1] + [0] * 63, blocks)]), 4000, seed=blocks)
     if f64:
         m = widen_to_f64(m)
     check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
-                         num_workers=1, fixed_fraction_q8=256, heavy_group_rounds=1024)
+                         num_workers=1, threads_per_worker=1024, fixed_fraction_q8=256, heavy_group_rounds=1024)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("blocks", [5, 1100])                      # lists first and last
+@pytest.mark.parametrize("big", [0, 63, 64, 65, 71])
+def test_heavy_groups_of_both_kinds(H, oracle, big, blocks, f64):
+    """Groups with a row of more than 2048 nonzeros, up to more than their list holds, and three that are heavy because they
+    outweigh the others; no such group among a hundred of them."""
+    from workloads import widen_to_f64
+    rows = lambda n, length: np.r_[np.full(n, length), np.zeros(64 - n, int)]
+    others = [rows(1, 2100)] * big if big else [rows(64, 150)] * 100
+    lens = np.concatenate([rows(64, 500)] * 3 + others + [rows(1, 1)] * blocks)
+    m = _matrix_of_lengths(lens, 4000, seed=big)
+    if f64:
+        m = widen_to_f64(m)
+    for q8 in (256, 128):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
+                             num_workers=1, threads_per_worker=1024, fixed_fraction_q8=q8)
 
 
 @pytest.mark.parametrize("threads", [256, 512, 1024])

@@ -1,0 +1,43 @@
+"""Which way the workers' kernel walks a group: the rules of hbp_internal.h against matrices for which both ways were timed on an
+MI355X."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _ask(tmp_path, lines):
+    """What the C++ expressions give, one number each."""
+    src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
+    src.write_text("\n".join(['#include <cstdio>', '#include "hbp_internal.h"', 'int main() {'] +
+                             [f'  std::printf("%lld\\n", (long long)({x}));' for x in lines] + ['  return 0; }']))
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2504_08860_amd", "csrc"), str(src), "-o", str(exe)])
+    return [int(v) for v in subprocess.check_output([str(exe)]).decode().split()]
+
+
+# (nonzeros of a long group, of the range it is in, wavefronts of the worker, whether sharing it was faster)
+OUTWEIGHING = [
+    ("rows of 150 and 20 in equal parts, 300K", 9600, 100_000, 16, False),
+    ("rows of 150 and 20 in equal parts, 1M", 9600, 332_000, 16, False),
+    ("rows of 150 and 20, 1 to 9, 3M", 9600, 386_000, 16, False),
+    ("rows of 500, 150 and 20, 1 to 20 to 300, 1M", 9600, 116_000, 16, False),
+    ("R-MAT 2^20, rows of 1000", 64_000, 65_500, 16, True),
+    ("R-MAT 2^20", 20_000, 65_500, 16, True),
+]
+
+
+def test_groups_that_outweigh_the_others(tmp_path):
+    got = _ask(tmp_path, [f"hbp::outweighs({e}u, {r}u, {w})" for _, e, r, w, _ in OUTWEIGHING])
+    for (name, *_, shared), g in zip(OUTWEIGHING, got, strict=True):
+        assert bool(g) == shared, name
+
+
+def test_outweighing_groups_have_their_places(tmp_path):
+    """As many as can be of a range, and the largest counts."""
+    for wavefronts in (4, 8, 16):
+        most = wavefronts // 2 - 1
+        assert _ask(tmp_path, [f"hbp::outweighs({e}u, {r}u, {wavefronts}) && {most} <= hbp::kMaxOutweighing"
+                               for e, r in ((1000, 1000 * most), (2**31 // (most + 1), 2**31 - 1))][:1] +
+                              [f"hbp::outweighs(1000u, 1000u * {most + 1}u, {wavefronts})"]) == [1, 0]
+    assert _ask(tmp_path, ["hbp::outweighs(2147483647u, 2147483647u, 16)", "hbp::outweighs(268435455u, 2147483647u, 16)"]) == [1, 0]
