@@ -149,9 +149,9 @@ typedef struct {
                                   its longest row), in nonzeros: 0..1024; -1 = default 100 (10)      */
     int32_t heavy_group_rounds;/* a group with a row of more nonzeros than this (inside the block) is walked
                                   by several wavefronts of its worker together, each taking an equal share of
-                                  its nonzeros, instead of by one: >= 1; 0 = default 2048 (where long groups, see below, go
-                                  first, one of more than 8192 nonzeros and more than twice a wavefront's share of its
-                                  worker's range in a block column is, too).  A group with a row of
+                                  its nonzeros, instead of by one: >= 1; 0 = default 2048 (with the default, and
+                                  where long groups, see below, go first, one of more than 8192 nonzeros and more than twice a
+                                  wavefront's share of its worker's range in a block column is, too).  A group with a row of
                                   more than a 64th of this (an eighth, up to 32 nonzeros, if that is more) is walked by
                                   a wavefront of its own, like the heavy ones before the worker's other groups; with
                                   1024 groups per worker and more: with a row of more than an eighth, after them.  With the default, rows that are not much

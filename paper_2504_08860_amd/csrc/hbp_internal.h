@@ -38,7 +38,7 @@ inline int32_t long_rounds_of(int32_t heavy_rounds, bool long_first)
 // wavefronts it costs the worker about 5 us, which fewer nonzeros are not worth.  Products, us, by rows alone / from 32768
 // nonzeros on / 16384 / 8192 / 4096: R-MAT 2^20 119 / 118 / 92 / 90 / 94, fp64 117 / 117 / 115 / 109 / 105.  (Where they go last, with 1024 groups
 // per worker and more, it gains nothing: 2^22 253 / 253 / 253 / 278 / 320.)
-constexpr int32_t kHeavyElements = 8192;
+inline int32_t heavy_elements_of(bool heavy_chosen) { return heavy_chosen ? 8192 : 0x7fffffff; }  // (a given heavy_group_rounds alone counts)
 
 // Does it?  Where the other wavefronts have as much to do, nobody waits for the one that walks it, and sharing it costs more.
 // Fewer than half as many groups as wavefronts can have more than twice a wavefront's share of the range's nonzeros.

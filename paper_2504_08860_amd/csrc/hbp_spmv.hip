@@ -44,7 +44,7 @@ Layout hbp_view(const hbp_handle_s *h)
     L.steal_min = steal_weight(h->column_weight);
     L.heavy_rounds = h->heavy_rounds;
     L.lists_first = walk_long_first(h->G, h->P) ? 1 : 0;
-    L.heavy_elements = kHeavyElements;
+    L.heavy_elements = heavy_elements_of(h->heavy_chosen);
     L.long_rounds = long_rounds_of(h->heavy_rounds, L.lists_first);
     if (h->heavy_chosen && h->G > 0) L.long_rounds = std::min(h->heavy_rounds, std::max(L.long_rounds, long_rounds_beside(h->nnz / (h->G * h->W))));
     return L;

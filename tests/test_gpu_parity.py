@@ -275,14 +275,38 @@ def test_ranges_worth_entering_and_not(H, oracle, column_weight, workers):
     (1100, [255, 256, 257, 258, 300]),     # 1024 groups and more, lists last: never
 ])
 def test_groups_heavy_by_their_nonzeros(H, oracle, blocks, lens, f64):
-    """Groups of 64 rows of up to heavy_group_rounds nonzeros, just under, at and over the line, among blocks of one nonzero: each
-    has more than an eighth of the range's nonzeros."""
+    """Groups of 64 rows of up to 300 nonzeros, just under, at and over the line, among blocks of one nonzero: each has more than an
+    eighth of the range's nonzeros."""
     from workloads import widen_to_f64
     m = _matrix_of_lengths(np.concatenate([np.repeat(lens, 64), np.tile([1] + [0] * 63, blocks)]), 4000, seed=blocks)
     if f64:
         m = widen_to_f64(m)
     check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
-                         num_workers=1, threads_per_worker=1024, fixed_fraction_q8=256, heavy_group_rounds=1024)
+                         num_workers=1, threads_per_worker=1024, fixed_fraction_q8=256)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_given_heavy_group_rounds_decide_alone(H, f64):
+    """A group that would be shared for its nonzeros is not where the caller's heavy_group_rounds are more than its rows have: its
+    sums have the order that they have where no group is listed at all."""
+    import torch
+    from workloads import widen_to_f64
+    m = _matrix_of_lengths(np.r_[np.full(32, 1600), np.full(32, 1601), np.full(640, 3)], 4000, seed=4)
+    if f64:
+        m = widen_to_f64(m)
+    ptr, col, val, x = to_dev(m)
+    build, spmv = (H.hbp_build_f64, H.hbp_spmv_f64) if f64 else (H.hbp_build, H.hbp_spmv)
+    ys = {}
+    for heavy in (0, 100000, 2**30):
+        h = build(ptr, col, val, m.n_rows, m.n_cols, rows_per_block=64, cols_per_block=4096, rounds_per_batch=16, num_workers=1,
+                  threads_per_worker=1024, fixed_fraction_q8=256, heavy_group_rounds=heavy)
+        try:
+            ys[heavy] = torch.empty(m.n_rows, device="cuda", dtype=x.dtype)
+            spmv(h, x, ys[heavy])
+            torch.cuda.synchronize()
+        finally:
+            H.hbp_free(h)
+    assert torch.equal(ys[100000], ys[2**30]) and not torch.equal(ys[0], ys[2**30])
 
 
 @pytest.mark.parametrize("f64", [False, True])
