@@ -145,6 +145,20 @@ inline int combine_wavefronts(int64_t cus, int64_t units, int64_t R, int32_t val
     return units > cus * combine_units_by_lds(copy, 4) && units <= cus * (by_lds < by_waves ? by_lds : by_waves) ? 3 : 4;
 }
 
+// Short batches of fp32 values are walked in steps where a worker has many groups and the average one fits a wavefront's place in LDS:
+// a group that does not is walked with nothing of its own in flight.  Products, us, packs / steps: 20M rows along the
+// diagonal of 1 nonzero and, one in 11, 20 (175 elements a group) 224 / 209, of 1 and 10, three to one (208) 239 / 233, of 1 and
+// 4 (160) 196 / 192, two to one (128) 186 / 177, of 1 to 5 (192) 226 / 230, of 2 (128) 154 / 159, of 3 (192) 169 / 176, of 4 (256) 191 / 199,
+// of 5 (320) 237 / 252; 5-point grid of 4300^2 (253) 276 / 274; 2^20 rows from templates (98) 98.7 / 96.5; lognormal 4M x 1M (126) 275 / 260,
+// x 400K (203) 249 / 244, 5M x 200K (318) 287 / 289; R-MAT 2^22 (143) 254 / 252.
+// (With few groups, 71 a worker on lognormal 150001 x 400009, the packs' four groups at once start sooner: 36.0 against 38.3.  fp64 windows
+// hold half as many elements, so half of the groups would be walked on their own: lognormal 1.2M x 300K 128 against 139.)
+constexpr int kStepElements = 224;
+inline bool walk_in_steps(int32_t rounds_per_batch, bool long_first, int64_t nnz, int64_t G)
+{
+    return rounds_per_batch <= 4 && !long_first && nnz <= kStepElements * G;
+}
+
 // Weight that another worker's range must have left for a worker to enter it: what entering a block column costs (the fetch of
 // its slice of x), twice, counting the restart of the pipeline.
 __host__ __device__ inline int32_t steal_weight(int32_t column_weight) { return 2 * column_weight; }

@@ -273,7 +273,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     __shared__ int32_t sh_col[3];  // whose competitive part is being claimed, its first group, its end
     // per wavefront: elements (value, x) on their way to the lanes of their rows, or 64 sums
     // (With 224 and 112 for the packs, too, R-MAT 2^20 takes 90.2 us a product against 90.1, fp64 110.1 against 109.8.)
-    constexpr int kRoute = STEPS ? 224 : sizeof(T) == 4 ? 192 : 96;
+    constexpr int kRoute = STEPS ? kStepElements : sizeof(T) == 4 ? 192 : 96;
     // STEPS: groups are taken in steps instead of packs (see run_range)
     constexpr int E = 16 / (int)sizeof(T), kWindow = 64 * E;  // elements of a step per lane and in all
     constexpr int kChunk = 8, kDepth = 3;  // groups of a draw at most, steps in flight (two to five measured within 3 % of each other)
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             // from group_ptr alone, so the loads of kDepth steps are in flight, whatever the rows' lengths.  In a run of rows
             // of one nonzero the products are the sums: no lengths are read, and E sums per lane are stored together.
             // Otherwise values and gathered x go through LDS, and every lane picks the elements of its row there round by round.
-            // Groups of more than kRoute elements are walked after the others of a turn, as in the packs.
+            // What does not fit there is walked after the others of a turn, as in the packs, with nothing of its own in flight.
             // (Bound by HBM where segments are short: 340 MB at 5.4 TB/s on 2^20 rows of 32 from templates, a quarter of it stores; half of the groups there and of
             // 4M x 1M lognormal rows have rows of one nonzero.  Products, packs / steps: 107.5 / 104.9 us and 281 / 274; R-MAT 2^22 267 / 264.)
             int32_t e = 0, e1 = 0;  // ends of the chunks g and g1 of groups
@@ -714,6 +714,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             uint32_t len[kDepth];
             int32_t at[kDepth], slot[kDepth];   // the step's first group and slot
             uint32_t pos[kDepth], slots[kDepth], count[kDepth];  // its first element, its slots and elements
+            // Does a step's group fit the wavefront's place in LDS: all of it, or what is left once its first two rounds are done?
+            // (Asked about in `fetch`, too, it costs bands of 2 nonzeros per row 4 %: groups of so few rows are loaded and then walked.)
+            auto fits = [&](uint32_t elements, uint32_t rows) __attribute__((always_inline)) {
+                return elements <= (uint32_t)kRoute || (elements <= (uint32_t)kWindow && rows >= (uint32_t)(kWindow - kRoute) + E);
+            };
             auto fetch = [&](int d) __attribute__((always_inline)) {
                 const int i = __builtin_ctz(starts);
                 const uint32_t rest = starts & (starts - 1u);
@@ -795,7 +800,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                     } else {
                         int32_t n = rest[d];
                         T acc = T(0);
-                        bool stored = count[d] <= (uint32_t)kRoute;
+                        const bool walk = !fits(count[d], slots[d]);
+                        bool stored = !walk;
                         if constexpr (HEAVY) {
                             // (see below: what the lists hold looks empty here)
                             if (__ballot(n > L.long_rounds)) {
@@ -815,7 +821,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                                 }
                             }
                         }
-                        if (count[d] > (uint32_t)kRoute) {
+                        if (walk) {
                             walked |= 1u << d;
                             const int l = lane - 4 * d;
                             long_step = l == 0 ? (uint32_t)slot[d] : l == 1 ? slots[d] : l == 2 ? pos[d] : l == 3 ? count[d] : long_step;
@@ -837,6 +843,18 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                             const T two = fma_of(v1, x1, acc);
                             acc = n > 1 ? two : acc;
                             for (int32_t k = 2; (live = __ballot(k < n)) != 0; k += 2) {
+                                if (k == 2 && count[d] > (uint32_t)kRoute) {
+                                    // the elements of these rounds take the place of the first two rounds'
+                                    const uint32_t done = off & ~(uint32_t)(E - 1), place = (uint32_t)(E * lane) - done;
+                                    off -= done;
+                                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                                    __builtin_amdgcn_wave_barrier();
+                                    const bool left = place < (uint32_t)kRoute;  // (in front of `done`: wrapped around)
+                                    __builtin_memcpy(left ? way_v + place : sh_nowhere, vv, 16);
+                                    __builtin_memcpy(left ? way_x + place : sh_nowhere, xv, 16);
+                                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                                    __builtin_amdgcn_wave_barrier();
+                                }
                                 const uint32_t ia = rank_from(live, off);
                                 off += (uint32_t)__popcll(live);
                                 live = __ballot(k + 1 < n);
@@ -1653,11 +1671,8 @@ static int launch_part_u(const hbp_handle_s *h, const Layout &L, const T *x, T *
     // (256 and 512 threads with all eight or four: 64 to 196 registers spilled; 3M rows of 1 to 5 nonzeros over 7900 columns 96 against
     // 58 us, 1M lognormal rows in blocks of 7900 columns 472 against 155.)
     constexpr int kHalf = sizeof(T) == 8 ? 2 : 1;
-    // Short batches of fp32 values in steps, where a worker has many groups.  (With few, 71 a worker on lognormal 150001 x 400009, the packs' four
-    // groups at once start sooner: 36.0 us a product against 38.3.  fp64 windows hold half as many elements, so half of the
-    // groups would be walked on their own: lognormal 1.2M x 300K 128 against 139 us.)
     if constexpr (sizeof(T) == 4)
-        if (h->unroll <= 4 && L.lists_first == 0) return launch_part<THREADS, 4, 4, HEAVY, true, T>(h, L, x, y, st, sc);
+        if (walk_in_steps(h->unroll, L.lists_first, h->nnz, h->G)) return launch_part<THREADS, 4, 4, HEAVY, true, T>(h, L, x, y, st, sc);
     switch (h->unroll) {  // rounds per batch; short batches walk several groups at once
     case 2: return launch_part<THREADS, 2, 4 / kHalf, HEAVY, false, T>(h, L, x, y, st, sc);  // (eight: up to 45 registers spilled, 119 against 80 us)
     case 4: return launch_part<THREADS, 4, 4 / kHalf, HEAVY, false, T>(h, L, x, y, st, sc);

@@ -343,6 +343,21 @@ def test_steps_of_short_rows(H, oracle, threads, q8):
                          threads_per_worker=threads, num_workers=1, fixed_fraction_q8=q8)
 
 
+@pytest.mark.parametrize("threads", [256, 1024])
+@pytest.mark.parametrize("heavy", [0, 16])
+def test_steps_of_groups_that_nearly_fit(H, oracle, threads, heavy):
+    """224 elements are a wavefront's place in LDS, 256 a step's loads; between them the first two rounds make room for the
+    others, in groups of 36 rows and more.  Beside short groups, so that the average one fits."""
+    rows = lambda *parts: np.concatenate([np.full(n, v) for n, v in parts] + [np.zeros(64 - sum(n for n, _ in parts), int)])
+    nearly = [rows((64, 4)), rows((63, 4), (1, 3)), rows((33, 4), (31, 3)), rows((32, 4), (32, 3)), rows((1, 193), (63, 1)), rows((1, 162), (63, 1)),
+              rows((64, 2), ), rows((36, 7)), rows((36, 7), (1, 4)), rows((4, 8), (32, 7)), rows((35, 7)), rows((34, 7), (1, 18)), rows((37, 6), (1, 34)),
+              rows((1, 256)), rows((2, 128)), rows((40, 6), (1, 17)), rows((51, 5), (1, 1)), rows((51, 5), (1, 2)), rows((1, 221), (35, 1)),
+              rows((1, 222), (34, 1)), rows((1, 220), (36, 1)), rows((64, 3), (0, 0)), rows((32, 7), (32, 1)), rows((33, 7), (25, 1))]
+    m = _matrix_of_lengths(np.concatenate([g for group in nearly for g in (group, rows((64, 1)), rows((3, 2)))] * 15), 4000, seed=threads)
+    check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
+                         threads_per_worker=threads, num_workers=1, fixed_fraction_q8=200, heavy_group_rounds=heavy)
+
+
 def test_many_columns_competition(H, oracle):
     """More block columns than a wavefront has lanes (the scan for the fullest column loops), tiny
     tickets, more workers than groups."""
