@@ -134,7 +134,8 @@ typedef struct {
                                   block column at a time, 1..1024; 0 = default (a few draws per wavefront) */
     int32_t threads_per_worker;/* workgroup size of the SpMV-part kernel: 256, 512, 1024; 0 = default */
     int32_t rounds_per_batch;  /* rounds a wavefront loads per group before accumulating: 2, 4, 8, 9, 16
-                                  (2 and 4 walk 4 groups at once; fp64: 2);
+                                  (2 and 4 walk 4 groups at once; fp64: 2; fp32 with 1024 groups per worker and more, of up
+                                  to 224 nonzeros on average: both the same, up to 256 elements at once);
                                   0 = chosen with R: 8 for long row segments, 4 for short ones        */
     int32_t slot_weight;       /* schedule weight of a slot, in nonzeros: 0..64; -1 = default 20 (2 when the groups
                                   average 512 nonzeros or more: see group_weight)                      */

@@ -147,7 +147,7 @@ static int build_any(int32_t value_bytes, const int32_t *csr_ptr, const int32_t 
     h->NBR = (n_rows + h->R - 1) / h->R;
     h->NBC = (n_cols + h->C - 1) / h->C;
     h->claim_chunk = p.claim_chunk;
-    if (h->claim_chunk == 0)  // a few draws per wavefront; a draw is 4 groups (fp64: 2) for 2 or 4 rounds per batch, else 1
+    if (h->claim_chunk == 0)  // a few draws per wavefront; a draw is 4 groups (fp64: 2; in steps up to 8) for 2 or 4 rounds per batch, else 1
         h->claim_chunk = p.rounds_per_batch == 2 ? 16 : p.rounds_per_batch == 4 ? 8 : 2;
     int rc = HBP_OK;
     if (h->NBR * h->NBC > hbp::kMaxDense) rc = HBP_ERR_TOO_LARGE;

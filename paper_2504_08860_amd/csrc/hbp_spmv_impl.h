@@ -194,30 +194,11 @@ __device__ __forceinline__ uint32_t rank_from(uint64_t mask, uint32_t first)  //
 {
     return (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, first));
 }
-template <typename T>
-struct Columns;  // of a lane's 16 bytes of values
-template <>
-struct Columns<float> {
-    typedef u32x2 type;
-    static __device__ __forceinline__ type load(Window w, int lane) { return __builtin_amdgcn_raw_buffer_load_b64(w, lane * 8, 0, kNonTemporal); }
-    static __device__ __forceinline__ void unpack(type c, uint32_t (&out)[4])
-    {
-        out[0] = c.x & 0xffffu; out[1] = c.x >> 16; out[2] = c.y & 0xffffu; out[3] = c.y >> 16;
-    }
-};
-template <>
-struct Columns<double> {
-    typedef uint32_t type;
-    static __device__ __forceinline__ type load(Window w, int lane) { return __builtin_amdgcn_raw_buffer_load_b32(w, lane * 4, 0, kNonTemporal); }
-    static __device__ __forceinline__ void unpack(type c, uint32_t (&out)[2]) { out[0] = c & 0xffffu; out[1] = c >> 16; }
-};
-__device__ __forceinline__ void store_word(float v, Window w, int lane)
+// block-local columns of a lane's 16 bytes of fp32 values
+__device__ __forceinline__ u32x2 load_columns(Window w, int lane) { return __builtin_amdgcn_raw_buffer_load_b64(w, lane * 8, 0, kNonTemporal); }
+__device__ __forceinline__ void unpack_columns(u32x2 c, uint32_t (&out)[4])
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), w, lane * 4, 0, 0);
-}
-__device__ __forceinline__ void store_word(double v, Window w, int lane)
-{
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), w, lane * 8, 0, 0);
+    out[0] = c.x & 0xffffu; out[1] = c.x >> 16; out[2] = c.y & 0xffffu; out[3] = c.y >> 16;
 }
 
 // An element on its way to the lane of its row.
@@ -274,8 +255,9 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
     // per wavefront: elements (value, x) on their way to the lanes of their rows, or 64 sums
     // (With 224 and 112 for the packs, too, R-MAT 2^20 takes 90.2 us a product against 90.1, fp64 110.1 against 109.8.)
     constexpr int kRoute = STEPS ? kStepElements : sizeof(T) == 4 ? 192 : 96;
-    // STEPS: groups are taken in steps instead of packs (see run_range)
-    constexpr int E = 16 / (int)sizeof(T), kWindow = 64 * E;  // elements of a step per lane and in all
+    // STEPS: fp32 groups are taken in steps instead of packs, where lists come last (see run_range)
+    static_assert(!STEPS || sizeof(T) == 4, "a step's loads are of fp32 values");
+    constexpr int E = 4, kWindow = 64 * E;  // elements of a step per lane and in all
     constexpr int kChunk = 8, kDepth = 3;  // groups of a draw at most, steps in flight (two to five measured within 3 % of each other)
     __shared__ __align__(16) Routed<T> sh_route[THREADS / 64 * kRoute + 1];
     constexpr int kHeavyCap = 64;
@@ -574,7 +556,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
         __syncthreads();
         bool first_heavy = false, first_long = false;  // are the range's own heavy and long groups on the lists?
         if (HEAVY && bn != staged_bn) copy_slice(bn);
-        if (HEAVY && L.lists_first) {
+        if (HEAVY && !STEPS && L.lists_first) {
             const uint32_t in_range = (uint32_t)uniform_load(L.group_ptr, g_end) - (uint32_t)uniform_load(L.group_ptr, g_begin);
             for (int32_t i = g_begin + (int32_t)threadIdx.x; i < g_end; i += THREADS) {
                 const int32_t longest = L.group_rounds[i + 1] - L.group_rounds[i];
@@ -710,7 +692,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 starts = (starts & ((1u << count) - 1u)) | 1u << count;
             };
             u32x4 v[kDepth];
-            typename Columns<T>::type c[kDepth];
+            u32x2 c[kDepth];
             uint32_t len[kDepth];
             int32_t at[kDepth], slot[kDepth];   // the step's first group and slot
             uint32_t pos[kDepth], slots[kDepth], count[kDepth];  // its first element, its slots and elements
@@ -731,7 +713,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                 count[d] = (uint32_t)__builtin_amdgcn_readlane(chunk_pos, j) - pos[d];
                 const uint32_t n = count[d] <= (uint32_t)kWindow ? count[d] : 0u;
                 v[d] = __builtin_amdgcn_raw_buffer_load_b128(window_of(data + pos[d], n * (uint32_t)sizeof(T)), lane * 16, 0, kNonTemporal);
-                c[d] = Columns<T>::load(window_of(L.col_local + pos[d], ((n + 3u) & ~3u) * 2u), lane);  // (whole words; the arrays are padded)
+                c[d] = load_columns(window_of(L.col_local + pos[d], ((n + 3u) & ~3u) * 2u), lane);  // (whole words; the arrays are padded)
                 len[d] = __builtin_amdgcn_raw_buffer_load_b16(window_of(L.seg_len + slot[d], count[d] == slots[d] ? 0u : slots[d] * 2u), lane * 2, 0, 0);
             };
             uint32_t next_at = chunk_at(g, e);
@@ -783,7 +765,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                     T vv[E];
                     __builtin_memcpy(vv, &v[d], 16);
                     uint32_t cc[E];
-                    Columns<T>::unpack(c[d], cc);
+                    unpack_columns(c[d], cc);
                     rest[d] = (int32_t)len[d];
                     asm volatile("" : "+v"(rest[d]));  // (the value from here on: a copy made elsewhere would wait for loads just issued)
                     const Window out = window_of(partial + slot[d], slots[d] * (uint32_t)sizeof(T));
@@ -806,15 +788,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                             // (see below: what the lists hold looks empty here)
                             if (__ballot(n > L.long_rounds)) {
                                 const bool heavy = __ballot(n > L.heavy_rounds) != 0;
-                                bool listed = heavy ? first_heavy : first_long;
-                                if (at[d] >= g_end || !L.lists_first) {
-                                    int32_t idx = 0;
-                                    if (lane == 0) idx = atomicAdd(heavy ? &sh_heavy_n[1] : &sh_long_n[1], 1);
-                                    idx = __builtin_amdgcn_readfirstlane(idx);
-                                    listed = idx < (heavy ? kHeavyCap : kLongCap);
-                                    if (listed && lane == 0) (heavy ? sh_heavy : sh_long)[idx] = at[d];
-                                }
-                                if (listed) {
+                                int32_t idx = 0;
+                                if (lane == 0) idx = atomicAdd(heavy ? &sh_heavy_n[1] : &sh_long_n[1], 1);
+                                idx = __builtin_amdgcn_readfirstlane(idx);
+                                if (idx < (heavy ? kHeavyCap : kLongCap)) {
+                                    if (lane == 0) (heavy ? sh_heavy : sh_long)[idx] = at[d];
                                     n = 0;
                                     rest[d] = 0;
                                     stored = false;
@@ -869,7 +847,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                             __builtin_amdgcn_wave_barrier();
                         }
-                        store_word(acc, window_of(partial + slot[d], stored ? slots[d] * (uint32_t)sizeof(T) : 0u), lane);
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, acc), window_of(partial + slot[d], stored ? slots[d] * 4u : 0u), lane * 4, 0, 0);
                     }
                     fetch(d);
                 }
