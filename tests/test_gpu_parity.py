@@ -250,8 +250,8 @@ def _mixed_matrix(seed=5):
 @pytest.mark.parametrize("rounds", [2, 4, 8, 9, 16])
 @pytest.mark.parametrize("threads", [256, 512, 1024])
 def test_kernel_variants(H, oracle, rounds, threads):
-    """Every instantiation of the SpMV-part kernel (rounds per batch x workgroup size), on a
-    matrix that reaches all three walking modes, with and without a competitive part."""
+    """Every instantiation of the SpMV-part kernel (rounds per batch x workgroup size) for workers of few groups, on a
+    matrix that reaches all three walking modes, with and without a competitive part.  (Of many: test_steps_*.)"""
     m = _mixed_matrix()
     for q8, workers in ((256, 7), (160, 5)):
         check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=1024, cols_per_block=8192,
@@ -259,14 +259,22 @@ def test_kernel_variants(H, oracle, rounds, threads):
                              num_workers=workers, slot_weight=3)
 
 
-@pytest.mark.parametrize("column_weight", [0, 1, 100, 2000, -1])
+@pytest.mark.parametrize("column_weight,ranges_open", [(0, 4), (1, 4), (100, 4), (450, 2), (2000, 0), (-1, 0)])
 @pytest.mark.parametrize("workers", [1, 5])
-def test_ranges_worth_entering_and_not(H, oracle, column_weight, workers):
-    """The library's own share: competitive groups that weigh at least twice the column weight are claimed (all of them, those
-    of some ranges), the others are run like the fixed part."""
-    check_against_oracle(H, oracle, _mixed_matrix(), check_add_sign=False, rows_per_block=1024, cols_per_block=2048,
-                         rounds_per_batch=4, num_workers=workers, slot_weight=1, group_weight=10, round_weight=1,
-                         column_weight=column_weight)
+def test_ranges_worth_entering_and_not(H, oracle, column_weight, ranges_open, workers):
+    """The library's own share: competitive groups that weigh at least twice the column weight are claimed (those of all ranges that
+    have any, of some, of none), the others are run like the fixed part."""
+    m = _mixed_matrix()
+    info = check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=1024, cols_per_block=2048,
+                                rounds_per_batch=4, num_workers=workers, slot_weight=1, group_weight=10, round_weight=1,
+                                column_weight=column_weight)
+    o = oracle.OracleHbp(m.ptr, m.col, m.val, m.n_rows, m.n_cols, R=1024, C=2048, W=64, num_workers=workers, fixed_q8=info.fixed_fraction_q8,
+                         slot_weight=1, round_weight=1, group_weight=10, column_weight=info.column_weight)
+    before = o.array("group_ptr").astype(np.int64) + o.array("group_slot") + o.array("group_rounds") + 10 * np.arange(o.G + 1)
+    lo, end = o.array("comp_lo"), o.array("fixed_start")[1:]
+    is_open = (lo < end) & (before[end] - before[np.minimum(lo, end)] >= 2 * info.column_weight)
+    assert is_open.sum() == (ranges_open if workers == 5 else column_weight >= 0)
+    o.close()
 
 
 @pytest.mark.parametrize("f64", [False, True])
@@ -350,9 +358,9 @@ def test_steps_of_groups_that_nearly_fit(H, oracle, threads, heavy):
     others, in groups of 36 rows and more.  Beside short groups, so that the average one fits."""
     rows = lambda *parts: np.concatenate([np.full(n, v) for n, v in parts] + [np.zeros(64 - sum(n for n, _ in parts), int)])
     nearly = [rows((64, 4)), rows((63, 4), (1, 3)), rows((33, 4), (31, 3)), rows((32, 4), (32, 3)), rows((1, 193), (63, 1)), rows((1, 162), (63, 1)),
-              rows((64, 2), ), rows((36, 7)), rows((36, 7), (1, 4)), rows((4, 8), (32, 7)), rows((35, 7)), rows((34, 7), (1, 18)), rows((37, 6), (1, 34)),
+              rows((64, 2)), rows((36, 7)), rows((36, 7), (1, 4)), rows((4, 8), (32, 7)), rows((35, 7)), rows((34, 7), (1, 18)), rows((37, 6), (1, 34)),
               rows((1, 256)), rows((2, 128)), rows((40, 6), (1, 17)), rows((51, 5), (1, 1)), rows((51, 5), (1, 2)), rows((1, 221), (35, 1)),
-              rows((1, 222), (34, 1)), rows((1, 220), (36, 1)), rows((64, 3), (0, 0)), rows((32, 7), (32, 1)), rows((33, 7), (25, 1))]
+              rows((1, 222), (34, 1)), rows((1, 220), (36, 1)), rows((64, 3)), rows((32, 7), (32, 1)), rows((33, 7), (25, 1))]
     m = _matrix_of_lengths(np.concatenate([g for group in nearly for g in (group, rows((64, 1)), rows((3, 2)))] * 15), 4000, seed=threads)
     check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
                          threads_per_worker=threads, num_workers=1, fixed_fraction_q8=200, heavy_group_rounds=heavy)
@@ -802,7 +810,7 @@ def test_small_matrices_without_workers(H, oracle, lens, n_cols, R, C, W, f64):
 @pytest.mark.parametrize("rounds,threads", [(2, 256), (4, 512), (8, 1024), (9, 256), (16, 512)])
 def test_infinities_and_nan_stay_in_their_rows(H, rounds, threads, heavy, f64):
     """An infinity or NaN in x reaches the rows that hold its column and no other, through every walk of the
-    workers' kernel (a small matrix without workers: test_small_matrices_without_workers)."""
+    workers' kernel but the steps (next test; a small matrix without workers: test_small_matrices_without_workers)."""
     import torch
     from workloads import widen_to_f64
     m = _mixed_matrix(seed=19)
@@ -829,6 +837,35 @@ def test_infinities_and_nan_stay_in_their_rows(H, rounds, threads, heavy, f64):
                 assert np.array_equal(np.flatnonzero(~np.isfinite(y.cpu().numpy())), hit), (C, bad)
         finally:
             H.hbp_free(h)
+
+
+@pytest.mark.parametrize("threads", [256, 1024])
+@pytest.mark.parametrize("heavy", [0, 64])    # without and with lists
+def test_infinities_and_nan_stay_in_their_rows_in_steps(H, threads, heavy):
+    """1024 groups per worker and more, fp32, short batches: groups that fit a wavefront's place in LDS, that nearly do and that do
+    not, runs of rows of one nonzero, and blocks with few rows, whose steps have lanes without a row."""
+    import torch
+    rows = lambda *parts: np.concatenate([np.full(n, v) for n, v in parts] + [np.zeros(64 - sum(n for n, _ in parts), int)])
+    pattern = [rows((64, 1)), rows((64, 1)), rows((64, 3)), rows((64, 1)), rows((3, 2)), rows((64, 4)), rows((5, 1)), rows((63, 1), (1, 70)),
+               rows((17, 2)), rows((36, 7)), rows((1, 1)), rows((32, 9)), rows((40, 1), (1, 2))]
+    m = _matrix_of_lengths(np.concatenate(pattern * 90), 4000, seed=threads)
+    ptr, cols, val, x = to_dev(m)
+    of_row = np.repeat(np.arange(m.n_rows), np.diff(m.ptr))
+    rare = np.argsort(np.bincount(m.col, minlength=m.n_cols), kind="stable")[:3]
+    h = H.hbp_build(ptr, cols, val, m.n_rows, m.n_cols, rows_per_block=64, cols_per_block=4096, rounds_per_batch=4,
+                    threads_per_worker=threads, num_workers=1, heavy_group_rounds=heavy)
+    try:
+        assert H.hbp_get_info(h).groups >= 1024
+        for bad in ({int(rare[0]): float("inf")}, {int(rare[1]): float("nan"), int(rare[2]): float("-inf")}, {0: float("inf")}, {0: float("nan")}):
+            xb = x.clone()
+            for c, v in bad.items():
+                xb[c] = v
+            y = torch.zeros(m.n_rows, device="cuda", dtype=x.dtype)
+            H.hbp_spmv(h, xb, y)
+            hit = np.unique(of_row[np.isin(m.col, list(bad))])
+            assert np.array_equal(np.flatnonzero(~np.isfinite(y.cpu().numpy())), hit), bad
+    finally:
+        H.hbp_free(h)
 
 
 @pytest.mark.parametrize("f64", [False, True])

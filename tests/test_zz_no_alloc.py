@@ -24,10 +24,10 @@ def test_static_scratch_matches_hbp_spmv(oracle):
     import paper_2504_08860_amd as H
     L = H.lib()
     stream = torch.cuda.current_stream().cuda_stream
-    # the larger one first (competitive part on, several block columns), then a smaller one: the second
-    # call finds the first one's partial sums and counters in the array
+    # the larger one first (competitive part on, several block columns), then a smaller one, competitive, too: the second
+    # call finds the first one's partial sums in the array, and its counters (zero again)
     cases = [(make_config(5, 0.02), dict(rows_per_block=512, cols_per_block=2048, fixed_fraction_q8=160, num_workers=48)),
-             (random_csr(3000, 2500, 0.01, 5, empty_row_frac=0.2), dict(rows_per_block=64, cols_per_block=256, num_workers=7))]
+             (random_csr(3000, 2500, 0.01, 5, empty_row_frac=0.2), dict(rows_per_block=64, cols_per_block=256, num_workers=7, fixed_fraction_q8=128))]
     first_call = True
     for m, params in cases:
         print(f"[no-alloc] {m.name} nnz={m.nnz} {params}", flush=True)
