@@ -591,13 +591,12 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             // first worker's range, which took 247 us where the average worker took 160.  Product 296 -> 267 us.)
             const int32_t n_by_row = pass ? min(sh_heavy_n[1], kHeavyCap) : first_heavy ? sh_heavy_n[0] : 0;
             const int32_t n_heavy = n_by_row + (!pass && first_long ? sh_outweighing_n : 0);
-            // Where the range competes, how many of them a worker has claimed differs from call to call, and a group's sum must not:
-            // there a group has kWaves parts whatever runs beside it, `parts` successive ones to a wavefront, and the sums meet in fours.
-            const bool same_cut = pass && compete;
-            const int log_at_once = n_heavy >= 4 ? 2 : n_heavy >= 2 ? same_cut ? 2 : 1 : 0, share = kWaves >> log_at_once;
-            const int parts = same_cut ? 1 << log_at_once : 1, all_parts = share * parts;
+            // Where the range competes, how many of them a worker has claimed differs from call to call, and how a group is cut, hence the last
+            // bits of its sums, must not: there it is two at a time, whatever has been claimed.  (With a share given, us per product, one at
+            // a time / two / four: R-MAT 2^22 317 / 254 / 256, 2^20 124 / 118 / 113, fp64 137 / 136 / 143, 2^19 81 / 80 / 80.)
+            const int log_at_once = pass && compete ? 1 : n_heavy >= 4 ? 2 : n_heavy >= 2 ? 1 : 0, share = kWaves >> log_at_once;
             for (int32_t i0 = 0; i0 < n_heavy; i0 += 1 << log_at_once) {
-                const int32_t i = i0 + wave / share, first_part = wave % share * parts;
+                const int32_t i = i0 + wave / share, part = wave % share;
                 T *const sums = reinterpret_cast<T *>(sh_route + wave * kRoute);  // the wavefront's place: lengths, what the walk holds there, its sums
                 int32_t hs0 = 0, hs1 = 0;
                 if (i < n_heavy) {
@@ -608,35 +607,27 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
                     const uint32_t b0 = (uint32_t)uniform_load(L.group_ptr, gh);
                     const uint32_t total = (uint32_t)uniform_load(L.group_ptr, gh + 1) - b0;
                     const int32_t len = hs0 + lane < hs1 ? (int32_t)L.seg_len[hs0 + lane] : 0;
+                    int32_t *lens = reinterpret_cast<int32_t *>(sums);
+                    lens[lane] = len;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    int32_t k_lo, k_hi = 1 << 16;
+                    uint32_t lo, hi = total;
+                    cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)part) / (uint32_t)share), lane, k_lo, lo);
+                    if (part + 1 < share) cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)(part + 1)) / (uint32_t)share), lane, k_hi, hi);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    uint32_t pos = b0 + lo;
                     T sum = T(0);
-                    for (int part = first_part; part < first_part + parts; part++) {
-                        int32_t *lens = reinterpret_cast<int32_t *>(sums);
-                        lens[lane] = len;
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        int32_t k_lo, k_hi = 1 << 16;
-                        uint32_t lo, hi = total;
-                        cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)part) / (uint32_t)all_parts), lane, k_lo, lo);
-                        if (part + 1 < all_parts) cut_rounds(lens, (uint32_t)(((uint64_t)total * (uint32_t)(part + 1)) / (uint32_t)all_parts), lane, k_hi, hi);
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        uint32_t pos = b0 + lo;
-                        T of_part = T(0);
-                        walk_rounds(pos, b0 + hi, min(len, k_hi), k_lo, of_part);
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        sum += of_part;
-                    }
+                    walk_rounds(pos, b0 + hi, min(len, k_hi), k_lo, sum);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
                     sums[lane] = sum;
                 }
                 __syncthreads();
-                if (first_part == 0 && hs0 + lane < hs1) {
-                    auto sum_of = [&](int w) __attribute__((always_inline)) { return reinterpret_cast<const T *>(sh_route + (wave + w) * kRoute)[lane]; };
-                    T total_sum = T(0);
-                    if (same_cut && parts == 1)
-                        for (int w = 0; w < share; w += 4) total_sum += ((sum_of(w) + sum_of(w + 1)) + sum_of(w + 2)) + sum_of(w + 3);
-                    else
-                        for (int w = 0; w < share; w++) total_sum += sum_of(w);
+                if (part == 0 && hs0 + lane < hs1) {
+                    T total_sum = sums[lane];
+                    for (int w = 1; w < share; w++) total_sum += reinterpret_cast<const T *>(sh_route + (wave + w) * kRoute)[lane];
                     partial[hs0 + lane] = total_sum;
                 }
                 __syncthreads();  // the places are used again
