@@ -1749,8 +1749,8 @@ static int launch_schedule(hbp_handle_s *h, hipStream_t st)
                          (int64_t)h->group_weight};
         // Where the share is the library's choice, groups that nobody would enter the range for are not left to competition: claims from
         // a counter that one worker alone adds to, and the search for another range at the end, gain nothing.  Products,
-        // us, with / without: 27-point grid of 67^3 26.4 / 23.0, of 128^3 82.6 / 80.1, lognormal 150001 x 400009 37.4 / 32.6, R-MAT 2^18
-        // 44.5 / 40.8, fp64 lognormal 1.2M x 300K 135.5 / 129.0; 4M x 1M and R-MAT 2^22 as they were.
+        // us, with / without: 27-point grid of 67^3 24.5 / 20.6, of 128^3 83.6 / 81.1, lognormal 150001 x 400009 36.1 / 31.7, 4M x 1M 281 /
+        // 277, fp64 1.2M x 300K 129.4 / 124.0, R-MAT 2^22 258 / 255, 2^18 51.7 / 50.8.
         const int64_t least_open = h->share_chosen ? steal_weight(h->column_weight) : 0;
         k_schedule<<<blocks_for((int64_t)h->P + 1, 4), 256, 0, st>>>(h->col_group_ptr, wt, h->col_rank, (int64_t)h->column_weight, NBC,
                                                                      (int32_t)h->G, h->P, h->fixed_q8, h->fixed_start, h->fixed_col,

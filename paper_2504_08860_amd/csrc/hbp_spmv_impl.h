@@ -580,7 +580,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             first_heavy = sh_heavy_n[0] <= kFirstHeavyCap && g_end - g_begin <= 65536;
             first_long = sh_long_n[0] <= kFirstLongCap && g_end - g_begin <= 65536;  // (those that outweigh the others with them)
         }
-        // (HEAVY: the listed groups, the others, what the claims brought)
+        // (HEAVY: the listed groups, the others, what was listed meanwhile)
         for (int pass = 0;; pass++) {
         if constexpr (HEAVY) {
             // Heavy groups: the wavefronts of the worker walk up to four of them at a time, `share` wavefronts each.  The w-th of
@@ -656,8 +656,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_spmv_part(Layout L,
             // of one nonzero the products are the sums: no lengths are read, and E sums per lane are stored together.
             // Otherwise values and gathered x go through LDS, and every lane picks the elements of its row there round by round.
             // What does not fit there is walked after the others of a turn, as in the packs, with nothing of its own in flight.
-            // (Bound by HBM where segments are short: 340 MB at 5.4 TB/s on 2^20 rows of 32 from templates, a quarter of it stores; half of the groups there and of
-            // 4M x 1M lognormal rows have rows of one nonzero.  Products, packs / steps: 107.5 / 104.9 us and 281 / 274; R-MAT 2^22 267 / 264.)
+            // (Bound by HBM where segments are short: 340 MB at 5.4 TB/s on 2^20 rows of 32 from templates, a quarter of it stores; half of the
+            // groups there and of 4M x 1M lognormal rows have rows of one nonzero.  Products: walk_in_steps.)
             int32_t e = 0, e1 = 0;  // ends of the chunks g and g1 of groups
             per_draw = draw_of(g_end - g_begin);
             int32_t g = draw_resolve(draw_issue(), e), g1 = draw_resolve(draw_issue(), e1);
