@@ -366,6 +366,19 @@ def test_steps_of_groups_that_nearly_fit(H, oracle, threads, heavy):
                          threads_per_worker=threads, num_workers=1, fixed_fraction_q8=200, heavy_group_rounds=heavy)
 
 
+@pytest.mark.parametrize("rounds,threads", [(2, 256), (4, 1024)])
+@pytest.mark.parametrize("heavy", [0, 16])
+def test_packs_of_many_groups(H, oracle, rounds, threads, heavy):
+    """1024 groups per worker and more whose average does not fit the steps: packs, with the lists last (and without lists)."""
+    rows = lambda *parts: np.concatenate([np.full(n, v) for n, v in parts] + [np.zeros(64 - sum(n for n, _ in parts), int)])
+    pattern = [rows((64, 5)), rows((64, 4)), rows((60, 6), (3, 40)), rows((64, 1)), rows((33, 7), (20, 3)), rows((64, 5)), rows((1, 200), (40, 5))]
+    m = _matrix_of_lengths(np.concatenate((pattern * 160)[:1063]), 4000, seed=rounds)
+    assert m.nnz > 224 * 1063
+    for q8 in (256, 100):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=64, cols_per_block=4096, rounds_per_batch=rounds,
+                             threads_per_worker=threads, num_workers=1, fixed_fraction_q8=q8, heavy_group_rounds=heavy)
+
+
 def test_many_columns_competition(H, oracle):
     """More block columns than a wavefront has lanes (the scan for the fullest column loops), tiny
     tickets, more workers than groups."""
