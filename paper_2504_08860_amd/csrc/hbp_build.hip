@@ -418,11 +418,6 @@ __global__ void k_set_i32(int32_t *p, int32_t v)
 
 // ------------------------------------------------------------------ steps 1-3: segments
 
-__device__ __forceinline__ int32_t block_column(int32_t c, int32_t C, int32_t shift_c)
-{
-    return shift_c >= 0 ? c >> shift_c : c / C;
-}
-
 constexpr int kTile = 4096, kTileThreads = 512, kTileWords = kTile / 64, kWordsPerWave = kTileWords / (kTileThreads / 64);
 constexpr int kTileCounters = 4096;  // 16 KB of LDS
 // A tile with as many rows and more between its first and its last has its nonzeros look for their rows instead of walking
@@ -445,8 +440,13 @@ struct Findings {
 };
 __device__ __forceinline__ auto &findings_of_workgroup(Findings *found) { return found->copy[blockIdx.x % 64]; }
 
-// Checks csr_ptr; tile_row[t] = the row that holds nonzero t kTile (where the pointers are valid).
-__global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t *__restrict__ tile_row,
+// kTile consecutive nonzeros: the row that holds the first of them, and the segments that start there.
+struct Tile {
+    int32_t row, first, count, unused;  // first: where the first segment starts; -1: none does
+};
+
+// Checks csr_ptr and notes every tile's row (where the pointers are valid).
+__global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, Tile *__restrict__ tiles,
                                                    Findings *__restrict__ found)
 {
     const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void k_check_ptr(const int32_t *__restrict__ p
         if (p0 < 0 || p1 < p0 || p1 > nnz) {
             atomicOr(&found->err, kErrPtr);
         } else {
-            for (int64_t t = (p0 + kTile - 1) / kTile; t * kTile < p1; t++) tile_row[t] = (int32_t)r;
+            for (int64_t t = (p0 + kTile - 1) / kTile; t * kTile < p1; t++) tiles[t].row = (int32_t)r;
             length = (uint32_t)(p1 - p0);
         }
     }
@@ -521,18 +521,30 @@ __device__ __forceinline__ int32_t highest_up_to_lane(int32_t v)
     v = highest_moved<0x142, 0xa>(v);
     return highest_moved<0x143, 0xc>(v);
 }
+// v with `value` (the same in all lanes) in place of what lane `l` (a constant) holds
+__device__ __forceinline__ int32_t with_lane(int32_t value, int32_t l, int32_t v)
+{
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(value), "i"(l));
+    return v;
+}
 // the value of the lane below; lane 0 gets `first`
 __device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false); }
+
+enum class Pass { kCount, kCountAndList, kEmit };
+constexpr int kPlaceBits = 12;  // of a list's entry: the segment's first nonzero, counted from its tile's
+static_assert(kTile == 1 << kPlaceBits, "a place in a tile");
+constexpr uint32_t kNoSegment = 0xffffffffu;  // no entry whose place is still zero
 
 // The segments of kTile consecutive nonzeros per workgroup: a nonzero starts one when it starts a row or
 // its block column differs from its left neighbour's.  The rows that start inside the tile are read from
 // csr_ptr (empty rows own no position) into an LDS table by position, or looked for from the nonzeros where most
-// rows are empty; a segment's row is the last one that starts at or before it.  Two passes over the matrix (reading csr_col, 4 bytes per
-// nonzero, and in the second pass writing 8 bytes per segment), with the scans over the block table between them:
-//   EMIT false  counts the segments of every block (cursor: the block table) and notes every tile's first
-//               segment start and whether a tile shows a long segment;
-//   EMIT true   drops (length << 16 | local row, first nonzero) of every segment into its block's slot range
-//               (cursor: the blocks' next free slots), in no particular order: k_order_block sorts them.
+// rows are empty; a segment's row is the last one that starts at or before it.  The matrix's columns are read once, 4 bytes per nonzero:
+//   kCountAndList  counts the segments of every block (cursor: the block table), notes every tile's first segment start and whether a tile
+//                  shows a long segment, and leaves the tile's segments in a list, a word each: block column, row in its
+//                  block, place in the tile.  After the scans over the block table k_place reads the list, 4 bytes per segment.
+//   kCount, kEmit  where an entry takes more than a word (R = 2048: over 512 block columns): the same without a list, and a second pass that
+//                  finds the segments again and drops (length << 16 | local row, first nonzero) of every one into its block's
+//                  slot range (cursor: the blocks' next free slots), in no particular order: k_order_block sorts them.
 // A tile's rows are neighbours, so it touches the blocks of a few row blocks only: (bm_hi - bm_lo + 1) * NBC
 // counters.  When those fit in LDS the tile counts there (LDS integer atomics are two orders of magnitude
 // faster than scattered global ones) and goes to global memory once per counter it has touched;
@@ -543,19 +555,25 @@ __device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return
 // tile is a chain of dependent loads of some 8 us, four tiles to a CU at a time.  With a nonzero's row found by a maximum over the lanes up to
 // it in place of a bit search and an LDS read, and the scans over a tile's words without LDS, 517, 227 and 118: first pass 197 -> 182 us on the
 // lognormal matrix and 115 -> 98 us on the grid, second pass 160 -> 129 us on the grid by the scans alone (65 -> 62 registers: all four tiles of
-// a CU).  Issuing vector instructions takes 77 and 88 % of the passes' time on the grid, 73 and 59 % on the lognormal matrix.
+// a CU).  Issuing vector instructions takes 77 and 88 % of the passes' time on the grid, 73 and 59 % on the lognormal matrix.  With the list in
+// place of the second reading 100 + 133 -> 106 + 28 us on the grid, 183 + 337 -> 186 + 300 on the lognormal matrix, 52 + 65 -> 51 + 46 on R-MAT
+// 2^20 in fp64 (the first pass with the list, but before the shifts, masks and stores by words below: 123, 216, 56; with more than 80 scalar
+// registers a compute unit holds three tiles in place of four: 139, 247, 60).
 // Rows that hold a nonzero far apart, 40M rows, build in us, one in 200 / one in 1000: 440 / 410; walked 512 at a time with a
 // jump over the gaps 3260 / 20900.)
-template <bool EMIT>
-__global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col, int64_t n_rows,
+template <Pass PASS, bool POW2>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_num_sgpr(80)))
+void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col, int64_t n_rows,
                                                            int64_t nnz, int64_t n_cols, int32_t R, int32_t shift_r, int32_t C, int32_t shift_c,
-                                                           int32_t NBR, int32_t NBC, int validate, const int32_t *__restrict__ tile_row,
-                                                           int32_t *__restrict__ tile_first, uint32_t *__restrict__ cursor,
-                                                           uint2 *__restrict__ bucket, Findings *found)
+                                                           int32_t NBR, int32_t NBC, int validate, Tile *__restrict__ tiles,
+                                                           uint32_t *__restrict__ cursor, uint2 *__restrict__ bucket,
+                                                           uint32_t *__restrict__ list, int32_t row_bits, Findings *found)
 {
+    constexpr bool EMIT = PASS == Pass::kEmit, LIST = PASS == Pass::kCountAndList;
     __shared__ uint32_t cnt[kTileCounters];
     __shared__ __align__(16) int32_t row_at[kTile];  // row that starts at a position, counted from the tile's first row; -1: none
     __shared__ int32_t word_last[kTileWords], word_first[kTileWords];  // last row start, first segment start of a word; -1, kTile: none
+    __shared__ uint32_t word_starts[kTileWords];  // LIST: segments that start in a word
     __shared__ int32_t sh_next;
     if (found->err & kErrPtr) return;  // k_check_ptr's finding: the rows below would not ascend
     const int lane = threadIdx.x & 63;
@@ -567,25 +585,26 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
         const int32_t i = (first_word + u) * 64 + lane;
-        c[u] = i < count ? col[j0 + i] : 0;
+        c[u] = i < count ? lane_at(col + j0, i) : 0;
     }
     if (lane == 0 && j0 + first_word * 64 > 0 && first_word * 64 < count) before = col[j0 + first_word * 64 - 1];
     for (int i = threadIdx.x; i < kTile / 4; i += kTileThreads) reinterpret_cast<int4 *>(row_at)[i] = int4{-1, -1, -1, -1};
     if (EMIT && wave == 0) {  // where the segment that is open at the tile's end ends: a segment has fewer than 2^16 nonzeros, 16 tiles
-        const int64_t tiles = (nnz + kTile - 1) / kTile, t = (int64_t)blockIdx.x + 1 + lane;
-        const int32_t f = t < tiles ? tile_first[t] : (int32_t)nnz;
+        const int64_t n_tiles = (nnz + kTile - 1) / kTile, t = (int64_t)blockIdx.x + 1 + lane;
+        const int32_t f = t < n_tiles ? tiles[t].first : (int32_t)nnz;
         const uint64_t there = __ballot(f >= 0);
         const int32_t next = there ? __shfl(f, __builtin_ctzll(there)) : (int32_t)nnz;
         if (lane == 0) sh_next = next;
     }
     __syncthreads();
     // the rows that can start in the tile: from the one that holds its first nonzero to the one that holds the next tile's
-    const int32_t row_lo = tile_row[blockIdx.x];
-    const int32_t row_hi = j0 + count < nnz ? tile_row[blockIdx.x + 1] : (int32_t)(n_rows - 1);
+    const int32_t row_lo = tiles[blockIdx.x].row;
+    const int32_t row_hi = j0 + count < nnz ? tiles[blockIdx.x + 1].row : (int32_t)(n_rows - 1);
     if (row_hi - row_lo < kTileRowsWalked) {
-        for (int64_t r = (int64_t)row_lo + threadIdx.x; r <= row_hi; r += kTileThreads) {
-            const int64_t p0 = ptr[r], p1 = ptr[r + 1];
-            if (p1 > p0 && p0 >= j0 && p0 < j0 + count) row_at[p0 - j0] = (int32_t)(r - row_lo);
+        const int32_t *const first = ptr + row_lo;
+        for (int32_t r = threadIdx.x; r <= row_hi - row_lo; r += kTileThreads) {
+            const uint32_t p0 = (uint32_t)lane_at(first, r), p1 = (uint32_t)lane_at(first + 1, r), place = p0 - (uint32_t)j0;
+            if (p1 > p0 && place < (uint32_t)count) row_at[place] = r;
         }
     } else {
         // Empty rows by the thousand: every nonzero looks for its row, the last one that starts at or before it, a lane's
@@ -617,18 +636,22 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
     __syncthreads();
     uint64_t rows_here[kWordsPerWave];
     int32_t latest[kWordsPerWave];  // the last row that starts in the word, up to this lane; -1: none
+    int32_t of_word = 0;            // lane u: something about the wavefront's word u, on its way to LDS
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
         const int32_t w = first_word + u, r = row_at[w * 64 + lane];
         rows_here[u] = __builtin_amdgcn_ballot_w64(r >= 0);
         latest[u] = highest_up_to_lane(r);
-        const int32_t last = __builtin_amdgcn_readlane(latest[u], 63);
-        if (lane == 0) word_last[w] = last;
+        of_word = with_lane(__builtin_amdgcn_readlane(latest[u], 63), u, of_word);
     }
+    if (lane < kWordsPerWave) word_last[first_word + lane] = of_word;
     __syncthreads();
     // lane w: the last row that starts in the words 0 .. w (rows ascend)
     const int32_t last_row = highest_up_to_lane(max(0, word_last[lane]));
-    auto row_block = [&](int32_t row) { return shift_r >= 0 ? row >> shift_r : row / R; };
+    // POW2: both block sizes are powers of two (or there is one block column, and shift_c 31)
+    auto row_block = [&](int32_t row) { return POW2 ? row >> shift_r : row / R; };
+    auto row_in_block = [&](int32_t row) { return (uint32_t)(POW2 ? row & (R - 1) : row - row / R * R); };
+    auto block_column = [&](int32_t column) { return POW2 ? column >> shift_c : column / C; };
     const int32_t bm_lo = row_block(row_lo), bm_hi = row_block(row_lo + __builtin_amdgcn_readlane(last_row, 63));
     const int64_t counters = (int64_t)(bm_hi - bm_lo + 1) * NBC;
     const bool in_lds = counters <= kTileCounters;
@@ -637,10 +660,11 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
         __syncthreads();
     }
     int32_t row[kWordsPerWave], local[kWordsPerWave];
-    uint32_t rank[kWordsPerWave];
+    uint32_t rank[kWordsPerWave];  // LIST: the segment's entry but for its place
     uint64_t starts[kWordsPerWave];
     const uint32_t cols = (uint32_t)n_cols;  // below 2^31
     int32_t last_bn = 0;  // block column of the last nonzero of the word before
+    int32_t n_of_word = 0;
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
         const int32_t w = first_word + u, i = w * 64 + lane;
@@ -651,24 +675,32 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
         const int32_t c_prev = lane_below(c[u], u > 0 ? __builtin_amdgcn_readlane(c[u > 0 ? u - 1 : 0], 63) : __builtin_amdgcn_readfirstlane(before));
         const bool in_range = (uint32_t)c[u] < cols;
         if (!EMIT && valid && (!in_range || (validate && !row_start && c[u] <= c_prev))) atomicOr(&found->err, kErrCol);
-        const int32_t bn = block_column(c[u], C, shift_c);
-        const int32_t bn_prev = lane_below(bn, u > 0 ? last_bn : block_column(__builtin_amdgcn_readfirstlane(before), C, shift_c));
+        const int32_t bn = block_column(c[u]);
+        const int32_t bn_prev = lane_below(bn, u > 0 ? last_bn : block_column(__builtin_amdgcn_readfirstlane(before)));
         last_bn = __builtin_amdgcn_readlane(bn, 63);
         const bool start = valid && (row_start || bn != bn_prev);
         starts[u] = __builtin_amdgcn_ballot_w64(start);
-        if (lane == 0) word_first[w] = starts[u] ? w * 64 + __builtin_ctzll(starts[u]) : kTile;
+        of_word = with_lane(starts[u] ? w * 64 + __builtin_ctzll(starts[u]) : kTile, u, of_word);
+        if (LIST) n_of_word = with_lane(__popcll(starts[u]), u, n_of_word);
         local[u] = -1;
         rank[u] = 0;
+        if (LIST) rank[u] = start ? ((uint32_t)bn << row_bits | row_in_block(row[u])) << kPlaceBits : kNoSegment;
         const bool mine = start && in_range;  // (a column out of range has been reported; never index with it)
         if (in_lds) {
             if (mine) {
                 local[u] = (int32_t)__umul24((uint32_t)(row_block(row[u]) - bm_lo), (uint32_t)NBC) + bn;  // (below kTileCounters)
-                rank[u] = atomicAdd(&cnt[local[u]], 1u);
+                const uint32_t before_me = atomicAdd(&cnt[local[u]], 1u);
+                if (EMIT) rank[u] = before_me;
             }
         } else {
-            rank[u] = aggregated_add(cursor, mine ? (int64_t)bn * NBR + row_block(row[u]) : 0, mine);
+            const uint32_t before_me = aggregated_add(cursor, mine ? (int64_t)bn * NBR + row_block(row[u]) : 0, mine);
+            if (EMIT) rank[u] = before_me;
             if (mine) local[u] = 0;
         }
+    }
+    if (lane < kWordsPerWave) {
+        word_first[first_word + lane] = of_word;
+        if (LIST) word_starts[first_word + lane] = (uint32_t)n_of_word;
     }
     __syncthreads();
     if (in_lds) {
@@ -685,9 +717,21 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
             const int32_t f = word_first[lane];
             const uint64_t there = __ballot(f < kTile);
             const int32_t first = there ? __shfl(f, __builtin_ctzll(there)) : -1;
-            if (lane == 0) tile_first[blockIdx.x] = first < 0 ? -1 : (int32_t)(j0 + first);
+            if (lane == 0) tiles[blockIdx.x].first = first < 0 ? -1 : (int32_t)(j0 + first);
             if (lane == 0 && shows_long_segment(there, count))  // (several workgroups may write it, side by side)
                 __hip_atomic_store(&findings_of_workgroup(found).long_segment, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if constexpr (LIST) {
+            const uint32_t upto = sum_up_to_lane(word_starts[lane]);  // lane w: segments that start in the words 0 .. w
+            if (wave == 0 && lane == 63) tiles[blockIdx.x].count = (int32_t)upto;
+            uint32_t *const mine = list + j0;  // (as many entries as nonzeros: where a tile's begin does not depend on the others)
+#pragma unroll
+            for (int u = 0; u < kWordsPerWave; u++) {
+                const int32_t w = first_word + u;
+                const uint32_t at = w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, w > 0 ? w - 1 : 0) : 0u;
+                const uint64_t there = __builtin_amdgcn_ballot_w64(rank[u] != kNoSegment);  // (`starts` kept until here would take 14 more scalar registers)
+                if (rank[u] != kNoSegment) lane_at(mine + at, (uint32_t)lanes_below(there)) = rank[u] | (uint32_t)(w * 64 + lane);
+            }
         }
     } else {
         __syncthreads();
@@ -702,8 +746,80 @@ __global__ __launch_bounds__(kTileThreads) void k_segments(const int32_t *__rest
             const int32_t end = above ? (int32_t)(j0 + w * 64) + __builtin_ctzll(above) : later < kTile ? (int32_t)(j0 + later) : sh_next;
             if (local[u] < 0) continue;
             const uint32_t pos = rank[u] + (in_lds ? cnt[local[u]] : 0u);
-            bucket[pos] = {((uint32_t)(end - j) << 16) | (uint32_t)(row[u] - row_block(row[u]) * R), (uint32_t)j};  // length <= C <= 32768
+            bucket[pos] = {((uint32_t)(end - j) << 16) | row_in_block(row[u]), (uint32_t)j};  // length <= C <= 32768
         }
+    }
+}
+
+// Drops the segments of the list into their blocks' slot ranges: `parts` wavefronts to a tile, a lane per segment.  A segment's row block is
+// the last one that begins at or before its first nonzero.
+// (Bound by the stores, 8 bytes to a line of their own for most lanes, where segments are short; by a tile's chain of loads where they are long,
+// hence several tiles to a workgroup there.)
+__global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t R, int32_t shift_r,
+                                                        int32_t NBR, int32_t NBC, int32_t n_tiles, int32_t parts, const Tile *__restrict__ tiles,
+                                                        const uint32_t *__restrict__ list, int32_t row_bits, uint32_t *__restrict__ cursor,
+                                                        uint2 *__restrict__ bucket)
+{
+    constexpr int kWaves = kTileThreads / 64;
+    __shared__ uint32_t cnt[kTileCounters];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t here = kWaves / parts, t0 = (int32_t)blockIdx.x * here, t = t0 + wave / parts, part = wave % parts;
+    auto row_block = [&](int32_t row) { return shift_r >= 0 ? row >> shift_r : row / R; };
+    // the row block that holds the first nonzero of tile i, or the last one behind the last tile
+    auto first_block = [&](int32_t i) { return i < n_tiles ? row_block(tiles[i].row) : NBR - 1; };
+    auto begin_of = [&](int32_t bm) { return ptr[min((int64_t)bm * R, n_rows)]; };  // (of row block NBR: the end)
+    const int32_t bm_lo = first_block(t0), bm_hi = first_block(min(t0 + here, n_tiles));
+    const int64_t counters = (int64_t)(bm_hi - bm_lo + 1) * NBC;
+    const bool in_lds = counters <= kTileCounters;
+    if (in_lds) {
+        for (int i = threadIdx.x; i < (int)counters; i += kTileThreads) cnt[i] = 0u;
+        __syncthreads();
+    }
+    const int32_t count = t < n_tiles ? tiles[t].count : 0;
+    const int32_t tile_lo = t < n_tiles ? row_block(tiles[t].row) : 0, tile_hi = t < n_tiles ? first_block(t + 1) : 0;
+    const uint32_t *const mine = list + (int64_t)t * kTile;
+    const uint32_t j0 = (uint32_t)t * kTile, second = tile_hi > tile_lo ? (uint32_t)begin_of(tile_lo + 1) : 0xffffffffu;
+    const int32_t row_mask = (1 << row_bits) - 1;
+    auto block_of = [&](uint32_t j) {
+        int32_t lo = tile_lo, hi = tile_hi;
+        if (hi - lo <= 1) return j >= second ? hi : lo;  // wave-uniform
+        while (lo < hi) {
+            const int32_t mid = lo + ((hi - lo + 1) >> 1);
+            if ((uint32_t)begin_of(mid) <= j) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    if (in_lds) {
+        for (int32_t i = part * 64 + lane; i < count; i += 64 * parts) {
+            const uint32_t e = mine[i];
+            const int32_t bm = block_of(j0 + (e & (kTile - 1)));
+            atomicAdd(&cnt[(int32_t)__umul24((uint32_t)(bm - bm_lo), (uint32_t)NBC) + (int32_t)(e >> kPlaceBits >> row_bits)], 1u);
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < (int)counters; i += kTileThreads) {
+            const uint32_t n = cnt[i];
+            if (n) cnt[i] = atomicAdd(&cursor[(int64_t)(i % NBC) * NBR + bm_lo + i / NBC], n);
+        }
+        __syncthreads();
+    }
+    // where the segment that is open at the tile's end ends: a segment has fewer than 2^16 nonzeros, 16 tiles
+    const int32_t next_tile = t + 1 + lane;
+    const int32_t f = next_tile < n_tiles ? tiles[next_tile].first : (int32_t)nnz;
+    const uint64_t there = __ballot(f >= 0);
+    const uint32_t next = there ? (uint32_t)__builtin_amdgcn_readlane(f, __builtin_ctzll(there)) : (uint32_t)nnz;
+    for (int32_t i0 = part * 64; i0 < count; i0 += 64 * parts) {  // wave-uniform
+        const int32_t i = i0 + lane;
+        const bool valid = i < count;
+        const uint32_t e = valid ? mine[i] : 0u, j = j0 + (e & (kTile - 1));
+        const uint32_t end = i + 1 < count ? j0 + (mine[i + 1] & (kTile - 1)) : next;
+        const int32_t bm = valid ? block_of(j) : tile_lo, bn = (int32_t)(e >> kPlaceBits >> row_bits);
+        uint32_t pos = 0;
+        if (in_lds) {
+            if (valid) pos = atomicAdd(&cnt[(int32_t)__umul24((uint32_t)(bm - bm_lo), (uint32_t)NBC) + bn], 1u);
+        } else {
+            pos = aggregated_add(cursor, valid ? (int64_t)bn * NBR + bm : 0, valid);
+        }
+        if (valid) bucket[pos] = {(end - j) << 16 | (e >> kPlaceBits & (uint32_t)row_mask), j};
     }
 }
 
@@ -1840,13 +1956,19 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
     Findings *found;
     uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
-    int32_t *tile_row, *tile_first, *d_a;
+    int32_t *d_a;
+    Tile *tiles;
+    uint32_t *list = nullptr;
+    // The first pass leaves a list of the segments, one word each (block column, row, place in the tile), where these fit a word.
+    auto bits_for = [](int64_t values) { int32_t b = 0; while ((int64_t(1) << b) < values) b++; return b; };
+    const int32_t row_bits = bits_for(R);
+    const bool listed = kPlaceBits + row_bits + bits_for(NBC) <= 32;
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, 16);
     tmp.reserve(&found, 1);
-    tmp.reserve(&tile_first, n_tiles);
-    tmp.reserve(&tile_row, n_tiles);
+    tmp.reserve(&tiles, n_tiles);
+    if (listed) tmp.reserve(&list, nnz);
     tmp.reserve(&slot_off, D + 1);
     tmp.reserve(&group_off, D + 1);
     tmp.reserve(&blk_id, D + 1);
@@ -1854,7 +1976,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&scan_tmp, 3 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
     HBP_TRY(tmp.commit());
-    HBP_HIP(hipMemsetAsync(dense_cnt, 0, (size_t)((char *)tile_first - (char *)dense_cnt), st));
+    HBP_HIP(hipMemsetAsync(dense_cnt, 0, (size_t)((char *)tiles - (char *)dense_cnt), st));
 
     // Section 3.2: shift a, sampled or given
     if (p.hash_shift >= 0) {
@@ -1866,15 +1988,19 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     }
 
     // steps 1-3
-    int32_t shift_c = -1, shift_r = -1;  // C = 2^shift_c, R = 2^shift_r, or -1
+    int32_t shift_c = -1, shift_r = -1;  // C = 2^shift_c (or one block column, 31), R = 2^shift_r, or -1
     for (int32_t b = 0; b < 31; b++) {
         if (C == (int32_t(1) << b)) shift_c = b;
         if (R == (int32_t(1) << b)) shift_r = b;
     }
-    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tile_row, found);
-    k_segments<false><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
-                                                                        (int32_t)NBC, (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, tile_row,
-                                                                        tile_first, dense_cnt, nullptr, found);
+    if (NBC == 1) shift_c = 31;
+    const bool pow2 = shift_c >= 0 && shift_r >= 0;
+    k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tiles, found);
+    const auto first_pass = listed ? (pow2 ? k_segments<Pass::kCountAndList, true> : k_segments<Pass::kCountAndList, false>)
+                                   : (pow2 ? k_segments<Pass::kCount, true> : k_segments<Pass::kCount, false>);
+    first_pass<<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
+                                                                 (int32_t)NBC, (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, tiles,
+                                                                 dense_cnt, nullptr, list, row_bits, found);
     // step 4: scans over the block table
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
@@ -1963,8 +2089,17 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                      h->unit_stripe, h->unit_k, h->multi_stripes);
     // steps 5-6 (slot_off doubles as the per-block cursor from here on)
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
-    k_segments<true><<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
-                                                                       (int32_t)NBC, 0, tile_row, tile_first, slot_off, bucket, found);
+    if (listed) {
+        // a wavefront per tile where it holds few segments, up to eight where it holds many
+        int32_t wavefronts = 1;
+        while (wavefronts < kTileThreads / 64 && S > 256 * wavefronts * n_tiles) wavefronts *= 2;
+        k_place<<<blocks_for(n_tiles * wavefronts, kTileThreads / 64), kTileThreads, 0, st>>>(
+            csr_ptr, n_rows, nnz, R, shift_r, (int32_t)NBR, (int32_t)NBC, (int32_t)n_tiles, wavefronts, tiles, list, row_bits, slot_off, bucket);
+    } else {
+        const auto second_pass = pow2 ? k_segments<Pass::kEmit, true> : k_segments<Pass::kEmit, false>;
+        second_pass<<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
+                                                                      (int32_t)NBC, 0, tiles, slot_off, bucket, nullptr, row_bits, found);
+    }
     const dim3 stripe_grid((unsigned)(8 * ((NBR + 7) / 8) * std::max(parts, 1)));
     const size_t order_cap = ((size_t)R + 63) & ~(size_t)63;
     size_t small_n2 = 1;  // the bitonic network of a small block: 8-byte words, the next power of two above min(R, 256) slots
