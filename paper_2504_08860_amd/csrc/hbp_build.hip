@@ -435,7 +435,9 @@ constexpr int kLongRow = 4 * kFillRounds;
 // place of 10 where one row in 40 has to be told), and all behind one pointer (another argument, two more scalar registers, and
 // a compute unit holds three tiles of k_segments<false> instead of four: 98 -> 114 us on the 27-point grid of 128^3).
 struct Findings {
-    int32_t err, apart[15];
+    int32_t err;
+    uint32_t most_slots, most_nonzeros;  // of a row block
+    int32_t apart[13];
     struct { uint32_t longest_row, long_segment, apart[14]; } copy[64];
 };
 __device__ __forceinline__ auto &findings_of_workgroup(Findings *found) { return found->copy[blockIdx.x % 64]; }
@@ -530,10 +532,16 @@ __device__ __forceinline__ int32_t with_lane(int32_t value, int32_t l, int32_t v
 // the value of the lane below; lane 0 gets `first`
 __device__ __forceinline__ int32_t lane_below(int32_t v, int32_t first) { return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false); }
 
-enum class Pass { kCount, kCountAndList, kEmit };
+enum class Pass { kCount, kCountAndList, kCountListAndWords, kEmit };
 constexpr int kPlaceBits = 12;  // of a list's entry: the segment's first nonzero, counted from its tile's
 static_assert(kTile == 1 << kPlaceBits, "a place in a tile");
 constexpr uint32_t kNoSegment = 0xffffffffu;  // no entry whose place is still zero
+
+// 64 consecutive nonzeros: which of them start a segment, and how many segments start in the words of the tile before.
+struct SegmentWords {
+    uint64_t *starts;
+    uint16_t *at;
+};
 
 // The segments of kTile consecutive nonzeros per workgroup: a nonzero starts one when it starts a row or
 // its block column differs from its left neighbour's.  The rows that start inside the tile are read from
@@ -542,6 +550,7 @@ constexpr uint32_t kNoSegment = 0xffffffffu;  // no entry whose place is still z
 //   kCountAndList  counts the segments of every block (cursor: the block table), notes every tile's first segment start and whether a tile
 //                  shows a long segment, and leaves the tile's segments in a list, a word each: block column, row in its
 //                  block, place in the tile.  After the scans over the block table k_place reads the list, 4 bytes per segment.
+//   kCountListAndWords  the same, and which nonzeros start a segment, for k_panel_fill.
 //   kCount, kEmit  where an entry takes more than a word (R = 2048: over 512 block columns): the same without a list, and a second pass that
 //                  finds the segments again and drops (length << 16 | local row, first nonzero) of every one into its block's
 //                  slot range (cursor: the blocks' next free slots), in no particular order: k_order_block sorts them.
@@ -567,9 +576,9 @@ void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col
                                                            int64_t nnz, int64_t n_cols, int32_t R, int32_t shift_r, int32_t C, int32_t shift_c,
                                                            int32_t NBR, int32_t NBC, int validate, Tile *__restrict__ tiles,
                                                            uint32_t *__restrict__ cursor, uint2 *__restrict__ bucket,
-                                                           uint32_t *__restrict__ list, int32_t row_bits, Findings *found)
+                                                           uint32_t *__restrict__ list, int32_t row_bits, SegmentWords words, Findings *found)
 {
-    constexpr bool EMIT = PASS == Pass::kEmit, LIST = PASS == Pass::kCountAndList;
+    constexpr bool EMIT = PASS == Pass::kEmit, WORDS = PASS == Pass::kCountListAndWords, LIST = PASS == Pass::kCountAndList || WORDS;
     __shared__ uint32_t cnt[kTileCounters];
     __shared__ __align__(16) int32_t row_at[kTile];  // row that starts at a position, counted from the tile's first row; -1: none
     __shared__ int32_t word_last[kTileWords], word_first[kTileWords];  // last row start, first segment start of a word; -1, kTile: none
@@ -664,7 +673,7 @@ void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col
     uint64_t starts[kWordsPerWave];
     const uint32_t cols = (uint32_t)n_cols;  // below 2^31
     int32_t last_bn = 0;  // block column of the last nonzero of the word before
-    int32_t n_of_word = 0;
+    int32_t n_of_word = 0, lo_of_word = 0, hi_of_word = 0;
 #pragma unroll
     for (int u = 0; u < kWordsPerWave; u++) {
         const int32_t w = first_word + u, i = w * 64 + lane;
@@ -682,6 +691,10 @@ void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col
         starts[u] = __builtin_amdgcn_ballot_w64(start);
         of_word = with_lane(starts[u] ? w * 64 + __builtin_ctzll(starts[u]) : kTile, u, of_word);
         if (LIST) n_of_word = with_lane(__popcll(starts[u]), u, n_of_word);
+        if (WORDS) {
+            lo_of_word = with_lane((int32_t)(uint32_t)starts[u], u, lo_of_word);
+            hi_of_word = with_lane((int32_t)(starts[u] >> 32), u, hi_of_word);
+        }
         local[u] = -1;
         rank[u] = 0;
         if (LIST) rank[u] = start ? ((uint32_t)bn << row_bits | row_in_block(row[u])) << kPlaceBits : kNoSegment;
@@ -724,6 +737,11 @@ void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col
         if constexpr (LIST) {
             const uint32_t upto = sum_up_to_lane(word_starts[lane]);  // lane w: segments that start in the words 0 .. w
             if (wave == 0 && lane == 63) tiles[blockIdx.x].count = (int32_t)upto;
+            if constexpr (WORDS) {
+                const int64_t word0 = (int64_t)blockIdx.x * kTileWords;
+                if (lane < kWordsPerWave) words.starts[word0 + first_word + lane] = (uint64_t)(uint32_t)hi_of_word << 32 | (uint32_t)lo_of_word;
+                if (wave == 0) words.at[word0 + lane] = (uint16_t)(upto - word_starts[lane]);
+            }
             uint32_t *const mine = list + j0;  // (as many entries as nonzeros: where a tile's begin does not depend on the others)
 #pragma unroll
             for (int u = 0; u < kWordsPerWave; u++) {
@@ -855,32 +873,53 @@ __global__ __launch_bounds__(256) void k_compact_blocks(const uint32_t *__restri
 constexpr int kStripeSlices = 16;
 
 __device__ __forceinline__ uint32_t stripe_slice_count(const uint32_t *__restrict__ dense_cnt, int64_t bm, int32_t NBR, int32_t NBC,
-                                                       int32_t &bn0, int32_t &bn1)
+                                                       int32_t &bn0, int32_t &bn1, uint32_t &slots)
 {
     const int32_t slice = threadIdx.x >> 6;
     bn0 = (int32_t)(((int64_t)NBC * slice) / kStripeSlices);
     bn1 = (int32_t)(((int64_t)NBC * (slice + 1)) / kStripeSlices);
     uint32_t n = 0;
+    slots = 0;
     if (bm < NBR) {
 #pragma unroll 8
-        for (int64_t bn = bn0; bn < bn1; bn++) n += dense_cnt[bn * NBR + bm] ? 1u : 0u;
+        for (int64_t bn = bn0; bn < bn1; bn++) {
+            const uint32_t here = dense_cnt[bn * NBR + bm];
+            n += here ? 1u : 0u;
+            slots += here;
+        }
     }
     return n;
 }
 
-__global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC,
-                                                       uint32_t *__restrict__ stripe_cnt)
+__global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC, const int32_t *__restrict__ ptr,
+                                                       int64_t n_rows, int32_t R, uint32_t *__restrict__ stripe_cnt, Findings *__restrict__ found)
 {
-    __shared__ uint32_t sh[kStripeSlices * 64];
+    __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     int32_t bn0, bn1;
-    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1);
+    uint32_t slots;
+    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1, slots);
+    sh_slots[threadIdx.x] = slots;
     __syncthreads();
-    if (threadIdx.x >= 64 || bm >= NBR) return;
+    if (threadIdx.x >= 64) return;
     uint32_t n = 0;
+    slots = 0;
 #pragma unroll
-    for (int i = 0; i < kStripeSlices; i++) n += sh[i * 64 + threadIdx.x];
-    stripe_cnt[bm] = n;
+    for (int i = 0; i < kStripeSlices; i++) {
+        n += sh[i * 64 + threadIdx.x];
+        slots += sh_slots[i * 64 + threadIdx.x];
+    }
+    uint32_t nonzeros = 0;
+    if (bm < NBR) {
+        stripe_cnt[bm] = n;
+        nonzeros = (uint32_t)(ptr[min((bm + 1) * R, n_rows)] - ptr[bm * R]);
+    }
+    slots = wave_max(slots);
+    nonzeros = wave_max(nonzeros);
+    if (threadIdx.x == 0) {
+        atomicMax(&found->most_slots, slots);
+        atomicMax(&found->most_nonzeros, nonzeros);
+    }
 }
 
 __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ blk_id,
@@ -890,7 +929,8 @@ __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict
     __shared__ uint32_t sh[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     int32_t bn0, bn1;
-    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1);
+    uint32_t slots;
+    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1, slots);
     __syncthreads();
     if (bm >= NBR) return;
     int32_t k = stripe_ptr[bm];
@@ -1380,6 +1420,459 @@ __global__ __launch_bounds__(256) void k_fill_rest(const int2 *__restrict__ rest
     }
 }
 
+// ------------------------------------------------------------------ steps 5-7 by row blocks
+//
+// Where row segments are short, steps 5 to 7 above are scattered accesses of a few bytes: the segments' way to their blocks, and the fill's gather,
+// a 128-byte line per segment and array.  In CSR order a row block's segments and nonzeros lie side by side, and a workgroup holds
+// all of a row block's segments (k_panel_slots) or a good part of its nonzeros (k_panel_fill) in registers and LDS: everything is then read and
+// written in runs, and sorted on the chip.
+
+constexpr int kPanelThreads = 1024, kPanelWaves = kPanelThreads / 64;
+// A segment in two registers: length - 1, block column, row (15, 6, 11 bits); first nonzero counted from the row block's, rank in its block (18, 11).
+constexpr int kPanelRows = 2048, kPanelColumns = 64;
+constexpr int kPanelPer = 32, kPanelSlots = kPanelPer * kPanelThreads;  // segments of a row block at most
+constexpr int kPanelNonzeros = 1 << 16;                                 // its nonzeros at most: places of 16 bits, and in 64 tiles
+constexpr int kPanelLds = 154 * 1024;                                   // dynamic LDS of k_panel_slots at most (its own arrays: below 6 KB)
+constexpr int kPanelShift = 2;                                          // a at most: a band of 64 rows and more keeps 4 remainders apart
+constexpr int kPanelLeast = 128;                                        // row blocks, at least: fewer leave the device idle
+constexpr int kPanelLongest = 16384;                                    // longest row where segments are long
+
+// Words of 64 rows; an odd number of them, so that neighbouring segments, which differ in their block columns, lie in different banks.
+__host__ __device__ inline uint32_t panel_row_words(int32_t R) { return (((uint32_t)R + 63u) / 64u) | 1u; }
+
+// Bytes of a group's row in k_panel_slots' table, 8 * 2^a entries (an odd number of words: neighbouring groups' entries for a round lie in different banks).
+__host__ __device__ inline uint32_t panel_table_row(uint32_t a) { return 2u * ((8u << a) + 2u); }
+
+// The part of the list that holds a row block's segments.
+struct Panel {
+    uint32_t p0, p1;    // its nonzeros
+    int32_t t0;         // tile of the first of them
+    uint32_t skip;      // segments of that tile that belong to the row block before
+    uint32_t upto;      // lane l: the row block's segments in the tiles t0 .. t0 + l
+};
+
+__device__ __forceinline__ Panel panel_of(int32_t bm, const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, const Tile *__restrict__ tiles,
+                                          const uint64_t *__restrict__ word_starts, const uint16_t *__restrict__ word_at)
+{
+    const int lane = threadIdx.x & 63;
+    Panel p;
+    p.p0 = (uint32_t)ptr[(int64_t)bm * R];
+    p.p1 = (uint32_t)ptr[min(((int64_t)bm + 1) * R, n_rows)];
+    p.t0 = (int32_t)(p.p0 / kTile);
+    p.skip = p.upto = 0;
+    if (p.p0 == p.p1) return p;
+    const uint32_t last = p.p1 - 1;
+    const int32_t t1 = (int32_t)(last / kTile), t = p.t0 + lane;
+    p.skip = word_at[p.p0 / 64] + (uint32_t)__popcll(word_starts[p.p0 / 64] & ((1ull << (p.p0 & 63u)) - 1ull));
+    const uint32_t up_to_last = word_at[last / 64] + (uint32_t)__popcll(word_starts[last / 64] & ((2ull << (last & 63u)) - 1ull));
+    uint32_t n = t < t1 ? (uint32_t)tiles[t].count : t == t1 ? up_to_last : 0u;
+    if (lane == 0) n -= p.skip;
+    p.upto = sum_up_to_lane(n);
+    return p;
+}
+
+// One workgroup per row block: the segments of all its blocks are put in order of (key, row), which gives every segment its slot, and every
+// nonzero its place in the layout, counted in the row block's nonzeros: `places`, in the order of the CSR arrays.
+// Compact sort codes only (see k_order_block): `codes` of them, (9 << a) - 1.  A bit per row, code and block column; the bits in front of a
+// segment's own, counted, are its rank in the block, whatever order the bits were set in.
+// In a group the rows of fewer than 8 * 2^a (`head`) nonzeros are in the order of their lengths and the others come behind, so in each of the first `head`
+// rounds the lanes from some lane on have a nonzero: lane q's is the q-th behind table[group][round].  The places of the rounds behind these, which
+// few groups have, come from a list of their lanes, or, where there is no room for them in it, are written group by group.
+// The LDS holds in turn where the segments start, the bits with their counts, the slots with the table behind them, and in place of the slots, in CSR order,
+// a segment's group and lane (10 and 6 bits) and the last 16 bits of where it starts.
+__global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC,
+                                                               const Tile *__restrict__ tiles, const uint64_t *__restrict__ word_starts,
+                                                               const uint16_t *__restrict__ word_at, const uint32_t *__restrict__ list, int32_t row_bits,
+                                                               const uint32_t *__restrict__ slot_off, const uint32_t *__restrict__ group_off,
+                                                               const uint32_t *__restrict__ blk_id, uint32_t a, uint32_t heavy_rounds,
+                                                               uint32_t *__restrict__ longest_all, uint16_t *__restrict__ row_local,
+                                                               uint16_t *__restrict__ seg_len, uint32_t *__restrict__ slot_key,
+                                                               uint32_t *__restrict__ group_nnz, uint32_t *__restrict__ group_longest,
+                                                               int32_t *__restrict__ group_slot, int32_t *__restrict__ group_blk,
+                                                               int32_t *__restrict__ blk_shift, uint16_t *__restrict__ places,
+                                                               int32_t *__restrict__ slot_j, uint32_t most_tails)
+{
+    extern __shared__ __align__(8) uint32_t panel_lds[];
+    __shared__ uint32_t sh_slot[kPanelColumns + 1], sh_group[kPanelColumns + 1];  // slots and groups of the row block in front of a block column
+    __shared__ uint32_t sh_first[kPanelColumns];                                  // the block's first slot
+    constexpr int kGroups = kPanelSlots / 64 + kPanelColumns;
+    __shared__ uint32_t sh_sum[kGroups];  // nonzeros of a group; nonzeros in front of it
+    __shared__ uint32_t sh_tail_rounds, sh_tails_n;
+    __shared__ uint16_t sh_tails[kGroups];  // groups with more rounds than the table and the list of tails hold
+    const int32_t bm = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Panel p = panel_of(bm, ptr, n_rows, R, tiles, word_starts, word_at);
+    if (p.p0 == p.p1) return;
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, 63);
+    // lane bn: the block's first slot and group, slots and groups in front of it
+    const int64_t d = (int64_t)min(lane, NBC - 1) * NBR + bm;
+    const uint32_t s0 = slot_off[d], slots = lane < NBC ? slot_off[d + 1] - s0 : 0u, g0 = group_off[d], groups = (slots + 63) / 64, id = blk_id[d];
+    const uint32_t slots_upto = sum_up_to_lane(slots), groups_upto = sum_up_to_lane(groups);
+    if (wave == 0) {
+        sh_slot[lane + 1] = slots_upto;
+        sh_group[lane + 1] = groups_upto;
+        if (lane == 0) sh_slot[0] = sh_group[0] = sh_tail_rounds = sh_tails_n = 0u;
+        sh_first[lane] = s0;
+        if (slots) blk_shift[id] = (int32_t)a;
+    }
+    // the segments: u-th of this lane the (64 (16 u + wave) + lane)-th of the row block
+    uint32_t x[kPanelPer], y[kPanelPer];
+    // (between the phases: what one has computed of x and y is not kept in registers for the next)
+    auto forget = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kPanelPer; u++) asm volatile("" : "+v"(x[u]), "+v"(y[u]));
+    };
+    auto first_of = [&](int u) { return (uint32_t)(64 * (kPanelWaves * u + wave)); };
+    const uint32_t *const here = list + (int64_t)p.t0 * kTile;
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++) {  // where in the list
+        const uint32_t first = first_of(u), i = first + lane;
+        y[u] = p.skip;
+        if (first >= total) continue;
+        int32_t t = __popcll(__ballot(p.upto <= first));
+        uint32_t begin = t > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t > 0 ? t - 1 : 0) : 0u;
+        uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t);
+        uint32_t at = (uint32_t)t * kTile + i - begin;
+        while (end < min(first + 64u, total)) {  // wave-uniform
+            t++;
+            begin = end;
+            end = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t);
+            if (i >= begin) at = (uint32_t)t * kTile + i - begin;
+        }
+        if (at < (uint32_t)kTile) at += p.skip;
+        if (i < total) y[u] = at;
+    }
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++) {
+        x[u] = 0u;
+        if (first_of(u) < total) x[u] = lane_at(here, y[u]);
+    }
+    forget();  // (all loads are on their way at once)
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++) {
+        const uint32_t e = x[u], bn = e >> kPlaceBits >> row_bits, row = e >> kPlaceBits & ((1u << row_bits) - 1u);
+        y[u] = (uint32_t)p.t0 * kTile + (y[u] & ~(uint32_t)(kTile - 1)) + (e & (kTile - 1)) - p.p0;
+        x[u] = bn << 11 | row;
+        if (first_of(u) + lane < total) panel_lds[first_of(u) + lane] = y[u];
+    }
+    __syncthreads();
+    forget();
+    const uint32_t row_words = panel_row_words(R), codes = (9u << a) - 1u, words = row_words * codes;
+    auto word_of = [&](uint32_t v) {  // of the segment in v
+        const uint32_t n = (v >> 17) + 1u, code = ((min(n >> a, 8u) << a) | (n & ((1u << a) - 1u))) - 1u;
+        return __umul24(__umul24(v >> 11 & 63u, codes) + code, row_words) + ((v & 2047u) >> 6);
+    };
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++) {
+        const uint32_t i = first_of(u) + lane;
+        if (i < total) x[u] |= ((i + 1 < total ? panel_lds[i + 1] : p.p1 - p.p0) - y[u] - 1u) << 17;
+        y[u] |= word_of(x[u]) << 18;  // (below 2^14: ten bytes each fit the LDS)
+    }
+    __syncthreads();
+    forget();
+    uint64_t *const bits = reinterpret_cast<uint64_t *>(panel_lds);
+    uint16_t *const before = reinterpret_cast<uint16_t *>(bits + (uint32_t)NBC * words);
+    for (uint32_t i = threadIdx.x; i < (uint32_t)NBC * words; i += kPanelThreads) bits[i] = 0ull;
+    __syncthreads();
+    forget();
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++)
+        if (first_of(u) + lane < total) (void)atomicOr(panel_lds + 2 * (y[u] >> 18) + (x[u] >> 5 & 1u), 1u << (x[u] & 31u));
+    __syncthreads();
+    forget();
+    const uint32_t per = (words + 63) / 64;
+    for (int bn = wave; bn < NBC; bn += kPanelWaves) {
+        const uint32_t lo = min((uint32_t)lane * per, words), hi = min(lo + per, words);
+        const uint64_t *const mine = bits + (uint32_t)bn * words;
+        uint32_t n = 0;
+        for (uint32_t i = lo; i < hi; i++) n += (uint32_t)__popcll(mine[i]);
+        uint32_t run = sum_up_to_lane(n) - n;
+        for (uint32_t i = lo; i < hi; i++) {
+            before[(uint32_t)bn * words + i] = (uint16_t)run;
+            run += (uint32_t)__popcll(mine[i]);
+        }
+    }
+    __syncthreads();
+    forget();
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++)
+        if (first_of(u) + lane < total) {
+            const uint32_t w = y[u] >> 18;
+            y[u] = (y[u] & 0x3ffffu) | (before[w] + (uint32_t)__popcll(bits[w] & ((1ull << (x[u] & 63u)) - 1ull))) << 18;
+        }
+    __syncthreads();
+    forget();
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++)
+        if (first_of(u) + lane < total) panel_lds[sh_slot[x[u] >> 11 & 63u] + (y[u] >> 18)] = (x[u] & 2047u) << 16 | ((x[u] >> 17) + 1u);
+    __syncthreads();
+    forget();
+    // a wavefront per group
+    const uint32_t all_groups = (uint32_t)__builtin_amdgcn_readlane((int)groups_upto, 63);
+    const int32_t head = 8 << a;
+    const uint32_t stride = panel_table_row(a) / 2u;
+    // behind the slots, or what takes their place: lanes and places of the rounds behind the first `head`; the table
+    uint64_t *const tail_lanes = reinterpret_cast<uint64_t *>(panel_lds + ((total + 1u) & ~1u));
+    uint16_t *const tail_places = reinterpret_cast<uint16_t *>(tail_lanes + most_tails), *const table = tail_places + most_tails;
+    for (uint32_t gi = wave; gi < all_groups; gi += kPanelWaves) {
+        const int bn = __popcll(__ballot(groups_upto <= gi));
+        const uint32_t q0 = 64u * (gi - (uint32_t)__builtin_amdgcn_readlane((int)(groups_upto - groups), bn));  // the group's first slot in its block
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)(slots_upto - slots), bn) + q0;             // and in the row block
+        const uint32_t count = min((uint32_t)__builtin_amdgcn_readlane((int)slots, bn) - q0, 64u);
+        const uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)s0, bn) + q0, g = (uint32_t)__builtin_amdgcn_readlane((int)g0, bn) + q0 / 64u;
+        const bool valid = (uint32_t)lane < count;
+        const uint32_t v = valid ? panel_lds[at + lane] : 0u, n = v & 0xffffu;
+        if (valid) {
+            lane_at(row_local + slot, lane) = (uint16_t)(v >> 16);
+            lane_at(seg_len + slot, lane) = (uint16_t)n;
+            if (slot_key) lane_at(slot_key + slot, lane) = hash_key(n, a, (uint32_t)R / 9u, (uint32_t)R);
+        }
+        uint32_t longest = (uint32_t)__builtin_amdgcn_readlane((int)n, (int)count - 1);
+        if (longest >= (uint32_t)head) longest = wave_max(n);
+        // the table's row, from the group's first nonzero on: the rounds' places less the lanes that have none
+        int32_t base = -(int32_t)count;
+        for (int32_t k = 0; k < head && k < (int32_t)longest; k += 8) {  // wave-uniform
+            int32_t entry = 0;
+#pragma unroll
+            for (int t = 0; t < 8; t++) {
+                base += __popcll(__builtin_amdgcn_ballot_w64((int32_t)n > k + t));
+                entry = with_lane(base, t, entry);
+            }
+            if (lane < 8) table[gi * stride + (uint32_t)(k + lane)] = (uint16_t)entry;
+        }
+        uint32_t sum = (uint32_t)(base + (int32_t)count);
+        if (longest > (uint32_t)head) {
+            const uint32_t rounds = longest - (uint32_t)head;
+            uint32_t tail = 0;
+            if (lane == 0) tail = atomicAdd(&sh_tail_rounds, rounds);
+            tail = (uint32_t)__builtin_amdgcn_readfirstlane((int)tail);
+            const bool room = tail + rounds <= most_tails;
+            if (lane == 0) {
+                table[gi * stride + (uint32_t)head] = room ? (uint16_t)tail : (uint16_t)0xffffu;
+                if (!room) sh_tails[atomicAdd(&sh_tails_n, 1u)] = (uint16_t)gi;
+            }
+            if (room) {
+                for (uint32_t i = 0; i < rounds; i += 8) {
+                    int32_t lanes_lo = 0, lanes_hi = 0, begin = 0;
+#pragma unroll
+                    for (int t = 0; t < 8; t++) {
+                        const uint64_t live = __builtin_amdgcn_ballot_w64((int32_t)n > head + (int32_t)i + t);
+                        lanes_lo = with_lane((int32_t)(uint32_t)live, t, lanes_lo);
+                        lanes_hi = with_lane((int32_t)(live >> 32), t, lanes_hi);
+                        begin = with_lane((int32_t)sum, t, begin);
+                        sum += (uint32_t)__popcll(live);
+                    }
+                    if (lane < 8 && i + (uint32_t)lane < rounds) {
+                        tail_lanes[tail + i + (uint32_t)lane] = (uint64_t)(uint32_t)lanes_hi << 32 | (uint32_t)lanes_lo;
+                        tail_places[tail + i + (uint32_t)lane] = (uint16_t)begin;
+                    }
+                }
+            } else {
+                sum = wave_sum(n);
+            }
+        }
+        if (lane == 0) {
+            sh_sum[gi] = sum;
+            group_nnz[g] = sum;
+            group_longest[g] = longest;
+            if (longest > heavy_rounds && longest > __hip_atomic_load(longest_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(longest_all, longest);
+            group_slot[g] = (int32_t)slot;
+            group_blk[g] = (int32_t)__builtin_amdgcn_readlane((int)id, bn);
+        }
+    }
+    __syncthreads();
+    forget();
+    if (wave == 0) {
+        uint32_t run = 0;
+        for (uint32_t i0 = 0; i0 < all_groups; i0 += 64) {
+            const uint32_t n = i0 + lane < all_groups ? sh_sum[i0 + lane] : 0u, upto = sum_up_to_lane(n);
+            if (i0 + lane < all_groups) sh_sum[i0 + lane] = run + upto - n;
+            run += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kPanelPer; u++) {
+        const uint32_t i = first_of(u) + lane, bn = x[u] >> 11 & 63u, q = y[u] >> 18, j = y[u] & 0x3ffffu;
+        if (i < total) {
+            panel_lds[i] = (64u * sh_group[bn] + q) << 16 | (j & 0xffffu);
+            if ((x[u] >> 17) >= (uint32_t)head) slot_j[sh_first[bn] + q] = (int32_t)(p.p0 + j);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < all_groups * (uint32_t)head; i += kPanelThreads) {
+        const uint32_t gi = i >> (3u + a);
+        table[gi * stride + (i & (uint32_t)(head - 1))] += (uint16_t)sh_sum[gi];
+    }
+    __syncthreads();
+    // the rounds for which there was no room: the first 64 of a group by a wavefront, the rest by all, 32 rounds at a time
+    const uint32_t n_tails = sh_tails_n;
+    auto place_rounds = [&](uint32_t gi, int32_t k0, int32_t most, int32_t step) __attribute__((always_inline)) {  // k0 .. k0 + most - 1, and so on every `step`
+        const int bn = __popcll(__ballot(groups_upto <= gi));
+        const uint32_t q0 = 64u * (gi - (uint32_t)__builtin_amdgcn_readlane((int)(groups_upto - groups), bn));
+        const uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)s0, bn) + q0;
+        const int32_t n = (uint32_t)lane < (uint32_t)__builtin_amdgcn_readlane((int)slots, bn) - q0 ? (int32_t)lane_at(seg_len + slot, lane) : 0;
+        uint16_t *const mine = n > head ? places + lane_at(slot_j + slot, lane) : places;
+        for (; __ballot(n > k0); k0 += step) {
+            uint32_t at = sh_sum[gi] + wave_sum((uint32_t)min(n, k0));
+            for (int32_t k = k0; k < k0 + most; k++) {
+                const uint64_t live = __ballot(n > k);
+                if (!live) break;
+                if (n > k) mine[k] = (uint16_t)(at + (uint32_t)lanes_below(live));
+                at += (uint32_t)__popcll(live);
+            }
+            if (step == 0) return (bool)__ballot(n > k0 + most);
+        }
+        return false;
+    };
+    for (uint32_t i = wave; i < n_tails; i += kPanelWaves) {
+        const uint32_t gi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_tails[i]);
+        if (place_rounds(gi, head, 64, 0) && lane == 0) sh_tails[i] = (uint16_t)(gi | 0x8000u);
+    }
+    // The other nonzeros, 64 neighbouring ones at a time (a word of word_starts), the wavefront's l-th word in lane l, 64 words at a time.  A nonzero's
+    // segment is the last one that starts at or before it.
+    auto round_of = [&](uint32_t j, uint32_t f) { return (j - f) & 0xffffu; };  // j: in the row block
+    auto entry_of = [&](uint32_t j, uint32_t f) { return (uint32_t)table[__umul24(f >> 22, stride) + min(round_of(j, f), (uint32_t)head - 1u)] + (f >> 16 & 63u); };
+    auto place_tail = [&](uint32_t j, uint32_t f) __attribute__((always_inline)) {
+        const uint32_t k = round_of(j, f), gi = f >> 22;
+        if (k < (uint32_t)head) return;
+        const uint32_t tail = table[__umul24(gi, stride) + (uint32_t)head];
+        if (tail == 0xffffu) return;
+        const uint32_t i = tail + k - (uint32_t)head;
+        lane_at(places + p.p0, j) = (uint16_t)(sh_sum[gi] + tail_places[i] + (uint32_t)__popcll(tail_lanes[i] & ((1ull << (f >> 16 & 63u)) - 1ull)));
+    };
+    const uint32_t w0 = (p.p0 + 63u) / 64u, w1 = p.p1 / 64u;  // whole words
+    for (uint32_t b0 = w0 + wave; b0 < w1; b0 += 64u * kPanelWaves) {
+        const uint32_t w = min(b0 + (uint32_t)(kPanelWaves * lane), w1 - 1u);
+        const uint64_t starts = word_starts[w];
+        const int32_t t = (int32_t)(w / kTileWords) - p.t0;
+        const uint32_t in_tiles = (uint32_t)__shfl((int)p.upto, t > 0 ? t - 1 : 0);
+        const uint32_t base = (t > 0 ? in_tiles : 0u - p.skip) + word_at[w] + ((uint32_t)starts & 1u) - 1u;  // the segment of the word's first nonzero
+        const uint32_t behind_lo = (uint32_t)(starts >> 1), behind_hi = (uint32_t)(starts >> 33);
+        const int n_words = (int)min(64u, (w1 - b0 + kPanelWaves - 1) / kPanelWaves);
+        constexpr int kAtOnce = 8;
+        for (int l0 = 0; l0 < n_words; l0 += kAtOnce) {
+            uint32_t f[kAtOnce], entry[kAtOnce];
+            const uint32_t j = 64u * (b0 + (uint32_t)(kPanelWaves * l0)) - p.p0 + (uint32_t)lane;
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++) {
+                const int l = min(l0 + u, n_words - 1);
+                f[u] = panel_lds[__builtin_amdgcn_mbcnt_hi((uint32_t)__builtin_amdgcn_readlane((int)behind_hi, l),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)__builtin_amdgcn_readlane((int)behind_lo, l),
+                                                                                     (uint32_t)__builtin_amdgcn_readlane((int)base, l)))];
+            }
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++) entry[u] = entry_of(j + 64u * kPanelWaves * u, f[u]);
+            bool tails = false;
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++) {
+                const bool in_head = round_of(j + 64u * kPanelWaves * u, f[u]) < (uint32_t)head;
+                tails |= !in_head;
+                if (l0 + u < n_words && in_head) lane_at(places + 64ull * (b0 + (uint32_t)(kPanelWaves * (l0 + u))), lane) = (uint16_t)entry[u];
+            }
+            if (!__ballot(tails)) continue;
+#pragma unroll
+            for (int u = 0; u < kAtOnce; u++)
+                if (l0 + u < n_words) place_tail(j + 64u * kPanelWaves * u, f[u]);
+        }
+    }
+    if (wave < 2) {  // the words that hold the row block's first and last nonzero, and others'
+        const uint32_t w = wave == 0 ? p.p0 / 64u : w1, j = 64u * w + (uint32_t)lane;
+        if ((wave == 0 ? w < w0 : w * 64u < p.p1 && w >= w0) && j >= p.p0 && j < p.p1) {
+            const int32_t t = (int32_t)(w / kTileWords) - p.t0;
+            const uint32_t in_front = t > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t > 0 ? t - 1 : 0) : 0u - p.skip;
+            const uint32_t f = panel_lds[in_front + word_at[w] + (uint32_t)__popcll(word_starts[w] & ((2ull << lane) - 1ull)) - 1u];
+            if (round_of(j - p.p0, f) < (uint32_t)head) places[j] = (uint16_t)entry_of(j - p.p0, f);
+            place_tail(j - p.p0, f);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = 0; i < n_tails; i++) {
+        const uint32_t gi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_tails[i]);
+        if (gi & 0x8000u) (void)place_rounds(gi & 0x7fffu, head + 64 + 32 * wave, 32, 32 * kPanelWaves);
+    }
+}
+
+// The fill: a workgroup takes a share of a row block's nonzeros in the layout's order, `room` at most, and puts them in place in LDS; they come from the CSR arrays
+// in their order, and what it writes are whole runs.  `shares` workgroups per row block at most; those of one row block run on
+// one XCD, whose L2 then holds what all of them read.
+template <typename T>
+__global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC, int32_t C,
+                                                              int32_t shares, uint32_t room, const uint16_t *__restrict__ places,
+                                                              const int32_t *__restrict__ csr_col, const T *__restrict__ csr_val,
+                                                              const uint32_t *__restrict__ group_off, const int32_t *__restrict__ group_ptr,
+                                                              uint16_t *__restrict__ col_local, T *__restrict__ data)
+{
+    extern __shared__ __align__(8) uint32_t panel_lds[];
+    T *const vals = reinterpret_cast<T *>(panel_lds);
+    uint16_t *const cols = reinterpret_cast<uint16_t *>(vals + room);
+    const int32_t octet = (int32_t)(blockIdx.x >> 3) / shares, share = (int32_t)(blockIdx.x >> 3) % shares, bm = 8 * octet + (int32_t)(blockIdx.x & 7u);
+    if (bm >= NBR) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t p0 = (uint32_t)ptr[(int64_t)bm * R], p1 = (uint32_t)ptr[min(((int64_t)bm + 1) * R, n_rows)];
+    const int64_t d = (int64_t)min(lane, NBC - 1) * NBR + bm;
+    const uint32_t g0 = group_off[d], g1 = lane < NBC ? group_off[d + 1] : g0;
+    const uint32_t nonzeros = p1 - p0, parts = (nonzeros + room - 1) / room;
+    if ((uint32_t)share >= parts) return;
+    const uint32_t each = (nonzeros + parts - 1) / parts, lo = each * (uint32_t)share, hi = min(nonzeros, lo + each), size = hi - lo;
+    auto put = [&](uint32_t place, int32_t column, T value) __attribute__((always_inline)) {
+        const uint32_t at = place - lo;
+        if (at < size) {
+            vals[at] = value;
+            cols[at] = (uint16_t)column;
+        }
+    };
+    // whole runs of 256 nonzeros, four to a lane, and what lies in front of and behind them, one to a thread
+    const uint32_t run0 = (p0 + 255u) / 256u, run1 = p1 / 256u;
+    constexpr int kAtOnce = sizeof(T) == 4 ? 4 : 3;
+    for (uint32_t run = run0 + wave; run < run1; run += kAtOnce * kPanelWaves) {
+        uint16_t at[kAtOnce][4];
+        int32_t c[kAtOnce][4];
+        T v[kAtOnce][4];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; u++) {
+            const uint64_t j = 256ull * min(run + (uint32_t)(kPanelWaves * u), run1 - 1u);
+            __builtin_memcpy(at[u], reinterpret_cast<const char *>(places + j) + 8u * (uint32_t)lane, sizeof at[u]);
+            __builtin_memcpy(c[u], reinterpret_cast<const char *>(csr_col + j) + 16u * (uint32_t)lane, sizeof c[u]);  // (at any multiple of 4 bytes)
+            __builtin_memcpy(v[u], reinterpret_cast<const char *>(csr_val + j) + 4u * (uint32_t)sizeof(T) * (uint32_t)lane, sizeof v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kAtOnce; u++) {
+            if (run + (uint32_t)(kPanelWaves * u) >= run1) break;
+#pragma unroll
+            for (int i = 0; i < 4; i++) put(at[u][i], c[u][i], v[u][i]);
+        }
+    }
+    const uint32_t in_front = run0 < run1 ? 256u * run0 : p1, behind = run0 < run1 ? 256u * run1 : p1;
+    for (uint32_t j = p0 + threadIdx.x; j < in_front; j += kPanelThreads) put(places[j], csr_col[j], csr_val[j]);
+    for (uint32_t j = behind + threadIdx.x; j < p1; j += kPanelThreads) put(places[j], csr_col[j], csr_val[j]);
+    // lane bn: the block's place in the layout, its nonzeros, those in front of it
+    const uint32_t e0 = (uint32_t)group_ptr[g0], elements = (uint32_t)group_ptr[g1] - e0, elements_upto = sum_up_to_lane(elements);
+    const uint32_t to_layout = e0 + lo - (elements_upto - elements);  // a place in the share and this: the place in the layout
+    const int bn_first = __popcll(__ballot(elements_upto <= lo)), bn_last = __popcll(__ballot(elements_upto < hi));
+    __syncthreads();
+    uint32_t next = (uint32_t)wave;  // 256 nonzeros of a block at a time
+    for (int bn = bn_first; bn <= bn_last; bn++) {
+        const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)elements_upto, bn);
+        const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)(elements_upto - elements), bn), lo) - lo, b = min(upto, hi) - lo, col0 = (uint32_t)bn * (uint32_t)C;
+        const uint32_t turns = b > a ? (b - a + 255u) / 256u : 0u, shift = (uint32_t)__builtin_amdgcn_readlane((int)to_layout, bn);
+        for (; next < turns; next += kPanelWaves) {
+            const uint32_t i0 = a + 256u * next;
+            uint16_t *const to_col = col_local + (i0 + shift);
+            T *const to_val = data + (i0 + shift);
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const uint32_t i = i0 + 64u * u + (uint32_t)lane;
+                if (i < b) {
+                    lane_at(to_col, 64u * u + (uint32_t)lane) = (uint16_t)(cols[i] - col0);
+                    lane_at(to_val, 64u * u + (uint32_t)lane) = vals[i];
+                }
+            }
+        }
+        next -= turns;
+    }
+}
+
 // add_sign derived from seg_len (Section 3.2: distance to the row's next nonzero = nonzeros
 // after it in this round + nonzeros before it in the next round + 1; -1 at the row's end).
 __global__ __launch_bounds__(256) void k_add_sign(const int32_t *__restrict__ group_ptr, const int32_t *__restrict__ group_slot,
@@ -1713,6 +2206,8 @@ __global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint
     if (i == 0) {
         host[count] = longest;
         host[count + 1] = segment;
+        host[count + 2] = found->most_slots;
+        host[count + 3] = found->most_nonzeros;
     }
 }
 
@@ -1963,12 +2458,20 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     auto bits_for = [](int64_t values) { int32_t b = 0; while ((int64_t(1) << b) < values) b++; return b; };
     const int32_t row_bits = bits_for(R);
     const bool listed = kPlaceBits + row_bits + bits_for(NBC) <= 32;
+    const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
+    // could steps 5 to 7 go by row blocks? (see below)
+    const bool short_rows = h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast;
+    SegmentWords words{nullptr, nullptr};
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, 16);
     tmp.reserve(&found, 1);
     tmp.reserve(&tiles, n_tiles);
     if (listed) tmp.reserve(&list, nnz);
+    if (short_rows) {
+        tmp.reserve(&words.starts, n_tiles * kTileWords);
+        tmp.reserve(&words.at, n_tiles * kTileWords);
+    }
     tmp.reserve(&slot_off, D + 1);
     tmp.reserve(&group_off, D + 1);
     tmp.reserve(&blk_id, D + 1);
@@ -1996,15 +2499,16 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     if (NBC == 1) shift_c = 31;
     const bool pow2 = shift_c >= 0 && shift_r >= 0;
     k_check_ptr<<<blocks_for(n_rows, 256), 256, 0, st>>>(csr_ptr, n_rows, nnz, tiles, found);
-    const auto first_pass = listed ? (pow2 ? k_segments<Pass::kCountAndList, true> : k_segments<Pass::kCountAndList, false>)
+    const auto first_pass = short_rows ? (pow2 ? k_segments<Pass::kCountListAndWords, true> : k_segments<Pass::kCountListAndWords, false>)
+                            : listed ? (pow2 ? k_segments<Pass::kCountAndList, true> : k_segments<Pass::kCountAndList, false>)
                                    : (pow2 ? k_segments<Pass::kCount, true> : k_segments<Pass::kCount, false>);
     first_pass<<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
                                                                  (int32_t)NBC, (p.flags & HBP_FLAG_VALIDATE) ? 1 : 0, tiles,
-                                                                 dense_cnt, nullptr, list, row_bits, found);
+                                                                 dense_cnt, nullptr, list, row_bits, words, found);
     // step 4: scans over the block table
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
-    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, stripe_cnt);
+    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, csr_ptr, n_rows, R, stripe_cnt, found);
     HBP_TRY(exclusive_scan(stripe_cnt, (uint32_t *)h->stripe_ptr, NBR, scan_tmp, st));
     HBP_HIP(hipGetLastError());
 
@@ -2017,6 +2521,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     if (err & kErrCol) return HBP_ERR_BAD_CSR_COL;
     const int64_t S = host[0], G = host[1], B = host[2], longest_row = host[5];
     const bool long_segments = host[6] != 0;
+    const int64_t most_slots = host[7], most_nonzeros = host[8];
     h->S = S; h->G = G; h->B = B; h->a = a;
 
     Arena own1(true, h->device);
@@ -2051,6 +2556,11 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // stencil) or 86 slots per block (R-MAT, whose dense row blocks then also wait for a few
     // workgroups) it is slower than the layout's own order with a wavefront per group.
     const bool by_row_block = NBR >= 64 && nnz < 4 * S && S >= 256 * B;
+    const size_t panel_words = (size_t)NBC * ((9u << a) - 1u) * panel_row_words(R);
+    const size_t slots_table = sizeof(uint32_t) * (size_t)most_slots + (size_t)(most_slots / 64 + NBC) * panel_table_row((uint32_t)(a & 15)) + 8;
+    const size_t slots_lds = std::max<size_t>(slots_table, panel_words * (sizeof(uint64_t) + sizeof(uint16_t)));
+    const bool by_panel = short_rows && by_row_block && !h->flat_wpg && a <= kPanelShift && most_slots <= kPanelSlots && most_nonzeros <= kPanelNonzeros &&
+                          slots_lds <= (size_t)kPanelLds && !(long_segments && longest_row > kPanelLongest);
     const int32_t parts = !by_row_block ? 0 : (int32_t)std::min<int64_t>(32, std::max<int64_t>(1, (B + NBR - 1) / NBR));
     // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
     // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us), nor
@@ -2066,7 +2576,9 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint2 *bucket;
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
-    tmp2.reserve(&bucket, S);
+    uint16_t *places = nullptr;
+    if (by_panel) tmp2.reserve(&places, n_tiles * kTile);
+    else tmp2.reserve(&bucket, S);
     tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 3);
     int2 *rest = nullptr;  // an entry per kFillRounds nonzeros of a group's longest row at most
     if (cut) tmp2.reserve(&rest, nnz / kFillRounds + 1);
@@ -2087,30 +2599,39 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_TRY(exclusive_scans(Scans{{unit_cnt, unit_cnt}, {(uint32_t *)h->unit_ptr, multi_idx}, {kOpIdentity, kOpAboveOne}}, 2, NBR, 1, scan_tmp, st));
     k_unit_fill<<<blocks_for(NBR, 256), 256, 0, st>>>(h->stripe_ptr, stripe_cum, h->unit_ptr, multi_idx, (int32_t)NBR, (int32_t)B,
                                                      h->unit_stripe, h->unit_k, h->multi_stripes);
-    // steps 5-6 (slot_off doubles as the per-block cursor from here on)
-    const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
-    if (listed) {
-        // a wavefront per tile where it holds few segments, up to eight where it holds many
-        int32_t wavefronts = 1;
-        while (wavefronts < kTileThreads / 64 && S > 256 * wavefronts * n_tiles) wavefronts *= 2;
-        k_place<<<blocks_for(n_tiles * wavefronts, kTileThreads / 64), kTileThreads, 0, st>>>(
-            csr_ptr, n_rows, nnz, R, shift_r, (int32_t)NBR, (int32_t)NBC, (int32_t)n_tiles, wavefronts, tiles, list, row_bits, slot_off, bucket);
-    } else {
-        const auto second_pass = pow2 ? k_segments<Pass::kEmit, true> : k_segments<Pass::kEmit, false>;
-        second_pass<<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
-                                                                      (int32_t)NBC, 0, tiles, slot_off, bucket, nullptr, row_bits, found);
-    }
     const dim3 stripe_grid((unsigned)(8 * ((NBR + 7) / 8) * std::max(parts, 1)));
-    const size_t order_cap = ((size_t)R + 63) & ~(size_t)63;
-    size_t small_n2 = 1;  // the bitonic network of a small block: 8-byte words, the next power of two above min(R, 256) slots
-    while (small_n2 < (size_t)std::min(R, 256)) small_n2 <<= 1;
-    const size_t order_lds = std::max(sizeof(uint32_t) * (2 * order_cap + 16 * (order_cap / 64)),  // two entry arrays, 16 counters per tile
-                                      sizeof(uint64_t) * small_n2);
-    HBP_HIP(hipFuncSetAttribute((const void *)k_order_block, hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds));
-    k_order_block<<<dim3((unsigned)B), 256, order_lds, st>>>(bucket, h->slot_ptr, h->blk_group_ptr, W,
-                                                            h->row_local, h->seg_len, slot_j, group_nnz, group_longest, h->group_slot,
-                                                            h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all,
-                                                            d_n_long, h->long_groups, h->flat_wpg, reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);
+    // steps 5-6 (slot_off doubles as the per-block cursor from here on, but for row blocks as a whole)
+    if (by_panel) {
+        HBP_HIP(hipFuncSetAttribute((const void *)k_panel_slots, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
+        // rounds behind the table's, ten bytes each: as many as there is room for, up to what rows of 8 to 50 nonzeros beside one of each in every group take
+        const uint32_t most_tails = (uint32_t)std::min<size_t>(3072, ((size_t)kPanelLds - slots_table) / 10) & ~3u;
+        k_panel_slots<<<dim3((unsigned)NBR), kPanelThreads, std::max(slots_lds, slots_table + 10 * (size_t)most_tails), st>>>(
+            csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, tiles, words.starts, words.at, list, row_bits, slot_off, group_off, blk_id, (uint32_t)a,
+            (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all, h->row_local, h->seg_len, h->slot_key, group_nnz, group_longest,
+            h->group_slot, h->group_blk, h->blk_shift, places, slot_j, most_tails);
+    } else {
+        if (listed) {
+            // a wavefront per tile where it holds few segments, up to eight where it holds many
+            int32_t wavefronts = 1;
+            while (wavefronts < kTileThreads / 64 && S > 256 * wavefronts * n_tiles) wavefronts *= 2;
+            k_place<<<blocks_for(n_tiles * wavefronts, kTileThreads / 64), kTileThreads, 0, st>>>(
+                csr_ptr, n_rows, nnz, R, shift_r, (int32_t)NBR, (int32_t)NBC, (int32_t)n_tiles, wavefronts, tiles, list, row_bits, slot_off, bucket);
+        } else {
+            const auto second_pass = pow2 ? k_segments<Pass::kEmit, true> : k_segments<Pass::kEmit, false>;
+            second_pass<<<dim3((unsigned)n_tiles), kTileThreads, 0, st>>>(csr_ptr, csr_col, n_rows, nnz, n_cols, R, shift_r, C, shift_c, (int32_t)NBR,
+                                                                          (int32_t)NBC, 0, tiles, slot_off, bucket, nullptr, row_bits, SegmentWords{nullptr, nullptr}, found);
+        }
+        const size_t order_cap = ((size_t)R + 63) & ~(size_t)63;
+        size_t small_n2 = 1;  // the bitonic network of a small block: 8-byte words, the next power of two above min(R, 256) slots
+        while (small_n2 < (size_t)std::min(R, 256)) small_n2 <<= 1;
+        const size_t order_lds = std::max(sizeof(uint32_t) * (2 * order_cap + 16 * (order_cap / 64)),  // two entry arrays, 16 counters per tile
+                                          sizeof(uint64_t) * small_n2);
+        HBP_HIP(hipFuncSetAttribute((const void *)k_order_block, hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds));
+        k_order_block<<<dim3((unsigned)B), 256, order_lds, st>>>(bucket, h->slot_ptr, h->blk_group_ptr, W,
+                                                                h->row_local, h->seg_len, slot_j, group_nnz, group_longest, h->group_slot,
+                                                                h->group_blk, (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all,
+                                                                d_n_long, h->long_groups, h->flat_wpg, reorder, (uint32_t)R, d_a, h->blk_shift, h->slot_key);
+    }
     HBP_TRY(exclusive_scans(Scans{{group_nnz, group_longest}, {(uint32_t *)h->group_ptr, (uint32_t *)h->group_rounds}, {kOpIdentity, kOpIdentity}}, 2,
                             G, 1, scan_tmp, st));
     k_set_i32<<<1, 64, 0, st>>>(h->group_slot + G, (int32_t)S);
@@ -2120,6 +2641,14 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_HIP(hipMemsetAsync((char *)h->data + (size_t)nnz * h->value_bytes, 0, 256 * (size_t)h->value_bytes, st));
     auto fill = [&](const auto *val, auto *data) {
         using T = std::remove_reference_t<decltype(*data)>;
+        if (by_panel) {
+            const uint32_t room = (uint32_t)(kLdsPerCu / (int)(sizeof(T) + sizeof(uint16_t)));
+            const int32_t shares = (int32_t)std::max<int64_t>(1, (most_nonzeros + room - 1) / room);
+            (void)hipFuncSetAttribute((const void *)k_panel_fill<T>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
+            k_panel_fill<T><<<dim3((unsigned)(8 * ((NBR + 7) / 8) * shares)), kPanelThreads, room * (sizeof(T) + sizeof(uint16_t)), st>>>(
+                csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, C, shares, room, places, csr_col, val, group_off, h->group_ptr, h->col_local, data);
+            return;
+        }
         if (parts > 0) {
             k_fill<T><<<stripe_grid, 256, 0, st>>>(h->stripe_ptr, h->stripe_blk, (int32_t)NBR, (int32_t)B, parts, csr_col, val, h->group_ptr,
                                                    h->group_slot, h->blk_group_ptr, h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, data);

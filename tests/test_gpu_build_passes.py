@@ -52,3 +52,53 @@ def test_tiles_over_many_row_blocks(H, oracle, every, R, C):
     lens = np.zeros(3000 * every, dtype=np.int64)[:400_000]
     lens[::every] = np.random.default_rng(3).integers(1, 6, lens[::every].size)
     check_against_oracle(H, oracle, matrix(lens, 300), rows_per_block=R, cols_per_block=C)
+
+
+def quick(lens, n_cols, seed, f64, long=()):
+    """Like `matrix`, for many rows: columns drawn with replacement and merged; `long`: (row, first column, columns) runs of neighbouring
+    columns in place of a row's own."""
+    rng = np.random.default_rng(seed)
+    lens = np.asarray(lens, dtype=np.int64)
+    rows = np.repeat(np.arange(lens.size, dtype=np.int64), lens)
+    keys = rows * n_cols + rng.integers(0, n_cols, rows.size)
+    for r, c0, n in long:
+        keys = np.concatenate([keys[keys // n_cols != r], r * n_cols + np.arange(c0, c0 + n)])
+    keys = np.unique(keys)
+    ptr = np.searchsorted(keys, np.arange(lens.size + 1) * n_cols).astype(np.int32)
+    dt = np.float64 if f64 else np.float32
+    return CsrMatrix("row blocks", lens.size, n_cols, ptr, (keys % n_cols).astype(np.int32), rng.standard_normal(keys.size).astype(dt),
+                     rng.uniform(-1, 1, n_cols).astype(dt))
+
+
+# Row blocks as a whole: 128 and more of them, rows short in every block column, blocks of 256 slots on average.  One to 64 block columns, block
+# sizes that are no powers of two, ragged last blocks, row blocks without a nonzero and tiles over several row blocks, every shift that fits and one that does
+# not (which goes the other way, like 64 block columns at a = 1).
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("R,n_rows,C,n_cols,mean,shift", [
+    (512, 512 * 127 + 1, 900, 900, 3, -1), (512, 512 * 127, 900, 900, 3, -1),
+    (512, 66_000, 300, 599, 6, 0), (700, 90_001, 500, 2_500, 9, 1), (512, 66_000, 64, 4_096, 62, 0), (512, 66_000, 64, 4_096, 62, 1),
+    (1000, 130_000, 333, 1_000, 6, 2), (2048, 270_000, 700, 4_000, 9, 3), (2048, 270_000, 700, 4_000, 9, -1), (2047, 262_016, 32, 64, 5, 6),
+])
+def test_row_blocks_as_a_whole(H, oracle, R, n_rows, C, n_cols, mean, shift, f64):
+    rng = np.random.default_rng(R + n_cols)
+    lens = rng.poisson(mean, n_rows)
+    lens[R * 5:R * 7] = 0
+    lens[R * 20 + 3:R * 20 + 40] = 0
+    m = quick(lens, n_cols, 5, f64)
+    check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=R, cols_per_block=C, rounds_per_batch=4, hash_shift=shift)
+
+
+# Row blocks in one and several shares (an fp32 share holds 25,941 nonzeros, an fp64 one 15,564), groups that lie in two of them, rows
+# of up to a block's width, alone and 70 in a row, at rounds around the 64 that a wavefront writes alone and the turns of 32 behind them.
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("long", [
+    [(9, 0, 63), (70, 5, 64), (90, 600, 65), (2100, 0, 96), (2200, 0, 97), (4200, 7, 576), (5000, 7, 577)],
+    [(r, 10 * (r % 50), 1500) for r in range(100, 170)], [(300, 0, 3000), (301, 0, 3000), (302, 0, 2999), (303, 1, 1)],
+    [(r, 0, 700) for r in range(600, 650)],       # more nonzeros than a row block may have: the other way
+])
+@pytest.mark.parametrize("mean", [6, 13])
+def test_shares_of_row_blocks(H, oracle, long, mean, f64):
+    lens = np.random.default_rng(mean).poisson(mean, 262_145)
+    m = quick(lens, 3_000, 6, f64, long)
+    for R in (2048, 1024):
+        check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=R, cols_per_block=600, rounds_per_batch=4)
