@@ -526,7 +526,9 @@ __device__ __forceinline__ int32_t highest_up_to_lane(int32_t v)
 // v with `value` (the same in all lanes) in place of what lane `l` (a constant) holds
 __device__ __forceinline__ int32_t with_lane(int32_t value, int32_t l, int32_t v)
 {
-    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(value), "i"(l));
+    // (a vector instruction that reads a scalar register which another has written, as a ballot does, has to stay two wait states behind it; the
+    // compiler sees to that, but does not look into assembly)
+    asm("s_nop 1\n\tv_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(value), "i"(l));
     return v;
 }
 // the value of the lane below; lane 0 gets `first`
@@ -1432,7 +1434,8 @@ constexpr int kPanelThreads = 1024, kPanelWaves = kPanelThreads / 64;
 constexpr int kPanelRows = 2048, kPanelColumns = 64;
 constexpr int kPanelPer = 32, kPanelSlots = kPanelPer * kPanelThreads;  // segments of a row block at most
 constexpr int kPanelNonzeros = 1 << 16;                                 // its nonzeros at most: places of 16 bits, and in 64 tiles
-constexpr int kPanelLds = 154 * 1024;                                   // dynamic LDS of k_panel_slots at most (its own arrays: below 6 KB)
+constexpr int kPanelLds = 148 * 1024;                                   // dynamic LDS of k_panel_slots at most (its own arrays: below 12 KB)
+constexpr int kPanelTails = 12288;                                      // rounds in its list of tails at most: what a workgroup asks for of the LDS
 constexpr int kPanelShift = 2;                                          // a at most: a band of 64 rows and more keeps 4 remainders apart
 constexpr int kPanelLeast = 128;                                        // row blocks, at least: fewer leave the device idle
 constexpr int kPanelLongest = 16384;                                    // longest row where segments are long
@@ -1496,8 +1499,11 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     __shared__ uint32_t sh_slot[kPanelColumns + 1], sh_group[kPanelColumns + 1];  // slots and groups of the row block in front of a block column
     __shared__ uint32_t sh_first[kPanelColumns];                                  // the block's first slot
     constexpr int kGroups = kPanelSlots / 64 + kPanelColumns;
-    __shared__ uint32_t sh_sum[kGroups];  // nonzeros of a group; nonzeros in front of it
-    __shared__ uint32_t sh_tail_rounds, sh_tails_n;
+    __shared__ uint32_t sh_sum[kGroups];    // nonzeros of a group; nonzeros in front of it
+    __shared__ uint16_t sh_longest[kGroups];
+    __shared__ uint16_t sh_shorter[kPanelColumns << (3 + kPanelShift)];  // of a block, for each k below `head`: rows of up to k nonzeros
+    __shared__ uint32_t sh_tail_rounds, sh_tails_n, sh_uneven_n;
+    __shared__ uint16_t sh_uneven[kGroups];  // groups with rows of `head` nonzeros and more
     __shared__ uint16_t sh_tails[kGroups];  // groups with more rounds than the table and the list of tails hold
     const int32_t bm = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1511,33 +1517,37 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     if (wave == 0) {
         sh_slot[lane + 1] = slots_upto;
         sh_group[lane + 1] = groups_upto;
-        if (lane == 0) sh_slot[0] = sh_group[0] = sh_tail_rounds = sh_tails_n = 0u;
+        if (lane == 0) sh_slot[0] = sh_group[0] = sh_tail_rounds = sh_tails_n = sh_uneven_n = 0u;
         sh_first[lane] = s0;
         if (slots) blk_shift[id] = (int32_t)a;
     }
-    // the segments: u-th of this lane the (64 (16 u + wave) + lane)-th of the row block
+    // the segments: a wavefront takes `turns` times 64 neighbouring ones
     uint32_t x[kPanelPer], y[kPanelPer];
+    const uint32_t turns = (total + kPanelThreads - 1) / kPanelThreads;
+    const uint32_t first0 = 64u * turns * (uint32_t)wave;
+    uint32_t i0 = first0 + (uint32_t)lane;  // the u-th: i0 + 64 u
     // (between the phases: what one has computed of x and y is not kept in registers for the next)
     auto forget = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kPanelPer; u++) asm volatile("" : "+v"(x[u]), "+v"(y[u]));
+        asm volatile("" : "+v"(i0));
     };
-    auto first_of = [&](int u) { return (uint32_t)(64 * (kPanelWaves * u + wave)); };
+    auto there = [&](int u) { return (uint32_t)u < turns && i0 + 64u * u < total; };
     const uint32_t *const here = list + (int64_t)p.t0 * kTile;
+    int32_t tile = min(__popcll(__ballot(p.upto <= first0)), 63);
+    uint32_t begin = tile > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)p.upto, tile > 0 ? tile - 1 : 0) : 0u;
+    uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, tile);
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++) {  // where in the list
-        const uint32_t first = first_of(u), i = first + lane;
+        const uint32_t first = first0 + 64u * u, i = i0 + 64u * u;
         y[u] = p.skip;
-        if (first >= total) continue;
-        int32_t t = __popcll(__ballot(p.upto <= first));
-        uint32_t begin = t > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t > 0 ? t - 1 : 0) : 0u;
-        uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t);
-        uint32_t at = (uint32_t)t * kTile + i - begin;
+        if ((uint32_t)u >= turns || first >= total) continue;
+        uint32_t at = (uint32_t)tile * kTile - begin + i;
         while (end < min(first + 64u, total)) {  // wave-uniform
-            t++;
+            tile++;
             begin = end;
-            end = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, t);
-            if (i >= begin) at = (uint32_t)t * kTile + i - begin;
+            end = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, tile);
+            if (i >= begin) at = (uint32_t)tile * kTile - begin + i;
         }
         if (at < (uint32_t)kTile) at += p.skip;
         if (i < total) y[u] = at;
@@ -1545,7 +1555,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++) {
         x[u] = 0u;
-        if (first_of(u) < total) x[u] = lane_at(here, y[u]);
+        if ((uint32_t)u < turns) x[u] = lane_at(here, y[u]);
     }
     forget();  // (all loads are on their way at once)
 #pragma unroll
@@ -1553,7 +1563,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
         const uint32_t e = x[u], bn = e >> kPlaceBits >> row_bits, row = e >> kPlaceBits & ((1u << row_bits) - 1u);
         y[u] = (uint32_t)p.t0 * kTile + (y[u] & ~(uint32_t)(kTile - 1)) + (e & (kTile - 1)) - p.p0;
         x[u] = bn << 11 | row;
-        if (first_of(u) + lane < total) panel_lds[first_of(u) + lane] = y[u];
+        if (there(u)) panel_lds[i0 + 64u * u] = y[u];
     }
     __syncthreads();
     forget();
@@ -1564,8 +1574,8 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     };
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++) {
-        const uint32_t i = first_of(u) + lane;
-        if (i < total) x[u] |= ((i + 1 < total ? panel_lds[i + 1] : p.p1 - p.p0) - y[u] - 1u) << 17;
+        const uint32_t i = i0 + 64u * u;
+        if (there(u)) x[u] |= ((i + 1 < total ? panel_lds[i + 1] : p.p1 - p.p0) - y[u] - 1u) << 17;
         y[u] |= word_of(x[u]) << 18;  // (below 2^14: ten bytes each fit the LDS)
     }
     __syncthreads();
@@ -1577,7 +1587,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     forget();
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++)
-        if (first_of(u) + lane < total) (void)atomicOr(panel_lds + 2 * (y[u] >> 18) + (x[u] >> 5 & 1u), 1u << (x[u] & 31u));
+        if (there(u)) (void)atomicOr(panel_lds + 2 * (y[u] >> 18) + (x[u] >> 5 & 1u), 1u << (x[u] & 31u));
     __syncthreads();
     forget();
     const uint32_t per = (words + 63) / 64;
@@ -1594,9 +1604,12 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     }
     __syncthreads();
     forget();
+    const int32_t head = 8 << a;
+    for (uint32_t i = threadIdx.x; i < (uint32_t)NBC * (uint32_t)head; i += kPanelThreads)
+        sh_shorter[i] = before[(i >> (3u + a)) * words + (i & (uint32_t)(head - 1)) * row_words];
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++)
-        if (first_of(u) + lane < total) {
+        if (there(u)) {
             const uint32_t w = y[u] >> 18;
             y[u] = (y[u] & 0x3ffffu) | (before[w] + (uint32_t)__popcll(bits[w] & ((1ull << (x[u] & 63u)) - 1ull))) << 18;
         }
@@ -1604,82 +1617,122 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     forget();
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++)
-        if (first_of(u) + lane < total) panel_lds[sh_slot[x[u] >> 11 & 63u] + (y[u] >> 18)] = (x[u] & 2047u) << 16 | ((x[u] >> 17) + 1u);
+        if (there(u)) panel_lds[sh_slot[x[u] >> 11 & 63u] + (y[u] >> 18)] = (x[u] & 2047u) << 16 | ((x[u] >> 17) + 1u);
     __syncthreads();
     forget();
-    // a wavefront per group
     const uint32_t all_groups = (uint32_t)__builtin_amdgcn_readlane((int)groups_upto, 63);
-    const int32_t head = 8 << a;
     const uint32_t stride = panel_table_row(a) / 2u;
     // behind the slots, or what takes their place: lanes and places of the rounds behind the first `head`; the table
     uint64_t *const tail_lanes = reinterpret_cast<uint64_t *>(panel_lds + ((total + 1u) & ~1u));
     uint16_t *const tail_places = reinterpret_cast<uint16_t *>(tail_lanes + most_tails), *const table = tail_places + most_tails;
+    auto block_of = [&](uint32_t gi) __attribute__((always_inline)) {
+        int bn = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1)
+            if (sh_group[bn + step] <= gi) bn += step;
+        return bn;
+    };
+    // the slots' arrays, a wavefront per group
     for (uint32_t gi = wave; gi < all_groups; gi += kPanelWaves) {
         const int bn = __popcll(__ballot(groups_upto <= gi));
         const uint32_t q0 = 64u * (gi - (uint32_t)__builtin_amdgcn_readlane((int)(groups_upto - groups), bn));  // the group's first slot in its block
         const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)(slots_upto - slots), bn) + q0;             // and in the row block
-        const uint32_t count = min((uint32_t)__builtin_amdgcn_readlane((int)slots, bn) - q0, 64u);
-        const uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)s0, bn) + q0, g = (uint32_t)__builtin_amdgcn_readlane((int)g0, bn) + q0 / 64u;
-        const bool valid = (uint32_t)lane < count;
-        const uint32_t v = valid ? panel_lds[at + lane] : 0u, n = v & 0xffffu;
-        if (valid) {
+        const uint32_t slot = (uint32_t)__builtin_amdgcn_readlane((int)s0, bn) + q0;
+        if ((uint32_t)lane < (uint32_t)__builtin_amdgcn_readlane((int)slots, bn) - q0) {
+            const uint32_t v = panel_lds[at + lane];
             lane_at(row_local + slot, lane) = (uint16_t)(v >> 16);
-            lane_at(seg_len + slot, lane) = (uint16_t)n;
-            if (slot_key) lane_at(slot_key + slot, lane) = hash_key(n, a, (uint32_t)R / 9u, (uint32_t)R);
+            lane_at(seg_len + slot, lane) = (uint16_t)v;
+            if (slot_key) lane_at(slot_key + slot, lane) = hash_key(v & 0xffffu, a, (uint32_t)R / 9u, (uint32_t)R);
         }
-        uint32_t longest = (uint32_t)__builtin_amdgcn_readlane((int)n, (int)count - 1);
-        if (longest >= (uint32_t)head) longest = wave_max(n);
-        // the table's row, from the group's first nonzero on: the rounds' places less the lanes that have none
-        int32_t base = -(int32_t)count;
-        for (int32_t k = 0; k < head && k < (int32_t)longest; k += 8) {  // wave-uniform
-            int32_t entry = 0;
-#pragma unroll
-            for (int t = 0; t < 8; t++) {
-                base += __popcll(__builtin_amdgcn_ballot_w64((int32_t)n > k + t));
-                entry = with_lane(base, t, entry);
-            }
-            if (lane < 8) table[gi * stride + (uint32_t)(k + lane)] = (uint16_t)entry;
+    }
+    // The table, an entry per lane, 64 / head groups at a time: from the group's first nonzero on, the round's place less the lanes that have none.
+    for (uint32_t i0 = 64u * (uint32_t)wave; i0 < all_groups * (uint32_t)head; i0 += kPanelThreads) {
+        const uint32_t i = i0 + (uint32_t)lane, gi = min(i >> (3u + a), all_groups - 1u), k = i & (uint32_t)(head - 1);
+        const int bn = block_of(gi);
+        const int32_t q0 = 64 * (int32_t)(gi - sh_group[bn]), count = min((int32_t)(sh_slot[bn + 1] - sh_slot[bn]) - q0, 64);
+        const int32_t shorter = (int32_t)sh_shorter[((uint32_t)bn << (3u + a)) + k] - q0, none = min(max(shorter, 0), count);
+        int32_t upto = count - none;  // nonzeros of the rounds up to this one
+        for (int32_t d = 1; d < head; d <<= 1) {
+            const int32_t t = __shfl_up(upto, d);
+            if ((int32_t)k >= d) upto += t;
         }
-        uint32_t sum = (uint32_t)(base + (int32_t)count);
-        if (longest > (uint32_t)head) {
-            const uint32_t rounds = longest - (uint32_t)head;
-            uint32_t tail = 0;
-            if (lane == 0) tail = atomicAdd(&sh_tail_rounds, rounds);
-            tail = (uint32_t)__builtin_amdgcn_readfirstlane((int)tail);
-            const bool room = tail + rounds <= most_tails;
-            if (lane == 0) {
-                table[gi * stride + (uint32_t)head] = room ? (uint16_t)tail : (uint16_t)0xffffu;
-                if (!room) sh_tails[atomicAdd(&sh_tails_n, 1u)] = (uint16_t)gi;
-            }
-            if (room) {
-                for (uint32_t i = 0; i < rounds; i += 8) {
-                    int32_t lanes_lo = 0, lanes_hi = 0, begin = 0;
-#pragma unroll
-                    for (int t = 0; t < 8; t++) {
-                        const uint64_t live = __builtin_amdgcn_ballot_w64((int32_t)n > head + (int32_t)i + t);
-                        lanes_lo = with_lane((int32_t)(uint32_t)live, t, lanes_lo);
-                        lanes_hi = with_lane((int32_t)(live >> 32), t, lanes_hi);
-                        begin = with_lane((int32_t)sum, t, begin);
-                        sum += (uint32_t)__popcll(live);
-                    }
-                    if (lane < 8 && i + (uint32_t)lane < rounds) {
-                        tail_lanes[tail + i + (uint32_t)lane] = (uint64_t)(uint32_t)lanes_hi << 32 | (uint32_t)lanes_lo;
-                        tail_places[tail + i + (uint32_t)lane] = (uint16_t)begin;
-                    }
-                }
-            } else {
-                sum = wave_sum(n);
+        const uint64_t longer = __ballot(shorter < count);  // a row has more than k nonzeros
+        const uint32_t longest = (uint32_t)__popcll(longer >> (lane & ~(head - 1)) & ((1ull << head) - 1ull));
+        if (i < all_groups * (uint32_t)head) {
+            table[gi * stride + k] = (uint16_t)(upto - (count - none) - none);
+            if (k == (uint32_t)head - 1u) {
+                sh_sum[gi] = (uint32_t)upto;
+                sh_longest[gi] = (uint16_t)longest;
+                if (longest == (uint32_t)head) sh_uneven[atomicAdd(&sh_uneven_n, 1u)] = (uint16_t)gi;
             }
         }
+    }
+    __syncthreads();
+    // groups with rows of `head` nonzeros and more: their longest row and place in the list of tails
+    auto lengths_of = [&](uint32_t gi) __attribute__((always_inline)) {  // gi the same in all lanes
+        const int bn = __popcll(__ballot(groups_upto <= gi));
+        const uint32_t q0 = 64u * (gi - (uint32_t)__builtin_amdgcn_readlane((int)(groups_upto - groups), bn));
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)(slots_upto - slots), bn) + q0;
+        return (int32_t)((uint32_t)lane < (uint32_t)__builtin_amdgcn_readlane((int)slots, bn) - q0 ? panel_lds[at + lane] & 0xffffu : 0u);
+    };
+    const uint32_t uneven = sh_uneven_n;
+    for (uint32_t i = wave; i < uneven; i += kPanelWaves) {
+        const uint32_t gi = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_uneven[i]);
+        const uint32_t n = (uint32_t)lengths_of(gi), longest = wave_max(n), rounds = longest - (uint32_t)head, sum = wave_sum(n);
         if (lane == 0) {
             sh_sum[gi] = sum;
-            group_nnz[g] = sum;
-            group_longest[g] = longest;
-            if (longest > heavy_rounds && longest > __hip_atomic_load(longest_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                atomicMax(longest_all, longest);
-            group_slot[g] = (int32_t)slot;
-            group_blk[g] = (int32_t)__builtin_amdgcn_readlane((int)id, bn);
+            sh_longest[gi] = (uint16_t)longest;
+            const uint32_t tail = rounds ? atomicAdd(&sh_tail_rounds, rounds) : 0u;
+            const bool room = tail + rounds <= most_tails;
+            table[gi * stride + (uint32_t)head] = room ? (uint16_t)tail : (uint16_t)0xffffu;
+            if (!room) sh_tails[atomicAdd(&sh_tails_n, 1u)] = (uint16_t)gi;
         }
+    }
+    __syncthreads();
+    forget();
+    // the list of tails, the wavefronts taking 64 rounds of a group in turn
+    for (uint32_t b0 = 0; b0 < uneven; b0 += 64) {
+        const uint32_t mine = sh_uneven[min(b0 + (uint32_t)lane, uneven - 1u)], tail_of = table[mine * stride + (uint32_t)head];
+        const uint32_t rounds_of = b0 + (uint32_t)lane < uneven && tail_of != 0xffffu ? sh_longest[mine] - (uint32_t)head : 0u;
+        const uint32_t pieces = (rounds_of + 63u) / 64u, pieces_upto = sum_up_to_lane(pieces), all = (uint32_t)__builtin_amdgcn_readlane((int)pieces_upto, 63);
+        for (uint32_t piece = wave; piece < all; piece += kPanelWaves) {
+            const int l = __popcll(__ballot(pieces_upto <= piece));
+            const uint32_t r0 = 64u * (piece - (uint32_t)__builtin_amdgcn_readlane((int)(pieces_upto - pieces), l));
+            const uint32_t r1 = min((uint32_t)__builtin_amdgcn_readlane((int)rounds_of, l), r0 + 64u), tail = (uint32_t)__builtin_amdgcn_readlane((int)tail_of, l);
+            const int32_t n = lengths_of((uint32_t)__builtin_amdgcn_readlane((int)mine, l));
+            uint32_t at = wave_sum((uint32_t)min(n, head + (int32_t)r0));
+            for (uint32_t r = r0; r < r1; r += 8) {
+                int32_t lanes_lo = 0, lanes_hi = 0, begin = 0;
+#pragma unroll
+                for (int t = 0; t < 8; t++) {
+                    const uint64_t live = __builtin_amdgcn_ballot_w64(n > head + (int32_t)r + t);
+                    lanes_lo = with_lane((int32_t)(uint32_t)live, t, lanes_lo);
+                    lanes_hi = with_lane((int32_t)(live >> 32), t, lanes_hi);
+                    begin = with_lane((int32_t)at, t, begin);
+                    at += (uint32_t)__popcll(live);
+                }
+                if (lane < 8 && r + (uint32_t)lane < r1) {
+                    tail_lanes[tail + r + (uint32_t)lane] = (uint64_t)(uint32_t)lanes_hi << 32 | (uint32_t)lanes_lo;
+                    tail_places[tail + r + (uint32_t)lane] = (uint16_t)begin;
+                }
+            }
+        }
+    }
+    // the groups' numbers, 64 groups at a time
+    for (uint32_t b0 = 64u * (uint32_t)wave; b0 < all_groups; b0 += kPanelThreads) {
+        const uint32_t gi = min(b0 + (uint32_t)lane, all_groups - 1u), longest = sh_longest[gi];
+        const int bn = block_of(gi);
+        const uint32_t in_block = gi - sh_group[bn], g = (uint32_t)__shfl((int)g0, bn) + in_block;
+        const int32_t block = __shfl((int)id, bn);
+        if (b0 + (uint32_t)lane < all_groups) {
+            group_nnz[g] = sh_sum[gi];
+            group_longest[g] = longest;
+            group_slot[g] = (int32_t)(sh_first[bn] + 64u * in_block);
+            group_blk[g] = block;
+        }
+        const uint32_t most = wave_max(longest);  // only that long rows matter to the caller
+        if (lane == 0 && most > heavy_rounds && most > __hip_atomic_load(longest_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(longest_all, most);
     }
     __syncthreads();
     forget();
@@ -1693,9 +1746,9 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     }
 #pragma unroll
     for (int u = 0; u < kPanelPer; u++) {
-        const uint32_t i = first_of(u) + lane, bn = x[u] >> 11 & 63u, q = y[u] >> 18, j = y[u] & 0x3ffffu;
-        if (i < total) {
-            panel_lds[i] = (64u * sh_group[bn] + q) << 16 | (j & 0xffffu);
+        const uint32_t bn = x[u] >> 11 & 63u, q = y[u] >> 18, j = y[u] & 0x3ffffu;
+        if (there(u)) {
+            panel_lds[i0 + 64u * u] = (64u * sh_group[bn] + q) << 16 | (j & 0xffffu);
             if ((x[u] >> 17) >= (uint32_t)head) slot_j[sh_first[bn] + q] = (int32_t)(p.p0 + j);
         }
     }
@@ -2603,8 +2656,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // steps 5-6 (slot_off doubles as the per-block cursor from here on, but for row blocks as a whole)
     if (by_panel) {
         HBP_HIP(hipFuncSetAttribute((const void *)k_panel_slots, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
-        // rounds behind the table's, ten bytes each: as many as there is room for, up to what rows of 8 to 50 nonzeros beside one of each in every group take
-        const uint32_t most_tails = (uint32_t)std::min<size_t>(3072, ((size_t)kPanelLds - slots_table) / 10) & ~3u;
+        // rounds behind the table's, ten bytes each, as many as there is room for
+        const uint32_t most_tails = (uint32_t)std::min<size_t>(kPanelTails, ((size_t)kPanelLds - slots_table) / 10) & ~3u;
         k_panel_slots<<<dim3((unsigned)NBR), kPanelThreads, std::max(slots_lds, slots_table + 10 * (size_t)most_tails), st>>>(
             csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, tiles, words.starts, words.at, list, row_bits, slot_off, group_off, blk_id, (uint32_t)a,
             (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all, h->row_local, h->seg_len, h->slot_key, group_nnz, group_longest,
