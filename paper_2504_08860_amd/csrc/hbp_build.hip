@@ -771,10 +771,11 @@ void k_segments(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col
     }
 }
 
-// Drops the segments of the list into their blocks' slot ranges: `parts` wavefronts to a tile, a lane per segment.  A segment's row block is
+// Drops the segments of the list into their blocks' slot ranges: `parts` wavefronts to a tile (ALL: all of the workgroup), a lane per segment.  A segment's row block is
 // the last one that begins at or before its first nonzero.
 // (Bound by the stores, 8 bytes to a line of their own for most lanes, where segments are short; by a tile's chain of loads where they are long,
 // hence several tiles to a workgroup there.)
+template <bool ALL>
 __global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restrict__ ptr, int64_t n_rows, int64_t nnz, int32_t R, int32_t shift_r,
                                                         int32_t NBR, int32_t NBC, int32_t n_tiles, int32_t parts, const Tile *__restrict__ tiles,
                                                         const uint32_t *__restrict__ list, int32_t row_bits, uint32_t *__restrict__ cursor,
@@ -783,6 +784,7 @@ __global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restric
     constexpr int kWaves = kTileThreads / 64;
     __shared__ uint32_t cnt[kTileCounters];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (ALL) parts = kWaves;
     const int32_t here = kWaves / parts, t0 = (int32_t)blockIdx.x * here, t = t0 + wave / parts, part = wave % parts;
     auto row_block = [&](int32_t row) { return shift_r >= 0 ? row >> shift_r : row / R; };
     // the row block that holds the first nonzero of tile i, or the last one behind the last tile
@@ -809,11 +811,32 @@ __global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restric
         }
         return lo;
     };
+    auto counter_of = [&](uint32_t e, int32_t bm) { return (int32_t)__umul24((uint32_t)(bm - bm_lo), (uint32_t)NBC) + (int32_t)(e >> kPlaceBits >> row_bits); };
+    // ALL: a lane's segments stay in registers between the two passes, with their ranks in the tile
+    constexpr int kPer = ALL ? kTile / kTileThreads : 1;
+    uint32_t kept[kPer];
+    int32_t kept_at[kPer];  // counter << 12 | rank
     if (in_lds) {
-        for (int32_t i = part * 64 + lane; i < count; i += 64 * parts) {
-            const uint32_t e = mine[i];
-            const int32_t bm = block_of(j0 + (e & (kTile - 1)));
-            atomicAdd(&cnt[(int32_t)__umul24((uint32_t)(bm - bm_lo), (uint32_t)NBC) + (int32_t)(e >> kPlaceBits >> row_bits)], 1u);
+        if constexpr (ALL) {
+#pragma unroll
+            for (int u = 0; u < kPer; u++) {
+                const int32_t i = kTileThreads * u + (int32_t)threadIdx.x;
+                kept[u] = i < count ? lane_at(mine, i) : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kPer; u++) {
+                const int32_t i = kTileThreads * u + (int32_t)threadIdx.x;
+                kept_at[u] = 0;
+                if (i < count) {
+                    const int32_t at = counter_of(kept[u], block_of(j0 + (kept[u] & (kTile - 1))));
+                    kept_at[u] = at << 12 | (int32_t)atomicAdd(&cnt[at], 1u);  // (fewer than 4096 in front of the last)
+                }
+            }
+        } else {
+            for (int32_t i = part * 64 + lane; i < count; i += 64 * parts) {
+                const uint32_t e = mine[i];
+                atomicAdd(&cnt[counter_of(e, block_of(j0 + (e & (kTile - 1))))], 1u);
+            }
         }
         __syncthreads();
         for (int i = threadIdx.x; i < (int)counters; i += kTileThreads) {
@@ -827,6 +850,19 @@ __global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restric
     const int32_t f = next_tile < n_tiles ? tiles[next_tile].first : (int32_t)nnz;
     const uint64_t there = __ballot(f >= 0);
     const uint32_t next = there ? (uint32_t)__builtin_amdgcn_readlane(f, __builtin_ctzll(there)) : (uint32_t)nnz;
+    if constexpr (ALL) {
+        if (in_lds) {
+#pragma unroll
+            for (int u = 0; u < kPer; u++) {
+                const int32_t i = kTileThreads * u + (int32_t)threadIdx.x;
+                if (i >= count) break;
+                const uint32_t e = kept[u], j = j0 + (e & (kTile - 1));
+                const uint32_t end = i + 1 < count ? j0 + (lane_at(mine, i + 1) & (kTile - 1)) : next;
+                bucket[cnt[kept_at[u] >> 12] + (uint32_t)(kept_at[u] & 4095)] = {(end - j) << 16 | (e >> kPlaceBits & (uint32_t)row_mask), j};
+            }
+            return;
+        }
+    }
     for (int32_t i0 = part * 64; i0 < count; i0 += 64 * parts) {  // wave-uniform
         const int32_t i = i0 + lane;
         const bool valid = i < count;
@@ -835,7 +871,7 @@ __global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restric
         const int32_t bm = valid ? block_of(j) : tile_lo, bn = (int32_t)(e >> kPlaceBits >> row_bits);
         uint32_t pos = 0;
         if (in_lds) {
-            if (valid) pos = atomicAdd(&cnt[(int32_t)__umul24((uint32_t)(bm - bm_lo), (uint32_t)NBC) + bn], 1u);
+            if (valid) pos = atomicAdd(&cnt[counter_of(e, bm)], 1u);
         } else {
             pos = aggregated_add(cursor, valid ? (int64_t)bn * NBR + bm : 0, valid);
         }
@@ -2513,7 +2549,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const bool listed = kPlaceBits + row_bits + bits_for(NBC) <= 32;
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
     // could steps 5 to 7 go by row blocks? (see below)
-    const bool short_rows = h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast;
+    const bool short_rows = h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast &&
+                            10 * 8 * NBC * panel_row_words(R) <= kPanelLds;  // (the bits at a = 0)
     SegmentWords words{nullptr, nullptr};
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
@@ -2667,7 +2704,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
             // a wavefront per tile where it holds few segments, up to eight where it holds many
             int32_t wavefronts = 1;
             while (wavefronts < kTileThreads / 64 && S > 256 * wavefronts * n_tiles) wavefronts *= 2;
-            k_place<<<blocks_for(n_tiles * wavefronts, kTileThreads / 64), kTileThreads, 0, st>>>(
+            const auto place = wavefronts == kTileThreads / 64 ? k_place<true> : k_place<false>;
+            place<<<blocks_for(n_tiles * wavefronts, kTileThreads / 64), kTileThreads, 0, st>>>(
                 csr_ptr, n_rows, nnz, R, shift_r, (int32_t)NBR, (int32_t)NBC, (int32_t)n_tiles, wavefronts, tiles, list, row_bits, slot_off, bucket);
         } else {
             const auto second_pass = pow2 ? k_segments<Pass::kEmit, true> : k_segments<Pass::kEmit, false>;

@@ -88,8 +88,8 @@ def test_row_blocks_as_a_whole(H, oracle, R, n_rows, C, n_cols, mean, shift, f64
     check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=R, cols_per_block=C, rounds_per_batch=4, hash_shift=shift)
 
 
-# Row blocks in one and several shares (an fp32 share holds 25,941 nonzeros, an fp64 one 15,564), groups that lie in two of them, rows
-# of up to a block's width, alone and 70 in a row, at rounds around the 64 that a wavefront writes alone and the turns of 32 behind them.
+# Row blocks in one and several shares (an fp32 share holds 27,306 nonzeros, an fp64 one 16,384), groups that lie in two of them, rows
+# of up to a block's width, alone and 70 in a row, with tails of one and several pieces of 64 rounds, and more rounds than the list of tails holds.
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("long", [
     [(9, 0, 63), (70, 5, 64), (90, 600, 65), (2100, 0, 96), (2200, 0, 97), (4200, 7, 576), (5000, 7, 577)],
@@ -102,3 +102,12 @@ def test_shares_of_row_blocks(H, oracle, long, mean, f64):
     m = quick(lens, 3_000, 6, f64, long)
     for R in (2048, 1024):
         check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=R, cols_per_block=600, rounds_per_batch=4)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_more_rounds_than_the_list_of_tails_holds(H, oracle, f64):
+    """Five groups of each of five blocks with a row of 600 nonzeros among rows of 15: 14,800 rounds behind the first eight, the list holds 12,288."""
+    lens = np.random.default_rng(8).poisson(6, 262_145)
+    lens[:300] = 75
+    m = quick(lens, 3_000, 9, f64, [(r, 0, 3_000) for r in (10, 70, 130, 190, 250)])
+    check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=2048, cols_per_block=600, rounds_per_batch=4, hash_shift=0)
