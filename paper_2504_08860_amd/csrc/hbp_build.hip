@@ -101,10 +101,10 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t *to
 // Up to three scans of arrays of one length go through the same launches: the arrays are short (tens of
 // thousands of entries), so a scan costs its launches, some 5 us each, whatever it does.
 
-enum { kOpIdentity = 0, kOpCeilDivW = 1, kOpNonZero = 2, kOpAboveOne = 3 };
+enum { kOpIdentity = 0, kOpCeilDivW = 1, kOpNonZero = 2, kOpUnits = 3, kOpSplit = 4 };  // (the last two: combine units of W slots, see k_stripe_fill)
 __device__ __forceinline__ uint32_t scan_input(int32_t op, uint32_t v, uint32_t W)
 {
-    return op == kOpCeilDivW ? (v + W - 1) / W : op == kOpNonZero ? (v ? 1u : 0u) : op == kOpAboveOne ? (v > 1 ? 1u : 0u) : v;
+    return op == kOpCeilDivW ? (v + W - 1) / W : op == kOpNonZero ? (v ? 1u : 0u) : op == kOpUnits ? max(1u, (v + W - 1) / W) : op == kOpSplit ? (v > W ? 1u : 0u) : v;
 }
 
 constexpr int kScanTile = 2048;  // 256 threads x 8 consecutive items
@@ -236,11 +236,6 @@ int exclusive_scans(const Scans &s, int count, int64_t n, uint32_t W, uint32_t *
     return HBP_OK;
 }
 
-int exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tile_tmp, hipStream_t st)
-{
-    return exclusive_scans(Scans{{in}, {out}, {kOpIdentity}}, 1, n, 1, tile_tmp, st);
-}
-
 // ------------------------------------------------------------------ Section 3.2: hash
 
 // key(n) = min(min(n >> a, 8) * b + (((n mod 2^a) * d) >> a), R - 1) with b = d = max(1, R / 9):
@@ -257,12 +252,14 @@ __device__ __forceinline__ uint32_t hash_key(uint32_t n, uint32_t a, uint32_t b,
 
 // Sampling of the shift a: histogram, over the segments of up to 4096 evenly spaced rows, of
 // the smallest a in 0..12 with n < 9 * 2^a.  One wavefront walks one sampled row.  hist[14] also
-// counts the sampled segments with at least kLongSegment nonzeros (block sizes are chosen by it).
+// counts the sampled segments with at least kLongSegment nonzeros (block sizes are chosen by it).  hist: kHistCopies copies, kHistStride words
+// apart (one copy, to which 1024 workgroups add: 16.2 against 5.0 us on the 27-point grid of 128^3, 19.8 against 14.2 on 4M x 1M lognormal rows).
 // row_stats: kStatsCopies copies that add up to the statistics of all rows, where they matter (and the grid has the workgroups).
 // (Every wavefront of the sampling workgroups counting its share of the rows into 16 copies: 15 to 20 us more per build.)
 constexpr int kLongSegment = 6;
 constexpr int kStatsCopies = 64;  // so that the workgroups do not queue up for one address
 constexpr int kStatsGroups = 1024;
+constexpr int kHistCopies = 16, kHistStride = 32;
 __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__ ptr, const int32_t *__restrict__ col,
                                                      int64_t n_rows, int32_t C, int32_t S, uint32_t *__restrict__ hist,
                                                      RowStats *__restrict__ row_stats)
@@ -372,33 +369,50 @@ __global__ __launch_bounds__(256) void k_sample_hist(const int32_t *__restrict__
         if (open >= 0 && lane == 0) tally((int)(j1 - open));
     }
     __syncthreads();
-    if (threadIdx.x < 15 && sh_hist[threadIdx.x]) atomicAdd(&hist[threadIdx.x], sh_hist[threadIdx.x]);
+    if (threadIdx.x < 15 && sh_hist[threadIdx.x]) atomicAdd(&hist[kHistStride * (blockIdx.x % kHistCopies) + threadIdx.x], sh_hist[threadIdx.x]);
 }
 
-// a = smallest shift for which at least 15/16 of the sampled segments aggregate into 0..8.
-__global__ __launch_bounds__(64) void k_pick_shift(const uint32_t *__restrict__ hist, int32_t *__restrict__ a_out, RowStats *__restrict__ row_stats)
+// a = smallest shift for which at least 15/16 of the sampled segments aggregate into 0..8.  host: pinned words for what the build's parameters are
+// chosen by, or null.
+__global__ __launch_bounds__(64) void k_pick_shift(const uint32_t *__restrict__ hist, int32_t *__restrict__ a_out, const RowStats *__restrict__ row_stats,
+                                                   const int32_t *__restrict__ ptr, int64_t n_rows, uint32_t *__restrict__ host)
 {
-    if (row_stats) {  // the copies' sum goes to the first
-        RowStats all = row_stats[threadIdx.x];
+    const int i = threadIdx.x;
+    uint32_t here = 0;  // lane i: segments in bin i
+    if (i < 15)
+        for (int c = 0; c < kHistCopies; c++) here += hist[kHistStride * c + i];
+    const uint32_t counted = i < 14 ? here : 0u;
+    const uint64_t upto = sum_up_to_lane(counted);  // (fewer than 2^31 nonzeros in all)
+    const uint64_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    const uint64_t enough = __ballot(i <= 12 && 16 * upto >= 15 * total);
+    const int a = total == 0 ? 0 : enough ? __builtin_ctzll(enough) : 12;
+    if (i == 0) *a_out = a;
+    if (!host) return;
+    RowStats all = row_stats[i];
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            all.rows += __shfl_xor(all.rows, d);
-            all.skew += __shfl_xor(all.skew, d);
-        }
-        if (threadIdx.x == 0) row_stats[0] = all;
+    for (int d = 32; d > 0; d >>= 1) {
+        all.rows += __shfl_xor(all.rows, d);
+        all.skew += __shfl_xor(all.skew, d);
     }
-    if (threadIdx.x || blockIdx.x) return;
-    uint64_t total = 0, below = 0;
-    for (int i = 0; i < 14; i++) total += hist[i];
-    int a = 0;
-    if (total) {
-        a = 12;
-        for (int i = 0; i <= 12; i++) {
-            below += hist[i];
-            if (16 * below >= 15 * total) { a = i; break; }
-        }
+    if (i < 16) host[i] = here;
+    if (i == 0) {
+        host[16] = (uint32_t)a;
+        host[17] = (uint32_t)ptr[0];
+        host[18] = (uint32_t)ptr[n_rows];
+        host[19] = all.rows;
+        host[20] = (uint32_t)all.skew;
+        host[21] = (uint32_t)(all.skew >> 32);
     }
-    *a_out = a;
+}
+
+// What a build begins with: zeros in two ranges of words, and the shift where it is given.
+__global__ __launch_bounds__(256) void k_begin(uint32_t *__restrict__ first, int64_t n_first, uint32_t *__restrict__ second, int64_t n_second,
+                                               int32_t *__restrict__ a_out, int32_t a)
+{
+    const int64_t threads = (int64_t)gridDim.x * 256, t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = t; i < n_first; i += threads) first[i] = 0u;
+    for (int64_t i = t; i < n_second; i += threads) second[i] = 0u;
+    if (t == 0 && a >= 0) *a_out = a;
 }
 
 // Empty matrix: one empty combine unit per row block (it writes the zeros of y).
@@ -409,11 +423,6 @@ __global__ __launch_bounds__(256) void k_iota_units(int32_t *unit_ptr, int32_t *
     unit_ptr[i] = (int32_t)i;
     unit_k[i] = 0;
     if (i < NBR) unit_stripe[i] = (int32_t)i;
-}
-
-__global__ void k_set_i32(int32_t *p, int32_t v)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
 // ------------------------------------------------------------------ steps 1-3: segments
@@ -881,20 +890,34 @@ __global__ __launch_bounds__(kTileThreads) void k_place(const int32_t *__restric
 
 // ------------------------------------------------------------------ step 4: block table
 
-// Non-empty blocks get their coordinates and ranges; thread d also fills col_blk_ptr[d].
+// Non-empty blocks get their coordinates and ranges; thread d also fills col_blk_ptr[d] and col_group_ptr[d].  And what else can be written once the
+// totals are known: the padding behind the layout's last group, which is read (and its products dropped) by lanes without an element, the
+// end of the last group, zeros in the counters.
 __global__ __launch_bounds__(256) void k_compact_blocks(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ slot_off,
                                                         const uint32_t *__restrict__ group_off, const uint32_t *__restrict__ blk_id,
                                                         int64_t D, int32_t NBR, int32_t NBC, int32_t *__restrict__ blk_bm,
                                                         int32_t *__restrict__ blk_bn, int32_t *__restrict__ slot_ptr,
-                                                        int32_t *__restrict__ blk_group_ptr, int32_t *__restrict__ col_blk_ptr)
+                                                        int32_t *__restrict__ blk_group_ptr, int32_t *__restrict__ col_blk_ptr,
+                                                        int32_t *__restrict__ col_group_ptr, uint16_t *__restrict__ col_padding,
+                                                        uint32_t *__restrict__ data_padding, int32_t padding_words, int32_t *__restrict__ last_group_end,
+                                                        uint32_t *__restrict__ counters)
 {
     const int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (d <= NBC) col_blk_ptr[d] = (int32_t)blk_id[d * NBR];   // blk_id[D] = B closes the last column
+    if (blockIdx.x == 0) {
+        col_padding[threadIdx.x] = 0;
+        for (int32_t i = threadIdx.x; i < padding_words; i += 256) data_padding[i] = 0u;
+        if (threadIdx.x < 3) counters[threadIdx.x] = 0u;
+    }
+    if (d <= NBC) {
+        col_blk_ptr[d] = (int32_t)blk_id[d * NBR];   // blk_id[D] = B closes the last column
+        col_group_ptr[d] = (int32_t)group_off[d * NBR];
+    }
     if (d > D) return;
     if (d == D) {
         const uint32_t B = blk_id[D];
         slot_ptr[B] = (int32_t)slot_off[D];
         blk_group_ptr[B] = (int32_t)group_off[D];
+        *last_group_end = (int32_t)slot_off[D];
         return;
     }
     if (!dense_cnt[d]) return;
@@ -930,7 +953,8 @@ __device__ __forceinline__ uint32_t stripe_slice_count(const uint32_t *__restric
 }
 
 __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC, const int32_t *__restrict__ ptr,
-                                                       int64_t n_rows, int32_t R, uint32_t *__restrict__ stripe_cnt, Findings *__restrict__ found)
+                                                       int64_t n_rows, int32_t R, uint32_t *__restrict__ stripe_cnt, uint32_t *__restrict__ stripe_slots,
+                                                       Findings *__restrict__ found)
 {
     __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
@@ -950,6 +974,7 @@ __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restric
     uint32_t nonzeros = 0;
     if (bm < NBR) {
         stripe_cnt[bm] = n;
+        stripe_slots[bm] = slots;
         nonzeros = (uint32_t)(ptr[min((bm + 1) * R, n_rows)] - ptr[bm * R]);
     }
     slots = wave_max(slots);
@@ -960,24 +985,52 @@ __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restric
     }
 }
 
+// The combine index and the combine work units.  A row block with many slots is cut into u = ceil(slots / unit_slots) units of consecutive
+// stripe_blk entries, so that no workgroup of the combine part gets much more than unit_slots slots; unit i starts at the first entry whose
+// preceding slots, times u, reach i times the row block's slots.
 __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ blk_id,
-                                                      const int32_t *__restrict__ stripe_ptr, int32_t NBR, int32_t NBC,
-                                                      int32_t *__restrict__ stripe_blk)
+                                                      const int32_t *__restrict__ stripe_ptr, const uint32_t *__restrict__ stripe_slots,
+                                                      const int32_t *__restrict__ unit_ptr, const uint32_t *__restrict__ multi_idx, int32_t NBR,
+                                                      int32_t NBC, int32_t B, int32_t *__restrict__ stripe_blk, int32_t *__restrict__ unit_stripe,
+                                                      int32_t *__restrict__ unit_k, int32_t *__restrict__ multi_stripes)
 {
-    __shared__ uint32_t sh[kStripeSlices * 64];
+    __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     int32_t bn0, bn1;
     uint32_t slots;
     sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1, slots);
+    sh_slots[threadIdx.x] = slots;
     __syncthreads();
     if (bm >= NBR) return;
     int32_t k = stripe_ptr[bm];
-    for (uint32_t i = threadIdx.x & 63; i < threadIdx.x; i += 64) k += (int32_t)sh[i];
+    const int32_t u0 = unit_ptr[bm], u = unit_ptr[bm + 1] - u0;
+    const int64_t all = stripe_slots[bm];
+    int64_t before = 0;
+    if (threadIdx.x < 64) {
+        unit_stripe[u0] = (int32_t)bm;
+        unit_k[u0] = k;
+        if (u > 1) multi_stripes[multi_idx[bm]] = (int32_t)bm;
+        if (bm == NBR - 1) unit_k[u0 + u] = B;
+    }
+    for (uint32_t i = threadIdx.x & 63; i < threadIdx.x; i += 64) {
+        k += (int32_t)sh[i];
+        before += sh_slots[i];
+    }
 #pragma unroll 8
     for (int64_t bn = bn0; bn < bn1; bn++) {
         const int64_t d = bn * NBR + bm;
         const int32_t id = (int32_t)blk_id[d];
-        if (dense_cnt[d]) stripe_blk[k++] = id;
+        const uint32_t here = dense_cnt[d];
+        if (!here) continue;
+        stripe_blk[k++] = id;
+        if (u > 1) {  // the units that start behind this entry
+            const int64_t next = (before + here) * u / all;
+            for (int64_t i = before * u / all + 1; i <= next && i < u; i++) {
+                unit_stripe[u0 + i] = (int32_t)bm;
+                unit_k[u0 + i] = k;
+            }
+        }
+        before += here;
     }
 }
 
@@ -1986,55 +2039,6 @@ __global__ __launch_bounds__(256) void k_add_sign(const int32_t *__restrict__ gr
     }
 }
 
-// ------------------------------------------------------------------ combine work units
-//
-// A row block with many slots is cut into u = ceil(slots / unit_slots) units of consecutive
-// stripe_blk entries, so that no workgroup of the combine part gets much more than unit_slots
-// slots; unit i starts at the first entry whose preceding slots, times u, reach i times the row
-// block's slots.
-
-__global__ __launch_bounds__(256) void k_stripe_sizes(const int32_t *__restrict__ stripe_blk, const int32_t *__restrict__ slot_ptr,
-                                                      int32_t B, uint32_t *__restrict__ size)
-{
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= B) return;
-    const int32_t b = stripe_blk[k];
-    size[k] = (uint32_t)(slot_ptr[b + 1] - slot_ptr[b]);
-}
-
-__global__ __launch_bounds__(256) void k_unit_count(const int32_t *__restrict__ stripe_ptr, const uint32_t *__restrict__ cum,
-                                                    int32_t NBR, int32_t unit_slots, uint32_t *__restrict__ units)
-{
-    const int64_t bm = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (bm >= NBR) return;
-    const int64_t slots = (int64_t)cum[stripe_ptr[bm + 1]] - (int64_t)cum[stripe_ptr[bm]];
-    const int64_t u = (slots + unit_slots - 1) / unit_slots;
-    units[bm] = (uint32_t)(u < 1 ? 1 : u);
-}
-
-__global__ __launch_bounds__(256) void k_unit_fill(const int32_t *__restrict__ stripe_ptr, const uint32_t *__restrict__ cum,
-                                                   const int32_t *__restrict__ unit_ptr, const uint32_t *__restrict__ multi_idx,
-                                                   int32_t NBR, int32_t B, int32_t *__restrict__ unit_stripe,
-                                                   int32_t *__restrict__ unit_k, int32_t *__restrict__ multi_stripes)
-{
-    const int64_t bm = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (bm >= NBR) return;
-    const int32_t k0 = stripe_ptr[bm], k1 = stripe_ptr[bm + 1];
-    const int32_t u0 = unit_ptr[bm], u = unit_ptr[bm + 1] - u0;
-    const int64_t base = cum[k0], slots = (int64_t)cum[k1] - base;
-    for (int32_t i = 0; i < u; i++) {
-        int32_t lo = k0, hi = k1;  // smallest k in [k0, k1] with (cum[k] - base) * u >= i * slots
-        while (lo < hi) {
-            const int32_t mid = lo + ((hi - lo) >> 1);
-            if (((int64_t)cum[mid] - base) * u >= (int64_t)i * slots) hi = mid; else lo = mid + 1;
-        }
-        unit_stripe[u0 + i] = (int32_t)bm;
-        unit_k[u0 + i] = lo;
-    }
-    if (u > 1) multi_stripes[multi_idx[bm]] = (int32_t)bm;
-    if (bm == NBR - 1) unit_k[u0 + u] = B;
-}
-
 // ------------------------------------------------------------------ Section 3.3: schedule
 //
 // Weight of a group = GW + its nonzeros + SW times its slots + RW times its rounds (GW =
@@ -2052,15 +2056,17 @@ struct Weights {
     }
 };
 
-// col_group_ptr[c]: first group of block column c; col_rank[c], c in 0..NBC: block columns before c that hold a
-// group.  One workgroup: every thread counts a contiguous piece, the pieces' counts are scanned, every
+// A few words that kernels write for the host: one synchronisation instead of a blocking copy per word.
+constexpr int kReadback = 32;
+struct Words { const void *at[kReadback]; };
+
+constexpr int kColumnsKept = 2048;  // block columns whose first groups and ranks k_schedule keeps in LDS
+
+// For more of them, col_rank[c], c in 0..NBC: block columns before c that hold a group (col_group_ptr[c]: first group of block column c).  One workgroup: every thread counts a contiguous piece, the pieces' counts are scanned, every
 // thread writes its piece.
-__global__ __launch_bounds__(256) void k_col_groups(const int32_t *__restrict__ col_blk_ptr, const int32_t *__restrict__ blk_group_ptr,
-                                                    int32_t NBC, int32_t *__restrict__ col_group_ptr, int32_t *__restrict__ col_rank)
+__global__ __launch_bounds__(256) void k_col_ranks(const int32_t *__restrict__ col_group_ptr, int32_t NBC, int32_t *__restrict__ col_rank)
 {
     __shared__ uint32_t sh[4];
-    for (int32_t c = threadIdx.x; c <= NBC; c += 256) col_group_ptr[c] = blk_group_ptr[col_blk_ptr[c]];
-    __syncthreads();
     const int32_t per = (NBC + 255) / 256, c0 = min(NBC, (int32_t)threadIdx.x * per), c1 = min(NBC, c0 + per);
     uint32_t mine = 0, total;
     for (int32_t c = c0; c < c1; c++) mine += col_group_ptr[c + 1] > col_group_ptr[c];
@@ -2085,13 +2091,28 @@ __global__ __launch_bounds__(256) void k_schedule(const int32_t *__restrict__ co
                                                   const int32_t *__restrict__ col_rank, int64_t CW, int32_t NBC, int32_t G, int32_t P,
                                                   int32_t fixed_q8, int32_t *__restrict__ fixed_start, int32_t *__restrict__ fixed_col,
                                                   int32_t *__restrict__ comp_lo, int32_t *__restrict__ comp_col,
-                                                  int64_t least_open, int32_t *__restrict__ own_end, int32_t *__restrict__ any_open)
+                                                  int64_t least_open, int32_t *__restrict__ own_end, int32_t *__restrict__ any_open,
+                                                  Words words, int32_t n_words, uint32_t *__restrict__ host)
 {
-    constexpr int kKept = 2048;  // block columns whose first groups are kept in LDS
-    __shared__ int32_t sh_first[kKept + 1];
-    const bool kept = NBC <= kKept;
-    if (kept)
+    // (for the host, words that are final since the kernels before)
+    if (blockIdx.x == 0 && (int32_t)threadIdx.x < n_words) host[threadIdx.x] = *static_cast<const uint32_t *>(words.at[threadIdx.x]);
+    __shared__ int32_t sh_first[kColumnsKept + 1];
+    __shared__ uint16_t sh_rank[kColumnsKept + 1];  // block columns that hold a group before each
+    __shared__ uint32_t sh[4];
+    const bool kept = NBC <= kColumnsKept;
+    if (kept) {
         for (int32_t c = threadIdx.x; c <= NBC; c += 256) sh_first[c] = col_group_ptr[c];
+        __syncthreads();
+        const int32_t per = (NBC + 255) / 256, c0 = min(NBC, (int32_t)threadIdx.x * per), c1 = min(NBC, c0 + per);
+        uint32_t mine = 0, total;
+        for (int32_t c = c0; c < c1; c++) mine += sh_first[c + 1] > sh_first[c];
+        uint32_t run = block_excl_scan_256(mine, &total, sh);
+        for (int32_t c = c0; c < c1; c++) {
+            sh_rank[c] = (uint16_t)run;
+            run += sh_first[c + 1] > sh_first[c];
+        }
+        if (threadIdx.x == 0) sh_rank[NBC] = (uint16_t)total;
+    }
     __syncthreads();
     const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (w > P) return;
@@ -2104,7 +2125,7 @@ __global__ __launch_bounds__(256) void k_schedule(const int32_t *__restrict__ co
                 const int32_t mid = c_lo + ((c_hi - c_lo) >> 1);
                 if (first_group(mid) >= g) c_hi = mid; else c_lo = mid + 1;
             }
-            v += CW * col_rank[c_lo];
+            v += CW * (kept ? (int32_t)sh_rank[c_lo] : col_rank[c_lo]);
         }
         return v;
     };
@@ -2272,8 +2293,6 @@ int block_get(int device, size_t bytes, void **out, size_t *got)
     return device_alloc(device, bytes, out);
 }
 
-// A few words that kernels write for the host: one synchronisation instead of a blocking copy per word.
-constexpr int kReadback = 32;
 uint32_t *g_readback[kWorkspaceDevices];  // pinned; guarded by the device's workspace lock
 
 int readback_get(int device, uint32_t **out)
@@ -2284,7 +2303,6 @@ int readback_get(int device, uint32_t **out)
     return HBP_OK;
 }
 
-struct Words { const void *at[kReadback]; };
 // found: the largest of the copies go behind the words
 __global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host, const Findings *__restrict__ found)
 {
@@ -2378,23 +2396,15 @@ int choose_block_parameters(const int32_t *csr_ptr, const int32_t *csr_col, int6
     uint32_t *host = nullptr;
     HBP_TRY(readback_get(device, &host));
     void *buf = nullptr;
-    HBP_TRY(workspace_get(device, 1, 2048, &buf));
-    uint32_t *hist = static_cast<uint32_t *>(buf);
-    int32_t *d_a = reinterpret_cast<int32_t *>(hist + 16);
-    RowStats *row_stats = reinterpret_cast<RowStats *>(hist + 32);
-    HBP_HIP(hipMemsetAsync(hist, 0, 32 * sizeof(uint32_t) + kStatsCopies * sizeof(RowStats), st));
+    constexpr size_t kHistWords = kHistCopies * kHistStride;
+    HBP_TRY(workspace_get(device, 1, sizeof(uint32_t) * (kHistWords + 1) + kStatsCopies * sizeof(RowStats), &buf));
+    RowStats *row_stats = static_cast<RowStats *>(buf);
+    uint32_t *hist = reinterpret_cast<uint32_t *>(row_stats + kStatsCopies);
+    int32_t *d_a = reinterpret_cast<int32_t *>(hist + kHistWords);
+    HBP_HIP(hipMemsetAsync(buf, 0, sizeof(uint32_t) * kHistWords + kStatsCopies * sizeof(RowStats), st));
     const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
     k_sample_hist<<<blocks_for(S_rows, 4) + kStatsGroups, 256, 0, st>>>(csr_ptr, csr_col, n_rows, p.cols_per_block, S_rows, hist, row_stats);
-    k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, row_stats);
-    Words words;
-    for (int i = 0; i < 16; i++) words.at[i] = hist + i;
-    words.at[16] = d_a;
-    words.at[17] = csr_ptr;
-    words.at[18] = csr_ptr + n_rows;
-    words.at[19] = &row_stats->rows;
-    words.at[20] = &row_stats->skew;
-    words.at[21] = reinterpret_cast<uint32_t *>(&row_stats->skew) + 1;
-    k_publish<<<1, 64, 0, st>>>(words, 22, host, nullptr);
+    k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, row_stats, csr_ptr, n_rows, host);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     const int32_t a = (int32_t)host[16], first = (int32_t)host[17];
@@ -2435,15 +2445,16 @@ static void choose_schedule(hbp_handle_s *h, const hbp_params_t &p)
 }
 
 // Section 3.3: which groups are pre-assigned to which worker and which are left to competition.
-static int launch_schedule(hbp_handle_s *h, hipStream_t st)
+static int launch_schedule(hbp_handle_s *h, hipStream_t st, const Words &words, int32_t n_words, uint32_t *host)  // and reads `words` back
 {
     const int32_t NBC = (int32_t)h->NBC;
-    k_col_groups<<<1, 256, 0, st>>>(h->col_blk_ptr, h->blk_group_ptr, NBC, h->col_group_ptr, h->col_rank);
+    if (NBC > kColumnsKept && !(h->flags & HBP_FLAG_PAPER_SCHEDULE)) k_col_ranks<<<1, 256, 0, st>>>(h->col_group_ptr, NBC, h->col_rank);
     if (h->flags & HBP_FLAG_PAPER_SCHEDULE) {
         const int64_t F = (h->B * (int64_t)h->fixed_q8) / (256 * (int64_t)h->P);
         h->first_ticket_block = F * h->P;
         k_paper_schedule<<<blocks_for((int64_t)h->P + 1, 256), 256, 0, st>>>(h->blk_group_ptr, h->blk_bn, F, (int32_t)h->B, NBC, h->P,
                                                                              h->fixed_start, h->fixed_col, h->comp_lo, h->comp_col);
+        k_publish<<<1, 64, 0, st>>>(words, n_words, host, nullptr);
     } else {
         const Weights wt{h->group_ptr, h->group_slot, h->group_rounds, (int64_t)h->slot_weight, (int64_t)h->round_weight,
                          (int64_t)h->group_weight};
@@ -2454,7 +2465,7 @@ static int launch_schedule(hbp_handle_s *h, hipStream_t st)
         const int64_t least_open = h->share_chosen ? steal_weight(h->column_weight) : 0;
         k_schedule<<<blocks_for((int64_t)h->P + 1, 4), 256, 0, st>>>(h->col_group_ptr, wt, h->col_rank, (int64_t)h->column_weight, NBC,
                                                                      (int32_t)h->G, h->P, h->fixed_q8, h->fixed_start, h->fixed_col,
-                                                                     h->comp_lo, h->comp_col, least_open, h->own_end, h->any_open);
+                                                                     h->comp_lo, h->comp_col, least_open, h->own_end, h->any_open, words, n_words, host);
     }
     HBP_HIP(hipGetLastError());
     return HBP_OK;
@@ -2510,9 +2521,9 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own0.reserve(&h->col_rank, NBC + 1);
     HBP_TRY(own0.commit());
     h->arena[0] = own0.base(); h->arena_bytes[0] = own0.bytes();
-    HBP_HIP(hipMemsetAsync(own0.base(), 0, own0.total(), st));
 
     if (nnz == 0) {  // empty matrix: no blocks; the combine part alone writes y = 0
+        HBP_HIP(hipMemsetAsync(own0.base(), 0, own0.total(), st));
         h->B = h->S = h->G = 0;
         h->a = p.hash_shift >= 0 ? p.hash_shift : 0;
         Arena own1(true, h->device);
@@ -2539,7 +2550,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const int64_t n_tiles = (nnz + kTile - 1) / kTile;
     const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
     Findings *found;
-    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt;
+    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt, *stripe_slots;
     int32_t *d_a;
     Tile *tiles;
     uint32_t *list = nullptr;
@@ -2554,7 +2565,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     SegmentWords words{nullptr, nullptr};
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
-    tmp.reserve(&hist, 16);
+    tmp.reserve(&hist, kHistCopies * kHistStride);
     tmp.reserve(&found, 1);
     tmp.reserve(&tiles, n_tiles);
     if (listed) tmp.reserve(&list, nnz);
@@ -2566,18 +2577,19 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&group_off, D + 1);
     tmp.reserve(&blk_id, D + 1);
     tmp.reserve(&stripe_cnt, NBR);
+    tmp.reserve(&stripe_slots, NBR);
     tmp.reserve(&scan_tmp, 3 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
     HBP_TRY(tmp.commit());
-    HBP_HIP(hipMemsetAsync(dense_cnt, 0, (size_t)((char *)tiles - (char *)dense_cnt), st));
+    const int64_t first_words = (int64_t)(own0.total() / sizeof(uint32_t)), second_words = ((char *)tiles - (char *)dense_cnt) / (int64_t)sizeof(uint32_t);
+    k_begin<<<(unsigned)std::min<int64_t>(1024, (first_words + second_words + 1023) / 1024), 256, 0, st>>>(
+        static_cast<uint32_t *>(own0.base()), first_words, dense_cnt, second_words, d_a, p.hash_shift);
 
     // Section 3.2: shift a, sampled or given
-    if (p.hash_shift >= 0) {
-        k_set_i32<<<1, 64, 0, st>>>(d_a, p.hash_shift);
-    } else {
+    if (p.hash_shift < 0) {
         const int32_t S_rows = (int32_t)std::min<int64_t>(n_rows, 4096);
         k_sample_hist<<<blocks_for(S_rows, 4), 256, 0, st>>>(csr_ptr, csr_col, n_rows, C, S_rows, hist, nullptr);
-        k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, nullptr);
+        k_pick_shift<<<1, 64, 0, st>>>(hist, d_a, nullptr, csr_ptr, n_rows, nullptr);
     }
 
     // steps 1-3
@@ -2598,8 +2610,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // step 4: scans over the block table
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
-    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, csr_ptr, n_rows, R, stripe_cnt, found);
-    HBP_TRY(exclusive_scan(stripe_cnt, (uint32_t *)h->stripe_ptr, NBR, scan_tmp, st));
+    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, csr_ptr, n_rows, R, stripe_cnt, stripe_slots, found);
     HBP_HIP(hipGetLastError());
 
     // the one host round trip of the build: totals (and the error word)
@@ -2661,8 +2672,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // for k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
     const bool cut = parts == 0 && long_segments && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
     Arena tmp2(false, h->device, 1);
-    uint32_t *stripe_cum, *unit_cnt, *multi_idx;
-    tmp2.reserve(&stripe_cum, B + 1); tmp2.reserve(&unit_cnt, NBR + 1); tmp2.reserve(&multi_idx, NBR + 1);
+    uint32_t *multi_idx;
+    tmp2.reserve(&multi_idx, NBR + 1);
     uint2 *bucket;
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
@@ -2675,20 +2686,15 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_TRY(tmp2.commit());
     d_n_long = longest_all + 1;
     uint32_t *const d_n_rest = longest_all + 2;
-    HBP_HIP(hipMemsetAsync(longest_all, 0, 3 * sizeof(uint32_t), st));
 
     k_compact_blocks<<<blocks_for(std::max<int64_t>(D, NBC) + 1, 256), 256, 0, st>>>(
         dense_cnt, slot_off, group_off, blk_id, D, (int32_t)NBR, (int32_t)NBC, h->blk_bm, h->blk_bn, h->slot_ptr,
-        h->blk_group_ptr, h->col_blk_ptr);
-    k_stripe_fill<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, (int32_t)NBR, (int32_t)NBC,
-                                                       h->stripe_blk);
-    // combine work units
-    k_stripe_sizes<<<blocks_for(B, 256), 256, 0, st>>>(h->stripe_blk, h->slot_ptr, (int32_t)B, stripe_cum);
-    HBP_TRY(exclusive_scan(stripe_cum, stripe_cum, B, scan_tmp, st));
-    k_unit_count<<<blocks_for(NBR, 256), 256, 0, st>>>(h->stripe_ptr, stripe_cum, (int32_t)NBR, h->unit_slots, unit_cnt);
-    HBP_TRY(exclusive_scans(Scans{{unit_cnt, unit_cnt}, {(uint32_t *)h->unit_ptr, multi_idx}, {kOpIdentity, kOpAboveOne}}, 2, NBR, 1, scan_tmp, st));
-    k_unit_fill<<<blocks_for(NBR, 256), 256, 0, st>>>(h->stripe_ptr, stripe_cum, h->unit_ptr, multi_idx, (int32_t)NBR, (int32_t)B,
-                                                     h->unit_stripe, h->unit_k, h->multi_stripes);
+        h->blk_group_ptr, h->col_blk_ptr, h->col_group_ptr, h->col_local + nnz, reinterpret_cast<uint32_t *>((char *)h->data + (size_t)nnz * h->value_bytes),
+        256 * h->value_bytes / 4, h->group_slot + G, longest_all);
+    HBP_TRY(exclusive_scans(Scans{{stripe_cnt, stripe_slots, stripe_slots}, {(uint32_t *)h->stripe_ptr, (uint32_t *)h->unit_ptr, multi_idx},
+                                  {kOpIdentity, kOpUnits, kOpSplit}}, 3, NBR, (uint32_t)h->unit_slots, scan_tmp, st));
+    k_stripe_fill<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, stripe_slots, h->unit_ptr, multi_idx, (int32_t)NBR, (int32_t)NBC,
+                                                       (int32_t)B, h->stripe_blk, h->unit_stripe, h->unit_k, h->multi_stripes);
     const dim3 stripe_grid((unsigned)(8 * ((NBR + 7) / 8) * std::max(parts, 1)));
     // steps 5-6 (slot_off doubles as the per-block cursor from here on, but for row blocks as a whole)
     if (by_panel) {
@@ -2725,11 +2731,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     }
     HBP_TRY(exclusive_scans(Scans{{group_nnz, group_longest}, {(uint32_t *)h->group_ptr, (uint32_t *)h->group_rounds}, {kOpIdentity, kOpIdentity}}, 2,
                             G, 1, scan_tmp, st));
-    k_set_i32<<<1, 64, 0, st>>>(h->group_slot + G, (int32_t)S);
     // step 7
-    // the padding behind the last group is read (and its products dropped) by lanes without an element
-    HBP_HIP(hipMemsetAsync(h->col_local + nnz, 0, 256 * sizeof(uint16_t), st));
-    HBP_HIP(hipMemsetAsync((char *)h->data + (size_t)nnz * h->value_bytes, 0, 256 * (size_t)h->value_bytes, st));
     auto fill = [&](const auto *val, auto *data) {
         using T = std::remove_reference_t<decltype(*data)>;
         if (by_panel) {
@@ -2757,8 +2759,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     else fill(static_cast<const float *>(csr_val), static_cast<float *>(h->data));
     HBP_HIP(hipGetLastError());
     choose_schedule(h, p);
-    HBP_TRY(launch_schedule(h, st));
-    k_publish<<<1, 64, 0, st>>>(Words{{h->unit_ptr + NBR, multi_idx + NBR, longest_all, d_n_long}}, 4, host, nullptr);
+    HBP_TRY(launch_schedule(h, st, Words{{h->unit_ptr + NBR, multi_idx + NBR, longest_all, d_n_long}}, 4, host));
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
     h->U = host[0]; h->NM = host[1];

@@ -111,3 +111,12 @@ def test_more_rounds_than_the_list_of_tails_holds(H, oracle, f64):
     lens[:300] = 75
     m = quick(lens, 3_000, 9, f64, [(r, 0, 3_000) for r in (10, 70, 130, 190, 250)])
     check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=2048, cols_per_block=600, rounds_per_batch=4, hash_shift=0)
+
+
+# Block columns up to which the schedule keeps their ranks in LDS, and one more; with row blocks cut into combine units.
+@pytest.mark.parametrize("n_cols", [2048, 2049])
+@pytest.mark.parametrize("unit_slots", [0, 64])
+def test_block_columns_kept_and_not(H, oracle, n_cols, unit_slots):
+    lens = np.random.default_rng(4).integers(0, 60, 300)
+    check_against_oracle(H, oracle, matrix(lens, n_cols), rows_per_block=128, cols_per_block=1, num_workers=7, column_weight=50,
+                         combine_unit_slots=unit_slots)
