@@ -98,7 +98,7 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t *to
 
 // ------------------------------------------------------------------ device-wide exclusive scans
 //
-// Up to three scans of arrays of one length go through the same launches: the arrays are short (tens of
+// Up to four scans of arrays of one length go through the same launches: the arrays are short (tens of
 // thousands of entries), so a scan costs its launches, some 5 us each, whatever it does.
 
 enum { kOpIdentity = 0, kOpCeilDivW = 1, kOpNonZero = 2, kOpUnits = 3, kOpSplit = 4 };  // (the last two: combine units of W slots, see k_stripe_fill)
@@ -111,9 +111,9 @@ constexpr int kScanTile = 2048;  // 256 threads x 8 consecutive items
 
 // out[0..n) = exclusive scan of op(in), out[n] = total.  `in` and `out` may alias where only one scan reads `in`.
 struct Scans {
-    const uint32_t *in[3];
-    uint32_t *out[3];
-    int32_t op[3];
+    const uint32_t *in[4];
+    uint32_t *out[4];
+    int32_t op[4];
 };
 
 __global__ __launch_bounds__(256) void k_scan_reduce(Scans s, int64_t n, uint32_t W, int64_t n_tiles, uint32_t *__restrict__ tile_sum)
@@ -934,47 +934,53 @@ __global__ __launch_bounds__(256) void k_compact_blocks(const uint32_t *__restri
 constexpr int kStripeSlices = 16;
 
 __device__ __forceinline__ uint32_t stripe_slice_count(const uint32_t *__restrict__ dense_cnt, int64_t bm, int32_t NBR, int32_t NBC,
-                                                       int32_t &bn0, int32_t &bn1, uint32_t &slots)
+                                                       uint32_t W, int32_t &bn0, int32_t &bn1, uint32_t &slots, uint32_t &groups)
 {
     const int32_t slice = threadIdx.x >> 6;
     bn0 = (int32_t)(((int64_t)NBC * slice) / kStripeSlices);
     bn1 = (int32_t)(((int64_t)NBC * (slice + 1)) / kStripeSlices);
     uint32_t n = 0;
-    slots = 0;
+    slots = groups = 0;
     if (bm < NBR) {
 #pragma unroll 8
         for (int64_t bn = bn0; bn < bn1; bn++) {
             const uint32_t here = dense_cnt[bn * NBR + bm];
             n += here ? 1u : 0u;
             slots += here;
+            groups += (here + W - 1) / W;
         }
     }
     return n;
 }
 
 __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC, const int32_t *__restrict__ ptr,
-                                                       int64_t n_rows, int32_t R, uint32_t *__restrict__ stripe_cnt, uint32_t *__restrict__ stripe_slots,
+                                                       int64_t n_rows, int32_t R, uint32_t W, uint32_t *__restrict__ stripe_cnt,
+                                                       uint32_t *__restrict__ stripe_slots, uint32_t *__restrict__ stripe_groups,
                                                        Findings *__restrict__ found)
 {
-    __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64];
+    __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64], sh_groups[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     int32_t bn0, bn1;
-    uint32_t slots;
-    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1, slots);
+    uint32_t slots, groups_in_slice;
+    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, W, bn0, bn1, slots, groups_in_slice);
     sh_slots[threadIdx.x] = slots;
+    sh_groups[threadIdx.x] = groups_in_slice;
     __syncthreads();
     if (threadIdx.x >= 64) return;
     uint32_t n = 0;
+    uint32_t groups = 0;
     slots = 0;
 #pragma unroll
     for (int i = 0; i < kStripeSlices; i++) {
         n += sh[i * 64 + threadIdx.x];
+        groups += sh_groups[i * 64 + threadIdx.x];
         slots += sh_slots[i * 64 + threadIdx.x];
     }
     uint32_t nonzeros = 0;
     if (bm < NBR) {
         stripe_cnt[bm] = n;
         stripe_slots[bm] = slots;
+        stripe_groups[bm] = groups;
         nonzeros = (uint32_t)(ptr[min((bm + 1) * R, n_rows)] - ptr[bm * R]);
     }
     slots = wave_max(slots);
@@ -988,24 +994,28 @@ __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restric
 // The combine index and the combine work units.  A row block with many slots is cut into u = ceil(slots / unit_slots) units of consecutive
 // stripe_blk entries, so that no workgroup of the combine part gets much more than unit_slots slots; unit i starts at the first entry whose
 // preceding slots, times u, reach i times the row block's slots.
+// blk_turn: the groups that come before the block's where groups are taken row block by row block.
 __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ blk_id,
                                                       const int32_t *__restrict__ stripe_ptr, const uint32_t *__restrict__ stripe_slots,
-                                                      const int32_t *__restrict__ unit_ptr, const uint32_t *__restrict__ multi_idx, int32_t NBR,
-                                                      int32_t NBC, int32_t B, int32_t *__restrict__ stripe_blk, int32_t *__restrict__ unit_stripe,
+                                                      const int32_t *__restrict__ unit_ptr, const uint32_t *__restrict__ multi_idx,
+                                                      const uint32_t *__restrict__ stripe_turn, uint32_t W, int32_t NBR, int32_t NBC, int32_t B,
+                                                      int32_t *__restrict__ stripe_blk, uint32_t *__restrict__ blk_turn, int32_t *__restrict__ unit_stripe,
                                                       int32_t *__restrict__ unit_k, int32_t *__restrict__ multi_stripes)
 {
-    __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64];
+    __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64], sh_groups[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     int32_t bn0, bn1;
-    uint32_t slots;
-    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, bn0, bn1, slots);
+    uint32_t slots, groups_in_slice;
+    sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, W, bn0, bn1, slots, groups_in_slice);
     sh_slots[threadIdx.x] = slots;
+    sh_groups[threadIdx.x] = groups_in_slice;
     __syncthreads();
     if (bm >= NBR) return;
     int32_t k = stripe_ptr[bm];
     const int32_t u0 = unit_ptr[bm], u = unit_ptr[bm + 1] - u0;
     const int64_t all = stripe_slots[bm];
     int64_t before = 0;
+    uint32_t turn = stripe_turn[bm];
     if (threadIdx.x < 64) {
         unit_stripe[u0] = (int32_t)bm;
         unit_k[u0] = k;
@@ -1015,6 +1025,7 @@ __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict
     for (uint32_t i = threadIdx.x & 63; i < threadIdx.x; i += 64) {
         k += (int32_t)sh[i];
         before += sh_slots[i];
+        turn += sh_groups[i];
     }
 #pragma unroll 8
     for (int64_t bn = bn0; bn < bn1; bn++) {
@@ -1023,6 +1034,8 @@ __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict
         const uint32_t here = dense_cnt[d];
         if (!here) continue;
         stripe_blk[k++] = id;
+        blk_turn[id] = turn;
+        turn += (here + W - 1) / W;
         if (u > 1) {  // the units that start behind this entry
             const int64_t next = (before + here) * u / all;
             for (int64_t i = before * u / all + 1; i <= next && i < u; i++) {
@@ -1455,18 +1468,34 @@ __global__ __launch_bounds__(256) void k_fill(const int32_t *__restrict__ stripe
     }
 }
 
-// The same with one wavefront per group, in the layout's own order.  CUT: the first kFillRounds rounds of a group alone.
-template <bool CUT, typename T>
-__global__ __launch_bounds__(256) void k_fill_flat(const int32_t *__restrict__ csr_col, const T *__restrict__ csr_val,
-                                                   const int32_t *__restrict__ group_ptr, const int32_t *__restrict__ group_slot,
-                                                   const int32_t *__restrict__ group_blk, const int32_t *__restrict__ blk_bn,
-                                                   const uint16_t *__restrict__ seg_len, const int32_t *__restrict__ slot_j,
-                                                   int32_t G, int32_t C, int64_t nnz, uint16_t *__restrict__ col_local, T *__restrict__ data)
+// fill_order: the groups row block by row block.
+__global__ __launch_bounds__(256) void k_group_turns(const int32_t *__restrict__ group_blk, const int32_t *__restrict__ blk_group_ptr,
+                                                    const uint32_t *__restrict__ blk_turn, int32_t G, int32_t *__restrict__ fill_order)
 {
-    const int64_t g = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= G) return;
-    fill_group<CUT, T>((int32_t)g, 0, blk_bn[group_blk[g]] * C, (int)(threadIdx.x & 63), nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j,
-                  col_local, data);
+    const int32_t b = group_blk[g];
+    fill_order[blk_turn[b] + (uint32_t)((int32_t)g - blk_group_ptr[b])] = (int32_t)g;
+}
+
+// The same with one wavefront per group, in the layout's own order, or in that of `fill_order`: then kFillChunk workgroups' groups in a row on one XCD, as
+// the blocks of a row block share the lines of the CSR arrays (32 of them: R-MAT 2^20 in fp64 195 against 200 us, the 27-point grid of 128^3
+// 243 against 220; 256: 208 and 220).  CUT: the first kFillRounds rounds of a group alone.
+constexpr int kFillChunk = 128;
+template <bool CUT, typename T>
+__global__ __launch_bounds__(256) void k_fill_flat(const int32_t *__restrict__ fill_order, const int32_t *__restrict__ csr_col,
+                                                   const T *__restrict__ csr_val, const int32_t *__restrict__ group_ptr,
+                                                   const int32_t *__restrict__ group_slot, const int32_t *__restrict__ group_blk,
+                                                   const int32_t *__restrict__ blk_bn, const uint16_t *__restrict__ seg_len,
+                                                   const int32_t *__restrict__ slot_j, int32_t G, int32_t C, int64_t nnz,
+                                                   uint16_t *__restrict__ col_local, T *__restrict__ data)
+{
+    const uint32_t x = blockIdx.x & 7u, q = blockIdx.x >> 3;
+    const int64_t turn = ((int64_t)(8u * (q / kFillChunk) + x) * kFillChunk + q % kFillChunk) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t at = fill_order ? turn : (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (at >= G) return;
+    const int32_t g = fill_order ? fill_order[at] : (int32_t)at;
+    fill_group<CUT, T>(g, 0, blk_bn[group_blk[g]] * C, (int)(threadIdx.x & 63), nnz, csr_col, csr_val, group_ptr, group_slot, seg_len, slot_j, col_local, data);
 }
 
 // The rest of groups that are cut, entries (group, first round) of a list.  A workgroup of k_list_rest looks at 1024 groups and goes to
@@ -2550,7 +2579,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const int64_t n_tiles = (nnz + kTile - 1) / kTile;
     const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
     Findings *found;
-    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt, *stripe_slots;
+    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt, *stripe_slots, *stripe_groups;
     int32_t *d_a;
     Tile *tiles;
     uint32_t *list = nullptr;
@@ -2578,7 +2607,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&blk_id, D + 1);
     tmp.reserve(&stripe_cnt, NBR);
     tmp.reserve(&stripe_slots, NBR);
-    tmp.reserve(&scan_tmp, 3 * (scan_n / kScanTile + 2));
+    tmp.reserve(&stripe_groups, NBR);
+    tmp.reserve(&scan_tmp, 4 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
     HBP_TRY(tmp.commit());
     const int64_t first_words = (int64_t)(own0.total() / sizeof(uint32_t)), second_words = ((char *)tiles - (char *)dense_cnt) / (int64_t)sizeof(uint32_t);
@@ -2610,7 +2640,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // step 4: scans over the block table
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
-    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, csr_ptr, n_rows, R, stripe_cnt, stripe_slots, found);
+    k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, csr_ptr, n_rows, R, (uint32_t)W, stripe_cnt, stripe_slots,
+                                                      stripe_groups, found);
     HBP_HIP(hipGetLastError());
 
     // the one host round trip of the build: totals (and the error word)
@@ -2672,8 +2703,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // for k_fill, whose short segments have few such groups: the 4M x 1M lognormal matrix lost 60 us.
     const bool cut = parts == 0 && long_segments && longest_row > kLongRow && longest_row > 8 * (nnz / n_rows);
     Arena tmp2(false, h->device, 1);
-    uint32_t *multi_idx;
-    tmp2.reserve(&multi_idx, NBR + 1);
+    uint32_t *multi_idx, *stripe_turn, *blk_turn;
+    tmp2.reserve(&multi_idx, NBR + 1); tmp2.reserve(&stripe_turn, NBR + 1); tmp2.reserve(&blk_turn, B);
+    // k_fill_flat takes the groups row block by row block, too, where segments are short and there are several block columns.  Fill kernels, us, in the
+    // layout's order / row block by row block: R-MAT 2^22 827 / 574, 2^20 (fp64) 223 / 200, 2^18 51 / 43; 13 nonzeros per segment (27-point
+    // grid of 128^3) 226 / 220, 4.4 (5-point grid of 1500^2) 33.2 / 31.7, which the 4 us of k_group_turns are not worth.
+    int32_t *fill_order = nullptr;
+    if (parts == 0 && nnz < 4 * S && NBC > 1) tmp2.reserve(&fill_order, G);
     uint2 *bucket;
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
@@ -2691,10 +2727,10 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         dense_cnt, slot_off, group_off, blk_id, D, (int32_t)NBR, (int32_t)NBC, h->blk_bm, h->blk_bn, h->slot_ptr,
         h->blk_group_ptr, h->col_blk_ptr, h->col_group_ptr, h->col_local + nnz, reinterpret_cast<uint32_t *>((char *)h->data + (size_t)nnz * h->value_bytes),
         256 * h->value_bytes / 4, h->group_slot + G, longest_all);
-    HBP_TRY(exclusive_scans(Scans{{stripe_cnt, stripe_slots, stripe_slots}, {(uint32_t *)h->stripe_ptr, (uint32_t *)h->unit_ptr, multi_idx},
-                                  {kOpIdentity, kOpUnits, kOpSplit}}, 3, NBR, (uint32_t)h->unit_slots, scan_tmp, st));
-    k_stripe_fill<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, stripe_slots, h->unit_ptr, multi_idx, (int32_t)NBR, (int32_t)NBC,
-                                                       (int32_t)B, h->stripe_blk, h->unit_stripe, h->unit_k, h->multi_stripes);
+    HBP_TRY(exclusive_scans(Scans{{stripe_cnt, stripe_slots, stripe_slots, stripe_groups}, {(uint32_t *)h->stripe_ptr, (uint32_t *)h->unit_ptr, multi_idx, stripe_turn},
+                                  {kOpIdentity, kOpUnits, kOpSplit, kOpIdentity}}, 4, NBR, (uint32_t)h->unit_slots, scan_tmp, st));
+    k_stripe_fill<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, stripe_slots, h->unit_ptr, multi_idx, stripe_turn, (uint32_t)W,
+                                                       (int32_t)NBR, (int32_t)NBC, (int32_t)B, h->stripe_blk, blk_turn, h->unit_stripe, h->unit_k, h->multi_stripes);
     const dim3 stripe_grid((unsigned)(8 * ((NBR + 7) / 8) * std::max(parts, 1)));
     // steps 5-6 (slot_off doubles as the per-block cursor from here on, but for row blocks as a whole)
     if (by_panel) {
@@ -2747,8 +2783,9 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                    h->group_slot, h->blk_group_ptr, h->blk_bn, h->seg_len, slot_j, C, nnz, h->col_local, data);
             return;
         }
+        if (fill_order) k_group_turns<<<blocks_for(G, 256), 256, 0, st>>>(h->group_blk, h->blk_group_ptr, blk_turn, (int32_t)G, fill_order);
         const auto flat = cut ? k_fill_flat<true, T> : k_fill_flat<false, T>;
-        flat<<<blocks_for(G, 4), 256, 0, st>>>(csr_col, val, h->group_ptr, h->group_slot, h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C,
+        flat<<<fill_order ? 8 * kFillChunk * blocks_for(G, 32 * kFillChunk) : blocks_for(G, 4), 256, 0, st>>>(fill_order, csr_col, val, h->group_ptr, h->group_slot, h->group_blk, h->blk_bn, h->seg_len, slot_j, (int32_t)G, C,
                                                nnz, h->col_local, data);
         if (!cut) return;
         k_list_rest<<<blocks_for(G, 1024), 256, 0, st>>>(group_longest, (int32_t)G, rest, d_n_rest);
