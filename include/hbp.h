@@ -90,7 +90,8 @@ typedef enum {
     HBP_ERR_TOO_LARGE = -4,          /* nnz or NBR*NBC beyond the supported range */
     HBP_ERR_OUT_OF_MEMORY = -5,
     HBP_ERR_HIP = -6,                /* a HIP runtime call failed; see hbp_last_hip_error() */
-    HBP_ERR_INTERNAL = -7
+    HBP_ERR_INTERNAL = -7,
+    HBP_ERR_WRONG_LENGTH = -8        /* x or y given to hbp_spmv_sized is not as long as the matrix is wide or tall */
 } hbp_status;
 
 /* flags for hbp_params_t.flags */
@@ -264,6 +265,11 @@ int hbp_spmv_f64(hbp_handle_t h, const double *x, double *y, void *stream);
  * streams, different handles) race and must be ordered by the caller.  (A call leaves its claim counters zero for the next one, as
  * hbp_spmv does in the handle.) */
 int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stream);
+
+/* hbp_spmv (kind 0), hbp_spmv_f64 (1) or hbp_spmv_static_scratch (2) for callers that know how long their vectors are, in one
+ * call: n_x and n_y other than n_cols and n_rows are refused with HBP_ERR_WRONG_LENGTH, other kinds with
+ * HBP_ERR_INVALID_ARGUMENT, before anything else is looked at. */
+int hbp_spmv_sized(hbp_handle_t h, int kind, const void *x, int64_t n_x, void *y, int64_t n_y, void *stream);
 
 /* Frees the handle (synchronises the device first).  NULL is allowed.  The library keeps the handle's device
  * memory for the next builds (a build of much the same size then allocates nothing): at most 4 GiB in 16

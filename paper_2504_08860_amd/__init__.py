@@ -13,6 +13,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhbp.so")
 
 HBP_OK = 0
+HBP_ERR_WRONG_LENGTH = -8
 HBP_FLAG_VALIDATE = 1
 HBP_FLAG_NO_REORDER = 2
 HBP_FLAG_KEY_LENGTH = 4
@@ -41,7 +42,7 @@ EXPORTED_SYMBOLS = (
     "hbp_default_params", "hbp_build", "hbp_spmv", "hbp_free", "hbp_get_info", "hbp_export", "hbp_spmv_timed",
     "hbp_csr_spmv", "hbp_status_string", "hbp_last_hip_error",
     "hbp_build_f64", "hbp_spmv_f64", "hbp_spmv_timed_f64", "hbp_csr_spmv_f64", "hbp_release_workspace", "hbp_hash_keys",
-    "hbp_spmv_static_scratch",
+    "hbp_spmv_static_scratch", "hbp_spmv_sized",
 )
 
 
@@ -76,11 +77,12 @@ class HbpError(RuntimeError):
 
 
 _lib = None
+_torch = _raw_stream = None  # set with _lib; _raw_stream(device): its current stream as a number, where this torch has that
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library.  Raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _torch, _raw_stream
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2504_08860_amd.build` "
@@ -88,7 +90,9 @@ def lib() -> ctypes.CDLL:
         # PyTorch ships its own HIP runtime (same soname as the system one).  It has to be in
         # the process before libhbp.so is loaded, so that both share one runtime and device
         # pointers from torch tensors are valid in the library's calls.
-        import torch  # noqa: F401
+        import torch
+        _torch = torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         L.hbp_default_params.argtypes = [ctypes.POINTER(hbp_params_t)]
@@ -102,6 +106,7 @@ def lib() -> ctypes.CDLL:
         L.hbp_build_f64.argtypes = L.hbp_build.argtypes
         L.hbp_spmv_f64.argtypes = L.hbp_spmv.argtypes
         L.hbp_spmv_static_scratch.argtypes = L.hbp_spmv.argtypes
+        L.hbp_spmv_sized.argtypes = [vp, ctypes.c_int, vp, i64, vp, i64, vp]
         L.hbp_spmv_timed_f64.argtypes = L.hbp_spmv_timed.argtypes
         L.hbp_csr_spmv_f64.argtypes = L.hbp_csr_spmv.argtypes
         L.hbp_status_string.argtypes = [ctypes.c_int]
@@ -123,8 +128,9 @@ def _check(status: int, where: str) -> None:
 
 def _stream_ptr(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is not None:
+            return _raw_stream(_torch._C._cuda_getDevice())
+        return _torch.cuda.current_stream().cuda_stream
     return int(getattr(stream, "cuda_stream", stream))
 
 
@@ -198,23 +204,31 @@ def hbp_build_f64(csr_ptr, csr_col, csr_val, n_rows: int, n_cols: int, params: h
     return _build(True, csr_ptr, csr_col, csr_val, n_rows, n_cols, params, stream, overrides)
 
 
+def _product(kind: int, where: str, handle: int, x, y, stream) -> None:
+    # (One call into the library, torch's current stream as a plain number: a small product is 4 us of GPU time, and this function what a
+    # loop of them waits for.  64 x 64 grid, us a call: sizes by hbp_get_info and the stream as an object 8.2, now 5.2.)
+    L = _lib or lib()
+    torch = _torch
+    dtype = torch.float64 if kind == 1 else torch.float32
+    assert x.is_cuda and x.dtype == dtype and x.is_contiguous(), f"x: contiguous {str(dtype)[6:]} CUDA tensor required"
+    assert y.is_cuda and y.dtype == dtype and y.is_contiguous(), f"y: contiguous {str(dtype)[6:]} CUDA tensor required"
+    status = L.hbp_spmv_sized(handle, kind, x.data_ptr(), x.numel(), y.data_ptr(), y.numel(), _stream_ptr(stream))
+    if status != HBP_OK:
+        assert status != HBP_ERR_WRONG_LENGTH, "x and y need n_cols and n_rows elements"
+        raise HbpError(status, where)
+
+
 def hbp_spmv(handle: int, x, y, stream=None) -> None:
-    info = hbp_get_info(handle)
-    assert x.numel() == info.n_cols and y.numel() == info.n_rows
-    _check(lib().hbp_spmv(handle, _dev_f32(x, "x"), _dev_f32(y, "y"), _stream_ptr(stream)), "hbp_spmv")
+    _product(0, "hbp_spmv", handle, x, y, stream)
 
 
 def hbp_spmv_static_scratch(handle: int, x, y, stream=None) -> None:
     """hbp_spmv with the call's intermediates in the library's fixed scratch array (no allocation anywhere)."""
-    info = hbp_get_info(handle)
-    assert x.numel() == info.n_cols and y.numel() == info.n_rows
-    _check(lib().hbp_spmv_static_scratch(handle, _dev_f32(x, "x"), _dev_f32(y, "y"), _stream_ptr(stream)), "hbp_spmv_static_scratch")
+    _product(2, "hbp_spmv_static_scratch", handle, x, y, stream)
 
 
 def hbp_spmv_f64(handle: int, x, y, stream=None) -> None:
-    info = hbp_get_info(handle)
-    assert x.numel() == info.n_cols and y.numel() == info.n_rows
-    _check(lib().hbp_spmv_f64(handle, _dev_f64(x, "x"), _dev_f64(y, "y"), _stream_ptr(stream)), "hbp_spmv_f64")
+    _product(1, "hbp_spmv_f64", handle, x, y, stream)
 
 
 def hbp_spmv_timed(handle: int, x, y, iters: int, stream=None):

@@ -16,13 +16,15 @@ namespace {
 
 struct DeviceGuard {  // makes the handle's device current for the duration of a call
     int prev = -1;
-    bool ok = true;
+    bool ok = true, changed = false;
     explicit DeviceGuard(int device)
     {
         if (hipGetDevice(&prev) != hipSuccess) { ok = false; return; }
-        if (prev != device && hipSetDevice(device) != hipSuccess) ok = false;
+        if (prev == device) return;
+        changed = true;
+        if (hipSetDevice(device) != hipSuccess) ok = false;
     }
-    ~DeviceGuard() { if (prev >= 0) (void)hipSetDevice(prev); }
+    ~DeviceGuard() { if (changed) (void)hipSetDevice(prev); }
 };
 
 // `idle`: the caller has waited, successfully, for everything on the device that uses the handle
@@ -404,6 +406,14 @@ int hbp_spmv_static_scratch(hbp_handle_t h, const float *x, float *y, void *stre
     return product(h, x, y, (hipStream_t)stream, fixed);
 }
 
+int hbp_spmv_sized(hbp_handle_t h, int kind, const void *x, int64_t n_x, void *y, int64_t n_y, void *stream)
+{
+    if (!h || kind < 0 || kind > 2) return HBP_ERR_INVALID_ARGUMENT;
+    if (n_x != h->n_cols || n_y != h->n_rows) return HBP_ERR_WRONG_LENGTH;
+    if (kind == 2) return hbp_spmv_static_scratch(h, static_cast<const float *>(x), static_cast<float *>(y), stream);
+    return spmv_any(kind == 1 ? 8 : 4, h, x, y, stream);
+}
+
 int hbp_spmv_timed(hbp_handle_t h, const float *x, float *y, void *stream, int iters, float *ms_part, float *ms_combine,
                    float *ms_total)
 {
@@ -439,6 +449,7 @@ const char *hbp_status_string(int status)
     case HBP_ERR_OUT_OF_MEMORY: return "out of device memory";
     case HBP_ERR_HIP: return "HIP runtime error";
     case HBP_ERR_INTERNAL: return "internal error";
+    case HBP_ERR_WRONG_LENGTH: return "a vector is not as long as the matrix is wide or tall";
     default: return "unknown status";
     }
 }
