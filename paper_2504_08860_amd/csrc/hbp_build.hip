@@ -2526,13 +2526,29 @@ static int launch_schedule(hbp_handle_s *h, hipStream_t st, const Words &words, 
 }
 
 static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
-                               const hbp_params_t &p, hipStream_t st);
+                               const hbp_params_t &p, bool may_list, hipStream_t st);
 
 int build_layout(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
                  const hbp_params_t &p, hipStream_t st)
 {
     std::lock_guard<std::mutex> workspace_lock(workspace_mutex(h->device));
-    const int rc = build_layout_locked(h, csr_ptr, csr_col, csr_val, p, st);
+    int rc = build_layout_locked(h, csr_ptr, csr_col, csr_val, p, true, st);
+    if (rc == HBP_ERR_OUT_OF_MEMORY && h->device >= 0 && h->device < kWorkspaceDevices) {
+        // The list of segments takes 4 bytes per nonzero of scratch memory that a build can do without.
+        (void)hipStreamSynchronize(st);
+        (void)hipGetLastError();
+        for (int i = 0; i < 2; i++) {
+            release_block(h->device, h->arena[i], h->arena_bytes[i], false);
+            h->arena[i] = nullptr;
+            h->arena_bytes[i] = 0;
+        }
+        for (auto &w : g_workspace[h->device]) {
+            if (w.base) (void)hipFree(w.base);
+            w.base = nullptr;
+            w.bytes = 0;
+        }
+        rc = build_layout_locked(h, csr_ptr, csr_col, csr_val, p, false, st);
+    }
     // A build that gives up may have kernels in flight that still use the shared workspace: they
     // have to finish before the lock is released and the next build takes the workspace over.
     if (rc != HBP_OK) (void)hipStreamSynchronize(st);
@@ -2540,7 +2556,7 @@ int build_layout(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col
 }
 
 static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
-                               const hbp_params_t &p, hipStream_t st)
+                               const hbp_params_t &p, bool may_list, hipStream_t st)
 {
     const int64_t n_rows = h->n_rows, n_cols = h->n_cols;
     const int32_t R = h->R, C = h->C, W = h->W;
@@ -2611,10 +2627,10 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // The first pass leaves a list of the segments, one word each (block column, row, place in the tile), where these fit a word.
     auto bits_for = [](int64_t values) { int32_t b = 0; while ((int64_t(1) << b) < values) b++; return b; };
     const int32_t row_bits = bits_for(R);
-    const bool listed = kPlaceBits + row_bits + bits_for(NBC) <= 32;
+    const bool listed = may_list && kPlaceBits + row_bits + bits_for(NBC) <= 32;
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
     // could steps 5 to 7 go by row blocks? (see below)
-    const bool short_rows = h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast &&
+    const bool short_rows = listed && h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast &&
                             10 * 8 * NBC * panel_row_words(R) <= kPanelLds;  // (the bits at a = 0)
     SegmentWords words{nullptr, nullptr};
     // the arrays that start at zero side by side: one fill
