@@ -6,10 +6,10 @@
 //   1-3. segments, counted the row pointers are checked; a nonzero starts a segment when it starts a row or its column
 //                          block differs from its left neighbour's (Algorithm 2's inner
 //                          while loop, evaluated for all nonzeros at once); segments per
-//                          (column block, row block)
+//                          (column block, row block), and a list of the segments
 //   4. block table         scans give each non-empty block its slot range, group range and
 //                          list position
-//   5. segments, again     every segment drops (length, local row, first nonzero) into its
+//   5. segments, placed    every segment drops (length, local row, first nonzero) into its
 //                          block's slot range through an atomic cursor
 //   6. block ordering      each block's range is ordered by (key, local row) in LDS; the
 //                          pair is unique inside a block, so the result does not depend on
@@ -17,6 +17,7 @@
 //                          deterministic limit of the paper's atomic hash-table insertion.
 //   7. fill                one wavefront per group writes col/data round by round
 //                          (column-major inside the group, Section 3.2 last paragraph)
+// Where row segments are short, steps 5 to 7 are done by row blocks as a whole instead (k_panel_slots, k_panel_fill), with the same result.
 #include "hbp_internal.h"
 
 #include <chrono>
@@ -442,7 +443,7 @@ constexpr int kLongRow = 4 * kFillRounds;
 // What k_check_ptr and k_segments find out, zeros to begin with: what is wrong; the longest row, where it has more than kLongRow
 // nonzeros; whether a tile shows a long segment.  The last two in copies apart from each other (one word for all: 101 us for k_check_ptr in
 // place of 10 where one row in 40 has to be told), and all behind one pointer (another argument, two more scalar registers, and
-// a compute unit holds three tiles of k_segments<false> instead of four: 98 -> 114 us on the 27-point grid of 128^3).
+// a compute unit holds three tiles of k_segments instead of four: 98 -> 114 us on the 27-point grid of 128^3).
 struct Findings {
     int32_t err;
     uint32_t most_slots, most_nonzeros;  // of a row block
@@ -1578,8 +1579,11 @@ constexpr int kPanelNonzeros = 1 << 16;                                 // its n
 constexpr int kPanelLds = 148 * 1024;                                   // dynamic LDS of k_panel_slots at most (its own arrays: below 12 KB)
 constexpr int kPanelTails = 12288;                                      // rounds in its list of tails at most: what a workgroup asks for of the LDS
 constexpr int kPanelShift = 2;                                          // a at most: a band of 64 rows and more keeps 4 remainders apart
-constexpr int kPanelLeast = 128;                                        // row blocks, at least: fewer leave the device idle
-constexpr int kPanelLongest = 16384;                                    // longest row where segments are long
+// Row blocks, at least.  With 128 of them half of the device is idle; builds, us, block by block / by row blocks: templates of 262K rows (128 row blocks) 335 /
+// 318, of 300K (147) 314 / 269, 524K (256) 428 / 333; lognormal 300K x 300K (147) 269 / 261, in fp64 280 / 285, 500K x 200K (245) in fp64 380 / 332.
+constexpr int kPanelLeast = 128;
+// Longest row where segments are long: a row segment's rounds behind the table are gone through one after the other, eight to a step.
+constexpr int kPanelLongest = 16384;
 
 // Words of 64 rows; an odd number of them, so that neighbouring segments, which differ in their block columns, lie in different banks.
 __host__ __device__ inline uint32_t panel_row_words(int32_t R) { return (((uint32_t)R + 63u) / 64u) | 1u; }
@@ -1624,6 +1628,10 @@ __device__ __forceinline__ Panel panel_of(int32_t bm, const int32_t *__restrict_
 // few groups have, come from a list of their lanes, or, where there is no room for them in it, are written group by group.
 // The LDS holds in turn where the segments start, the bits with their counts, the slots with the table behind them, and in place of the slots, in CSR order,
 // a segment's group and lane (10 and 6 bits) and the last 16 bits of where it starts.
+// Bound by its instructions and by the waits between its phases, since the LDS has room for one workgroup on a CU: lognormal 4M x 1M, 1954 row blocks of 24,500
+// segments, 470 us, in place of 301 + 368 for k_place and k_order_block.  Of 140,000 cycles a row block 21,000 pass until the segments are there, 52,000 with bits,
+// ranks and slots (with an even number of words per code 64 neighbouring segments met in two banks: 495 against 343 us for the kernel as it was then),
+// 29,000 with table and tails (the table by ballots, group by group: 50,000), 33,000 with the places.
 __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC,
                                                                const Tile *__restrict__ tiles, const uint64_t *__restrict__ word_starts,
                                                                const uint16_t *__restrict__ word_at, const uint32_t *__restrict__ list, int32_t row_bits,
@@ -1990,6 +1998,8 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
 // The fill: a workgroup takes a share of a row block's nonzeros in the layout's order, `room` at most, and puts them in place in LDS; they come from the CSR arrays
 // in their order, and what it writes are whole runs.  `shares` workgroups per row block at most; those of one row block run on
 // one XCD, whose L2 then holds what all of them read.
+// Bound by what it reads, 10 bytes a nonzero and share at 8 TB/s, and by its stores, one after the other as the LDS has room for one workgroup on a CU: lognormal
+// 4M x 1M in 2.05 shares a row block 411 us, in place of 880 for k_fill.  (Two workgroups of 80 KB to a CU, so four shares: 488; of 512 threads 471.)
 template <typename T>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC, int32_t C,
                                                               int32_t shares, uint32_t room, const uint16_t *__restrict__ places,
@@ -2685,7 +2695,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
                                                       stripe_groups, found);
     HBP_HIP(hipGetLastError());
 
-    // the one host round trip of the build: totals (and the error word)
+    // a host round trip: totals (and the error word)
     k_publish<<<1, 64, 0, st>>>(Words{{slot_off + D, group_off + D, blk_id + D, &found->err, d_a}}, 5, host, found);
     HBP_HIP(hipGetLastError());
     HBP_HIP(hipStreamSynchronize(st));
@@ -2729,6 +2739,9 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // stencil) or 86 slots per block (R-MAT, whose dense row blocks then also wait for a few
     // workgroups) it is slower than the layout's own order with a wavefront per group.
     const bool by_row_block = NBR >= 64 && nnz < 4 * S && S >= 256 * B;
+    // Steps 5 to 7 by row blocks as a whole under the same rule, where a row block fits the registers and the LDS of a workgroup (a, the row blocks' slots
+    // and nonzeros, the bits).  Builds, us, block by block / by row blocks: templates of 400K rows 359 / 295; lognormal 1M x 1M 615 / 483, 4M x 1M
+    // 1946 / 1253; fp64 1.2M x 300K 734 / 629, 2M x 500K 1251 / 905.
     const size_t panel_words = (size_t)NBC * ((9u << a) - 1u) * panel_row_words(R);
     const size_t slots_table = sizeof(uint32_t) * (size_t)most_slots + (size_t)(most_slots / 64 + NBC) * panel_table_row((uint32_t)(a & 15)) + 8;
     const size_t slots_lds = std::max<size_t>(slots_table, panel_words * (sizeof(uint64_t) + sizeof(uint16_t)));
