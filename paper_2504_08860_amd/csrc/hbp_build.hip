@@ -2536,29 +2536,13 @@ static int launch_schedule(hbp_handle_s *h, hipStream_t st, const Words &words, 
 }
 
 static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
-                               const hbp_params_t &p, bool may_list, hipStream_t st);
+                               const hbp_params_t &p, hipStream_t st);
 
 int build_layout(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
                  const hbp_params_t &p, hipStream_t st)
 {
     std::lock_guard<std::mutex> workspace_lock(workspace_mutex(h->device));
-    int rc = build_layout_locked(h, csr_ptr, csr_col, csr_val, p, true, st);
-    if (rc == HBP_ERR_OUT_OF_MEMORY && h->device >= 0 && h->device < kWorkspaceDevices) {
-        // The list of segments takes 4 bytes per nonzero of scratch memory that a build can do without.
-        (void)hipStreamSynchronize(st);
-        (void)hipGetLastError();
-        for (int i = 0; i < 2; i++) {
-            release_block(h->device, h->arena[i], h->arena_bytes[i], false);
-            h->arena[i] = nullptr;
-            h->arena_bytes[i] = 0;
-        }
-        for (auto &w : g_workspace[h->device]) {
-            if (w.base) (void)hipFree(w.base);
-            w.base = nullptr;
-            w.bytes = 0;
-        }
-        rc = build_layout_locked(h, csr_ptr, csr_col, csr_val, p, false, st);
-    }
+    const int rc = build_layout_locked(h, csr_ptr, csr_col, csr_val, p, st);
     // A build that gives up may have kernels in flight that still use the shared workspace: they
     // have to finish before the lock is released and the next build takes the workspace over.
     if (rc != HBP_OK) (void)hipStreamSynchronize(st);
@@ -2566,7 +2550,7 @@ int build_layout(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col
 }
 
 static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const int32_t *csr_col, const void *csr_val,
-                               const hbp_params_t &p, bool may_list, hipStream_t st)
+                               const hbp_params_t &p, hipStream_t st)
 {
     const int64_t n_rows = h->n_rows, n_cols = h->n_cols;
     const int32_t R = h->R, C = h->C, W = h->W;
@@ -2599,11 +2583,16 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own0.reserve(&h->fixed_col, (int64_t)h->P);
     own0.reserve(&h->unit_ptr, NBR + 1);
     own0.reserve(&h->col_rank, NBC + 1);
+    const size_t own0_zeros = own0.total();
+    if (nnz > 0) {  // 256 elements of padding: the SpMV part reads whole aligned 256-element chunks
+        own0.reserve(&h->col_local, nnz + 256);
+        own0.reserve_bytes(&h->data, (nnz + 256) * h->value_bytes);
+    }
     HBP_TRY(own0.commit());
     h->arena[0] = own0.base(); h->arena_bytes[0] = own0.bytes();
 
     if (nnz == 0) {  // empty matrix: no blocks; the combine part alone writes y = 0
-        HBP_HIP(hipMemsetAsync(own0.base(), 0, own0.total(), st));
+        HBP_HIP(hipMemsetAsync(own0.base(), 0, own0_zeros, st));
         h->B = h->S = h->G = 0;
         h->a = p.hash_shift >= 0 ? p.hash_shift : 0;
         Arena own1(true, h->device);
@@ -2633,26 +2622,24 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt, *stripe_slots, *stripe_groups;
     int32_t *d_a;
     Tile *tiles;
-    uint32_t *list = nullptr;
-    // The first pass leaves a list of the segments, one word each (block column, row, place in the tile), where these fit a word.
+    // The first pass leaves a list of the segments, one word each (block column, row, place in the tile), where these fit a word.  A tile's part of
+    // it begins where the tile does, so it takes the room of as many words as there are nonzeros: that of the layout's values, which are written last.
     auto bits_for = [](int64_t values) { int32_t b = 0; while ((int64_t(1) << b) < values) b++; return b; };
     const int32_t row_bits = bits_for(R);
-    const bool listed = may_list && kPlaceBits + row_bits + bits_for(NBC) <= 32;
+    const bool listed = kPlaceBits + row_bits + bits_for(NBC) <= 32;
     const int32_t reorder = (p.flags & HBP_FLAG_NO_REORDER) ? 0 : (p.flags & HBP_FLAG_KEY_LENGTH) ? 2 : (p.flags & HBP_FLAG_BLOCK_SHIFT) ? 3 : 1;
-    // could steps 5 to 7 go by row blocks? (see below)
-    const bool short_rows = listed && h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast &&
+    uint32_t *const list = static_cast<uint32_t *>(h->data);
+    // could steps 5 to 7 go by row blocks? (see below)  Which nonzeros start a segment is kept where the layout's columns come to be, ten bytes for
+    // 64 nonzeros (only a matrix of a few hundred nonzeros has not the room).
+    const bool short_rows = listed && n_tiles * kTileWords * 10 <= 2 * nnz && h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast &&
                             10 * 8 * NBC * panel_row_words(R) <= kPanelLds;  // (the bits at a = 0)
-    SegmentWords words{nullptr, nullptr};
+    const SegmentWords words{reinterpret_cast<uint64_t *>(h->col_local), h->col_local + 4 * n_tiles * kTileWords};
+    static_assert(sizeof(*words.starts) == 4 * sizeof(*h->col_local) && sizeof(*words.at) == sizeof(*h->col_local), "where the second array begins");
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, kHistCopies * kHistStride);
     tmp.reserve(&found, 1);
     tmp.reserve(&tiles, n_tiles);
-    if (listed) tmp.reserve(&list, nnz);
-    if (short_rows) {
-        tmp.reserve(&words.starts, n_tiles * kTileWords);
-        tmp.reserve(&words.at, n_tiles * kTileWords);
-    }
     tmp.reserve(&slot_off, D + 1);
     tmp.reserve(&group_off, D + 1);
     tmp.reserve(&blk_id, D + 1);
@@ -2662,7 +2649,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&scan_tmp, 4 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
     HBP_TRY(tmp.commit());
-    const int64_t first_words = (int64_t)(own0.total() / sizeof(uint32_t)), second_words = ((char *)tiles - (char *)dense_cnt) / (int64_t)sizeof(uint32_t);
+    const int64_t first_words = (int64_t)(own0_zeros / sizeof(uint32_t)), second_words = ((char *)tiles - (char *)dense_cnt) / (int64_t)sizeof(uint32_t);
     k_begin<<<(unsigned)std::min<int64_t>(1024, (first_words + second_words + 1023) / 1024), 256, 0, st>>>(
         static_cast<uint32_t *>(own0.base()), first_words, dense_cnt, second_words, d_a, p.hash_shift);
 
@@ -2718,8 +2705,6 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     own1.reserve(&h->row_local, S + 1); own1.reserve(&h->seg_len, S + 1);
     own1.reserve(&h->blk_shift, B + 1);
     if (p.flags & HBP_FLAG_KEEP_KEYS) own1.reserve(&h->slot_key, S + 1);
-    // 256 elements of padding: the SpMV part reads whole aligned 256-element chunks
-    own1.reserve(&h->col_local, nnz + 256); own1.reserve_bytes(&h->data, (nnz + 256) * h->value_bytes);
     own1.reserve_bytes(&h->partial, (S + 1) * h->value_bytes);
     if (h->unit_slots == 0) {
         // default: only row blocks with more than twice the average number of slots are cut
@@ -2762,9 +2747,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // k_fill_flat takes the groups row block by row block, too, where segments are short and there are several block columns.  Fill kernels, us, in the
     // layout's order / row block by row block: R-MAT 2^22 827 / 574, 2^20 (fp64) 223 / 200, 2^18 51 / 43; 13 nonzeros per segment (27-point
     // grid of 128^3) 226 / 220, 4.4 (5-point grid of 1500^2) 33.2 / 31.7, which the 4 us of k_group_turns are not worth.
-    int32_t *fill_order = nullptr;
-    if (parts == 0 && nnz < 4 * S && NBC > 1) tmp2.reserve(&fill_order, G);
-    uint2 *bucket;
+    const bool by_turns = parts == 0 && nnz < 4 * S && NBC > 1;
+    uint2 *bucket = nullptr;
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
     uint16_t *places = nullptr;
@@ -2774,6 +2758,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     int2 *rest = nullptr;  // an entry per kFillRounds nonzeros of a group's longest row at most
     if (cut) tmp2.reserve(&rest, nnz / kFillRounds + 1);
     HBP_TRY(tmp2.commit());
+    int32_t *const fill_order = by_turns ? reinterpret_cast<int32_t *>(bucket) : nullptr;  // (k_order_block has read the buckets by then; G <= S)
     d_n_long = longest_all + 1;
     uint32_t *const d_n_rest = longest_all + 2;
 

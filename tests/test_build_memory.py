@@ -1,44 +1,53 @@
-"""A build whose scratch memory does not hold the list of segments goes without it (the noting runtime of test_launches.py, CPU)."""
+"""The scratch memory of a build goes by its segments and blocks, not by its nonzeros (the noting runtime of test_launches.py, CPU)."""
 import pytest
 
 from test_launches import run  # noqa: F401  (a fixture)
 
+# rows, columns, R, C, segments, groups, blocks, most slots and nonzeros of a row block, what places the segments and fills the layout
+ROUTES = {
+    "segments of any length": (1 << 20, 30_000, 512, 30_000, 1 << 20, 1 << 14, 1 << 11, 512, 40_000, ["k_place", "k_fill_flat"]),
+    "no list": (1 << 20, 30_000, 2048, 50, 1 << 20, 1 << 18, 1 << 17, 2048, 40_000, ["PassE3", "k_fill_flat"]),
+    "short, small blocks": (1 << 20, 600_000, 512, 30_000, 8_000_000, 1_200_000, 40_960, 5_000, 12_000, ["k_place", "k_group_turns", "k_fill_flat"]),
+    "short, row blocks": (1 << 20, 300_000, 2048, 30_000, 8_000_000, 130_000, 5_120, 16_000, 40_000, ["k_panel_slots", "k_panel_fill"]),
+    "short, no row blocks": (1 << 20, 300_000, 2048, 30_000, 8_000_000, 130_000, 5_120, 40_000, 70_000, ["k_place", "k_fill"]),
+}
 
-@pytest.mark.parametrize("n_rows,n_cols,R,C,nnz,S,G,B", [
-    (1 << 20, 30_000, 512, 30_000, 64_000_000, 1 << 20, 1 << 14, 1 << 11),       # long segments
-    (1 << 20, 300_000, 2048, 30_000, 16_000_000, 8_000_000, 130_000, 5_120),     # short ones
-])
-def test_builds_without_the_list_where_memory_is_short(run, n_rows, n_cols, R, C, nnz, S, G, B):  # noqa: F811
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("route", ROUTES)
+def test_scratch_memory(run, route, f64):  # noqa: F811
+    n_rows, n_cols, R, C, S, G, B, most_slots, most_nonzeros, kernels = ROUTES[route]
+    C = C // 2 if f64 else C
+    short = route.startswith("short")
+    sizes = (8_000_000, 31_000_000) if short else (8_000_000, 64_000_000)
     got = run(f"""
-        def first_passes():
-            return [k for k in noted()[0] if "k_segments" in k or "k_place" in k or "k_panel" in k]
-        rt.live_bytes.restype = ctypes.c_size_t
-        args = (False, {n_rows}, {n_cols}, {R}, {C}, {nnz}, {S}, {G}, {B}, [0] * 2, 100)
-        rt.set_capacity(1 << 34)
-        h = build(*args)
-        with_list, most = first_passes(), rt.live_bytes()
-        assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0 and rt.live_bytes() == 0
-        rt.set_capacity(most - 1)
-        for wait, words in enumerate([[0, {nnz}], [{S}, {G}, {B}, 0, 4, 0, 0], [0, {nnz}], [100, 0, 0, 0], [100, 0, 0, 0], [100, 0, 0, 0]]):
-            for i, w in enumerate(words):
-                rt.set_word(wait, i, w)
-        # (the build waits for nnz, for the totals, once more when it starts again, and for the totals again)
-        p = H.hbp_params_t()
-        assert lib.hbp_default_params(ctypes.byref(p)) == 0
-        p.rows_per_block, p.cols_per_block, p.rounds_per_batch, p.hash_shift = {R}, {C}, 4, 4
-        rt.set_word(3, 0, {S}); rt.set_word(3, 1, {G}); rt.set_word(3, 2, {B}); rt.set_word(3, 3, 0); rt.set_word(3, 4, 4)
-        rt.begin()
-        h = ctypes.c_void_p()
-        rc = lib.hbp_build(word, word, word, {n_rows}, {n_cols}, ctypes.byref(p), None, ctypes.byref(h))
-        without, live = first_passes(), rt.live_bytes()
-        if rc == 0:
-            assert lib.hbp_free(h) == 0
-        assert lib.hbp_release_workspace() == 0
-        print((rc, with_list, without, most - live, rt.live_bytes()))
+        out = []
+        for nnz in {sizes}:
+            rt.set_capacity(1 << 34)
+            h = build({f64}, {n_rows}, {n_cols}, {R}, {C}, nnz, {S}, {G}, {B}, [0, 0, {most_slots}, {most_nonzeros}], 100, a=1)
+            out.append(noted())
+            assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0 and rt.live_bytes() == 0
+        print(out)
     """)
-    rc, with_list, without, saved, left = got
-    assert rc == 0 and left == 0
-    assert saved >= 4 * nnz
-    assert any("PassE1" in k or "PassE2" in k for k in with_list) and any("k_place" in k or "k_panel" in k for k in with_list)
-    tail = without[-2:]  # what the second attempt ran
-    assert "PassE0" in tail[0] and "PassE3" in tail[1]
+    NBR, NBC = -(-n_rows // R), -(-n_cols // C)
+    D = NBR * NBC
+    for nnz, (launched, allocated) in zip(sizes, got):
+        wrong = [k for k in kernels if not any(k in name for name in launched)]
+        assert not wrong, (wrong, launched)
+        assert len(allocated) == 4      # handle, scratch, handle, scratch
+        scan = 16 * ((max(D, NBR, nnz // 64 + D) + 1) // 2048 + 2)
+        tables = 16 * (D + 1) + 16 * (nnz // 4096 + 1) + 20 * (NBR + 1) + 4 * (B + 1) + scan + 16_384
+        assert allocated[1] + allocated[3] <= 9 * (tables + 12 * S + 8 * (G + 1)) // 8, (allocated, tables)
+
+
+def test_room_for_the_starts_of_segments(run):  # noqa: F811
+    """They lie where the layout's columns come to be, ten bytes for 64 nonzeros and whole tiles of 4096: no row blocks as a whole below 320 nonzeros."""
+    got = run("""
+        out = []
+        for nnz in (319, 320, 4096, 4097):
+            h = build(False, 1 << 18, 300, 2048, 300, nnz, nnz, 1, 1, [0, 0, nnz, nnz], 100, a=0)
+            out.append(any("PassE2" in k for k in noted()[0]))
+            assert lib.hbp_free(h) == 0
+        print(out)
+    """)
+    assert got == [False, True, True, True]

@@ -20,7 +20,7 @@ static struct { const void *f; const char *name; } kernels[kMax];
 static int n_kernels, n_launched, n_allocated, n_waits;
 static const char *launched[kMax];
 static size_t allocated[kMax];
-static unsigned *readback, script[8][8];
+static unsigned *readback, script[8][16];
 void __hipRegisterFunction(void **module, const void *f, char *device_f, const char *name, unsigned limit, void *a, void *b, void *c, void *d, int *e)
 {
     (void)module; (void)device_f; (void)limit; (void)a; (void)b; (void)c; (void)d; (void)e;
@@ -84,12 +84,12 @@ word = ctypes.create_string_buffer(64)
 def noted():
     return [rt.launch(i).decode() for i in range(rt.launches())], [rt.allocation(i) for i in range(rt.allocations())]
 
-def build(f64, n_rows, n_cols, R, C, nnz, S, G, B, counts, U):
+def build(f64, n_rows, n_cols, R, C, nnz, S, G, B, counts, U, a=4):
     # (given block parameters: no sampling pass; a given shift: no sampled one; given rounds: workers)
     p = H.hbp_params_t()
     assert lib.hbp_default_params(ctypes.byref(p)) == 0
-    p.rows_per_block, p.cols_per_block, p.rounds_per_batch, p.hash_shift = R, C, 4, 4
-    for wait, words in enumerate([[0, nnz], [S, G, B, 0, 4, *counts], [U, 0, 0, 0]]):
+    p.rows_per_block, p.cols_per_block, p.rounds_per_batch, p.hash_shift = R, C, 4, a
+    for wait, words in enumerate([[0, nnz], [S, G, B, 0, a, *counts], [U, 0, 0, 0]]):
         for i, w in enumerate(words):
             rt.set_word(wait, i, w)
     rt.begin()
