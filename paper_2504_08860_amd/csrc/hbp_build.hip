@@ -99,7 +99,7 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t *to
 
 // ------------------------------------------------------------------ device-wide exclusive scans
 //
-// Up to four scans of arrays of one length go through the same launches: the arrays are short (tens of
+// Up to five scans of arrays of one length go through the same launches: the arrays are short (tens of
 // thousands of entries), so a scan costs its launches, some 5 us each, whatever it does.
 
 enum { kOpIdentity = 0, kOpCeilDivW = 1, kOpNonZero = 2, kOpUnits = 3, kOpSplit = 4 };  // (the last two: combine units of W slots, see k_stripe_fill)
@@ -112,9 +112,9 @@ constexpr int kScanTile = 2048;  // 256 threads x 8 consecutive items
 
 // out[0..n) = exclusive scan of op(in), out[n] = total.  `in` and `out` may alias where only one scan reads `in`.
 struct Scans {
-    const uint32_t *in[4];
-    uint32_t *out[4];
-    int32_t op[4];
+    const uint32_t *in[5];
+    uint32_t *out[5];
+    int32_t op[5];
 };
 
 __global__ __launch_bounds__(256) void k_scan_reduce(Scans s, int64_t n, uint32_t W, int64_t n_tiles, uint32_t *__restrict__ tile_sum)
@@ -447,7 +447,8 @@ constexpr int kLongRow = 4 * kFillRounds;
 struct Findings {
     int32_t err;
     uint32_t most_slots, most_nonzeros;  // of a row block
-    int32_t apart[13];
+    uint32_t dealt[9];                   // shares of row blocks for the eight XCDs, row blocks that hold something (see deal_row_blocks)
+    int32_t apart[4];
     struct { uint32_t longest_row, long_segment, apart[14]; } copy[64];
 };
 __device__ __forceinline__ auto &findings_of_workgroup(Findings *found) { return found->copy[blockIdx.x % 64]; }
@@ -952,6 +953,8 @@ __global__ __launch_bounds__(256) void k_compact_blocks(const uint32_t *__restri
     blk_group_ptr[b] = (int32_t)group_off[d];
 }
 
+constexpr int kShareBits = 2;  // of an entry of the list of shares: which of its row block
+
 // Combine index.  A workgroup takes 64 row blocks (a wavefront reads 64 neighbouring entries of a row of the block
 // table) and deals the block columns out to its 16 wavefronts in contiguous slices.  (One thread per row
 // block walking all block columns: 15 + 33 us for 512 x 64 blocks in 2 workgroups.)
@@ -977,10 +980,52 @@ __device__ __forceinline__ uint32_t stripe_slice_count(const uint32_t *__restric
     return n;
 }
 
+// Where row blocks are taken as a whole: the lists of those that hold something, and of their shares (k_panel_fill's workgroups).  A wavefront deals the
+// ones of 64 row blocks out to the eight XCDs, a row block's shares all to one of them; a lane returns what becomes of one of them (or of none: no shares).
+// (Before, the grids had a workgroup for every row block and for every share that the fullest row block needs; one without work waits for a compute unit's
+// whole LDS, 5 us of the unit's time.  Builds, us, with them / without: fp64, 2000 row blocks of 5100 nonzeros and one of them of 60,000 531 / 401, none of them 394 /
+// 396; 20,000 row blocks, all but 300 empty, 357 / 299, all but 1000 413 / 327; lognormal 4M x 1M, 2.05 shares on average and 3 at most, 1465 / 1456.)
+struct Dealt {
+    int64_t bm;
+    uint32_t rank;          // of these row blocks
+    uint32_t shares, upto;  // upto: of this XCD in front of the row block's
+    uint32_t total;         // lanes 0 .. 7: shares of the XCD; lane 8: row blocks
+};
+
+__device__ __forceinline__ Dealt deal_row_blocks(int64_t bm, uint32_t nonzeros, uint32_t room)
+{
+    __shared__ uint32_t sh_shares[64], sh_row_block[64];
+    const int lane = threadIdx.x & 63;
+    const uint64_t some = __ballot(nonzeros > 0);
+    // (the first of them to the XCD of its number, so that neighbours that go on over several wavefronts' 64 are spread evenly)
+    const int count = __popcll(some), first = some ? __builtin_ctzll(some) & 7 : 0;
+    if (nonzeros) {
+        const int i = first + lanes_below(some);  // (below 64)
+        sh_shares[i] = (nonzeros + room - 1) / room;
+        sh_row_block[i] = (uint32_t)bm;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const bool there = lane >= first && lane < first + count;
+    Dealt d;
+    d.shares = there ? sh_shares[lane] : 0u;
+    d.bm = there ? (int64_t)sh_row_block[lane] : 0;
+    d.rank = (uint32_t)(lane - first);
+    uint32_t upto = d.shares;
+    for (int i = 8; i < 64; i <<= 1) {
+        const uint32_t t = __shfl_up(upto, i);
+        if (lane >= i) upto += t;
+    }
+    d.upto = upto - d.shares;
+    const uint32_t of_xcd = __shfl(upto, 56 + (lane & 7));
+    d.total = lane < 8 ? of_xcd : lane == 8 ? (uint32_t)count : 0u;
+    return d;
+}
+
 __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restrict__ dense_cnt, int32_t NBR, int32_t NBC, const int32_t *__restrict__ ptr,
                                                        int64_t n_rows, int32_t R, uint32_t W, uint32_t *__restrict__ stripe_cnt,
                                                        uint32_t *__restrict__ stripe_slots, uint32_t *__restrict__ stripe_groups,
-                                                       Findings *__restrict__ found)
+                                                       uint32_t room, uint32_t *__restrict__ dealt, Findings *__restrict__ found)
 {
     __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64], sh_groups[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
@@ -1007,11 +1052,21 @@ __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restric
         stripe_groups[bm] = groups;
         nonzeros = (uint32_t)(ptr[min((bm + 1) * R, n_rows)] - ptr[bm * R]);
     }
+    if (room) {
+        const uint32_t total = deal_row_blocks(bm, nonzeros, room).total;
+        if (threadIdx.x < 9) {
+            dealt[threadIdx.x * gridDim.x + blockIdx.x] = total;
+            if (total) atomicAdd(&found->dealt[threadIdx.x], total);
+        }
+    }
     slots = wave_max(slots);
     nonzeros = wave_max(nonzeros);
-    if (threadIdx.x == 0) {
-        atomicMax(&found->most_slots, slots);
-        atomicMax(&found->most_nonzeros, nonzeros);
+    if (threadIdx.x == 0) {  // (looked at first: atomics on one address queue up, 4.4 -> 10.5 us for the kernel where 20,000 row blocks are told)
+        auto raise = [](uint32_t *most, uint32_t v) {
+            if (v > __hip_atomic_load(most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(most, v);
+        };
+        raise(&found->most_slots, slots);
+        raise(&found->most_nonzeros, nonzeros);
     }
 }
 
@@ -1019,12 +1074,16 @@ __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restric
 // stripe_blk entries, so that no workgroup of the combine part gets much more than unit_slots slots; unit i starts at the first entry whose
 // preceding slots, times u, reach i times the row block's slots.
 // blk_turn: the groups that come before the block's where groups are taken row block by row block.
+// row_blocks, shares: the lists (where they are needed) of row blocks that hold something and of their shares, each XCD's at every eighth place.  dealt: prefix
+// sums over the XCDs' totals of k_stripe_count's workgroups, one XCD after the other, and the row blocks'.
 __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict__ dense_cnt, const uint32_t *__restrict__ blk_id,
                                                       const int32_t *__restrict__ stripe_ptr, const uint32_t *__restrict__ stripe_slots,
                                                       const int32_t *__restrict__ unit_ptr, const uint32_t *__restrict__ multi_idx,
                                                       const uint32_t *__restrict__ stripe_turn, uint32_t W, int32_t NBR, int32_t NBC, int32_t B,
                                                       int32_t *__restrict__ stripe_blk, uint32_t *__restrict__ blk_turn, int32_t *__restrict__ unit_stripe,
-                                                      int32_t *__restrict__ unit_k, int32_t *__restrict__ multi_stripes)
+                                                      int32_t *__restrict__ unit_k, int32_t *__restrict__ multi_stripes, const int32_t *__restrict__ ptr,
+                                                      int64_t n_rows, int32_t R, uint32_t room, const uint32_t *__restrict__ dealt,
+                                                      int32_t *__restrict__ row_blocks, uint32_t *__restrict__ shares)
 {
     __shared__ uint32_t sh[kStripeSlices * 64], sh_slots[kStripeSlices * 64], sh_groups[kStripeSlices * 64];
     const int64_t bm = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
@@ -1033,6 +1092,12 @@ __global__ __launch_bounds__(1024) void k_stripe_fill(const uint32_t *__restrict
     sh[threadIdx.x] = stripe_slice_count(dense_cnt, bm, NBR, NBC, W, bn0, bn1, slots, groups_in_slice);
     sh_slots[threadIdx.x] = slots;
     sh_groups[threadIdx.x] = groups_in_slice;
+    if (shares && threadIdx.x < 64) {
+        const Dealt d = deal_row_blocks(bm, bm < NBR ? (uint32_t)(ptr[min((bm + 1) * R, n_rows)] - ptr[bm * R]) : 0u, room);
+        const uint32_t xcd = threadIdx.x & 7u, at = dealt[xcd * gridDim.x + blockIdx.x] - dealt[xcd * gridDim.x] + d.upto;
+        if (row_blocks && d.shares) row_blocks[dealt[8 * gridDim.x + blockIdx.x] - dealt[8 * gridDim.x] + d.rank] = (int32_t)d.bm;
+        for (uint32_t i = 0; i < d.shares; i++) shares[8u * (at + i) + xcd] = (uint32_t)d.bm << kShareBits | i;
+    }
     __syncthreads();
     if (bm >= NBR) return;
     int32_t k = stripe_ptr[bm];
@@ -1591,7 +1656,7 @@ __host__ __device__ inline uint32_t panel_row_words(int32_t R) { return (((uint3
 // Bytes of a group's row in k_panel_slots' table, 8 * 2^a entries (an odd number of words: neighbouring groups' entries for a round lie in different banks).
 __host__ __device__ inline uint32_t panel_table_row(uint32_t a) { return 2u * ((8u << a) + 2u); }
 
-// The part of the list that holds a row block's segments.
+// The part of the list that holds the segments of a row block that has some.
 struct Panel {
     uint32_t p0, p1;    // its nonzeros
     int32_t t0;         // tile of the first of them
@@ -1607,8 +1672,6 @@ __device__ __forceinline__ Panel panel_of(int32_t bm, const int32_t *__restrict_
     p.p0 = (uint32_t)ptr[(int64_t)bm * R];
     p.p1 = (uint32_t)ptr[min(((int64_t)bm + 1) * R, n_rows)];
     p.t0 = (int32_t)(p.p0 / kTile);
-    p.skip = p.upto = 0;
-    if (p.p0 == p.p1) return p;
     const uint32_t last = p.p1 - 1;
     const int32_t t1 = (int32_t)(last / kTile), t = p.t0 + lane;
     p.skip = word_at[p.p0 / 64] + (uint32_t)__popcll(word_starts[p.p0 / 64] & ((1ull << (p.p0 & 63u)) - 1ull));
@@ -1632,7 +1695,7 @@ __device__ __forceinline__ Panel panel_of(int32_t bm, const int32_t *__restrict_
 // segments, 470 us, in place of 301 + 368 for k_place and k_order_block.  Of 140,000 cycles a row block 21,000 pass until the segments are there, 52,000 with bits,
 // ranks and slots (with an even number of words per code 64 neighbouring segments met in two banks: 495 against 343 us for the kernel as it was then),
 // 29,000 with table and tails (the table by ballots, group by group: 50,000), 33,000 with the places.
-__global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC,
+__global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__restrict__ row_blocks, const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC,
                                                                const Tile *__restrict__ tiles, const uint64_t *__restrict__ word_starts,
                                                                const uint16_t *__restrict__ word_at, const uint32_t *__restrict__ list, int32_t row_bits,
                                                                const uint32_t *__restrict__ slot_off, const uint32_t *__restrict__ group_off,
@@ -1654,10 +1717,9 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     __shared__ uint32_t sh_tail_rounds, sh_tails_n, sh_uneven_n;
     __shared__ uint16_t sh_uneven[kGroups];  // groups with rows of `head` nonzeros and more
     __shared__ uint16_t sh_tails[kGroups];  // groups with more rounds than the table and the list of tails hold
-    const int32_t bm = blockIdx.x;
+    const int32_t bm = row_blocks ? row_blocks[blockIdx.x] : (int32_t)blockIdx.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Panel p = panel_of(bm, ptr, n_rows, R, tiles, word_starts, word_at);
-    if (p.p0 == p.p1) return;
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, 63);
     // lane bn: the block's first slot and group, slots and groups in front of it
     const int64_t d = (int64_t)min(lane, NBC - 1) * NBR + bm;
@@ -1996,13 +2058,13 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
 }
 
 // The fill: a workgroup takes a share of a row block's nonzeros in the layout's order, `room` at most, and puts them in place in LDS; they come from the CSR arrays
-// in their order, and what it writes are whole runs.  `shares` workgroups per row block at most; those of one row block run on
-// one XCD, whose L2 then holds what all of them read.
+// in their order, and what it writes are whole runs.  The shares of one row block run on one XCD, whose L2 then holds what all of them read.
 // Bound by what it reads, 10 bytes a nonzero and share at 8 TB/s, and by its stores, one after the other as the LDS has room for one workgroup on a CU: lognormal
 // 4M x 1M in 2.05 shares a row block 411 us, in place of 880 for k_fill.  (Two workgroups of 80 KB to a CU, so four shares: 488; of 512 threads 471.)
 template <typename T>
-__global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC, int32_t C,
-                                                              int32_t shares, uint32_t room, const uint16_t *__restrict__ places,
+__global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const uint32_t *__restrict__ shares, const Findings *__restrict__ found,
+                                                              const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC, int32_t C,
+                                                              uint32_t room, const uint16_t *__restrict__ places,
                                                               const int32_t *__restrict__ csr_col, const T *__restrict__ csr_val,
                                                               const uint32_t *__restrict__ group_off, const int32_t *__restrict__ group_ptr,
                                                               uint16_t *__restrict__ col_local, T *__restrict__ data)
@@ -2010,15 +2072,15 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const int32_t *__r
     extern __shared__ __align__(8) uint32_t panel_lds[];
     T *const vals = reinterpret_cast<T *>(panel_lds);
     uint16_t *const cols = reinterpret_cast<uint16_t *>(vals + room);
-    const int32_t octet = (int32_t)(blockIdx.x >> 3) / shares, share = (int32_t)(blockIdx.x >> 3) % shares, bm = 8 * octet + (int32_t)(blockIdx.x & 7u);
-    if (bm >= NBR) return;
+    const uint32_t entry = shares ? shares[blockIdx.x] : blockIdx.x << kShareBits, share = entry & ((1u << kShareBits) - 1u);
+    const int32_t bm = (int32_t)(entry >> kShareBits);
+    if (shares && (blockIdx.x >> 3) >= found->dealt[blockIdx.x & 7u]) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t p0 = (uint32_t)ptr[(int64_t)bm * R], p1 = (uint32_t)ptr[min(((int64_t)bm + 1) * R, n_rows)];
     const int64_t d = (int64_t)min(lane, NBC - 1) * NBR + bm;
     const uint32_t g0 = group_off[d], g1 = lane < NBC ? group_off[d + 1] : g0;
     const uint32_t nonzeros = p1 - p0, parts = (nonzeros + room - 1) / room;
-    if ((uint32_t)share >= parts) return;
-    const uint32_t each = (nonzeros + parts - 1) / parts, lo = each * (uint32_t)share, hi = min(nonzeros, lo + each), size = hi - lo;
+    const uint32_t each = (nonzeros + parts - 1) / parts, lo = each * share, hi = min(nonzeros, lo + each), size = hi - lo;
     auto put = [&](uint32_t place, int32_t column, T value) __attribute__((always_inline)) {
         const uint32_t at = place - lo;
         if (at < size) {
@@ -2367,18 +2429,21 @@ int readback_get(int device, uint32_t **out)
     return HBP_OK;
 }
 
-// found: the largest of the copies go behind the words
+// found: the largest of the copies, and the rest, go behind the words
 __global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint32_t *__restrict__ host, const Findings *__restrict__ found)
 {
     const int i = threadIdx.x;
     if (i < count) host[i] = *static_cast<const uint32_t *>(words.at[i]);
     if (!found) return;
     const uint32_t longest = wave_max(found->copy[i].longest_row), segment = wave_max(found->copy[i].long_segment);
+    const uint32_t shares = wave_max(i < 8 ? found->dealt[i] : 0u);
     if (i == 0) {
         host[count] = longest;
         host[count + 1] = segment;
         host[count + 2] = found->most_slots;
         host[count + 3] = found->most_nonzeros;
+        host[count + 4] = found->dealt[8];
+        host[count + 5] = shares;
     }
 }
 
@@ -2619,7 +2684,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const int64_t n_tiles = (nnz + kTile - 1) / kTile;
     const int64_t scan_n = std::max<int64_t>(D, std::max<int64_t>(NBR, nnz / W + D)) + 1;
     Findings *found;
-    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt, *stripe_slots, *stripe_groups;
+    uint32_t *dense_cnt, *slot_off, *group_off, *blk_id, *scan_tmp, *hist, *stripe_cnt, *stripe_slots, *stripe_groups, *dealt;
     int32_t *d_a;
     Tile *tiles;
     // The first pass leaves a list of the segments, one word each (block column, row, place in the tile), where these fit a word.  A tile's part of
@@ -2633,12 +2698,15 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     // 64 nonzeros (only a matrix of a few hundred nonzeros has not the room).
     const bool short_rows = listed && n_tiles * kTileWords * 10 <= 2 * nnz && h->unroll <= 4 && reorder == 1 && W == 64 && R >= 64 && R <= kPanelRows && NBC <= kPanelColumns && NBR >= kPanelLeast &&
                             10 * 8 * NBC * panel_row_words(R) <= kPanelLds;  // (the bits at a = 0)
+    const uint32_t room = (uint32_t)(kLdsPerCu / (h->value_bytes + (int32_t)sizeof(uint16_t)));  // nonzeros that a workgroup of k_panel_fill puts in place
     const SegmentWords words{reinterpret_cast<uint64_t *>(h->col_local), h->col_local + 4 * n_tiles * kTileWords};
     static_assert(sizeof(*words.starts) == 4 * sizeof(*h->col_local) && sizeof(*words.at) == sizeof(*h->col_local), "where the second array begins");
     // the arrays that start at zero side by side: one fill
     tmp.reserve(&dense_cnt, D);
     tmp.reserve(&hist, kHistCopies * kHistStride);
     tmp.reserve(&found, 1);
+    tmp.reserve(&dealt, short_rows ? NBR + 1 : 1);  // nine entries for 64 row blocks
+    static_assert(9 * ((kPanelLeast + 63) / 64) <= kPanelLeast, "as long as the arrays that are scanned beside it");
     tmp.reserve(&tiles, n_tiles);
     tmp.reserve(&slot_off, D + 1);
     tmp.reserve(&group_off, D + 1);
@@ -2646,7 +2714,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp.reserve(&stripe_cnt, NBR);
     tmp.reserve(&stripe_slots, NBR);
     tmp.reserve(&stripe_groups, NBR);
-    tmp.reserve(&scan_tmp, 4 * (scan_n / kScanTile + 2));
+    tmp.reserve(&scan_tmp, 5 * (scan_n / kScanTile + 2));
     tmp.reserve(&d_a, 1);
     HBP_TRY(tmp.commit());
     const int64_t first_words = (int64_t)(own0_zeros / sizeof(uint32_t)), second_words = ((char *)tiles - (char *)dense_cnt) / (int64_t)sizeof(uint32_t);
@@ -2679,7 +2747,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     HBP_TRY(exclusive_scans(Scans{{dense_cnt, dense_cnt, dense_cnt}, {slot_off, group_off, blk_id}, {kOpIdentity, kOpCeilDivW, kOpNonZero}}, 3,
                             D, (uint32_t)W, scan_tmp, st));
     k_stripe_count<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, (int32_t)NBR, (int32_t)NBC, csr_ptr, n_rows, R, (uint32_t)W, stripe_cnt, stripe_slots,
-                                                      stripe_groups, found);
+                                                      stripe_groups, short_rows ? room : 0u, dealt, found);
     HBP_HIP(hipGetLastError());
 
     // a host round trip: totals (and the error word)
@@ -2691,7 +2759,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     if (err & kErrCol) return HBP_ERR_BAD_CSR_COL;
     const int64_t S = host[0], G = host[1], B = host[2], longest_row = host[5];
     const bool long_segments = host[6] != 0;
-    const int64_t most_slots = host[7], most_nonzeros = host[8];
+    const int64_t most_slots = host[7], most_nonzeros = host[8], n_row_blocks = host[9], most_shares = host[10];  // (the last two: see deal_row_blocks)
     h->S = S; h->G = G; h->B = B; h->a = a;
 
     Arena own1(true, h->device);
@@ -2752,8 +2820,18 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
     uint16_t *places = nullptr;
-    if (by_panel) tmp2.reserve(&places, n_tiles * kTile);
-    else tmp2.reserve(&bucket, S);
+    // (a list that says nothing, of each row block or of one share of each, costs a workgroup the wait for its entry: fp64, 2000 row blocks of 15,400 nonzeros, 575 ->
+    // 584 us)
+    const bool listed_shares = by_panel && (n_row_blocks < NBR || most_nonzeros > (int64_t)room);
+    int32_t *row_blocks = nullptr;
+    uint32_t *shares = nullptr;
+    if (by_panel) {
+        tmp2.reserve(&places, n_tiles * kTile);
+        if (n_row_blocks < NBR) tmp2.reserve(&row_blocks, n_row_blocks);
+        if (listed_shares) tmp2.reserve(&shares, 8 * most_shares);
+    } else {
+        tmp2.reserve(&bucket, S);
+    }
     tmp2.reserve(&slot_j, S); tmp2.reserve(&group_nnz, G + 1); tmp2.reserve(&group_longest, G + 1); tmp2.reserve(&longest_all, 3);
     int2 *rest = nullptr;  // an entry per kFillRounds nonzeros of a group's longest row at most
     if (cut) tmp2.reserve(&rest, nnz / kFillRounds + 1);
@@ -2766,18 +2844,19 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         dense_cnt, slot_off, group_off, blk_id, D, (int32_t)NBR, (int32_t)NBC, h->blk_bm, h->blk_bn, h->slot_ptr,
         h->blk_group_ptr, h->col_blk_ptr, h->col_group_ptr, h->col_local + nnz, reinterpret_cast<uint32_t *>((char *)h->data + (size_t)nnz * h->value_bytes),
         256 * h->value_bytes / 4, h->group_slot + G, longest_all);
-    HBP_TRY(exclusive_scans(Scans{{stripe_cnt, stripe_slots, stripe_slots, stripe_groups}, {(uint32_t *)h->stripe_ptr, (uint32_t *)h->unit_ptr, multi_idx, stripe_turn},
-                                  {kOpIdentity, kOpUnits, kOpSplit, kOpIdentity}}, 4, NBR, (uint32_t)h->unit_slots, scan_tmp, st));
+    HBP_TRY(exclusive_scans(Scans{{stripe_cnt, stripe_slots, stripe_slots, stripe_groups, dealt}, {(uint32_t *)h->stripe_ptr, (uint32_t *)h->unit_ptr, multi_idx, stripe_turn, dealt},
+                                  {kOpIdentity, kOpUnits, kOpSplit, kOpIdentity, kOpIdentity}}, shares ? 5 : 4, NBR, (uint32_t)h->unit_slots, scan_tmp, st));
     k_stripe_fill<<<blocks_for(NBR, 64), 1024, 0, st>>>(dense_cnt, blk_id, h->stripe_ptr, stripe_slots, h->unit_ptr, multi_idx, stripe_turn, (uint32_t)W,
-                                                       (int32_t)NBR, (int32_t)NBC, (int32_t)B, h->stripe_blk, blk_turn, h->unit_stripe, h->unit_k, h->multi_stripes);
+                                                       (int32_t)NBR, (int32_t)NBC, (int32_t)B, h->stripe_blk, blk_turn, h->unit_stripe, h->unit_k, h->multi_stripes,
+                                                       csr_ptr, n_rows, R, room, dealt, row_blocks, shares);
     const dim3 stripe_grid((unsigned)(8 * ((NBR + 7) / 8) * std::max(parts, 1)));
     // steps 5-6 (slot_off doubles as the per-block cursor from here on, but for row blocks as a whole)
     if (by_panel) {
         HBP_HIP(hipFuncSetAttribute((const void *)k_panel_slots, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
         // rounds behind the table's, ten bytes each, as many as there is room for
         const uint32_t most_tails = (uint32_t)std::min<size_t>(kPanelTails, ((size_t)kPanelLds - slots_table) / 10) & ~3u;
-        k_panel_slots<<<dim3((unsigned)NBR), kPanelThreads, std::max(slots_lds, slots_table + 10 * (size_t)most_tails), st>>>(
-            csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, tiles, words.starts, words.at, list, row_bits, slot_off, group_off, blk_id, (uint32_t)a,
+        k_panel_slots<<<dim3((unsigned)n_row_blocks), kPanelThreads, std::max(slots_lds, slots_table + 10 * (size_t)most_tails), st>>>(
+            row_blocks, csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, tiles, words.starts, words.at, list, row_bits, slot_off, group_off, blk_id, (uint32_t)a,
             (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all, h->row_local, h->seg_len, h->slot_key, group_nnz, group_longest,
             h->group_slot, h->group_blk, h->blk_shift, places, slot_j, most_tails);
     } else {
@@ -2810,11 +2889,11 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     auto fill = [&](const auto *val, auto *data) {
         using T = std::remove_reference_t<decltype(*data)>;
         if (by_panel) {
-            const uint32_t room = (uint32_t)(kLdsPerCu / (int)(sizeof(T) + sizeof(uint16_t)));
-            const int32_t shares = (int32_t)std::max<int64_t>(1, (most_nonzeros + room - 1) / room);
+            constexpr uint32_t kRoom = kLdsPerCu / (sizeof(T) + sizeof(uint16_t));
+            static_assert((kPanelNonzeros + kRoom - 1) / kRoom <= 1u << kShareBits, "the shares of a row block");
             (void)hipFuncSetAttribute((const void *)k_panel_fill<T>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
-            k_panel_fill<T><<<dim3((unsigned)(8 * ((NBR + 7) / 8) * shares)), kPanelThreads, room * (sizeof(T) + sizeof(uint16_t)), st>>>(
-                csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, C, shares, room, places, csr_col, val, group_off, h->group_ptr, h->col_local, data);
+            k_panel_fill<T><<<dim3((unsigned)(shares ? 8 * most_shares : NBR)), kPanelThreads, room * (sizeof(T) + sizeof(uint16_t)), st>>>(
+                shares, found, csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, C, room, places, csr_col, val, group_off, h->group_ptr, h->col_local, data);
             return;
         }
         if (parts > 0) {

@@ -24,7 +24,7 @@ def test_scratch_memory(run, route, f64):  # noqa: F811
         out = []
         for nnz in {sizes}:
             rt.set_capacity(1 << 34)
-            h = build({f64}, {n_rows}, {n_cols}, {R}, {C}, nnz, {S}, {G}, {B}, [0, 0, {most_slots}, {most_nonzeros}], 100, a=1)
+            h = build({f64}, {n_rows}, {n_cols}, {R}, {C}, nnz, {S}, {G}, {B}, [0, 0, {most_slots}, {most_nonzeros}, 500, 200], 100, a=1)
             out.append(noted())
             assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0 and rt.live_bytes() == 0
         print(out)
@@ -35,8 +35,8 @@ def test_scratch_memory(run, route, f64):  # noqa: F811
         wrong = [k for k in kernels if not any(k in name for name in launched)]
         assert not wrong, (wrong, launched)
         assert len(allocated) == 4      # handle, scratch, handle, scratch
-        scan = 16 * ((max(D, NBR, nnz // 64 + D) + 1) // 2048 + 2)
-        tables = 16 * (D + 1) + 16 * (nnz // 4096 + 1) + 20 * (NBR + 1) + 4 * (B + 1) + scan + 16_384
+        scan = 20 * ((max(D, NBR, nnz // 64 + D) + 1) // 2048 + 2)
+        tables = 16 * (D + 1) + 16 * (nnz // 4096 + 1) + 28 * (NBR + 1) + 32 * 200 + 4 * (B + 1) + scan + 16_384
         assert allocated[1] + allocated[3] <= 9 * (tables + 12 * S + 8 * (G + 1)) // 8, (allocated, tables)
 
 

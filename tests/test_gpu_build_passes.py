@@ -131,3 +131,19 @@ def test_groups_filled_row_block_by_row_block(H, oracle, n_rows, R, C, n_cols, f
     lens[::7] = 0
     for long in ([], [(n_rows // 2, 0, min(n_cols, 700))]):
         check_against_oracle(H, oracle, quick(lens, n_cols, 3, f64, long), check_add_sign=False, rows_per_block=R, cols_per_block=C, rounds_per_batch=4)
+
+
+# Row blocks that hold nothing between others (all of 64 that a wavefront deals out, every second, all but every eighth; the first and the last) and some of two, three
+# and four shares among them, in either type: each is taken once, whole.
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("some", [slice(0, 300), slice(70, 199), slice(0, 300, 2), slice(3, 1100, 8), slice(1163, 1300)])
+@pytest.mark.parametrize("heavy", [0, 60, 100, 127])
+def test_lists_of_row_blocks(H, oracle, some, heavy, f64):
+    R, rng = 512, np.random.default_rng(11)
+    lens = np.zeros((1300, R), dtype=np.int64)
+    lens[some] = rng.poisson(5, lens[some].shape)
+    if heavy:
+        lens[some.start] = heavy
+        lens[some.stop - 1 - (some.stop - 1 - some.start) % (some.step or 1)] = heavy
+    m = quick(lens.ravel()[:1300 * R - 7], 1_800, 12, f64)
+    check_against_oracle(H, oracle, m, check_add_sign=False, rows_per_block=R, cols_per_block=600, rounds_per_batch=4, hash_shift=0)

@@ -19,6 +19,7 @@ NOTES = r"""
 static struct { const void *f; const char *name; } kernels[kMax];
 static int n_kernels, n_launched, n_allocated, n_waits;
 static const char *launched[kMax];
+static unsigned pushed, grids[kMax];
 static size_t allocated[kMax];
 static unsigned *readback, script[8][16];
 void __hipRegisterFunction(void **module, const void *f, char *device_f, const char *name, unsigned limit, void *a, void *b, void *c, void *d, int *e)
@@ -28,14 +29,15 @@ void __hipRegisterFunction(void **module, const void *f, char *device_f, const c
     kernels[n_kernels].f = f;
     kernels[n_kernels++].name = name;
 }
-unsigned __hipPushCallConfiguration(dim3_ g, dim3_ b, size_t lds, void *s) { (void)g; (void)b; (void)lds; (void)s; return 0; }
-int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *lds, void **s) { *g = *b = (dim3_){1, 1, 1}; *lds = 0; *s = 0; return 0; }
+unsigned __hipPushCallConfiguration(dim3_ g, dim3_ b, size_t lds, void *s) { (void)b; (void)lds; (void)s; pushed = g.x; return 0; }
+int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *lds, void **s) { *g = *b = (dim3_){1, 1, 1}; g->x = pushed; *lds = 0; *s = 0; return 0; }
 int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t lds, void *s)
 {
-    (void)g; (void)b; (void)args; (void)lds; (void)s;
+    (void)b; (void)args; (void)lds; (void)s;
     int i = 0;
     while (i < n_kernels && kernels[i].f != f) i++;
     if (i == n_kernels || n_launched == kMax) abort();
+    grids[n_launched] = g.x;
     launched[n_launched++] = kernels[i].name;
     return 0;
 }
@@ -62,6 +64,7 @@ void begin(void) { n_launched = n_allocated = n_waits = 0; }
 void set_word(int wait, int i, unsigned value) { script[wait][i] = value; }
 int launches(void) { return n_launched; }
 const char *launch(int i) { return launched[i]; }
+unsigned grid(int i) { return grids[i]; }
 int allocations(void) { return n_allocated; }
 size_t allocation(int i) { return allocated[i]; }
 """
@@ -83,6 +86,9 @@ word = ctypes.create_string_buffer(64)
 
 def noted():
     return [rt.launch(i).decode() for i in range(rt.launches())], [rt.allocation(i) for i in range(rt.allocations())]
+
+def grids():
+    return {rt.launch(i).decode(): rt.grid(i) for i in range(rt.launches())}
 
 def build(f64, n_rows, n_cols, R, C, nnz, S, G, B, counts, U, a=4):
     # (given block parameters: no sampling pass; a given shift: no sampled one; given rounds: workers)
