@@ -2814,8 +2814,10 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     tmp2.reserve(&multi_idx, NBR + 1); tmp2.reserve(&stripe_turn, NBR + 1); tmp2.reserve(&blk_turn, B);
     // k_fill_flat takes the groups row block by row block, too, where segments are short and there are several block columns.  Fill kernels, us, in the
     // layout's order / row block by row block: R-MAT 2^22 827 / 574, 2^20 (fp64) 223 / 200, 2^18 51 / 43; 13 nonzeros per segment (27-point
-    // grid of 128^3) 226 / 220, 4.4 (5-point grid of 1500^2) 33.2 / 31.7, which the 4 us of k_group_turns are not worth.
-    const bool by_turns = parts == 0 && nnz < 4 * S && NBC > 1;
+    // grid of 128^3) 226 / 220, 4.4 (5-point grid of 1500^2) 33.2 / 31.7, which the 4 us of k_group_turns are not worth.  Nor are they where the CSR arrays are little
+    // more than the 4 MB of an XCD's L2, which then holds the lines anyway.  Builds, us, in the layout's order / row block by row block, by the MB of columns and values: 0.4
+    // 107 / 110, 1.6 111 / 115, 2.4 112 / 116, 3.2 116 / 120, 4.8 123 / 123, 6.4 129 / 127, 9.6 (fp64) 147 / 142, 12 161 / 159, 28 200 / 169.
+    const bool by_turns = parts == 0 && nnz < 4 * S && NBC > 1 && nnz * (4 + h->value_bytes) >= (6 << 20);
     uint2 *bucket = nullptr;
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;

@@ -31,3 +31,18 @@ def test_no_lists_of_all_row_blocks_in_one_share_each(run, f64):  # noqa: F811
     assert (a, b, c) == ([2000, 2000], [1999, 2000], [2000, 4000])
     for more, size in ((4 * 1999 + 32 * 250, both - none), (32 * 500, shares - none)):
         assert more <= size <= 9 * more // 8 + 1024   # (an eighth more is taken than needed, in steps of 256)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_groups_row_block_by_row_block_from_six_megabytes_on(run, f64):  # noqa: F811
+    """A launch more, and the list of the groups' order, only where the CSR arrays are larger than an XCD's L2."""
+    least = -(-(6 << 20) // (12 if f64 else 8))
+    got = run(f"""
+        out = []
+        for nnz in ({least} - 1, {least}):
+            h = build({f64}, 100_000, 100_000, 512, 10_000, nnz, nnz // 3, 6_000, 2_000, [0, 0], 100)
+            out.append([k for k in ("k_group_turns", "k_fill_flat") if any(k in name for name in noted()[0])])
+            assert lib.hbp_free(h) == 0
+        print(out)
+    """)
+    assert got == [["k_fill_flat"], ["k_group_turns", "k_fill_flat"]]

@@ -123,11 +123,16 @@ def test_block_columns_kept_and_not(H, oracle, n_cols, unit_slots):
 
 
 # Short segments in blocks too small for a workgroup (fewer than 256 slots on average): groups filled row block by row block, with and without groups
-# that are cut, in more and fewer workgroups than go to one XCD in a row (128 of four groups, on eight of them).
+# that are cut, in more and fewer workgroups than go to one XCD in a row (128 of four groups, on eight of them); and the same in the layout's order, as the first four
+# are too small.
+BY_TURNS = [(3_000, 64, 50, 1_000, 4), (3_000, 64, 50, 51, 4), (40_000, 64, 100, 1_500, 4), (66_000, 16, 600, 1_200, 4),
+            (6_400, 64, 100, 4_000, 154), (250_000, 64, 100, 1_500, 4), (240_000, 16, 600, 1_200, 4)]
+
+
 @pytest.mark.parametrize("f64", [False, True])
-@pytest.mark.parametrize("n_rows,R,C,n_cols", [(3_000, 64, 50, 1_000), (3_000, 64, 50, 51), (40_000, 64, 100, 1_500), (66_000, 16, 600, 1_200)])
-def test_groups_filled_row_block_by_row_block(H, oracle, n_rows, R, C, n_cols, f64):
-    lens = np.random.default_rng(n_rows).poisson(4, n_rows)
+@pytest.mark.parametrize("n_rows,R,C,n_cols,mean", BY_TURNS)
+def test_groups_filled_row_block_by_row_block(H, oracle, n_rows, R, C, n_cols, mean, f64):
+    lens = np.random.default_rng(n_rows).poisson(mean, n_rows)
     lens[::7] = 0
     for long in ([], [(n_rows // 2, 0, min(n_cols, 700))]):
         check_against_oracle(H, oracle, quick(lens, n_cols, 3, f64, long), check_add_sign=False, rows_per_block=R, cols_per_block=C, rounds_per_batch=4)
