@@ -1,6 +1,8 @@
 """Which kernels a build takes, and in what grids (the noting runtime of test_launches.py, CPU)."""
+import numpy as np
 import pytest
 
+from test_gpu_build_passes import BY_TURNS, RUNS, WHOLE, quick, runs, totals
 from test_launches import run  # noqa: F401  (a fixture)
 
 
@@ -46,3 +48,70 @@ def test_groups_row_block_by_row_block_from_six_megabytes_on(run, f64):  # noqa:
         print(out)
     """)
     assert got == [["k_fill_flat"], ["k_group_turns", "k_fill_flat"]]
+
+
+def test_matrices_that_go_by_row_blocks_as_a_whole(run, oracle):  # noqa: F811
+    """The matrices of test_gpu_build_passes.py go the way that they are meant to."""
+    asked, wanted = [], []
+    for name, make in WHOLE.items():
+        m, params, whole = make(True)
+        R, C, shift = params["rows_per_block"], params["cols_per_block"], params["hash_shift"] if "hash_shift" in params else -1
+        t = totals(m, R, C)
+        a = shift if shift >= 0 else oracle.sample_shift(m.ptr, m.col, m.n_rows, C)
+        for f64 in (False, True):
+            asked.append((f64, m.n_rows, m.n_cols, R, C, m.nnz, t["S"], t["G"], t["B"], [0, 0, t["most_slots"], t["most_nonzeros"], t["row_blocks"], 9999], 100, a))
+            wanted.append((name, f64, ["k_panel_fill", "k_panel_slots"] if whole else ["k_fill", "k_place"]))
+    got = run(f"""
+        rt.set_capacity(1 << 36)
+        out = []
+        for args in {asked}:
+            h = build(*args)
+            out.append(sorted(k for k in ("k_panel_slots", "k_panel_fill", "k_place", "k_fill", "k_fill_flat") if any(k + "I" in name or k + "E" in name for name in noted()[0])))
+            assert lib.hbp_free(h) == 0
+        print(out)
+    """)
+    wrong = [(case, kernels) for case, kernels in zip(wanted, got, strict=True) if case[2] != kernels]
+    assert not wrong, wrong
+
+
+def test_wavefronts_to_a_tile_of_runs(run):  # noqa: F811
+    """Those that test_gpu_build_passes.py says: by the grid of k_place, and with all of a workgroup by its template."""
+    asked = []
+    for length in RUNS:
+        m = runs(length, False)
+        for R in (512, 700, 64):
+            t = totals(m, R, length)
+            asked.append((False, m.n_rows, m.n_cols, R, length, m.nnz, t["S"], t["G"], t["B"], [0, 0, t["most_slots"], t["most_nonzeros"]], 100, 4))
+    got = run(f"""
+        out = []
+        for args in {asked}:
+            h = build(*args)
+            out.append([(name, grid) for name, grid in grids().items() if "k_place" in name])
+            assert lib.hbp_free(h) == 0
+        print(out)
+    """)
+    want = [n for n in RUNS.values() for _ in range(3)]
+    for n, kernels in zip(want, got, strict=True):
+        (name, grid), = kernels
+        assert grid == -(-9 * n // 8) and f"k_placeILb{int(n == 8)}E" in name
+
+
+def test_matrices_whose_groups_go_row_block_by_row_block(run):  # noqa: F811
+    asked, want = [], []
+    for n_rows, R, C, n_cols, mean in BY_TURNS:
+        lens = np.random.default_rng(n_rows).poisson(mean, n_rows)
+        lens[::7] = 0
+        m = quick(lens, n_cols, 3, True)
+        t = totals(m, R, C)
+        for f64 in (False, True):
+            asked.append((f64, n_rows, n_cols, R, C, m.nnz, t["S"], t["G"], t["B"], [0, 0, t["most_slots"], t["most_nonzeros"]], 100))
+            want.append(n_rows in (6_400, 240_000, 250_000))
+    got = run(f"""
+        out = []
+        for args in {asked}:
+            h = build(*args)
+            out.append(any("k_group_turns" in name for name in noted()[0]))
+            assert lib.hbp_free(h) == 0
+        print(out)
+    """)
+    assert got == want
