@@ -1647,8 +1647,6 @@ constexpr int kPanelShift = 2;                                          // a at 
 // Row blocks, at least.  With 128 of them half of the device is idle; builds, us, block by block / by row blocks: templates of 262K rows (128 row blocks) 335 /
 // 318, of 300K (147) 314 / 269, 524K (256) 428 / 333; lognormal 300K x 300K (147) 269 / 261, in fp64 280 / 285, 500K x 200K (245) in fp64 380 / 332.
 constexpr int kPanelLeast = 128;
-// Longest row where segments are long: a row segment's rounds behind the table are gone through one after the other, eight to a step.
-constexpr int kPanelLongest = 16384;
 
 // Words of 64 rows; an odd number of them, so that neighbouring segments, which differ in their block columns, lie in different banks.
 __host__ __device__ inline uint32_t panel_row_words(int32_t R) { return (((uint32_t)R + 63u) / 64u) | 1u; }
@@ -2794,12 +2792,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const bool by_row_block = NBR >= 64 && nnz < 4 * S && S >= 256 * B;
     // Steps 5 to 7 by row blocks as a whole under the same rule, where a row block fits the registers and the LDS of a workgroup (a, the row blocks' slots
     // and nonzeros, the bits).  Builds, us, block by block / by row blocks: templates of 400K rows 359 / 295; lognormal 1M x 1M 615 / 483, 4M x 1M
-    // 1946 / 1253; fp64 1.2M x 300K 734 / 629, 2M x 500K 1251 / 905.
+    // 1946 / 1253; fp64 1.2M x 300K 734 / 629, 2M x 500K 1251 / 905.  And with rows of any length: rows of 8 in 300 row blocks and a row in one segment of 5000 288 / 191,
+    // 16,000 590 / 272, 20,000 638 / 302, 32,000 997 / 383; forty of these 339 / 210, 674 / 308, 842 / 336, 1179 / 419.
     const size_t panel_words = (size_t)NBC * ((9u << a) - 1u) * panel_row_words(R);
     const size_t slots_table = sizeof(uint32_t) * (size_t)most_slots + (size_t)(most_slots / 64 + NBC) * panel_table_row((uint32_t)(a & 15)) + 8;
     const size_t slots_lds = std::max<size_t>(slots_table, panel_words * (sizeof(uint64_t) + sizeof(uint16_t)));
     const bool by_panel = short_rows && by_row_block && !h->flat_wpg && a <= kPanelShift && most_slots <= kPanelSlots && most_nonzeros <= kPanelNonzeros &&
-                          slots_lds <= (size_t)kPanelLds && !(long_segments && longest_row > kPanelLongest);
+                          slots_lds <= (size_t)kPanelLds;
     const int32_t parts = !by_row_block ? 0 : (int32_t)std::min<int64_t>(32, std::max<int64_t>(1, (B + NBR - 1) / NBR));
     // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
     // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us), nor

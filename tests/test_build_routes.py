@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from test_gpu_build_passes import BY_TURNS, RUNS, WHOLE, quick, runs, totals
+from test_gpu_build_passes import BY_TURNS, RUNS, WHOLE, WIDE, quick, runs, totals
 from test_launches import run  # noqa: F401  (a fixture)
 
 
@@ -53,13 +53,13 @@ def test_groups_row_block_by_row_block_from_six_megabytes_on(run, f64):  # noqa:
 def test_matrices_that_go_by_row_blocks_as_a_whole(run, oracle):  # noqa: F811
     """The matrices of test_gpu_build_passes.py go the way that they are meant to."""
     asked, wanted = [], []
-    for name, make in WHOLE.items():
+    for name, make in [*WHOLE.items(), ("segments as long as a block is wide", WIDE)]:
         m, params, whole = make(True)
         R, C, shift = params["rows_per_block"], params["cols_per_block"], params["hash_shift"] if "hash_shift" in params else -1
         t = totals(m, R, C)
         a = shift if shift >= 0 else oracle.sample_shift(m.ptr, m.col, m.n_rows, C)
-        for f64 in (False, True):
-            asked.append((f64, m.n_rows, m.n_cols, R, C, m.nnz, t["S"], t["G"], t["B"], [0, 0, t["most_slots"], t["most_nonzeros"], t["row_blocks"], 9999], 100, a))
+        for f64 in (False, True) if make is not WIDE else (False,):
+            asked.append((f64, m.n_rows, m.n_cols, R, C, m.nnz, t["S"], t["G"], t["B"], [t["longest"], t["long"], t["most_slots"], t["most_nonzeros"], t["row_blocks"], 9999], 100, a))
             wanted.append((name, f64, ["k_panel_fill", "k_panel_slots"] if whole else ["k_fill", "k_place"]))
     got = run(f"""
         rt.set_capacity(1 << 36)

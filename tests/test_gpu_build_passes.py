@@ -86,14 +86,18 @@ def quick(lens, n_cols, seed, f64, long=()):
 
 
 def totals(m, R, C):
-    """Segments, groups, blocks, row blocks that hold something, and the most segments and nonzeros of one."""
+    """Segments, groups, blocks, row blocks that hold something, and the most segments and nonzeros of one; the longest row, where it has more than 512 nonzeros, and
+    whether three words of 64 nonzeros in a row are without a segment's begin in one tile of 4096."""
     NBR, NBC = -(-m.n_rows // R), -(-m.n_cols // C)
     row, bn = np.repeat(np.arange(m.n_rows), np.diff(m.ptr)), m.col // C
     start = np.r_[True, (row[1:] != row[:-1]) | (bn[1:] != bn[:-1])]
     slots = np.bincount(row[start] // R * NBC + bn[start], minlength=NBR * NBC)
-    nonzeros = np.bincount(row // R, minlength=NBR)
+    nonzeros, longest = np.bincount(row // R, minlength=NBR), int(np.diff(m.ptr).max())
+    without = np.zeros((-(-m.nnz // 4096), 64), dtype=bool)
+    without.ravel()[:m.nnz // 64] = start[:m.nnz // 64 * 64].reshape(-1, 64).sum(1) == 0
     return dict(S=int(start.sum()), G=int((-(-slots // 64)).sum()), B=int((slots > 0).sum()), row_blocks=int((nonzeros > 0).sum()),
-                most_slots=int(slots.reshape(NBR, NBC).sum(1).max()), most_nonzeros=int(nonzeros.max()))
+                most_slots=int(slots.reshape(NBR, NBC).sum(1).max()), most_nonzeros=int(nonzeros.max()), longest=longest if longest > 512 else 0,
+                long=int((without[:, :-2] & without[:, 1:-1] & without[:, 2:]).any()))
 
 
 def behind_empty_row_blocks(m, R, C):
@@ -199,6 +203,25 @@ def full_row_block(one_more):
 WHOLE["32,768 segments"] = by_type(lambda: full_row_block(0))
 WHOLE["32,769 segments"] = by_type(lambda: full_row_block(1))
 
+# Segments longer than a tile of 4096 nonzeros, up to the widest block, that begin at a tile's first nonzero, next to it, and at its last.
+def long_segments(C):
+    rng = np.random.default_rng(17)
+    R, n_cols, lengths = 512, 2 * C, [n for n in (4096, 4097, 5000, 8191, 8192, 12_289, 16_384, 16_385, 32_768) if n <= C]
+    lens = rng.poisson(3, 140 * R)
+    long = []
+    for i, n in enumerate(lengths):       # in different row blocks, behind a row as long as it takes
+        m, r = quick(lens, n_cols, 18, True, long), (7 * i + 2) * R + 5
+        before = int(m.ptr[r] - m.ptr[r - 1])
+        long += [(r - 1, 7, before + ((0, 1, 4095)[i % 3] - int(m.ptr[r])) % 4096), (r, (i % 2) * C + (C - n) // 2, n)]
+    m = quick(lens, n_cols, 18, True, long)
+    assert [int(m.ptr[r]) % 4096 for r, _, _ in long[1::2]] == [(0, 1, 4095)[i % 3] for i in range(len(lengths))]
+    return behind_empty_row_blocks(m, R, C), dict(rows_per_block=R, cols_per_block=C, hash_shift=0), True
+
+
+WHOLE["segments longer than a tile, up to 16,384"] = by_type(lambda: long_segments(16_384))
+WIDE = by_type(lambda: long_segments(32_768))  # (fp32 only)
+
+
 # Row blocks that hold nothing between others (all of 64 that a wavefront deals out, every second, all but every eighth; the first and the last) and some of two, three
 # and four shares among them, in either type: each is taken once, whole.
 def lists(some, heavy):
@@ -220,6 +243,11 @@ for _some in (slice(0, 300), slice(70, 199), slice(0, 300, 2), slice(3, 1100, 8)
 @pytest.mark.parametrize("case", WHOLE)
 def test_row_blocks_as_a_whole(H, oracle, case, f64):
     m, params, _ = WHOLE[case](f64)
+    check_against_oracle(H, oracle, m, check_add_sign=False, rounds_per_batch=4, **params)
+
+
+def test_segments_as_long_as_a_block_is_wide(H, oracle):
+    m, params, _ = WIDE(False)
     check_against_oracle(H, oracle, m, check_add_sign=False, rounds_per_batch=4, **params)
 
 
