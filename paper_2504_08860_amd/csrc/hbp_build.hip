@@ -1052,18 +1052,18 @@ __global__ __launch_bounds__(1024) void k_stripe_count(const uint32_t *__restric
         stripe_groups[bm] = groups;
         nonzeros = (uint32_t)(ptr[min((bm + 1) * R, n_rows)] - ptr[bm * R]);
     }
-    if (room) {
-        const uint32_t total = deal_row_blocks(bm, nonzeros, room).total;
-        if (threadIdx.x < 9) {
-            dealt[threadIdx.x * gridDim.x + blockIdx.x] = total;
-            if (total) atomicAdd(&found->dealt[threadIdx.x], total);
-        }
+    if (!room) return;  // (what follows is for row blocks as a whole)
+    const uint32_t total = deal_row_blocks(bm, nonzeros, room).total;
+    if (threadIdx.x < 9) {
+        dealt[threadIdx.x * gridDim.x + blockIdx.x] = total;
+        if (total) atomicAdd(&found->dealt[threadIdx.x], total);
     }
     slots = wave_max(slots);
     nonzeros = wave_max(nonzeros);
-    if (threadIdx.x == 0) {  // (looked at first: atomics on one address queue up, 4.4 -> 10.5 us for the kernel where 20,000 row blocks are told)
+    if (threadIdx.x == 0) {
+        // (many look first: atomics on one address queue up, 4.4 -> 10.5 us for the kernel where 20,000 row blocks are told)
         auto raise = [](uint32_t *most, uint32_t v) {
-            if (v > __hip_atomic_load(most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(most, v);
+            if (gridDim.x < 64 || v > __hip_atomic_load(most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(most, v);
         };
         raise(&found->most_slots, slots);
         raise(&found->most_nonzeros, nonzeros);
@@ -1717,6 +1717,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
     __shared__ uint16_t sh_tails[kGroups];  // groups with more rounds than the table and the list of tails hold
     const int32_t bm = row_blocks ? row_blocks[blockIdx.x] : (int32_t)blockIdx.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (ptr[(int64_t)bm * R] == ptr[min(((int64_t)bm + 1) * R, n_rows)]) return;  // (few of them, or the list would leave them out)
     const Panel p = panel_of(bm, ptr, n_rows, R, tiles, word_starts, word_at);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)p.upto, 63);
     // lane bn: the block's first slot and group, slots and groups in front of it
@@ -2062,7 +2063,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
 template <typename T>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const uint32_t *__restrict__ shares, const Findings *__restrict__ found,
                                                               const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC, int32_t C,
-                                                              uint32_t room, const uint16_t *__restrict__ places,
+                                                              uint32_t most_parts, uint32_t room, const uint16_t *__restrict__ places,
                                                               const int32_t *__restrict__ csr_col, const T *__restrict__ csr_val,
                                                               const uint32_t *__restrict__ group_off, const int32_t *__restrict__ group_ptr,
                                                               uint16_t *__restrict__ col_local, T *__restrict__ data)
@@ -2070,14 +2071,17 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const uint32_t *__
     extern __shared__ __align__(8) uint32_t panel_lds[];
     T *const vals = reinterpret_cast<T *>(panel_lds);
     uint16_t *const cols = reinterpret_cast<uint16_t *>(vals + room);
-    const uint32_t entry = shares ? shares[blockIdx.x] : blockIdx.x << kShareBits, share = entry & ((1u << kShareBits) - 1u);
+    const uint32_t turn = blockIdx.x >> 3, xcd = blockIdx.x & 7u;
+    const uint32_t entry = shares ? shares[blockIdx.x] : (8u * (turn / most_parts) + xcd) << kShareBits | turn % most_parts;
+    const uint32_t share = entry & ((1u << kShareBits) - 1u);
     const int32_t bm = (int32_t)(entry >> kShareBits);
-    if (shares && (blockIdx.x >> 3) >= found->dealt[blockIdx.x & 7u]) return;
+    if (shares ? turn >= found->dealt[xcd] : bm >= NBR) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t p0 = (uint32_t)ptr[(int64_t)bm * R], p1 = (uint32_t)ptr[min(((int64_t)bm + 1) * R, n_rows)];
     const int64_t d = (int64_t)min(lane, NBC - 1) * NBR + bm;
     const uint32_t g0 = group_off[d], g1 = lane < NBC ? group_off[d + 1] : g0;
     const uint32_t nonzeros = p1 - p0, parts = (nonzeros + room - 1) / room;
+    if (share >= parts) return;
     const uint32_t each = (nonzeros + parts - 1) / parts, lo = each * share, hi = min(nonzeros, lo + each), size = hi - lo;
     auto put = [&](uint32_t place, int32_t column, T value) __attribute__((always_inline)) {
         const uint32_t at = place - lo;
@@ -2434,14 +2438,15 @@ __global__ __launch_bounds__(64) void k_publish(Words words, int32_t count, uint
     if (i < count) host[i] = *static_cast<const uint32_t *>(words.at[i]);
     if (!found) return;
     const uint32_t longest = wave_max(found->copy[i].longest_row), segment = wave_max(found->copy[i].long_segment);
-    const uint32_t shares = wave_max(i < 8 ? found->dealt[i] : 0u);
+    const uint32_t dealt = i < 8 ? found->dealt[i] : 0u, most_shares = wave_max(dealt), shares = wave_sum(dealt);
     if (i == 0) {
         host[count] = longest;
         host[count + 1] = segment;
         host[count + 2] = found->most_slots;
         host[count + 3] = found->most_nonzeros;
         host[count + 4] = found->dealt[8];
-        host[count + 5] = shares;
+        host[count + 5] = most_shares;
+        host[count + 6] = shares;
     }
 }
 
@@ -2757,7 +2762,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     if (err & kErrCol) return HBP_ERR_BAD_CSR_COL;
     const int64_t S = host[0], G = host[1], B = host[2], longest_row = host[5];
     const bool long_segments = host[6] != 0;
-    const int64_t most_slots = host[7], most_nonzeros = host[8], n_row_blocks = host[9], most_shares = host[10];  // (the last two: see deal_row_blocks)
+    const int64_t most_slots = host[7], most_nonzeros = host[8];
+    const int64_t n_row_blocks = host[9], most_shares = host[10], n_shares = host[11];  // (see deal_row_blocks; most_shares: of an XCD)
     h->S = S; h->G = G; h->B = B; h->a = a;
 
     Arena own1(true, h->device);
@@ -2821,14 +2827,15 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint32_t *group_nnz, *group_longest, *longest_all, *d_n_long;
     int32_t *slot_j;
     uint16_t *places = nullptr;
-    // (a list that says nothing, of each row block or of one share of each, costs a workgroup the wait for its entry: fp64, 2000 row blocks of 15,400 nonzeros, 575 ->
-    // 584 us)
-    const bool listed_shares = by_panel && (n_row_blocks < NBR || most_nonzeros > (int64_t)room);
+    // Where few of them would find nothing to do, all row blocks get a workgroup, and as many for their shares as the fullest needs: one that is told what to do by a list
+    // begins with the wait for its entry (2000 row blocks of 15,400 nonzeros, fp64, 575 -> 584 us; 1500 of 41,000, two shares each, 730 -> 740).
+    const int64_t most_parts = (most_nonzeros + room - 1) / room, all_parts = 8 * ((NBR + 7) / 8) * most_parts;
+    const bool listed_row_blocks = by_panel && 8 * (NBR - n_row_blocks) > NBR, listed_shares = by_panel && (listed_row_blocks || 8 * (all_parts - n_shares) > all_parts);
     int32_t *row_blocks = nullptr;
     uint32_t *shares = nullptr;
     if (by_panel) {
         tmp2.reserve(&places, n_tiles * kTile);
-        if (n_row_blocks < NBR) tmp2.reserve(&row_blocks, n_row_blocks);
+        if (listed_row_blocks) tmp2.reserve(&row_blocks, n_row_blocks);
         if (listed_shares) tmp2.reserve(&shares, 8 * most_shares);
     } else {
         tmp2.reserve(&bucket, S);
@@ -2856,7 +2863,7 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
         HBP_HIP(hipFuncSetAttribute((const void *)k_panel_slots, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds));
         // rounds behind the table's, ten bytes each, as many as there is room for
         const uint32_t most_tails = (uint32_t)std::min<size_t>(kPanelTails, ((size_t)kPanelLds - slots_table) / 10) & ~3u;
-        k_panel_slots<<<dim3((unsigned)n_row_blocks), kPanelThreads, std::max(slots_lds, slots_table + 10 * (size_t)most_tails), st>>>(
+        k_panel_slots<<<dim3((unsigned)(row_blocks ? n_row_blocks : NBR)), kPanelThreads, std::max(slots_lds, slots_table + 10 * (size_t)most_tails), st>>>(
             row_blocks, csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, tiles, words.starts, words.at, list, row_bits, slot_off, group_off, blk_id, (uint32_t)a,
             (uint32_t)long_rounds_of(h->heavy_rounds, true), longest_all, h->row_local, h->seg_len, h->slot_key, group_nnz, group_longest,
             h->group_slot, h->group_blk, h->blk_shift, places, slot_j, most_tails);
@@ -2893,8 +2900,8 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
             constexpr uint32_t kRoom = kLdsPerCu / (sizeof(T) + sizeof(uint16_t));
             static_assert((kPanelNonzeros + kRoom - 1) / kRoom <= 1u << kShareBits, "the shares of a row block");
             (void)hipFuncSetAttribute((const void *)k_panel_fill<T>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu);
-            k_panel_fill<T><<<dim3((unsigned)(shares ? 8 * most_shares : NBR)), kPanelThreads, room * (sizeof(T) + sizeof(uint16_t)), st>>>(
-                shares, found, csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, C, room, places, csr_col, val, group_off, h->group_ptr, h->col_local, data);
+            k_panel_fill<T><<<dim3((unsigned)(shares ? 8 * most_shares : all_parts)), kPanelThreads, room * (sizeof(T) + sizeof(uint16_t)), st>>>(
+                shares, found, csr_ptr, n_rows, R, (int32_t)NBR, (int32_t)NBC, C, (uint32_t)most_parts, room, places, csr_col, val, group_off, h->group_ptr, h->col_local, data);
             return;
         }
         if (parts > 0) {

@@ -24,7 +24,7 @@ def test_scratch_memory(run, route, f64):  # noqa: F811
         out = []
         for nnz in {sizes}:
             rt.set_capacity(1 << 34)
-            h = build({f64}, {n_rows}, {n_cols}, {R}, {C}, nnz, {S}, {G}, {B}, [0, 0, {most_slots}, {most_nonzeros}, 500, 200], 100, a=1)
+            h = build({f64}, {n_rows}, {n_cols}, {R}, {C}, nnz, {S}, {G}, {B}, [0, 0, {most_slots}, {most_nonzeros}, 500, 200, 700], 100, a=1)
             out.append(noted())
             assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0 and rt.live_bytes() == 0
         print(out)

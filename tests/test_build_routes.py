@@ -7,32 +7,31 @@ from test_launches import run  # noqa: F401  (a fixture)
 
 
 @pytest.mark.parametrize("f64", [False, True])
-def test_no_workgroups_for_row_blocks_and_shares_that_are_not_there(run, f64):  # noqa: F811
-    """20,000 row blocks, 600 of which hold something, one of them 60,000 nonzeros: as many workgroups as the device counts row blocks, and as shares for the XCD with most."""
-    got = run(f"""
-        h = build({f64}, 20_000 * 2048, 300_000, 2048, {15_000 if f64 else 30_000}, 10_000_000, 7_000_000, 120_000, 10_000, [0, 0, 30_000, 60_000, 600, 76], 100, a=0)
-        print(sorted((next(k for k in ("k_panel_slots", "k_panel_fill") if k in name), grid) for name, grid in grids().items() if "k_panel" in name))
-        assert lib.hbp_free(h) == 0
-    """)
-    assert got == [("k_panel_fill", 8 * 76), ("k_panel_slots", 600)]
-
-
-@pytest.mark.parametrize("f64", [False, True])
-def test_no_lists_of_all_row_blocks_in_one_share_each(run, f64):  # noqa: F811
-    """The lists, 4 bytes a row block, are there where a row block is empty or in two shares."""
-    room = 160 * 1024 // (10 if f64 else 6)
+def test_few_workgroups_for_row_blocks_and_shares_that_are_not_there(run, f64):  # noqa: F811
+    """2000 row blocks (the first cases 20,000, most of them empty; one of 60,000 nonzeros among light ones): a list, 4 bytes an entry, and no workgroup without work, where more than
+    an eighth of the workgroups would have none."""
+    room, most = 160 * 1024 // (10 if f64 else 6), 4 if f64 else 3
+    # row blocks, full ones, most nonzeros, shares, of the XCD with most; entries of the lists, grids of the places' and the fill's kernel
+    cases = [(20_000, 600, 60_000, 600 + most - 1, 78), (20_000, 600, 10_000, 600, 76),
+             (2000, 2000, room, 2000, 250), (2000, 1750, room, 1750, 219), (2000, 1749, room, 1749, 219),
+             (2000, 2000, 2 * room, 4000, 500), (2000, 2000, 2 * room, 3500, 438), (2000, 2000, 2 * room, 3499, 438)]
+    want = [(600 + 8 * 78, 600, 8 * 78), (600 + 8 * 76, 600, 8 * 76),
+            (0, 2000, 2000), (0, 2000, 2000), (1749 + 8 * 219, 1749, 8 * 219),
+            (0, 2000, 4000), (0, 2000, 4000), (8 * 438, 2000, 8 * 438)]
     got = run(f"""
         out = []
-        for most, there, xcd in (({room}, 2000, 250), ({room}, 1999, 250), ({room} + 1, 2000, 500)):
-            h = build({f64}, 2000 * 2048, 300_000, 2048, {15_000 if f64 else 30_000}, 30_000_000, 20_000_000, 400_000, 40_000, [0, 0, 15_000, most, there, xcd], 100, a=0)
-            out.append((noted()[1][3], sorted(grid for name, grid in grids().items() if "k_panel" in name)))
+        for NBR, there, most, shares, xcd in {cases}:
+            h = build({f64}, NBR * 2048, 300_000, 2048, {15_000 if f64 else 30_000}, 30_000_000, 20_000_000, 400_000, 40_000, [0, 0, 30_000, most, there, xcd, shares], 100, a=0)
+            seen = grids()
+            out.append((noted()[1][3], *(next(grid for name, grid in seen.items() if k in name) for k in ("k_panel_slots", "k_panel_fill"))))
             assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0
         print(out)
     """)
-    (none, a), (both, b), (shares, c) = got
-    assert (a, b, c) == ([2000, 2000], [1999, 2000], [2000, 4000])
-    for more, size in ((4 * 1999 + 32 * 250, both - none), (32 * 500, shares - none)):
-        assert more <= size <= 9 * more // 8 + 1024   # (an eighth more is taken than needed, in steps of 256)
+    none = {2000: got[2][0], 20_000: None}
+    for (NBR, *_), (entries, *kernels), (size, *launched) in zip(cases, want, got, strict=True):
+        assert launched == kernels
+        if none[NBR] is not None:                       # (an eighth more is taken than needed, in steps of 256)
+            assert 4 * entries <= size - none[NBR] <= 9 * 4 * entries // 8 + 1024
 
 
 @pytest.mark.parametrize("f64", [False, True])
