@@ -1647,6 +1647,20 @@ constexpr int kPanelShift = 2;                                          // a at 
 // Row blocks, at least.  With 128 of them half of the device is idle; builds, us, block by block / by row blocks: templates of 262K rows (128 row blocks) 335 /
 // 318, of 300K (147) 314 / 269, 524K (256) 428 / 333; lognormal 300K x 300K (147) 269 / 261, in fp64 280 / 285, 500K x 200K (245) in fp64 380 / 332.
 constexpr int kPanelLeast = 128;
+// Segments and 8-byte words of the CSR arrays, at least, for every 256 row blocks that hold something, a turn of the compute units with one row block to each: a turn's
+// phases and barriers take some 15 us whatever the row blocks hold, and block by block a million segments take some 9 us more than by row blocks, a million
+// words 2.  Where row blocks are empty fewer will do in proportion: the older kernels deal their workgroups out to all of them.  Builds, us, block by block / by row
+// blocks, rows of Poisson lengths over 300,000 columns, by row blocks and millions a turn: 256: 3.8 149 / 143, 4.6 155 / 147, 6.6 168 / 154; 300: 2.7 164 / 182, 5.0 198 / 205,
+// 7.0 235 / 227; 400: 3.6 179 / 187, 5.2 204 / 200, 6.6 227 / 217; 600: 3.6 216 / 228, 5.2 238 / 244, 6.6 295 / 276; 1000: 2.4 224 / 244, 3.7 260 / 268, 4.5 294 / 288, 6.5
+// 373 / 316; 1500: 2.4 282 / 320, 3.7 339 / 339, 4.5 401 / 374; 2000: 2.4 338 / 382, 4.5 500 / 454; fp64 300: 3.5 170 / 181, 6.5 214 / 219, 9.2 265 / 251; 600: 4.7 232 / 238, 6.7 296 /
+// 265; 1000: 3.0 245 / 254, 4.7 304 / 278; 100,000 columns, 1000: 3.8 246 / 271, 5.3 318 / 292, 6.7 379 / 330; 128 of 2000 row blocks 4.9 228 / 176, fp64, 60 of 2000 3.3 236 /
+// 178, 300 of 2000 2.2 236 / 200.  (The first turn: a million less, as not going by row blocks has by then cost the marks of where segments start, some 4 us.)
+// Where a long row lies in long segments, block by block all wait for the wavefront that fills its group, and row blocks pay whatever they hold: rows of 8 and one of
+// 600 / 2000 / 5000 / 10,000 / 20,000 / 32,000 in 300 row blocks 194 / 192, 220 / 192, 288 / 191, 397 / 197, 638 / 302, 997 / 383 (with forty of them 206 / 202, 246 / 200, 339 / 210,
+// 500 / 229, 842 / 336, 1179 / 419; fewer than that gain: ten of 3000 in one row block 261 / 291, 30 row blocks with fifteen of 2000 277 / 293).
+constexpr int kPanelTurn = 256;
+constexpr double kPanelWork = 4.5e6, kPanelWorkOnce = 1e6;
+constexpr int kPanelLongRow = 1024;
 
 // Words of 64 rows; an odd number of them, so that neighbouring segments, which differ in their block columns, lie in different banks.
 __host__ __device__ inline uint32_t panel_row_words(int32_t R) { return (((uint32_t)R + 63u) / 64u) | 1u; }
@@ -2798,12 +2812,13 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const bool by_row_block = NBR >= 64 && nnz < 4 * S && S >= 256 * B;
     // Steps 5 to 7 by row blocks as a whole under the same rule, where a row block fits the registers and the LDS of a workgroup (a, the row blocks' slots
     // and nonzeros, the bits).  Builds, us, block by block / by row blocks: templates of 400K rows 359 / 295; lognormal 1M x 1M 615 / 483, 4M x 1M
-    // 1946 / 1253; fp64 1.2M x 300K 734 / 629, 2M x 500K 1251 / 905.  And with rows of any length: rows of 8 in 300 row blocks and a row in one segment of 5000 288 / 191,
-    // 16,000 590 / 272, 20,000 638 / 302, 32,000 997 / 383; forty of these 339 / 210, 674 / 308, 842 / 336, 1179 / 419.
+    // 1946 / 1253; fp64 1.2M x 300K 734 / 629, 2M x 500K 1251 / 905. (Rows may be of any length: see kPanelLongRow.)
     const size_t panel_words = (size_t)NBC * ((9u << a) - 1u) * panel_row_words(R);
     const size_t slots_table = sizeof(uint32_t) * (size_t)most_slots + (size_t)(most_slots / 64 + NBC) * panel_table_row((uint32_t)(a & 15)) + 8;
     const size_t slots_lds = std::max<size_t>(slots_table, panel_words * (sizeof(uint64_t) + sizeof(uint16_t)));
-    const bool by_panel = short_rows && by_row_block && !h->flat_wpg && a <= kPanelShift && most_slots <= kPanelSlots && most_nonzeros <= kPanelNonzeros &&
+    const double panel_work = (double)S + (double)nnz * (double)(4 + h->value_bytes) / 8, panel_turns = (double)((n_row_blocks + kPanelTurn - 1) / kPanelTurn);
+    const bool worth_panels = (long_segments && longest_row > kPanelLongRow) || panel_work * (double)NBR >= (kPanelWork * panel_turns - kPanelWorkOnce) * (double)n_row_blocks;
+    const bool by_panel = short_rows && by_row_block && worth_panels && !h->flat_wpg && a <= kPanelShift && most_slots <= kPanelSlots && most_nonzeros <= kPanelNonzeros &&
                           slots_lds <= (size_t)kPanelLds;
     const int32_t parts = !by_row_block ? 0 : (int32_t)std::min<int64_t>(32, std::max<int64_t>(1, (B + NBR - 1) / NBR));
     // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us

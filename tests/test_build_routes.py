@@ -49,6 +49,24 @@ def test_groups_row_block_by_row_block_from_six_megabytes_on(run, f64):  # noqa:
     assert got == [["k_fill_flat"], ["k_group_turns", "k_fill_flat"]]
 
 
+# Row blocks, those that hold something, nonzeros, and the segments from which on they are taken as a whole where rows are short: segments and 8-byte words of the CSR arrays, 3.5
+# million for the first turn of 256 row blocks and 4.5 for each other, in proportion to the row blocks that hold something.
+@pytest.mark.parametrize("f64,NBR,there,nnz,least", [
+    (False, 256, 256, 1_800_000, 1_700_000), (False, 257, 257, 4_200_000, 3_800_000), (False, 600, 600, 7_000_000, 5_500_000), (False, 2000, 2000, 18_000_000, 17_000_000),
+    (True, 256, 256, 1_400_000, 1_400_000), (True, 600, 600, 5_000_000, 5_000_000), (False, 2000, 500, 1_450_000, 550_000), (True, 300, 200, 800_000, 1_133_334),
+])
+def test_work_that_row_blocks_as_a_whole_are_worth(run, f64, NBR, there, nnz, least):  # noqa: F811
+    got = run(f"""
+        out = []
+        for S, longest, shown in (({least} - 1, 0, 0), ({least}, 0, 0), ({nnz} // 3, 1024, 1), ({nnz} // 3, 1025, 1), ({nnz} // 3, 1025, 0)):
+            h = build({f64}, {NBR} * 2048, 300_000, 2048, {15_000 if f64 else 30_000}, {nnz}, S, S // 60, S // 300, [longest, shown, 30_000, 60_000, {there}, 99, 700], 100, a=0)
+            out.append(any("k_panel" in name for name in noted()[0]))
+            assert lib.hbp_free(h) == 0
+        print(out)
+    """)
+    assert got == [False, True, False, True, False]
+
+
 def test_matrices_that_go_by_row_blocks_as_a_whole(run, oracle):  # noqa: F811
     """The matrices of test_gpu_build_passes.py go the way that they are meant to."""
     asked, wanted = [], []
