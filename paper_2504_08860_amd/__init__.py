@@ -77,12 +77,12 @@ class HbpError(RuntimeError):
 
 
 _lib = None
-_torch = _raw_stream = None  # set with _lib; _raw_stream(device): its current stream as a number, where this torch has that
+_torch = _raw_stream = _device = None  # set with _lib; _raw_stream(_device()): the current stream as a number, where this torch has both
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library.  Raises if it has not been built (no fallback exists)."""
-    global _lib, _torch, _raw_stream
+    global _lib, _torch, _raw_stream, _device
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2504_08860_amd.build` "
@@ -92,7 +92,7 @@ def lib() -> ctypes.CDLL:
         # pointers from torch tensors are valid in the library's calls.
         import torch
         _torch = torch
-        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _raw_stream, _device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         L.hbp_default_params.argtypes = [ctypes.POINTER(hbp_params_t)]
@@ -128,8 +128,8 @@ def _check(status: int, where: str) -> None:
 
 def _stream_ptr(stream) -> int:
     if stream is None:
-        if _raw_stream is not None:
-            return _raw_stream(_torch._C._cuda_getDevice())
+        if _raw_stream is not None and _device is not None:
+            return _raw_stream(_device())
         return _torch.cuda.current_stream().cuda_stream
     return int(getattr(stream, "cuda_stream", stream))
 

@@ -11,6 +11,27 @@ def test_no_handle_is_an_invalid_argument():
     assert "long" in H.hbp_status_string(H.HBP_ERR_WRONG_LENGTH)
 
 
+@pytest.mark.parametrize("gone", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_a_torch_without_its_private_calls(monkeypatch, gone):
+    """The current stream is asked for in public where either is missing."""
+    import types
+
+    import torch
+    H.lib()
+    for name in ("_lib", "_torch", "_raw_stream", "_device"):
+        monkeypatch.setattr(H, name, getattr(H, name))      # (as they were, afterwards)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(torch._C, name, lambda *_: 5, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    H._lib = None
+    H.lib()
+    assert H._stream_ptr(None) == 5
+    monkeypatch.delattr(torch._C, gone)
+    H._lib = None
+    H.lib()
+    assert H._stream_ptr(None) == 77
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind", [0, 1, 2])
 def test_products_by_kind(kind):
