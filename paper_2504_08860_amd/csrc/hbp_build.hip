@@ -1659,6 +1659,7 @@ constexpr int kPanelLeast = 128;
 // 600 / 2000 / 5000 / 10,000 / 20,000 / 32,000 in 300 row blocks 194 / 192, 220 / 192, 288 / 191, 397 / 197, 638 / 302, 997 / 383 (with forty of them 206 / 202, 246 / 200, 339 / 210,
 // 500 / 229, 842 / 336, 1179 / 419; fewer than that gain: ten of 3000 in one row block 261 / 291, 30 row blocks with fifteen of 2000 277 / 293).
 constexpr int kPanelTurn = 256;
+constexpr int64_t kPanelMost = ((int64_t(1) << 32) - 1) / kPanelThreads;  // workgroups: a grid has fewer than 2^32 threads (the lists never name more than there would be without)
 constexpr double kPanelWork = 4.5e6, kPanelWorkOnce = 1e6;
 constexpr int kPanelLongRow = 1024;
 
@@ -2818,8 +2819,9 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     const size_t slots_lds = std::max<size_t>(slots_table, panel_words * (sizeof(uint64_t) + sizeof(uint16_t)));
     const double panel_work = (double)S + (double)nnz * (double)(4 + h->value_bytes) / 8, panel_turns = (double)((n_row_blocks + kPanelTurn - 1) / kPanelTurn);
     const bool worth_panels = (long_segments && longest_row > kPanelLongRow) || panel_work * (double)NBR >= (kPanelWork * panel_turns - kPanelWorkOnce) * (double)n_row_blocks;
+    const int64_t most_parts = (most_nonzeros + room - 1) / room, all_parts = 8 * ((NBR + 7) / 8) * most_parts;
     const bool by_panel = short_rows && by_row_block && worth_panels && !h->flat_wpg && a <= kPanelShift && most_slots <= kPanelSlots && most_nonzeros <= kPanelNonzeros &&
-                          slots_lds <= (size_t)kPanelLds;
+                          slots_lds <= (size_t)kPanelLds && all_parts <= kPanelMost;
     const int32_t parts = !by_row_block ? 0 : (int32_t)std::min<int64_t>(32, std::max<int64_t>(1, (B + NBR - 1) / NBR));
     // Rows much longer than the others: their groups are cut, or the longest is what the kernel waits for.  512 rounds are less than 60 us
     // for a wavefront; without such a row the two more launches are not worth their 10 us (27-point grid of 128^3 224 -> 234 us), nor
@@ -2844,7 +2846,6 @@ static int build_layout_locked(hbp_handle_s *h, const int32_t *csr_ptr, const in
     uint16_t *places = nullptr;
     // Where few of them would find nothing to do, all row blocks get a workgroup, and as many for their shares as the fullest needs: one that is told what to do by a list
     // begins with the wait for its entry (2000 row blocks of 15,400 nonzeros, fp64, 575 -> 584 us; 1500 of 41,000, two shares each, 730 -> 740).
-    const int64_t most_parts = (most_nonzeros + room - 1) / room, all_parts = 8 * ((NBR + 7) / 8) * most_parts;
     const bool listed_row_blocks = by_panel && 8 * (NBR - n_row_blocks) > NBR, listed_shares = by_panel && (listed_row_blocks || 8 * (all_parts - n_shares) > all_parts);
     int32_t *row_blocks = nullptr;
     uint32_t *shares = nullptr;

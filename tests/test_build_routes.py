@@ -67,6 +67,21 @@ def test_work_that_row_blocks_as_a_whole_are_worth(run, f64, NBR, there, nnz, le
     assert got == [False, True, False, True, False]
 
 
+def test_more_row_blocks_than_a_grid_has_workgroups(run):  # noqa: F811
+    """A grid has fewer than 2^32 threads, 4,194,303 workgroups of 1024: beyond, block by block (also where a long row would be waited for)."""
+    got = run("""
+        rt.set_capacity(1 << 37)
+        out = []
+        for NBR, most in ((4_194_296, 600), (4_194_304, 600), (2_097_144, 27_307), (2_097_152, 27_307)):
+            h = build(False, NBR * 256, 30_000, 256, 30_000, 3 * NBR * 128, NBR * 256, NBR * 4, NBR, [2000, 1, 256, most, NBR, NBR, 8 * NBR], 100, a=0)
+            out.append((any("k_panel" in name for name in noted()[0]), max(grid for name, grid in grids().items() if any(k in name for k in ("k_panel", "k_place", "k_fill")))))
+            assert lib.hbp_free(h) == 0 and lib.hbp_release_workspace() == 0
+        print(out)
+    """)
+    assert [panel for panel, _ in got] == [True, False, True, False]
+    assert all(grid * 1024 < 2**32 for panel, grid in got if panel)
+
+
 def test_matrices_that_go_by_row_blocks_as_a_whole(run, oracle):  # noqa: F811
     """The matrices of test_gpu_build_passes.py go the way that they are meant to."""
     asked, wanted = [], []
