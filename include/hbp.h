@@ -311,7 +311,7 @@ int hbp_csr_spmv_f64(int kind, const int32_t *csr_ptr, const int32_t *csr_col, c
 int hbp_hash_keys(const uint32_t *n, int64_t count, int32_t a, int32_t rows_per_block, uint32_t *keys, void *stream);
 
 /* hbp_build keeps its scratch memory (at most 12 bytes per row segment and 8 per group beside tables
- * of the blocks, and an eighth more: 440 MB for 98M nonzeros in 47M segments, 60 MB for 56M in 4.3M; per
+ * of the blocks, and an eighth more: 450 MB for 98M nonzeros in 48M segments, 70 MB for 56M in 4.2M; per
  * device) for the next build instead of freeing it: freeing costs a good part of a build.
  * Builds of one process therefore run one at a time.  This call gives the memory back (no build
  * may be running), and with it the memory of freed handles (see hbp_free), on every device. */

@@ -1642,7 +1642,9 @@ constexpr int kPanelRows = 2048, kPanelColumns = 64;
 constexpr int kPanelPer = 32, kPanelSlots = kPanelPer * kPanelThreads;  // segments of a row block at most
 constexpr int kPanelNonzeros = 1 << 16;                                 // its nonzeros at most: places of 16 bits, and in 64 tiles
 constexpr int kPanelLds = 148 * 1024;                                   // dynamic LDS of k_panel_slots at most (its own arrays: below 12 KB)
-constexpr int kPanelTails = 12288;                                      // rounds in its list of tails at most: what a workgroup asks for of the LDS
+// Rounds in its list of tails at most: what a workgroup asks for of the LDS.  Builds, us, with 0 / 4096 / 12288, rows of 8 in 300 row blocks and long rows: forty of
+// 5000 231 / 232 / 213, forty of 2000 214 / 204 / 206, ten of 1200 in one row block 235 / 225 / 204, 30 row blocks with 300 of 100 each 258 / 211 / 217.
+constexpr int kPanelTails = 12288;
 constexpr int kPanelShift = 2;                                          // a at most: a band of 64 rows and more keeps 4 remainders apart
 // Row blocks, at least.  With 128 of them half of the device is idle; builds, us, block by block / by row blocks: templates of 262K rows (128 row blocks) 335 /
 // 318, of 300K (147) 314 / 269, 524K (256) 428 / 333; lognormal 300K x 300K (147) 269 / 261, in fp64 280 / 285, 500K x 200K (245) in fp64 380 / 332.
@@ -1705,7 +1707,7 @@ __device__ __forceinline__ Panel panel_of(int32_t bm, const int32_t *__restrict_
 // The LDS holds in turn where the segments start, the bits with their counts, the slots with the table behind them, and in place of the slots, in CSR order,
 // a segment's group and lane (10 and 6 bits) and the last 16 bits of where it starts.
 // Bound by its instructions and by the waits between its phases, since the LDS has room for one workgroup on a CU: lognormal 4M x 1M, 1954 row blocks of 24,500
-// segments, 470 us, in place of 301 + 368 for k_place and k_order_block.  Of 140,000 cycles a row block 21,000 pass until the segments are there, 52,000 with bits,
+// segments, 461 us, in place of 301 + 368 for k_place and k_order_block.  Of 140,000 cycles a row block 21,000 pass until the segments are there, 52,000 with bits,
 // ranks and slots (with an even number of words per code 64 neighbouring segments met in two banks: 495 against 343 us for the kernel as it was then),
 // 29,000 with table and tails (the table by ballots, group by group: 50,000), 33,000 with the places.
 __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__restrict__ row_blocks, const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC,
@@ -2074,7 +2076,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_panel_slots(const int32_t *__
 // The fill: a workgroup takes a share of a row block's nonzeros in the layout's order, `room` at most, and puts them in place in LDS; they come from the CSR arrays
 // in their order, and what it writes are whole runs.  The shares of one row block run on one XCD, whose L2 then holds what all of them read.
 // Bound by what it reads, 10 bytes a nonzero and share at 8 TB/s, and by its stores, one after the other as the LDS has room for one workgroup on a CU: lognormal
-// 4M x 1M in 2.05 shares a row block 411 us, in place of 880 for k_fill.  (Two workgroups of 80 KB to a CU, so four shares: 488; of 512 threads 471.)
+// 4M x 1M in 2.05 shares a row block 398 us, in place of 880 for k_fill.  (Two workgroups of 80 KB to a CU, so four shares: 488; of 512 threads 471.)
 template <typename T>
 __global__ __launch_bounds__(kPanelThreads) void k_panel_fill(const uint32_t *__restrict__ shares, const Findings *__restrict__ found,
                                                               const int32_t *__restrict__ ptr, int64_t n_rows, int32_t R, int32_t NBR, int32_t NBC, int32_t C,
